@@ -101,11 +101,13 @@ int run_wah(LaunchCtx& c) {
   if (c.n > a[0].cap || c.n > a[1].cap) return c.env->fail(KA_E_ARG, "wah_encode_sorted: range exceeds an input");
   if (a[2].cap < c.n || a[3].cap < c.n + 1 || a[4].cap < 2 * c.n)
     return c.env->fail(KA_E_ARG, "wah_encode_sorted: outputs need capacities n, n+1 and 2n");
+  const IndexOut out{static_cast<uint32_t*>(a[2].ptr), static_cast<uint32_t*>(a[3].ptr),
+                     static_cast<uint32_t*>(a[4].ptr), const_cast<uint64_t*>(a[2].d_len),
+                     const_cast<uint64_t*>(a[3].d_len), const_cast<uint64_t*>(a[4].d_len)};
+  EncodeOpts opt;
+  opt.d_n = c.d_n;
   return launch_wah_encode(*c.env, static_cast<const uint32_t*>(a[0].ptr), static_cast<const uint32_t*>(a[1].ptr), c.n,
-                           static_cast<uint32_t*>(a[2].ptr), static_cast<uint32_t*>(a[3].ptr),
-                           static_cast<uint32_t*>(a[4].ptr), const_cast<uint64_t*>(a[2].d_len),
-                           const_cast<uint64_t*>(a[3].d_len), const_cast<uint64_t*>(a[4].d_len), nullptr, 32, nullptr, 32,
-                           c.d_n);
+                           out, opt);
 }
 
 // wah_index: (in values; priv value_bits [, format]; out keys; out offsets;
@@ -127,52 +129,35 @@ int run_wah_index(LaunchCtx& c) {
     return env.fail(KA_E_ARG, "wah_index: outputs need capacities n, n+1 and 2n");
   if (n >= (1ull << 30)) return env.fail(KA_E_ARG, "wah_index: n must be below 2^30");
   const uint32_t* values = static_cast<const uint32_t*>(a[0].ptr);
-  uint32_t* keys = static_cast<uint32_t*>(a[2].ptr);
-  uint32_t* offsets = static_cast<uint32_t*>(a[3].ptr);
-  uint32_t* words = static_cast<uint32_t*>(a[4].ptr);
-  uint64_t* lk = const_cast<uint64_t*>(a[2].d_len);
-  uint64_t* lo = const_cast<uint64_t*>(a[3].d_len);
-  uint64_t* lw = const_cast<uint64_t*>(a[4].d_len);
-  const uint32_t fmt = (uint32_t)a[1].priv[1];
-  const uint64_t* d_n = c.d_n;  // the count on the device (n is then the capacity)
-  if (fmt > 2) return env.fail(KA_E_ARG, "wah_index: format must be 0 (paper), 1 (canonical) or 2 (PLWAH)");
-  if (fmt == 2 && n > 31ull * 0x1FFFFFFull)
+  const IndexOut out{static_cast<uint32_t*>(a[2].ptr), static_cast<uint32_t*>(a[3].ptr),
+                     static_cast<uint32_t*>(a[4].ptr), const_cast<uint64_t*>(a[2].d_len),
+                     const_cast<uint64_t*>(a[3].d_len), const_cast<uint64_t*>(a[4].d_len)};
+  EncodeOpts opt;
+  opt.format = (uint32_t)a[1].priv[1];
+  opt.d_n = c.d_n;  // the count on the device (n is then the capacity)
+  if (opt.format > 2) return env.fail(KA_E_ARG, "wah_index: format must be 0 (paper), 1 (canonical) or 2 (PLWAH)");
+  if (opt.format == 2 && n > 31ull * 0x1FFFFFFull)
     return env.fail(KA_E_ARG, "wah_index: PLWAH fill lengths (25 bits) cover at most 31 * (2^25 - 1) rows");
-  if (n == 0) return launch_wah_encode(env, nullptr, nullptr, 0, keys, offsets, words, lk, lo, lw);
+  if (n == 0) return launch_wah_encode(env, nullptr, nullptr, 0, out);
   int rc;
-  if (fmt != 0) {  // canonical WAH or PLWAH: the sorted pairs' group list, then the format's encoder
-    uint32_t* reject = static_cast<uint32_t*>(env.scratch(4));
-    if (!reject) return env.fail(KA_E_OOM, "wah_index: scratch");
-    if (bits >= 1 && bits <= 16) {
-      uint16_t* sk = static_cast<uint16_t*>(env.scratch(2 * n));
-      uint32_t* sr = static_cast<uint32_t*>(env.scratch(4 * n));
-      if (!sk || !sr) return env.fail(KA_E_OOM, "wah_index: scratch");
-      if ((rc = launch_radix_sort_rows16(env, values, sk, sr, n, bits, reject, 0, d_n))) return rc;
-      return launch_wah_encode_format16(env, sk, sr, n, fmt, keys, offsets, words, lk, lo, lw, reject, d_n);
-    }
-    uint32_t* sk = static_cast<uint32_t*>(env.scratch(4 * n));
-    uint32_t* sr = static_cast<uint32_t*>(env.scratch(4 * n));
-    if (!sk || !sr) return env.fail(KA_E_OOM, "wah_index: scratch");
-    if ((rc = launch_zero_u32(env, reject))) return rc;
-    if ((rc = launch_radix_sort_pairs(env, values, nullptr, sk, sr, n, 0, d_n))) return rc;
-    if (bits >= 17 && bits <= 31 && (rc = launch_reject_above(env, sort_plan_keys_or(env), bits, reject))) return rc;
-    return launch_wah_encode_format(env, sk, sr, n, fmt, keys, offsets, words, lk, lo, lw, reject, d_n);
-  }
+  uint32_t* sr = static_cast<uint32_t*>(env.scratch(4 * n));
   if (bits >= 1 && bits <= 16) {
     uint32_t* reject = static_cast<uint32_t*>(env.scratch(4));
     uint16_t* sk = static_cast<uint16_t*>(env.scratch(2 * n));
-    uint32_t* sr = static_cast<uint32_t*>(env.scratch(4 * n));
     if (!reject || !sk || !sr) return env.fail(KA_E_OOM, "wah_index: scratch");
-    if ((rc = launch_radix_sort_rows16(env, values, sk, sr, n, bits, reject, 0, d_n))) return rc;
-    return launch_wah_encode16(env, sk, sr, n, keys, offsets, words, lk, lo, lw, reject, 0, d_n);
+    if ((rc = launch_radix_sort_rows16(env, values, sk, sr, n, bits, reject, 0, opt.d_n))) return rc;
+    opt.reject_flag = reject;
+    opt.reject_shift = 0;
+    return launch_wah_encode16(env, sk, sr, n, out, opt);
   }
   uint32_t* sk = static_cast<uint32_t*>(env.scratch(4 * n));
-  uint32_t* sr = static_cast<uint32_t*>(env.scratch(4 * n));
   if (!sk || !sr) return env.fail(KA_E_OOM, "wah_index: scratch");
-  if ((rc = launch_radix_sort_pairs(env, values, nullptr, sk, sr, n, 0, d_n))) return rc;
-  const bool check = bits >= 17 && bits <= 31;
-  return launch_wah_encode(env, sk, sr, n, keys, offsets, words, lk, lo, lw, nullptr, 32,
-                           check ? sort_plan_keys_or(env) : nullptr, check ? bits : 32u, d_n);
+  if ((rc = launch_radix_sort_pairs(env, values, nullptr, sk, sr, n, 0, opt.d_n))) return rc;
+  if (bits >= 17 && bits <= 31) {
+    opt.reject_flag = sort_plan_keys_or(env);
+    opt.reject_shift = bits;
+  }
+  return launch_wah_encode(env, sk, sr, n, out, opt);
 }
 
 // wah_lookup: (in queries; in keys; out slots) -- slots[i] = the index d of

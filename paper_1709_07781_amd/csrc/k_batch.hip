@@ -649,8 +649,13 @@ int launch_wah_batch(Env& env, const uint32_t* values, uint64_t n, const uint32_
     }
   }
   // The tagged keys are the encoder's keys; rows are (or become) request-relative.
-  if ((rc = launch_wah_encode(env, skeys, srows, n, keys, g_off, words, len_keys, g_len, len_words,
-                              segmented ? nullptr : req_off, segmented ? 32u : value_bits, nullptr, 32u, d_n)))
+  EncodeOpts opt;
+  opt.d_n = d_n;
+  if (!segmented) {
+    opt.req_base = req_off;
+    opt.req_shift = value_bits;
+  }
+  if ((rc = launch_wah_encode(env, skeys, srows, n, IndexOut{keys, g_off, words, len_keys, g_len, len_words}, opt)))
     return rc;
   const uint32_t sgrid = std::min<uint32_t>(kSplitGrid, (nreq + kSplitBlock) / kSplitBlock);
   env.prof_begin("batch_split");

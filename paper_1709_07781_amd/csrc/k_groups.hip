@@ -1,28 +1,17 @@
-// Encoder formats over group lists, bitmap decoding, AND / OR of bitmaps and
-// lookup by value -- the index in the two other word formats (the paper calls
-// fills "homogeneous blocks" compressed into one word, Sec. 4.1, and names
-// PLWAH as future work, Sec. 6) and the queries the index is built for (Sec.
-// 4.1 keeps a lookup table from values to bitmaps; Sec. 4.2 names interactive
-// searches and queries).
+// Bitmap decoding, AND / OR of bitmaps and lookup by value -- the queries the
+// index is built for (Sec. 4.1 keeps a lookup table from values to bitmaps;
+// Sec. 4.2 names interactive searches and queries).  The word formats are the
+// encoder's: the paper's form, canonical WAH (a run of full groups is one
+// 1-fill: bits 31 and 30 set, run length in bits 29..0), PLWAH (25-bit fill
+// lengths; a fill absorbs the group right after it when that differs from the
+// fill's groups in one bit only: bits 29..25 = 1 + that bit's index).
 //
-// A group is (key, chunk id, literal): the 31-row chunk of one value's bitmap
-// and its rows as a literal.  Groups sorted by (key, chunk) define the index;
-// the encoder turns them into words:
-//   paper form  one 0-fill (gap > 0) and one literal per group;
-//   canonical   the same, except that a run of full groups (all 31 rows, with
-//               consecutive chunk ids, one value) is one 1-fill word (bits 31
-//               and 30 set, run length in bits 29..0);
-//   PLWAH       canonical with 25-bit fill lengths; a fill absorbs the group
-//               right after it when that group differs from the fill's groups
-//               in one bit only (one row after a 0-fill, one missing row after
-//               a 1-fill): bits 29..25 = 1 + that bit's index.
-// What group i emits depends on groups i-1 and i (flags), except for the
-// length of a 1-fill (the run's end, found by binary search over the prefix
-// count of full groups) and its PLWAH position (the group after the run).  So
-// the encoding is: flags per group, prefix sums of words, values and full
-// groups (the look-back scan), then each group writes its words.  Group lists
-// come from sorted (key, row) pairs (k_group_heads, k_group_write) or from the
-// non-empty groups of a dense bitmap (the AND / OR of two decoded bitmaps).
+// AND / OR decodes both bitmaps, combines them group by group and encodes the
+// non-empty result groups, a list of (chunk id, literal), by their flags: what
+// group i emits depends on groups i-1 and i, except for the length of a 1-fill
+// (the run's end, found by binary search over the prefix count of full groups)
+// and its PLWAH position (the group after the run); prefix sums of words and
+// full groups (the look-back scan) then place the words.
 //
 // Every count that depends on the data stays on the device; grids are sized
 // by capacities and read the true counts there.
@@ -50,51 +39,6 @@ __device__ __forceinline__ uint32_t dev_count(uint64_t cap, const uint64_t* d_n)
 uint32_t grid_for(uint64_t cap) {
   const uint64_t g = (cap + kBlock - 1) / kBlock;
   return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(g, kMaxGrid));
-}
-
-// ---------------------------------------------------------------------------------
-// groups of sorted (key, row) pairs
-// ---------------------------------------------------------------------------------
-// head[i] = 1 if pair i starts a group (first pair, new key or new chunk).
-template <class KeyT>
-__global__ __launch_bounds__(kBlock) void k_group_heads(const KeyT* __restrict__ skeys,
-                                                        const uint32_t* __restrict__ srows, uint32_t n_cap,
-                                                        const uint64_t* __restrict__ d_n, uint32_t* __restrict__ head) {
-  const uint32_t n = dev_count(n_cap, d_n);
-  for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
-    bool h = i == 0;
-    if (!h) h = skeys[i] != skeys[i - 1] || srows[i] / kRows != srows[i - 1] / kRows;
-    head[i] = h ? 1u : 0u;
-  }
-}
-
-// Every head writes its group at gpos[i] (the exclusive scan of the heads):
-// key, chunk id and the literal of its rows (at most 31 pairs, read ahead).
-// The last pair writes the group count.
-template <class KeyT>
-__global__ __launch_bounds__(kBlock) void k_group_write(const KeyT* __restrict__ skeys,
-                                                        const uint32_t* __restrict__ srows, uint32_t n_cap,
-                                                        const uint64_t* __restrict__ d_n,
-                                                        const uint32_t* __restrict__ head,
-                                                        const uint32_t* __restrict__ gpos,
-                                                        uint32_t* __restrict__ gkey, uint32_t* __restrict__ gchunk,
-                                                        uint32_t* __restrict__ glit, uint64_t* __restrict__ k_len) {
-  const uint32_t n = dev_count(n_cap, d_n);
-  for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
-    if (i == n - 1) *k_len = (uint64_t)gpos[i] + head[i];
-    if (!head[i]) continue;
-    const uint32_t k = skeys[i], c = srows[i] / kRows;
-    uint32_t lit = 0;
-    for (uint32_t j = i; j < n && j < i + kRows; ++j) {
-      const uint32_t r = srows[j];
-      if (skeys[j] != k || r / kRows != c) break;
-      lit |= 1u << (r - c * kRows);
-    }
-    const uint32_t g = gpos[i];
-    gkey[g] = k;
-    gchunk[g] = c;
-    glit[g] = lit;
-  }
 }
 
 // ---------------------------------------------------------------------------------
@@ -358,11 +302,6 @@ __global__ void k_set_zero_u32(uint32_t* p) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *p = 0u;
 }
 
-// *reject = 1 if a key is at or above 2^bits (from the OR of all keys).
-__global__ void k_reject_above(const uint32_t* __restrict__ keys_or, uint32_t bits, uint32_t* __restrict__ reject) {
-  if (threadIdx.x == 0 && blockIdx.x == 0 && bits < 32 && (*keys_or >> bits) != 0u) *reject = 1u;
-}
-
 // *len = *reject ? 0 : value.
 __global__ void k_len_unless(uint64_t* __restrict__ len, uint64_t value, const uint32_t* __restrict__ reject) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *len = *reject ? 0u : value;
@@ -417,61 +356,6 @@ int encode_groups(Env& env, uint32_t fmt, const Groups& g, uint64_t cap, const u
 }
 
 }  // namespace
-
-template <class KeyT>
-int encode_format_impl(Env& env, const KeyT* skeys, const uint32_t* srows, uint64_t n, uint32_t fmt, uint32_t* keys,
-                       uint32_t* offsets, uint32_t* words, uint64_t* len_keys, uint64_t* len_offsets,
-                       uint64_t* len_words, uint32_t* reject, const uint64_t* d_n) {
-  if (fmt > kFmtPlwah) return env.fail(kErrArg, "unknown WAH format");
-  if (!offsets || !len_keys || !len_offsets || !len_words || !reject)
-    return env.fail(kErrArg, "wah encoder: null output");
-  if (n >= (1ull << 30)) return env.fail(kErrArg, "wah encoder: n must be below 2^30");
-  if (n && (!skeys || !srows || !keys || !words)) return env.fail(kErrArg, "wah encoder: null buffer");
-  const uint64_t c = std::max<uint64_t>(n, 1);
-  uint32_t* head = static_cast<uint32_t*>(env.scratch(4 * c));
-  uint32_t* gpos = static_cast<uint32_t*>(env.scratch(4 * c));
-  uint32_t* gkey = static_cast<uint32_t*>(env.scratch(4 * c));
-  uint32_t* gchunk = static_cast<uint32_t*>(env.scratch(4 * c));
-  uint32_t* glit = static_cast<uint32_t*>(env.scratch(4 * c));
-  uint64_t* k_len = static_cast<uint64_t*>(env.scratch(8));
-  if (!head || !gpos || !gkey || !gchunk || !glit || !k_len) return env.fail(kErrOom, "wah encoder: scratch");
-  int rc;
-  if ((rc = launch_set_len(env, k_len, 0))) return rc;
-  if (n) {
-    const uint32_t grid = grid_for(n), nn = (uint32_t)n;
-    env.prof_begin("group_heads");
-    k_group_heads<KeyT><<<dim3(grid), dim3(kBlock), 0, env.stream()>>>(skeys, srows, nn, d_n, head);
-    env.prof_end("group_heads");
-    if ((rc = check_launch(env, "group_heads launch"))) return rc;
-    if ((rc = launch_exclusive_scan(env, head, gpos, n, d_n))) return rc;
-    env.prof_begin("group_write");
-    k_group_write<KeyT><<<dim3(grid), dim3(kBlock), 0, env.stream()>>>(skeys, srows, nn, d_n, head, gpos, gkey,
-                                                                       gchunk, glit, k_len);
-    env.prof_end("group_write");
-    if ((rc = check_launch(env, "group_write launch"))) return rc;
-  }
-  return encode_groups(env, fmt, Groups{gkey, gchunk, glit}, c, k_len, keys, offsets, words, len_keys, len_offsets,
-                       len_words, reject);
-}
-
-int launch_wah_encode_format(Env& env, const uint32_t* skeys, const uint32_t* srows, uint64_t n, uint32_t fmt,
-                             uint32_t* keys, uint32_t* offsets, uint32_t* words, uint64_t* len_keys,
-                             uint64_t* len_offsets, uint64_t* len_words, uint32_t* reject, const uint64_t* d_n) {
-  return encode_format_impl(env, skeys, srows, n, fmt, keys, offsets, words, len_keys, len_offsets, len_words,
-                            reject, d_n);
-}
-
-int launch_wah_encode_format16(Env& env, const uint16_t* skeys, const uint32_t* srows, uint64_t n, uint32_t fmt,
-                               uint32_t* keys, uint32_t* offsets, uint32_t* words, uint64_t* len_keys,
-                               uint64_t* len_offsets, uint64_t* len_words, uint32_t* reject, const uint64_t* d_n) {
-  return encode_format_impl(env, skeys, srows, n, fmt, keys, offsets, words, len_keys, len_offsets, len_words,
-                            reject, d_n);
-}
-
-int launch_reject_above(Env& env, const uint32_t* keys_or, uint32_t bits, uint32_t* reject) {
-  k_reject_above<<<dim3(1), dim3(64), 0, env.stream()>>>(keys_or, bits, reject);
-  return check_launch(env, "reject_above launch");
-}
 
 int launch_len_unless(Env& env, uint64_t* len, uint64_t value, const uint32_t* reject) {
   k_len_unless<<<dim3(1), dim3(64), 0, env.stream()>>>(len, value, reject);

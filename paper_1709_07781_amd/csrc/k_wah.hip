@@ -16,7 +16,7 @@
 //   gap(e) = grp(e) and the fill before e is non-zero (chunk(e) != 0 for a
 //            value's first group, chunk(e) != chunk(e - 1) + 1 otherwise),
 // and e emits grp(e) + gap(e) words and seg(e) values.  So the encoding is one
-// single-pass kernel over tiles of kEncTile pairs, k_wah_write: each tile
+// single-pass kernel over tiles of 8 pairs per work-item, k_wah_write: each tile
 // counts its words and values, publishes both counts, finds the counts of all
 // earlier tiles by decoupled look-back (one status chain for words, one for
 // values; a silent predecessor is counted from its input by the waiting wave)
@@ -24,7 +24,23 @@
 // offsets[D] and the three output lengths.  The sorted pairs are read once.
 // A group spans at most 31 sorted elements (rows are distinct), so a tile
 // finishes a group that runs past its end by reading at most 30 elements
-// ahead (kLook).  Words are staged in LDS (over the staged input, which is
+// ahead (kLook).
+//
+// The other word formats (canonical WAH: a run of full groups is one 1-fill;
+// PLWAH: a fill also absorbs the group after it when that differs in one bit)
+// come out of the same pass, because what they add is decided by a few sorted
+// elements too -- rows of a value are distinct and ascending, so two elements
+// of one value whose rows differ by exactly their distance enclose a full run:
+//   full(e)   the group that e starts holds all 31 rows: e + 30 has the same
+//             value and row(e) + 30, and e's row starts its chunk;
+//   pfull(e)  the group before e's is the chunk before it and full: e - 31 has
+//             the same value and starts that chunk;
+//   thirty(e) the group holds 30 rows: e + 29 is in it and it is not full;
+//   one(e)    it holds one row: e + 1 is not in it;
+// and a run of L full groups ends where e + 31 L - 1 no longer has row(e) +
+// 31 L - 1 (monotone in L: exponential, then binary search, at run starts
+// only).  A group emits its fill (unless it is skipped) and its literal or
+// 1-fill (unless it is skipped or absorbed); positions are the same prefix sum.  Words are staged in LDS (over the staged input, which is
 // dead by then) and written out by consecutive work-items.  Sorted keys are
 // uint32, or uint16 when every value is below 2^16 (the index build's
 // narrow-key sort).
@@ -43,16 +59,14 @@ namespace {
 // (244 against 228 us at 512 x 16); 16384-pair tiles (one work-group per CU)
 // took 308 us.
 constexpr int kEncBlock = 1024;
-#ifndef KA_ENC_ITEMS
-#define KA_ENC_ITEMS 8
-#endif
-constexpr int kEncItems = KA_ENC_ITEMS;
-constexpr int kEncTile = kEncBlock * kEncItems;  // 8192 pairs
-constexpr int kVecs = kEncTile / 4 / kEncBlock;  // 16-byte loads per work-item and array
-constexpr int kLook = 32;                        // >= 30 elements of look-ahead
-constexpr int kStage = kEncTile + kLook;         // staged elements (the look-behind is kept apart)
+constexpr int kEncItems = 8;
+constexpr int kVecs = kEncItems / 4;  // 16-byte loads per work-item and array
+constexpr int kLook = 32;             // >= 30 elements of look-ahead
 constexpr uint32_t kGroupRows = 31;
 constexpr uint32_t kFill = 0x80000000u;
+constexpr uint32_t kOnes = 0x40000000u;      // fill bit of a 1-fill
+constexpr uint32_t kPlwahShift = 25;         // PLWAH: bits 29..25 = 1 + the absorbed group's bit
+enum { kFmtPaper = 0, kFmtCanonical = 1, kFmtPlwah = 2 };
 
 // Padded LDS index: four spare words after every 64 elements.  Groups of 4
 // elements stay 16-byte aligned, so the tile is staged with conflict-free
@@ -61,32 +75,32 @@ constexpr uint32_t kFill = 0x80000000u;
 // together (starting 32 bytes apart, plus 16 after every eighth) cover all 64
 // banks once.
 __device__ __forceinline__ uint32_t pidx(uint32_t i) { return i + 4 * (i >> 6); }
-constexpr int kStagePadded = kStage + 4 * (kStage / 64) + 4;
 static_assert(kEncItems == 8, "one padded run of 8 elements per work-item");
-static_assert(2 * kEncTile <= 2 * kStagePadded, "word staging fits over the input staging");
 
-// Words and values emitted by an element with key k and row r whose
-// predecessor has key kp and row rp (first: no predecessor).
-__device__ __forceinline__ void element_counts(uint32_t k, uint32_t r, uint32_t kp, uint32_t rp, bool first,
-                                               uint32_t& nw, uint32_t& ns) {
-  const uint32_t c = r / kGroupRows, cp = rp / kGroupRows;
-  const bool seg = first || k != kp;
-  const bool grp = seg || c != cp;
-  const bool gap = grp && (seg ? c != 0u : c != cp + 1u);
-  nw += (grp ? 1u : 0u) + (gap ? 1u : 0u);
-  ns += seg ? 1u : 0u;
-}
+// LDS of one tile of kBlock * kEncItems pairs.
+template <int kBlock, int kFmt>
+struct EncLds {
+  static constexpr int kTile = kBlock * kEncItems;
+  static constexpr int kStage = kTile + kLook;  // staged elements (the look-behind is kept apart)
+  static constexpr int kPadded = kStage + 4 * (kStage / 64) + 4;
+  static constexpr int kBehind = kFmt == kFmtPaper ? 1 : 32;  // elements base - kBehind .. base - 1
+  static_assert(2 * kTile <= 2 * kPadded, "word staging fits over the input staging");
+  __align__(16) uint32_t mem[2 * kPadded];  // keys, rows; then the tile's words
+  uint32_t bk[kBehind], br[kBehind];
+  uint32_t scan[kBlock / 64];
+  uint32_t pre[2];
+};
 
 // Tile elements in registers: slot (j, c) of work-item tid holds element
-// b + 4 (j * kEncBlock + tid) + c (0 beyond len).
-template <bool kVec, class KeyT>
+// b + 4 (j * kBlock + tid) + c (0 beyond len).
+template <int kBlock, bool kVec, class KeyT>
 __device__ __forceinline__ void load_pairs(const KeyT* __restrict__ skeys, const uint32_t* __restrict__ srows,
                                            uint32_t b, uint32_t len, uint32_t tid, uint32_t (&vk)[kVecs][4],
                                            uint32_t (&vr)[kVecs][4]) {
-  if (kVec && len == (uint32_t)kEncTile) {
+  if (kVec && len == (uint32_t)(kBlock * kEncItems)) {
 #pragma unroll
     for (int j = 0; j < kVecs; ++j) {
-      const uint32_t q = j * kEncBlock + tid;
+      const uint32_t q = j * kBlock + tid;
       load_key4(skeys + b, q, vk[j]);
       const u32x4 c = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(srows + b) + q);
       vr[j][0] = c.x, vr[j][1] = c.y, vr[j][2] = c.z, vr[j][3] = c.w;
@@ -96,7 +110,7 @@ __device__ __forceinline__ void load_pairs(const KeyT* __restrict__ skeys, const
     for (int j = 0; j < kVecs; ++j)
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        const uint32_t i = 4 * (j * kEncBlock + tid) + c;
+        const uint32_t i = 4 * (j * kBlock + tid) + c;
         vk[j][c] = i < len ? (uint32_t)skeys[b + i] : 0u;
         vr[j][c] = i < len ? srows[b + i] : 0u;
       }
@@ -114,15 +128,49 @@ struct BatchRows {
   }
 };
 
+// What the element with key k and row r emits whose predecessor has key kp and
+// row rp (first: no predecessor).  at(d, k, r) tells whether the element d
+// places further on (back for a negative d) exists and has key k and row r;
+// in_group(d, k, c) whether it exists and has key k and chunk c.
+struct Emits {
+  bool seg, grp;    // starts a value, a group
+  bool fill, main;  // a fill word (the gap's 0-fill), a literal or 1-fill word
+  bool full;        // main is the 1-fill of the run that starts here
+};
+
+template <int kFmt, class At, class InGroup>
+__device__ __forceinline__ Emits element_emits(uint32_t k, uint32_t c, uint32_t bit, uint32_t kp, uint32_t cp,
+                                               bool first, At&& at, InGroup&& in_group) {
+  Emits e;
+  e.seg = first || k != kp;
+  e.grp = e.seg || c != cp;
+  e.fill = e.grp && (e.seg ? c != 0u : c != cp + 1u);
+  e.main = e.grp;
+  e.full = false;
+  if (kFmt != kFmtPaper && e.grp) {
+    e.full = bit == 0u && at(30, k, c * kGroupRows + 30u);
+    // the group before is the chunk before (then there is no gap) and full
+    const bool pfull = !e.seg && c == cp + 1u && at(-31, k, cp * kGroupRows);
+    bool skip = e.full && pfull;  // inside the run's 1-fill
+    if (kFmt == kFmtPlwah) {
+      skip = skip || (pfull && !e.full && in_group(29, k, c));  // 30 rows: absorbed by the run's 1-fill
+      if (e.fill && !in_group(1, k, c)) e.main = false;         // one row: absorbed by its 0-fill
+    }
+    if (skip) e.main = false;
+    e.full = e.full && e.main;
+  }
+  return e;
+}
+
 // Words and values that tile u emits, counted from its input by one wave --
 // the look-back's fallback for a predecessor that has not published yet.  Lane
-// l takes 64 consecutive elements.
-template <class KeyT>
+// l takes consecutive elements.
+template <int kTile, int kFmt, class KeyT>
 __device__ LbPairSum wave_tile_count(const KeyT* __restrict__ skeys, const uint32_t* __restrict__ srows, uint32_t n,
                                      uint32_t u, BatchRows br) {
-  constexpr uint32_t kPer = kEncTile / 64;
-  const uint32_t b = u * kEncTile;
-  const uint32_t end = min(b + (uint32_t)kEncTile, n);
+  constexpr uint32_t kPer = kTile / 64;
+  const uint32_t b = u * kTile;
+  const uint32_t end = min(b + (uint32_t)kTile, n);
   const uint32_t e0 = b + lane_id() * kPer;
   uint32_t nw = 0, ns = 0;
   if (e0 < end) {
@@ -132,9 +180,18 @@ __device__ LbPairSum wave_tile_count(const KeyT* __restrict__ skeys, const uint3
       rp = br.local(kp, srows[e0 - 1]);
     }
     const uint32_t e1 = min(e0 + kPer, end);
+#pragma unroll 1
     for (uint32_t e = e0; e < e1; ++e) {
-      const uint32_t k = skeys[e], r = br.local(k, srows[e]);
-      element_counts(k, r, kp, rp, e == 0, nw, ns);
+      const uint32_t k = skeys[e], r = br.local(k, srows[e]), c = r / kGroupRows;
+      auto exists = [&](int d) { return d < 0 ? e >= (uint32_t)-d : e + (uint32_t)d < n; };
+      const Emits m = element_emits<kFmt>(
+          k, c, r - c * kGroupRows, kp, rp / kGroupRows, e == 0,
+          [&](int d, uint32_t kk, uint32_t rr) { return exists(d) && skeys[e + d] == kk && srows[e + d] == rr; },
+          [&](int d, uint32_t kk, uint32_t cc) {
+            return exists(d) && skeys[e + d] == kk && srows[e + d] / kGroupRows == cc;
+          });
+      nw += (m.fill ? 1u : 0u) + (m.main ? 1u : 0u);
+      ns += m.seg ? 1u : 0u;
       kp = k;
       rp = r;
     }
@@ -142,15 +199,16 @@ __device__ LbPairSum wave_tile_count(const KeyT* __restrict__ skeys, const uint3
   return {wave_sum(nw), wave_sum(ns)};
 }
 
-// An empty input: D = 0, W = 0, offsets = [0].
-__global__ void k_wah_empty(uint32_t* __restrict__ out_offsets, uint64_t* __restrict__ len_keys,
-                            uint64_t* __restrict__ len_offsets, uint64_t* __restrict__ len_words) {
-  if (threadIdx.x == 0) {
-    out_offsets[0] = 0;
-    *len_keys = 0;
-    *len_offsets = 1;
-    *len_words = 0;
-  }
+// An empty input's index, D = 0, W = 0, offsets = [0], by one work-item.
+__device__ __forceinline__ void write_empty_index(const IndexOut& out) {
+  out.offsets[0] = 0;
+  *out.len_keys = 0;
+  *out.len_offsets = 1;
+  *out.len_words = 0;
+}
+
+__global__ void k_wah_empty(IndexOut out) {
+  if (threadIdx.x == 0) write_empty_index(out);
 }
 
 // Rejection of the whole input, decided by earlier kernels: the encoding is
@@ -165,53 +223,43 @@ struct Reject {
 // ---------------------------------------------------------------------------------
 // write: literals, fills and lookup-table entries of one tile
 // ---------------------------------------------------------------------------------
-// status[kLbSpread * tile]: the tile's (words, values) look-back word, zeroed
-// before the launch.
-template <bool kVec, class KeyT>
-__global__ __launch_bounds__(kEncBlock, 8) void k_wah_write(const KeyT* __restrict__ skeys,
+// The other formats take up to 83 VGPRs (one work-group per CU): held to 64
+// they spill.
+// One work-group per tile; status[kLbSpread * tile] is the tile's (words, values)
+// look-back word, zeroed before the launch.
+template <int kBlock, int kFmt, bool kVec, class KeyT>
+__global__ __launch_bounds__(kBlock, kFmt == kFmtPaper ? 8 : 4) void k_wah_write(const KeyT* __restrict__ skeys,
                                                          const uint32_t* __restrict__ srows, uint32_t n_cap,
                                                          const uint64_t* __restrict__ d_n,
                                                          uint64_t* __restrict__ status, uint32_t spin_limit,
-                                                         uint32_t* __restrict__ out_keys,
-                                                         uint32_t* __restrict__ out_offsets,
-                                                         uint32_t* __restrict__ out_words, BatchRows br, Reject rej,
-                                                         uint64_t* __restrict__ len_keys,
-                                                         uint64_t* __restrict__ len_offsets,
-                                                         uint64_t* __restrict__ len_words) {
-  __shared__ __align__(16) uint32_t s_mem[2 * kStagePadded];
-  __shared__ uint32_t s_scan[kEncBlock / 64];
-  __shared__ uint32_t s_pre[2];
-  __shared__ uint32_t s_behind[2];  // key and row of element base - 1
-  uint32_t* s_k = s_mem;
-  uint32_t* s_r = s_mem + kStagePadded;
-  uint32_t* s_words = s_mem;  // after the literals are built
-
+                                                         IndexOut out, BatchRows br, Reject rej) {
+  constexpr int kTile = EncLds<kBlock, kFmt>::kTile, kBehind = EncLds<kBlock, kFmt>::kBehind;
+  __shared__ EncLds<kBlock, kFmt> L;
+  uint32_t* s_k = L.mem;
+  uint32_t* s_r = L.mem + EncLds<kBlock, kFmt>::kPadded;
+  uint32_t* s_words = L.mem;  // after the literals are built
   const uint32_t tid = threadIdx.x, tile = blockIdx.x;
-  const uint32_t base = tile * kEncTile;
+  const uint32_t base = tile * kTile;
   // n_cap pairs, or the count written on the device by an earlier stage: the
   // grid then covers the capacity and the tiles past the count leave at once
   // (tile 0 of an empty input writes the empty index).
   const uint32_t n = (uint32_t)device_count(n_cap, d_n);
   if (base >= n) {
-    if (tile == 0 && tid == 0) {
-      out_offsets[0] = 0;
-      *len_keys = 0;
-      *len_offsets = 1;
-      *len_words = 0;
-    }
+    if (tile == 0 && tid == 0) write_empty_index(out);
     return;
   }
-  const uint32_t tile_n = min((uint32_t)kEncTile, n - base);
-  const uint32_t avail = min((uint32_t)(kEncTile + kLook), n - base);  // readable from base on
+  const uint32_t tile_n = min((uint32_t)kTile, n - base);
+  const uint32_t avail = min((uint32_t)(kTile + kLook), n - base);  // readable from base on
 
-  // ---- stage elements base .. base+kEncTile+kLook-1 into slots 0.. ---------------
-  // Work-items 64..95 also load the look-ahead (slots kEncTile ..) and
-  // work-item 96 the look-behind element base - 1.
+  // ---- stage elements base .. base+kTile+kLook-1 into slots 0.. ---------------
+  // Work-items 64.. also load the look-ahead (slots kTile ..) and the kBehind
+  // elements before base.
   {
     uint32_t vk[kVecs][4], vr[kVecs][4];
-    load_pairs<kVec>(skeys, srows, base, tile_n, tid, vk, vr);
-    const bool extra = tid >= 64 && tid < 64 + kLook + 1;
-    const int64_t g = tid == 64 + kLook ? (int64_t)base - 1 : (int64_t)base + kEncTile + (tid - 64);
+    load_pairs<kBlock, kVec>(skeys, srows, base, tile_n, tid, vk, vr);
+    const bool extra = tid >= 64 && tid < 64 + kLook + kBehind;
+    const bool behind = tid >= 64 + kLook;
+    const int64_t g = behind ? (int64_t)base - kBehind + (tid - 64 - kLook) : (int64_t)base + kTile + (tid - 64);
     uint32_t xk = 0, xr = 0;
     if (extra) {
       const bool ok = g >= 0 && g < (int64_t)n;
@@ -220,7 +268,7 @@ __global__ __launch_bounds__(kEncBlock, 8) void k_wah_write(const KeyT* __restri
     }
 #pragma unroll
     for (int j = 0; j < kVecs; ++j) {
-      const uint32_t sl = pidx(4 * (j * kEncBlock + tid));
+      const uint32_t sl = pidx(4 * (j * kBlock + tid));
       u32x4 k4, r4;
       k4.x = vk[j][0], k4.y = vk[j][1], k4.z = vk[j][2], k4.w = vk[j][3];
       r4.x = br.local(vk[j][0], vr[j][0]), r4.y = br.local(vk[j][1], vr[j][1]);
@@ -229,11 +277,11 @@ __global__ __launch_bounds__(kEncBlock, 8) void k_wah_write(const KeyT* __restri
       *reinterpret_cast<u32x4*>(s_r + sl) = r4;
     }
     if (extra) {
-      if (tid == 64 + kLook) {
-        s_behind[0] = xk;
-        s_behind[1] = xr;
+      if (behind) {
+        L.bk[tid - 64 - kLook] = xk;
+        L.br[tid - 64 - kLook] = xr;
       } else {
-        const uint32_t sl = pidx((uint32_t)(kEncTile + (tid - 64)));
+        const uint32_t sl = pidx((uint32_t)(kTile + (tid - 64)));
         s_k[sl] = xk;
         s_r[sl] = xr;
       }
@@ -267,34 +315,48 @@ __global__ __launch_bounds__(kEncBlock, 8) void k_wah_write(const KeyT* __restri
   uint32_t kprev = (uint32_t)__shfl_up((int)key[kEncItems - 1], 1);
   uint32_t cprev = (uint32_t)__shfl_up((int)grp_of[kEncItems - 1], 1);
   if (lane == 0) {
-    kprev = tid ? s_k[pidx(e0 - 1)] : s_behind[0];
-    cprev = (tid ? s_r[pidx(e0 - 1)] : s_behind[1]) / kGroupRows;
+    constexpr int kLast = EncLds<kBlock, kFmt>::kBehind - 1;
+    kprev = tid ? s_k[pidx(e0 - 1)] : L.bk[kLast];
+    cprev = (tid ? s_r[pidx(e0 - 1)] : L.br[kLast]) / kGroupRows;
   }
 
   // ---- group and value heads, words and values emitted ------------------------------
-  uint32_t heads = 0, segs = 0, gaps = 0;  // bit i: element i starts a group / a value / has a fill
+  // bit i: element i starts a group / a value / has a fill word / a literal or
+  // 1-fill word (the paper's form: every head has one)
+  uint32_t heads = 0, segs = 0, gaps = 0, mains = 0;
+  uint32_t run_i = kEncItems;  // the element whose word is a 1-fill: full groups are 31 elements apart, so one at most
   const bool first_of_input = base + e0 == 0u;  // this work-item's element 0 is the input's first
 #pragma unroll
   for (int i = 0; i < kEncItems; ++i) {
-    const uint32_t c = grp_of[i];
-    const uint32_t kp = i ? key[i - 1] : kprev;
-    const uint32_t cp = i ? grp_of[i - 1] : cprev;
-    const bool seg = key[i] != kp || (i == 0 && first_of_input);
-    const bool grp = seg || c != cp;
-    const bool gap = grp && (seg ? c != 0u : c != cp + 1u);
-    heads |= (uint32_t)grp << i;
-    segs |= (uint32_t)seg << i;
-    gaps |= (uint32_t)gap << i;
+    const uint32_t x = e0 + i;
+    // keys and rows by tile-local position, from the look-behind to the look-ahead
+    auto key_at = [&](int d) { return d < 0 && x < (uint32_t)-d ? L.bk[(32 + x + d) & 31] : s_k[pidx(x + d)]; };
+    auto row_at = [&](int d) { return d < 0 && x < (uint32_t)-d ? L.br[(32 + x + d) & 31] : s_r[pidx(x + d)]; };
+    auto exists = [&](int d) { return d < 0 ? base + x >= (uint32_t)-d : x + (uint32_t)d < avail; };
+    const Emits m = element_emits<kFmt>(
+        key[i], grp_of[i], bit_of[i], i ? key[i - 1] : kprev, i ? grp_of[i - 1] : cprev, i == 0 && first_of_input,
+        [&](int d, uint32_t kk, uint32_t rr) { return exists(d) && key_at(d) == kk && row_at(d) == rr; },
+        [&](int d, uint32_t kk, uint32_t cc) {
+          return exists(d) && key_at(d) == kk && row_at(d) / kGroupRows == cc;
+        });
+    heads |= (uint32_t)m.grp << i;
+    segs |= (uint32_t)m.seg << i;
+    gaps |= (uint32_t)m.fill << i;
+    if (kFmt != kFmtPaper) {
+      mains |= (uint32_t)m.main << i;
+      if (m.full && ((valid >> i) & 1u)) run_i = i;
+    }
   }
   heads &= valid;
   segs &= valid;
   gaps &= valid;
-  const uint32_t nw = (uint32_t)__popc(heads) + (uint32_t)__popc(gaps);
+  mains = kFmt == kFmtPaper ? heads : mains & valid;
+  const uint32_t nw = (uint32_t)__popc(mains) + (uint32_t)__popc(gaps);
   const uint32_t ns = (uint32_t)__popc(segs);
   // Both counts in one scan: words in the low half, values in the high half
-  // (a tile emits at most 2*kEncTile words and kEncTile values).
+  // (a tile emits at most 2 * kTile words and kTile values).
   uint32_t packed_total;
-  const uint32_t packed_pre = block_excl_scan<kEncBlock>((ns << 16) | nw, s_scan, &packed_total);
+  const uint32_t packed_pre = block_excl_scan<kBlock>((ns << 16) | nw, L.scan, &packed_total);
   const uint32_t tile_nw = packed_total & 0xFFFFu, tile_ns = packed_total >> 16;
 
   // ---- publish the tile's counts at once: successors find them while this
@@ -336,6 +398,49 @@ __global__ __launch_bounds__(kEncBlock, 8) void k_wah_write(const KeyT* __restri
       }
     }
   }
+
+  // ---- a run of full groups starts here: its length, and the group that its
+  // 1-fill absorbs.  Elements of the stage from LDS, later ones from memory. ---------
+  uint32_t run_word = 0;
+  if (kFmt != kFmtPaper && run_i < (uint32_t)kEncItems) {
+    const uint32_t x = e0 + run_i;
+    auto key_at = [&](uint32_t j) { return j < avail ? s_k[pidx(j)] : (uint32_t)skeys[base + j]; };
+    auto row_at = [&](uint32_t j) { return j < avail ? s_r[pidx(j)] : srows[base + j]; };
+    const uint32_t k0 = key_at(x), r0 = row_at(x);
+    auto ok = [&](uint32_t len) {  // elements x .. x + 31 len - 1 are len full groups
+      const uint64_t d = 31ull * len - 1ull;
+      if (d >= n - base - x) return false;
+      return key_at(x + (uint32_t)d) == k0 && row_at(x + (uint32_t)d) == r0 + (uint32_t)d;
+    };
+    uint32_t lo = 1, step = 1;  // ok(lo) holds
+    while (ok(lo + step)) {
+      lo += step;
+      step <<= 1;
+    }
+    uint32_t hi = lo + step;  // ok(hi) fails
+    while (hi - lo > 1u) {
+      const uint32_t mid = lo + (hi - lo) / 2u;
+      if (ok(mid))
+        lo = mid;
+      else
+        hi = mid;
+    }
+    run_word = kFill | kOnes | lo;
+    if (kFmt == kFmtPlwah) {
+      const uint32_t j0 = x + kGroupRows * lo, c1 = r0 / kGroupRows + lo;  // the group after the run
+      if (base + j0 + 29u < n && key_at(j0 + 29u) == k0 && row_at(j0 + 29u) / kGroupRows == c1) {  // 30 rows
+        uint32_t a = 0, b = 30;  // its first a rows are the chunk's first a rows
+        while (a < b) {
+          const uint32_t mid = (a + b) / 2u;
+          if (row_at(j0 + mid) == c1 * kGroupRows + mid)
+            a = mid + 1u;
+          else
+            b = mid;
+        }
+        run_word |= (1u + a) << kPlwahShift;  // the missing row's bit
+      }
+    }
+  }
   __syncthreads();  // the staged input is dead from here on
 
   // ---- one backward sweep: literals (OR of the group's bits) and fills, placed in
@@ -348,11 +453,16 @@ __global__ __launch_bounds__(kEncBlock, 8) void k_wah_write(const KeyT* __restri
     for (int i = kEncItems - 1; i >= 0; --i) {
       acc |= 1u << bit_of[i];
       if ((heads >> i) & 1u) {
-        s_words[--w] = acc & ~kFill;  // drops the bit 31 of elements past the tile's end
+        if (kFmt == kFmtPaper || ((mains >> i) & 1u))
+          s_words[--w] = kFmt != kFmtPaper && (uint32_t)i == run_i
+                             ? run_word
+                             : acc & ~kFill;  // drops the bit 31 of elements past the tile's end
         acc = 0;
         if ((gaps >> i) & 1u) {
           const uint32_t cp = i ? grp_of[i - 1] : cprev;
-          s_words[--w] = kFill | (((segs >> i) & 1u) ? grp_of[i] : grp_of[i] - cp - 1u);
+          uint32_t word = kFill | (((segs >> i) & 1u) ? grp_of[i] : grp_of[i] - cp - 1u);
+          if (kFmt == kFmtPlwah && !((mains >> i) & 1u)) word |= (1u + bit_of[i]) << kPlwahShift;
+          s_words[--w] = word;
         }
       }
     }
@@ -362,18 +472,19 @@ __global__ __launch_bounds__(kEncBlock, 8) void k_wah_write(const KeyT* __restri
   if (tid < 64) {
     LbPairSum pre{0u, 0u};
     if (tile > 0) {
-      pre = lb_lookback_st<kLbSpread>(status, tile, LbPair{}, spin_limit,
-                                      [&](uint32_t u) { return wave_tile_count(skeys, srows, n, u, br); });
+      pre = lb_lookback_st<kLbSpread>(status, tile, LbPair{}, spin_limit, [&](uint32_t u) {
+        return wave_tile_count<kTile, kFmt>(skeys, srows, n, u, br);
+      });
       if (tid == 0)
         lb_publish_raw(status + kLbSpread * tile, lb_pack_pair(pre.a + tile_nw, pre.b + tile_ns, kLbInclusive));
     }
     if (tid == 0) {
-      s_pre[0] = pre.a;
-      s_pre[1] = pre.b;
+      L.pre[0] = pre.a;
+      L.pre[1] = pre.b;
     }
   }
   __syncthreads();
-  const uint32_t wpre = s_pre[0], dpre = s_pre[1];
+  const uint32_t wpre = L.pre[0], dpre = L.pre[1];
 
   // ---- words, then the lookup-table entries of the values starting here ----------------
   // Four words per work-item and step: an aligned 16-byte LDS read and a
@@ -382,9 +493,9 @@ __global__ __launch_bounds__(kEncBlock, 8) void k_wah_write(const KeyT* __restri
   // Zipf pairs).
   {
     const uint32_t nv = tile_nw / 4;
-    for (uint32_t v = tid; v < nv; v += kEncBlock)
-      *reinterpret_cast<u32x4w*>(out_words + wpre + 4 * v) = *reinterpret_cast<const u32x4*>(s_words + 4 * v);
-    if (tid < tile_nw - 4 * nv) out_words[wpre + 4 * nv + tid] = s_words[4 * nv + tid];
+    for (uint32_t v = tid; v < nv; v += kBlock)
+      *reinterpret_cast<u32x4w*>(out.words + wpre + 4 * v) = *reinterpret_cast<const u32x4*>(s_words + 4 * v);
+    if (tid < tile_nw - 4 * nv) out.words[wpre + 4 * nv + tid] = s_words[4 * nv + tid];
   }
   if (segs) {
     const uint32_t ls = packed_pre >> 16;  // tile-local index of this work-item's first value
@@ -393,18 +504,18 @@ __global__ __launch_bounds__(kEncBlock, 8) void k_wah_write(const KeyT* __restri
       if ((segs >> i) & 1u) {
         const uint32_t below = (1u << i) - 1u;
         const uint32_t d = dpre + ls + (uint32_t)__popc(segs & below);
-        out_keys[d] = key[i];
-        out_offsets[d] = wpre + wbeg + (uint32_t)__popc(heads & below) + (uint32_t)__popc(gaps & below);
+        out.keys[d] = key[i];
+        out.offsets[d] = wpre + wbeg + (uint32_t)__popc(mains & below) + (uint32_t)__popc(gaps & below);
       }
     }
   }
   if (base + tile_n == n && tid == 0) {  // the last tile: totals and lengths
     const uint32_t D = dpre + tile_ns, W = wpre + tile_nw;
-    out_offsets[D] = W;
+    out.offsets[D] = W;
     const bool void_ = rej();
-    *len_keys = void_ ? 0u : D;
-    *len_offsets = void_ ? 0u : (uint64_t)D + 1;
-    *len_words = void_ ? 0u : W;
+    *out.len_keys = void_ ? 0u : D;
+    *out.len_offsets = void_ ? 0u : (uint64_t)D + 1;
+    *out.len_words = void_ ? 0u : W;
   }
 }
 
@@ -415,60 +526,65 @@ __global__ void k_wah_clear(uint64_t* __restrict__ status, uint32_t ntiles) {
   if (i < ntiles) status[kLbSpread * i] = 0ull;
 }
 
-template <class KeyT>
-int encode_impl(Env& env, const KeyT* skeys, const uint32_t* srows, uint64_t n, uint32_t* keys, uint32_t* offsets,
-                uint32_t* words, uint64_t* d_len_keys, uint64_t* d_len_offsets, uint64_t* d_len_words,
-                const uint32_t* req_base, uint32_t req_shift, const uint32_t* reject_flag, uint32_t reject_shift,
-                const uint64_t* d_n) {
-  if (!offsets || !d_len_keys || !d_len_offsets || !d_len_words)
-    return env.fail(kErrArg, "wah_encode_sorted: null output");
-  if (n >= (1ull << 30)) return env.fail(kErrArg, "wah_encode_sorted: n must be below 2^30");
-  if (n && (!skeys || !srows || !keys || !words)) return env.fail(kErrArg, "wah_encode_sorted: null buffer");
-  const uint32_t ntiles = (uint32_t)((n + kEncTile - 1) / kEncTile);
-  if (!ntiles) {
-    k_wah_empty<<<dim3(1), dim3(64), 0, env.stream()>>>(offsets, d_len_keys, d_len_offsets, d_len_words);
-    return check_launch(env, "wah_empty launch");
-  }
+template <int kFmt, class KeyT>
+int encode_fmt(Env& env, const KeyT* skeys, const uint32_t* srows, uint32_t n, const IndexOut& out,
+               const EncodeOpts& opt) {
+  constexpr int kBlock = kEncBlock, kTile = EncLds<kBlock, kFmt>::kTile;
+  const uint32_t ntiles = (n + kTile - 1) / kTile;
   // The (words, values) chain has no epoch: its own status words, zeroed here.
   uint64_t* status = static_cast<uint64_t*>(env.scratch(8ull * kLbSpread * ntiles));
-  if (!status) return env.fail(kErrOom, "wah_encode_sorted: look-back status words");
-  int rc;
+  if (!status) return env.fail(kErrOom, "wah encoder: look-back status words");
   k_wah_clear<<<dim3((ntiles + 255) / 256), dim3(256), 0, env.stream()>>>(status, ntiles);
-  if ((rc = check_launch(env, "wah_clear launch"))) return rc;
+  const int rc = check_launch(env, "wah_clear launch");
+  if (rc) return rc;
   constexpr uintptr_t kKeyAlign = sizeof(KeyT) == 4 ? 15u : 7u;
   const bool vec = ((reinterpret_cast<uintptr_t>(skeys) & kKeyAlign) | (reinterpret_cast<uintptr_t>(srows) & 15u)) == 0;
-  const BatchRows br{req_base, req_shift};
-  const Reject rej{reject_flag, reject_shift};
-  const uint32_t nn = (uint32_t)n;
+  const BatchRows br{opt.req_base, opt.req_shift};
+  const Reject rej{opt.reject_flag, opt.reject_shift};
   env.prof_begin("wah_write");
   if (vec)
-    k_wah_write<true, KeyT><<<dim3(ntiles), dim3(kEncBlock), 0, env.stream()>>>(
-        skeys, srows, nn, d_n, status, env.spin_limit(), keys, offsets, words, br, rej, d_len_keys, d_len_offsets,
-        d_len_words);
+    k_wah_write<kBlock, kFmt, true, KeyT><<<dim3(ntiles), dim3(kBlock), 0, env.stream()>>>(
+        skeys, srows, n, opt.d_n, status, env.spin_limit(), out, br, rej);
   else
-    k_wah_write<false, KeyT><<<dim3(ntiles), dim3(kEncBlock), 0, env.stream()>>>(
-        skeys, srows, nn, d_n, status, env.spin_limit(), keys, offsets, words, br, rej, d_len_keys, d_len_offsets,
-        d_len_words);
+    k_wah_write<kBlock, kFmt, false, KeyT><<<dim3(ntiles), dim3(kBlock), 0, env.stream()>>>(
+        skeys, srows, n, opt.d_n, status, env.spin_limit(), out, br, rej);
   env.prof_end("wah_write");
   return check_launch(env, "wah_write launch");
 }
 
-}  // namespace
-
-int launch_wah_encode(Env& env, const uint32_t* skeys, const uint32_t* srows, uint64_t n, uint32_t* keys,
-                      uint32_t* offsets, uint32_t* words, uint64_t* d_len_keys, uint64_t* d_len_offsets,
-                      uint64_t* d_len_words, const uint32_t* req_base, uint32_t req_shift,
-                      const uint32_t* reject_flag, uint32_t reject_shift, const uint64_t* d_n) {
-  return encode_impl(env, skeys, srows, n, keys, offsets, words, d_len_keys, d_len_offsets, d_len_words, req_base,
-                     req_shift, reject_flag, reject_shift, d_n);
+template <class KeyT>
+int encode_impl(Env& env, const KeyT* skeys, const uint32_t* srows, uint64_t n, const IndexOut& out,
+                const EncodeOpts& opt) {
+  if (!out.offsets || !out.len_keys || !out.len_offsets || !out.len_words)
+    return env.fail(kErrArg, "wah encoder: null output");
+  if (n >= (1ull << 30)) return env.fail(kErrArg, "wah encoder: n must be below 2^30");
+  if (n && (!skeys || !srows || !out.keys || !out.words)) return env.fail(kErrArg, "wah encoder: null buffer");
+  if (n == 0) {
+    k_wah_empty<<<dim3(1), dim3(64), 0, env.stream()>>>(out);
+    return check_launch(env, "wah_empty launch");
+  }
+  switch (opt.format) {
+    case kFmtPaper:
+      return encode_fmt<kFmtPaper>(env, skeys, srows, (uint32_t)n, out, opt);
+    case kFmtCanonical:
+      return encode_fmt<kFmtCanonical>(env, skeys, srows, (uint32_t)n, out, opt);
+    case kFmtPlwah:
+      return encode_fmt<kFmtPlwah>(env, skeys, srows, (uint32_t)n, out, opt);
+    default:
+      return env.fail(kErrArg, "unknown WAH format");
+  }
 }
 
-int launch_wah_encode16(Env& env, const uint16_t* skeys, const uint32_t* srows, uint64_t n, uint32_t* keys,
-                        uint32_t* offsets, uint32_t* words, uint64_t* d_len_keys, uint64_t* d_len_offsets,
-                        uint64_t* d_len_words, const uint32_t* reject_flag, uint32_t reject_shift,
-                        const uint64_t* d_n) {
-  return encode_impl(env, skeys, srows, n, keys, offsets, words, d_len_keys, d_len_offsets, d_len_words, nullptr, 32u,
-                     reject_flag, reject_shift, d_n);
+}  // namespace
+
+int launch_wah_encode(Env& env, const uint32_t* skeys, const uint32_t* srows, uint64_t n, const IndexOut& out,
+                      const EncodeOpts& opt) {
+  return encode_impl(env, skeys, srows, n, out, opt);
+}
+
+int launch_wah_encode16(Env& env, const uint16_t* skeys, const uint32_t* srows, uint64_t n, const IndexOut& out,
+                        const EncodeOpts& opt) {
+  return encode_impl(env, skeys, srows, n, out, opt);
 }
 
 }  // namespace ka

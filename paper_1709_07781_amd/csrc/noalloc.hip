@@ -111,7 +111,7 @@ extern "C" KA_API int ka_wah_index_noalloc(const uint32_t* values, uint64_t n, u
     uint32_t* srows = static_cast<uint32_t*>(env.scratch(4 * (n ? n : 1)));
     if (!skeys || !srows) return set_error(KA_E_ARG, "ka_wah_index_noalloc: scratch exhausted");
     if ((rc = launch_radix_sort_pairs(env, values, nullptr, skeys, srows, n))) return rc;
-    return launch_wah_encode(env, skeys, srows, n, keys, offsets, words, lengths, lengths + 1, lengths + 2);
+    return launch_wah_encode(env, skeys, srows, n, IndexOut{keys, offsets, words, lengths, lengths + 1, lengths + 2});
   } catch (...) {
     return set_error(KA_E_DEVICE, "unexpected internal error");
   }
