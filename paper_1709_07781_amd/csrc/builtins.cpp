@@ -139,6 +139,9 @@ int run_wah_index(LaunchCtx& c) {
   if (opt.format == 2 && n > 31ull * 0x1FFFFFFull)
     return env.fail(KA_E_ARG, "wah_index: PLWAH fill lengths (25 bits) cover at most 31 * (2^25 - 1) rows");
   if (n == 0) return launch_wah_encode(env, nullptr, nullptr, 0, out);
+  // One launch up to what one work-group holds, faster over its whole range (us a request by the
+  // general path and by this one, 10-bit values: 300 71 / 40, 8192 78 / 50; any uint32: 8192 130 / 67).
+  if (n <= kSmallIndexMax) return launch_wah_small(env, values, n, bits, out, opt);
   int rc;
   uint32_t* sr = static_cast<uint32_t*>(env.scratch(4 * n));
   if (bits >= 1 && bits <= 16) {

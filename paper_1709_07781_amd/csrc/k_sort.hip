@@ -349,31 +349,6 @@ __global__ __launch_bounds__(kPlanBlock) void k_radix_plan(const uint32_t* __res
 // ---------------------------------------------------------------------------------
 // scatter: one tile, ranked in LDS, written to its offsets
 // ---------------------------------------------------------------------------------
-// Bit B of d spread over the word: 0 or ~0 (one v_bfe_i32; the compiler
-// otherwise emits a shift pair).
-template <int B>
-__device__ __forceinline__ uint32_t spread_bit(uint32_t d) {
-  uint32_t s;
-  asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(s) : "v"(d), "n"(B));
-  return s;
-}
-
-// Adds to (lo, hi) the lanes whose digit differs from this lane's in bit B or
-// B+1: for each bit, the ballot of the bit XOR this lane's bit spread over the
-// word.  One v_bitop3_b32 per bit and half computes lo | (m ^ s) (truth table
-// 0xF6 with operands in the order lo, m, s); together with the ballot's
-// compare and the extract that is 4 instructions per digit bit, which matters
-// because the scatter is bound by instruction issue, not by HBM.
-template <int B>
-__device__ __forceinline__ void differing_lanes(uint32_t d, uint32_t& lo, uint32_t& hi) {
-  const uint32_t s0 = spread_bit<B>(d), s1 = spread_bit<B + 1>(d);
-  const uint64_t m0 = __ballot(s0 != 0), m1 = __ballot(s1 != 0);
-  lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)m0, s0, 0xF6);
-  hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(m0 >> 32), s0, 0xF6);
-  lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)m1, s1, 0xF6);
-  hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(m1 >> 32), s1, 0xF6);
-}
-
 template <int kBlock, int kItems>
 struct ScatterLds {
   static constexpr int kWaves = kBlock / 64;

@@ -221,14 +221,133 @@ struct Reject {
 };
 
 // ---------------------------------------------------------------------------------
+// the sort of a small input inside one work-group
+// ---------------------------------------------------------------------------------
+// n <= 1024 * kItems values: sorted by value, equal values in row order, into
+// s_k (values) and s_r (rows) at their padded places; wave w owns 64 kItems
+// consecutive elements.  8-bit digits over the bits that differ between the
+// values at all, ranked inside each wave by ballots.  Returns the OR of the
+// values.  Ends with a barrier.
+constexpr int kSmallBlock = 1024;
+constexpr int kSmallWaves = kSmallBlock / 64;
+template <int kItems>
+__device__ __forceinline__ uint32_t small_sort(const uint32_t* __restrict__ values, uint32_t n, uint32_t* s_k,
+                                               uint32_t* s_r, uint16_t (*s_cnt)[256], uint32_t* s_scan,
+                                               uint32_t* s_or, uint32_t* s_and) {
+  const uint32_t tid = threadIdx.x, w = tid / 64, lane = lane_id();
+  const uint32_t i0 = w * 64 * kItems + lane;  // elements i0 + 64 i
+  uint32_t key[kItems], row[kItems];
+#pragma unroll
+  for (int i = 0; i < kItems; ++i) {
+    row[i] = i0 + 64 * i;
+    key[i] = row[i] < n ? values[row[i]] : 0u;
+  }
+  uint32_t o = 0, a = ~0u;
+#pragma unroll
+  for (int i = 0; i < kItems; ++i) {
+    o |= key[i];
+    if (row[i] < n) a &= key[i];
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    o |= (uint32_t)__shfl_xor((int)o, off);
+    a &= (uint32_t)__shfl_xor((int)a, off);
+  }
+  if (lane == 0) {
+    s_or[w] = o;
+    s_and[w] = a;
+  }
+  __syncthreads();
+  o = 0, a = ~0u;
+#pragma unroll
+  for (int ww = 0; ww < kSmallWaves; ++ww) {
+    o |= s_or[ww];
+    a &= s_and[ww];
+  }
+  const uint32_t diff = (uint32_t)__builtin_amdgcn_readfirstlane((int)(o ^ a));  // bits in which values differ
+  const uint32_t lo = diff ? (uint32_t)__builtin_ctz(diff) : 32u, hi = diff ? 32u - (uint32_t)__builtin_clz(diff) : 0u;
+  if (!diff) {  // all values equal: in order already
+#pragma unroll
+    for (int i = 0; i < kItems; ++i)
+      if (row[i] < n) {
+        s_k[pidx(row[i])] = key[i];
+        s_r[pidx(row[i])] = row[i];
+      }
+  }
+  for (uint32_t shift = lo; shift < hi; shift += 8) {
+    for (int i = tid; i < kSmallWaves * 256 / 2; i += kSmallBlock) reinterpret_cast<uint32_t*>(&s_cnt[0][0])[i] = 0u;
+    if (shift != lo) {  // what the pass before has placed
+#pragma unroll
+      for (int i = 0; i < kItems; ++i)
+        if (i0 + 64 * i < n) {
+          key[i] = s_k[pidx(i0 + 64 * i)];
+          row[i] = s_r[pidx(i0 + 64 * i)];
+        }
+    }
+    __syncthreads();
+    uint32_t rank[kItems];
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+      const bool valid = i0 + 64 * i < n;
+      const uint32_t d = (key[i] >> shift) & 255u;
+      uint32_t dl = 0, dh = 0;
+      differing_lanes<0>(d, dl, dh);
+      differing_lanes<2>(d, dl, dh);
+      differing_lanes<4>(d, dl, dh);
+      differing_lanes<6>(d, dl, dh);
+      const uint64_t peers = __builtin_amdgcn_ballot_w64(valid) & ~(((uint64_t)dh << 32) | dl);
+      rank[i] = 0;
+      if (valid) {
+        const uint32_t below =
+            __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0u));
+        const uint32_t old = s_cnt[w][d];
+        if (below == 0) s_cnt[w][d] = (uint16_t)(old + (uint32_t)__popcll(peers));
+        rank[i] = old + below;
+      }
+    }
+    __syncthreads();
+    uint32_t cnt[kSmallWaves], total = 0, all;
+    if (tid < 256) {
+#pragma unroll
+      for (int ww = 0; ww < kSmallWaves; ++ww) {
+        cnt[ww] = total;
+        total += s_cnt[ww][tid];
+      }
+    }
+    const uint32_t start = block_excl_scan<kSmallBlock>(total, s_scan, &all);
+    if (tid < 256) {
+#pragma unroll
+      for (int ww = 0; ww < kSmallWaves; ++ww) s_cnt[ww][tid] = (uint16_t)(start + cnt[ww]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kItems; ++i)
+      if (i0 + 64 * i < n) {
+        const uint32_t p = pidx(s_cnt[w][(key[i] >> shift) & 255u] + rank[i]);
+        s_k[p] = key[i];
+        s_r[p] = row[i];
+      }
+    __syncthreads();
+  }
+  __syncthreads();
+  return o;
+}
+
+// ---------------------------------------------------------------------------------
 // write: literals, fills and lookup-table entries of one tile
 // ---------------------------------------------------------------------------------
 // The other formats take up to 83 VGPRs (one work-group per CU): held to 64
 // they spill.
 // One work-group per tile; status[kLbSpread * tile] is the tile's (words, values)
 // look-back word, zeroed before the launch.
-template <int kBlock, int kFmt, bool kVec, class KeyT>
-__global__ __launch_bounds__(kBlock, kFmt == kFmtPaper ? 8 : 4) void k_wah_write(const KeyT* __restrict__ skeys,
+//
+// kSort > 0: the one work-group sorts the input itself, at most 1024 * kSort
+// values (skeys; no rows, no status), and the index is whole after this launch.
+// A small request is latency: eight launches of one or a few work-groups each
+// (two passes of count, scan and scatter, then clear and encode) and the gaps
+// between them took 56 us of a request of 777 values.
+template <int kBlock, int kFmt, bool kVec, int kSort, class KeyT>
+__global__ __launch_bounds__(kBlock, kFmt == kFmtPaper && !kSort ? 8 : 4) void k_wah_write(const KeyT* __restrict__ skeys,
                                                          const uint32_t* __restrict__ srows, uint32_t n_cap,
                                                          const uint64_t* __restrict__ d_n,
                                                          uint64_t* __restrict__ status, uint32_t spin_limit,
@@ -248,13 +367,19 @@ __global__ __launch_bounds__(kBlock, kFmt == kFmtPaper ? 8 : 4) void k_wah_write
     if (tile == 0 && tid == 0) write_empty_index(out);
     return;
   }
+  uint32_t small_or = 0;
   const uint32_t tile_n = min((uint32_t)kTile, n - base);
   const uint32_t avail = min((uint32_t)(kTile + kLook), n - base);  // readable from base on
 
+  if constexpr (kSort > 0) {
+    __shared__ __align__(16) uint16_t s_cnt[kSmallWaves][256];
+    __shared__ uint32_t s_or[kSmallWaves], s_and[kSmallWaves];
+    small_or = small_sort<kSort>(skeys, n, s_k, s_r, s_cnt, L.scan, s_or, s_and);
+  }
   // ---- stage elements base .. base+kTile+kLook-1 into slots 0.. ---------------
   // Work-items 64.. also load the look-ahead (slots kTile ..) and the kBehind
   // elements before base.
-  {
+  if constexpr (kSort == 0) {
     uint32_t vk[kVecs][4], vr[kVecs][4];
     load_pairs<kBlock, kVec>(skeys, srows, base, tile_n, tid, vk, vr);
     const bool extra = tid >= 64 && tid < 64 + kLook + kBehind;
@@ -286,8 +411,8 @@ __global__ __launch_bounds__(kBlock, kFmt == kFmtPaper ? 8 : 4) void k_wah_write
         s_r[sl] = xr;
       }
     }
+    __syncthreads();
   }
-  __syncthreads();
 
   // ---- this work-item's kEncItems consecutive elements, in registers: key, the
   // row's group (row / 31) and its bit inside the group; elements past the
@@ -361,7 +486,7 @@ __global__ __launch_bounds__(kBlock, kFmt == kFmtPaper ? 8 : 4) void k_wah_write
 
   // ---- publish the tile's counts at once: successors find them while this
   // tile builds its words --------------------------------------------------------------
-  if (tid == 0)
+  if (!kSort && tid == 0)
     lb_publish_raw(status + kLbSpread * tile,
                    lb_pack_pair(tile_nw, tile_ns, tile == 0 ? kLbInclusive : kLbAggregate));
 
@@ -471,7 +596,7 @@ __global__ __launch_bounds__(kBlock, kFmt == kFmtPaper ? 8 : 4) void k_wah_write
   // ---- the tile's first word and value: look back over the earlier tiles (wave 0)
   if (tid < 64) {
     LbPairSum pre{0u, 0u};
-    if (tile > 0) {
+    if (!kSort && tile > 0) {
       pre = lb_lookback_st<kLbSpread>(status, tile, LbPair{}, spin_limit, [&](uint32_t u) {
         return wave_tile_count<kTile, kFmt>(skeys, srows, n, u, br);
       });
@@ -512,7 +637,7 @@ __global__ __launch_bounds__(kBlock, kFmt == kFmtPaper ? 8 : 4) void k_wah_write
   if (base + tile_n == n && tid == 0) {  // the last tile: totals and lengths
     const uint32_t D = dpre + tile_ns, W = wpre + tile_nw;
     out.offsets[D] = W;
-    const bool void_ = rej();
+    const bool void_ = kSort ? rej.shift < 32 && (small_or >> rej.shift) != 0u : rej();
     *out.len_keys = void_ ? 0u : D;
     *out.len_offsets = void_ ? 0u : (uint64_t)D + 1;
     *out.len_words = void_ ? 0u : W;
@@ -543,13 +668,33 @@ int encode_fmt(Env& env, const KeyT* skeys, const uint32_t* srows, uint32_t n, c
   const Reject rej{opt.reject_flag, opt.reject_shift};
   env.prof_begin("wah_write");
   if (vec)
-    k_wah_write<kBlock, kFmt, true, KeyT><<<dim3(ntiles), dim3(kBlock), 0, env.stream()>>>(
+    k_wah_write<kBlock, kFmt, true, 0, KeyT><<<dim3(ntiles), dim3(kBlock), 0, env.stream()>>>(
         skeys, srows, n, opt.d_n, status, env.spin_limit(), out, br, rej);
   else
-    k_wah_write<kBlock, kFmt, false, KeyT><<<dim3(ntiles), dim3(kBlock), 0, env.stream()>>>(
+    k_wah_write<kBlock, kFmt, false, 0, KeyT><<<dim3(ntiles), dim3(kBlock), 0, env.stream()>>>(
         skeys, srows, n, opt.d_n, status, env.spin_limit(), out, br, rej);
   env.prof_end("wah_write");
   return check_launch(env, "wah_write launch");
+}
+
+template <int kFmt>
+void small_fmt(Env& env, const uint32_t* values, uint32_t n, const IndexOut& out, const EncodeOpts& opt,
+               const Reject& rej) {
+  static_assert(kSmallIndexMax == kSmallBlock * 8, "the largest small input fills the work-group");
+  const dim3 g(1), b(kSmallBlock);
+#define KA_SMALL(I)                                                                                          \
+  k_wah_write<kSmallBlock, kFmt, false, I, uint32_t><<<g, b, 0, env.stream()>>>(values, nullptr, n, opt.d_n, \
+                                                                                 nullptr, 0u, out, BatchRows{}, rej)
+  // values per work-item of the sort: each costs a ranking step in every pass
+  if (n <= 1024)
+    KA_SMALL(1);
+  else if (n <= 2048)
+    KA_SMALL(2);
+  else if (n <= 4096)
+    KA_SMALL(4);
+  else
+    KA_SMALL(8);
+#undef KA_SMALL
 }
 
 template <class KeyT>
@@ -580,6 +725,30 @@ int encode_impl(Env& env, const KeyT* skeys, const uint32_t* srows, uint64_t n, 
 int launch_wah_encode(Env& env, const uint32_t* skeys, const uint32_t* srows, uint64_t n, const IndexOut& out,
                       const EncodeOpts& opt) {
   return encode_impl(env, skeys, srows, n, out, opt);
+}
+
+int launch_wah_small(Env& env, const uint32_t* values, uint64_t n, uint32_t value_bits, const IndexOut& out,
+                     const EncodeOpts& opt) {
+  if (!values || !out.keys || !out.offsets || !out.words || !out.len_keys || !out.len_offsets || !out.len_words)
+    return env.fail(kErrArg, "wah index: null buffer");
+  if (n == 0 || n > kSmallIndexMax) return env.fail(kErrArg, "wah index: not a small input");
+  const Reject rej{nullptr, value_bits >= 1 && value_bits <= 31 ? value_bits : 32u};
+  env.prof_begin("wah_small");
+  switch (opt.format) {
+    case kFmtPaper:
+      small_fmt<kFmtPaper>(env, values, (uint32_t)n, out, opt, rej);
+      break;
+    case kFmtCanonical:
+      small_fmt<kFmtCanonical>(env, values, (uint32_t)n, out, opt, rej);
+      break;
+    case kFmtPlwah:
+      small_fmt<kFmtPlwah>(env, values, (uint32_t)n, out, opt, rej);
+      break;
+    default:
+      return env.fail(kErrArg, "unknown WAH format");
+  }
+  env.prof_end("wah_small");
+  return check_launch(env, "wah_small launch");
 }
 
 int launch_wah_encode16(Env& env, const uint16_t* skeys, const uint32_t* srows, uint64_t n, const IndexOut& out,

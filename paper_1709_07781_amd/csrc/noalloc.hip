@@ -104,6 +104,8 @@ extern "C" KA_API int ka_wah_index_noalloc(const uint32_t* values, uint64_t n, u
     int rc = scratch_address(dev, &base);
     if (rc) return rc;
     NoAllocEnv env(static_cast<char*>(base), static_cast<hipStream_t>(stream));
+    const IndexOut out{keys, offsets, words, lengths, lengths + 1, lengths + 2};
+    if (n && n <= kSmallIndexMax) return launch_wah_small(env, values, n, 0, out);
     // Status words start at zero in every call (a fill kernel: no memset node
     // if the caller captures the call into a graph).
     if ((rc = launch_fill_u64(env, reinterpret_cast<uint64_t*>(base), kStatusWords, 0))) return rc;
@@ -111,7 +113,7 @@ extern "C" KA_API int ka_wah_index_noalloc(const uint32_t* values, uint64_t n, u
     uint32_t* srows = static_cast<uint32_t*>(env.scratch(4 * (n ? n : 1)));
     if (!skeys || !srows) return set_error(KA_E_ARG, "ka_wah_index_noalloc: scratch exhausted");
     if ((rc = launch_radix_sort_pairs(env, values, nullptr, skeys, srows, n))) return rc;
-    return launch_wah_encode(env, skeys, srows, n, IndexOut{keys, offsets, words, lengths, lengths + 1, lengths + 2});
+    return launch_wah_encode(env, skeys, srows, n, out);
   } catch (...) {
     return set_error(KA_E_DEVICE, "unexpected internal error");
   }

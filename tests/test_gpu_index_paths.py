@@ -77,3 +77,29 @@ def test_formats_with_fallback(impatient, fmt):
     n = 300 * ENC_TILE + 77
     for v in columns(n).values():
         check(impatient, v, 12, fmt)
+
+
+SMALL_MAX = 8192
+
+
+@pytest.mark.parametrize("fmt", [0, 1, 2])
+@pytest.mark.parametrize("n", [1, 63, 1024, 1025, 2049, 4096, 4097, SMALL_MAX - 1, SMALL_MAX, SMALL_MAX + 1])
+def test_small_inputs(sess, fmt, n):
+    """One work-group's sort and encode: each count of values per work-item, digits that start at any bit, equal
+    values, all values distinct."""
+    u = workloads.u32(n + fmt, n)
+    cases = [(u % 1024, 10), (u, 0), (u & np.uint32(0x00FFF000), 24), (np.full(n, 1 << 31, np.uint32), 32),
+             (np.arange(n, dtype=np.uint32)[::-1].copy(), 14), (columns(n)["thirty"], 8)]
+    for v, bits in cases:
+        check(sess, v.astype(np.uint32), bits, fmt)
+
+
+@pytest.mark.parametrize("bits", [1, 9, 16, 31])
+def test_small_input_beyond_its_hint(sess, bits):
+    from paper_1709_07781_amd import KaError
+    v = np.zeros(5000, np.uint32)
+    v[4999] = 1 << bits
+    with pytest.raises(KaError):
+        sess.wah_index(v, value_bits=bits)
+    v[4999] -= 1
+    check(sess, v, bits, 0)
