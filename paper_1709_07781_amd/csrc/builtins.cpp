@@ -143,19 +143,21 @@ int run_wah_index(LaunchCtx& c) {
   // general path and by this one, 10-bit values: 300 71 / 40, 8192 78 / 50; any uint32: 8192 130 / 67).
   if (n <= kSmallIndexMax) return launch_wah_small(env, values, n, bits, out, opt);
   int rc;
+  opt.cleared = wah_status(env, n);
+  if (!opt.cleared.p) return env.fail(KA_E_OOM, "wah_index: scratch");
   uint32_t* sr = static_cast<uint32_t*>(env.scratch(4 * n));
   if (bits >= 1 && bits <= 16) {
     uint32_t* reject = static_cast<uint32_t*>(env.scratch(4));
     uint16_t* sk = static_cast<uint16_t*>(env.scratch(2 * n));
     if (!reject || !sk || !sr) return env.fail(KA_E_OOM, "wah_index: scratch");
-    if ((rc = launch_radix_sort_rows16(env, values, sk, sr, n, bits, reject, 0, opt.d_n))) return rc;
+    if ((rc = launch_radix_sort_rows16(env, values, sk, sr, n, bits, reject, opt.d_n, opt.cleared))) return rc;
     opt.reject_flag = reject;
     opt.reject_shift = 0;
     return launch_wah_encode16(env, sk, sr, n, out, opt);
   }
   uint32_t* sk = static_cast<uint32_t*>(env.scratch(4 * n));
   if (!sk || !sr) return env.fail(KA_E_OOM, "wah_index: scratch");
-  if ((rc = launch_radix_sort_pairs(env, values, nullptr, sk, sr, n, 0, opt.d_n))) return rc;
+  if ((rc = launch_radix_sort_pairs(env, values, nullptr, sk, sr, n, 0, opt.d_n, opt.cleared))) return rc;
   if (bits >= 17 && bits <= 31) {
     opt.reject_flag = sort_plan_keys_or(env);
     opt.reject_shift = bits;

@@ -38,6 +38,13 @@ struct LbArgs {
 
 constexpr uint32_t kLbSpinLimit = 16;  // the default spin_limit
 
+// Status slots of every look-back chain: one status word per 64-byte line,
+// at status[kLbSpread * tile].  Each slot is stored twice (aggregate, then
+// inclusive) while later tiles poll it, and with eight words to a line those
+// stores and polls queue on the same lines: the WAH encoder over 2^26 Zipf
+// pairs took 228 us packed and 215 us spread (4 to 32 words apart: 214-216 us).
+constexpr uint32_t kLbSpread = 8;
+
 class Env {
  public:
   virtual ~Env() = default;
@@ -67,8 +74,15 @@ int launch_affine(Env& env, uint32_t* x, uint64_t n_cap, const uint64_t* d_n, ui
 int launch_exclusive_scan(Env& env, const uint32_t* in, uint32_t* out, uint64_t n_cap, const uint64_t* d_n);
 int launch_compact_nonzero(Env& env, const uint32_t* in, uint32_t* out, uint64_t n_cap, const uint64_t* d_n,
                            uint64_t* d_out_len);
+// Look-back words (count of them, kLbSpread apart) that a sort's first launch
+// zeroes for the encoder after it.
+struct ClearWords {
+  uint64_t* p = nullptr;
+  uint32_t count = 0;
+};
 int launch_radix_sort_pairs(Env& env, const uint32_t* keys, const uint32_t* rows, uint32_t* skeys,
-                            uint32_t* srows, uint64_t n, int shape = 0, const uint64_t* d_n = nullptr);
+                            uint32_t* srows, uint64_t n, int shape = 0, const uint64_t* d_n = nullptr,
+                            ClearWords cw = {});
 // Number of tile shapes launch_radix_sort_pairs offers (shape 0 is the default).
 int sort_shape_count();
 // Number of variants of the batched index build (its sort_shape argument):
@@ -94,7 +108,8 @@ const uint32_t* sort_plan_keys_or(Env& env);
 // 1..16, with uint16 sorted keys; a key at or above 2^value_bits sets
 // *reject to 1 (0 otherwise; *reject is device memory).
 int launch_radix_sort_rows16(Env& env, const uint32_t* keys, uint16_t* skeys, uint32_t* srows, uint64_t n,
-                             uint32_t value_bits, uint32_t* reject, int shape = 0, const uint64_t* d_n = nullptr);
+                             uint32_t value_bits, uint32_t* reject, const uint64_t* d_n = nullptr,
+                             ClearWords cw = {});
 // Where an index goes, and its three device-resident lengths.
 struct IndexOut {
   uint32_t *keys, *offsets, *words;
@@ -112,7 +127,11 @@ struct EncodeOpts {
   const uint64_t* d_n = nullptr;
   const uint32_t* req_base = nullptr;
   uint32_t req_shift = 32;
+  ClearWords cleared;  // wah_status()'s words, zeroed by an earlier launch; none: the encoder zeroes its own
 };
+// The encoder's look-back words for n pairs (from env's scratch; p null if
+// that is exhausted), to be zeroed by the sort before it.
+ClearWords wah_status(Env& env, uint64_t n);
 // WAH encoder over sorted pairs.
 int launch_wah_encode(Env& env, const uint32_t* skeys, const uint32_t* srows, uint64_t n, const IndexOut& out,
                       const EncodeOpts& opt = {});
@@ -182,13 +201,6 @@ inline int check_launch(Env& env, const char* what) {
 
 constexpr uint32_t kLbAggregate = 1u;  // status flag: tile total only
 constexpr uint32_t kLbInclusive = 2u;  // status flag: prefix including the tile
-// Status slots of every look-back chain: one status word per 64-byte line,
-// at status[kLbSpread * tile].  Each slot is stored twice (aggregate, then
-// inclusive) while later tiles poll it, and with eight words to a line those
-// stores and polls queue on the same lines: the WAH encoder over 2^26 Zipf
-// pairs took 228 us packed and 215 us spread (4 to 32 words apart: 214-216 us).
-constexpr uint32_t kLbSpread = 8;
-
 __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
 
 // Native 4 x uint32 vector: one 16-byte global access.

@@ -155,22 +155,22 @@ __device__ __forceinline__ uint32_t tile_len(uint32_t tile, uint32_t kTile, uint
 // ---------------------------------------------------------------------------------
 // upsweep: digit counts of one tile into the digit-major table
 // ---------------------------------------------------------------------------------
-constexpr int kUpBlock = kRadix;                  // one work-item per digit when the counts are written
-constexpr int kUpWaves = kUpBlock / 64;
+constexpr int kUpBlock = kRadix;  // one work-item per digit when the counts are written
 
 // table[d * ntiles + tile] = number of keys of the tile with digit d.  The
 // exclusive scan of the table in this digit-major order is, entry by entry,
 // the position in the pass's output of the tile's first key with digit d.
 // All of a work-item's loads are issued before the first key is counted; with
 // kOrAnd the OR and the AND of the tile's keys are written too.
-// The tile is keys[base, base + len); digit d's count goes to
-// table[d * stride + col] (the plan-driven and fixed sorts: stride = tile
-// count, col = tile; the segmented sort: its request's part of the table).
-template <int kTile, int kRounds, bool kOrAnd, class SK>
+// The tile is keys[base, base + len); store(d, c) gets digit d's count (the
+// digit-major table: table[d * stride + col], the plan-driven and fixed sorts
+// with stride = tile count and col = tile, the segmented sort in its request's
+// part of the table; the tile-row sorts: rows[tile][d]).
+template <int kUpBlock, int kTile, int kRounds, bool kOrAnd, class SK, class Store>
 __device__ __forceinline__ void upsweep_tile(const SK* __restrict__ keys, uint32_t shift, uint32_t base, uint32_t len,
-                                             uint32_t* __restrict__ table, uint64_t col, uint64_t stride,
-                                             uint32_t tile, uint32_t* __restrict__ orand,
+                                             Store&& store, uint32_t tile, uint32_t* __restrict__ orand,
                                              uint32_t mask = kRadix - 1) {
+  constexpr int kUpWaves = kUpBlock / 64;
   constexpr int kUpVecs = kTile / 4 / kUpBlock;  // 4-key loads per work-item
   constexpr uintptr_t kAlign = 15;  // 16-byte loads
   __shared__ uint32_t s_hist[kUpWaves][kRadix];
@@ -181,11 +181,10 @@ __device__ __forceinline__ void upsweep_tile(const SK* __restrict__ keys, uint32
   // tile: key 8 (j/2 * kUpBlock + tid) + 4 (j mod 2) + c).
   uint32_t k[kUpVecs][4];
   if (len == (uint32_t)kTile && (reinterpret_cast<uintptr_t>(keys + base) & kAlign) == 0) {
-    if (sizeof(SK) == 2) {
+    if constexpr (sizeof(SK) == 2 && kUpVecs % 2 == 0) {
       // uint16 keys: 8 per 16-byte load (which keys a work-item holds does not
       // change the counts); half the loads of 8-byte ones: 40.5 -> 35.9 us for
       // the second pass over 2^26 keys
-      static_assert(kUpVecs % 2 == 0, "pairs of 4-key groups");
 #pragma unroll
       for (int j = 0; j < kUpVecs / 2; ++j) {
         const u32x4 a = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(keys + base) + j * kUpBlock + tid);
@@ -260,10 +259,12 @@ __device__ __forceinline__ void upsweep_tile(const SK* __restrict__ keys, uint32
     }
   }
   __syncthreads();
-  uint32_t c = 0;
+  if (kUpBlock == kRadix || tid < (uint32_t)kRadix) {
+    uint32_t c = 0;
 #pragma unroll
-  for (int ww = 0; ww < kUpWaves; ++ww) c += s_hist[ww][tid];
-  table[(uint64_t)tid * stride + col] = c;
+    for (int ww = 0; ww < kUpWaves; ++ww) c += s_hist[ww][tid];
+    store(tid, c);
+  }
   if (kOrAnd && tid == 0) {
     uint32_t o = 0, a = ~0u;
 #pragma unroll
@@ -276,22 +277,31 @@ __device__ __forceinline__ void upsweep_tile(const SK* __restrict__ keys, uint32
   }
 }
 
+// The look-back words of the encoder that follows the sort, zeroed by the
+// sort's first launch (work-group b takes words b, b + grid, ...).
+__device__ __forceinline__ void clear_words(const ClearWords& cw) {
+  if (threadIdx.x == 0)
+    for (uint32_t i = blockIdx.x; i < cw.count; i += gridDim.x) cw.p[kLbSpread * i] = 0ull;
+}
+
 // Plan-driven upsweep of pass `pass`; the pass-0 instance also writes the OR
 // and the AND of the tile's keys for the plan.
 template <bool kFirst, int kTile>
 __global__ __launch_bounds__(kUpBlock) void k_radix_upsweep(PassBuffers buf, const SortPlan* __restrict__ plan,
                                                             uint32_t* __restrict__ table, uint32_t* __restrict__ orand,
                                                             uint32_t pass, uint32_t n_cap, uint32_t ntiles,
-                                                            const uint64_t* __restrict__ d_n) {
+                                                            const uint64_t* __restrict__ d_n, ClearWords cw) {
   const uint32_t* keys = buf.keys_in;
+  if (kFirst) clear_words(cw);
   if (!kFirst) {
     const uint32_t active = plan->active;
     if (!((active >> pass) & 1u)) return;  // uniform over the grid
     keys = pass_io(buf, active, pass).src_keys;
   }
   const uint32_t tile = xcd_tile(blockIdx.x, ntiles);
-  upsweep_tile<kTile, kFirst ? 1 : -1, kFirst>(keys, pass * kRadixBits, tile * kTile, tile_len(tile, kTile, n_cap, d_n),
-                                              table, tile, ntiles, tile, orand);
+  upsweep_tile<kUpBlock, kTile, kFirst ? 1 : -1, kFirst>(
+      keys, pass * kRadixBits, tile * kTile, tile_len(tile, kTile, n_cap, d_n),
+      [&](uint32_t d, uint32_t c) { table[(uint64_t)d * ntiles + tile] = c; }, tile, orand);
 }
 
 // Upsweep of a fixed pass (no plan) over uint32 or uint16 keys.  Work-group 0
@@ -300,23 +310,34 @@ template <int kTile, int kRounds, class SK>
 __global__ __launch_bounds__(kUpBlock) void k_radix_count(const SK* __restrict__ keys, uint32_t* __restrict__ table,
                                                           uint32_t shift, uint32_t mask, uint32_t n_cap,
                                                           uint32_t ntiles, uint32_t* __restrict__ reject,
-                                                          const uint64_t* __restrict__ d_n) {
+                                                          const uint64_t* __restrict__ d_n, ClearWords cw) {
+  clear_words(cw);
   if (reject && blockIdx.x == 0 && threadIdx.x == 0) *reject = 0u;
   const uint32_t tile = xcd_tile(blockIdx.x, ntiles);
-  upsweep_tile<kTile, kRounds, false>(keys, shift, tile * kTile, tile_len(tile, kTile, n_cap, d_n), table, tile,
-                                      ntiles, tile, nullptr, mask);
+  upsweep_tile<kUpBlock, kTile, kRounds, false>(
+      keys, shift, tile * kTile, tile_len(tile, kTile, n_cap, d_n),
+      [&](uint32_t d, uint32_t c) { table[(uint64_t)d * ntiles + tile] = c; }, tile, nullptr, mask);
 }
 
-// The sort plan from the OR and the AND of every tile's keys: a pass moves
-// data unless its digit is the same in every key, i.e. the same in the OR and
-// the AND.  Also the length of each pass's table scan: the full table for an
-// active pass, 0 (nothing to scan) for a skipped one.  One work-group.
-constexpr int kPlanBlock = 1024;
-__global__ __launch_bounds__(kPlanBlock) void k_radix_plan(const uint32_t* __restrict__ orand, uint32_t ntiles,
-                                                           SortPlan* __restrict__ plan) {
-  __shared__ uint32_t s_or[kPlanBlock / 64], s_and[kPlanBlock / 64];
+// Passes that move data: those whose digit is not the same in every key, i.e.
+// differs between the OR and the AND of the keys (all keys equal: one pass
+// still moves them).
+__device__ __forceinline__ uint32_t active_passes(uint32_t keys_or, uint32_t keys_and) {
+  const uint32_t diff = keys_or ^ keys_and;
+  uint32_t act = 0;
+#pragma unroll
+  for (int p = 0; p < kPasses; ++p)
+    if ((diff >> (p * kRadixBits)) & (kRadix - 1)) act |= 1u << p;
+  return act ? act : 1u << (kPasses - 1);
+}
+
+// OR and AND over the tiles' (OR, AND) pairs, in every work-item; s_or and
+// s_and: kBlock / 64 words each.
+template <int kBlock>
+__device__ __forceinline__ void block_or_and(const uint32_t* __restrict__ orand, uint32_t ntiles, uint32_t* s_or,
+                                             uint32_t* s_and, uint32_t* keys_or, uint32_t* keys_and) {
   uint32_t o = 0, a = ~0u;
-  for (uint32_t t = threadIdx.x; t < ntiles; t += kPlanBlock) {
+  for (uint32_t t = threadIdx.x; t < ntiles; t += kBlock) {
     o |= orand[2 * t];
     a &= orand[2 * t + 1];
   }
@@ -330,16 +351,28 @@ __global__ __launch_bounds__(kPlanBlock) void k_radix_plan(const uint32_t* __res
     s_and[threadIdx.x / 64] = a;
   }
   __syncthreads();
+  o = 0, a = ~0u;
+#pragma unroll
+  for (int w = 0; w < kBlock / 64; ++w) {
+    o |= s_or[w];
+    a &= s_and[w];
+  }
+  *keys_or = o;
+  *keys_and = a;
+}
+
+// The sort plan from the OR and the AND of every tile's keys: a pass moves
+// data unless its digit is the same in every key, i.e. the same in the OR and
+// the AND.  Also the length of each pass's table scan: the full table for an
+// active pass, 0 (nothing to scan) for a skipped one.  One work-group.
+constexpr int kPlanBlock = 1024;
+__global__ __launch_bounds__(kPlanBlock) void k_radix_plan(const uint32_t* __restrict__ orand, uint32_t ntiles,
+                                                           SortPlan* __restrict__ plan) {
+  __shared__ uint32_t s_or[kPlanBlock / 64], s_and[kPlanBlock / 64];
+  uint32_t o, a;
+  block_or_and<kPlanBlock>(orand, ntiles, s_or, s_and, &o, &a);
   if (threadIdx.x == 0) {
-    for (int ww = 1; ww < kPlanBlock / 64; ++ww) {
-      o |= s_or[ww];
-      a &= s_and[ww];
-    }
-    const uint32_t diff = o ^ a;
-    uint32_t act = 0;
-    for (int p = 0; p < kPasses; ++p)
-      if ((diff >> (p * kRadixBits)) & (kRadix - 1)) act |= 1u << p;
-    if (act == 0) act = 1u << (kPasses - 1);  // all keys equal: one pass still moves them
+    const uint32_t act = active_passes(o, a);
     plan->active = act;
     plan->keys_or = o;
     for (int p = 0; p < kPasses; ++p) plan->scan_len[p] = ((act >> p) & 1u) ? (uint64_t)ntiles * kRadix : 0u;
@@ -570,13 +603,186 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter_fixed(PassIoT<SK, DK> 
                                                               reject);
 }
 
+// ---------------------------------------------------------------------------------
+// tile-row sorts: inputs of few tiles
+// ---------------------------------------------------------------------------------
+// With few tiles the scan of the digit table costs more as a launch of its own
+// than as a sum in every scatter work-group: the counts are kept tile by tile
+// (rows[tile][digit], uint16), and a scatter work-group adds up the rows before
+// its own, and all of them for the digits' totals, while its keys are on their
+// way.  A pass is two launches instead of three, and the tile shrinks with the
+// input so that there are about as many work-groups as CUs.  What bounds it is
+// the rows' traffic, tiles^2 * digits * 2 bytes out of L2, so wide digits stop
+// at 256 tiles and narrow ones at 512 (see row_shape).
+
+// This tile's output position of digit threadIdx.x (below kRadix): T rows of
+// 1 << kBits counts, this tile's is row `tile`; `origin` is added.  A wave
+// reads 512 bytes of rows at a time.  s_mem: 2 * kBlock / 64 * (1 << kBits)
+// words.  Ends with a barrier.
+template <int kBlock, int kBits>
+__device__ __forceinline__ uint32_t row_prefix(const uint16_t* __restrict__ rows, uint32_t T, uint32_t tile,
+                                               uint32_t origin, uint32_t* s_mem, uint32_t* s_scan) {
+  constexpr uint32_t kD = 1u << kBits, kWaves = kBlock / 64;
+  constexpr uint32_t kLanes = kD / 4, kRowsPer = 64 / kLanes;  // lanes per row, rows per wave and step
+  const uint32_t tid = threadIdx.x, w = tid / 64, lane = lane_id();
+  const uint32_t col = lane % kLanes, sub = lane / kLanes;
+  uint32_t bef[4] = {0, 0, 0, 0}, aft[4] = {0, 0, 0, 0};
+  const uint2* src = reinterpret_cast<const uint2*>(rows) + col;
+#pragma unroll 8
+  for (uint32_t r0 = w * kRowsPer; r0 < T; r0 += kWaves * kRowsPer) {
+    const uint32_t r = r0 + sub;
+    uint2 v = make_uint2(0u, 0u);
+    if (r < T) v = src[(uint64_t)r * kLanes];
+    const uint32_t c[4] = {v.x & 0xFFFFu, v.x >> 16, v.y & 0xFFFFu, v.y >> 16};
+    const bool b = r < tile;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      bef[i] += b ? c[i] : 0u;
+      aft[i] += b ? 0u : c[i];
+    }
+  }
+#pragma unroll
+  for (uint32_t off = kLanes; off < 64; off <<= 1) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      bef[i] += (uint32_t)__shfl_xor((int)bef[i], (int)off);
+      aft[i] += (uint32_t)__shfl_xor((int)aft[i], (int)off);
+    }
+  }
+  if (lane < kLanes) {
+    u32x4 b, a;
+    b.x = bef[0], b.y = bef[1], b.z = bef[2], b.w = bef[3];
+    a.x = aft[0], a.y = aft[1], a.z = aft[2], a.w = aft[3];
+    reinterpret_cast<u32x4*>(s_mem)[w * kLanes + col] = b;
+    reinterpret_cast<u32x4*>(s_mem)[(kWaves + w) * kLanes + col] = a;
+  }
+  __syncthreads();
+  uint32_t before = 0, total = 0;
+  if (tid < kD) {
+#pragma unroll
+    for (uint32_t ww = 0; ww < kWaves; ++ww) {
+      before += s_mem[ww * kD + tid];
+      total += s_mem[(kWaves + ww) * kD + tid];
+    }
+    total += before;
+  }
+  uint32_t all;
+  const uint32_t first = block_excl_scan<kBlock>(total, s_scan, &all);
+  __syncthreads();
+  return origin + first + before;
+}
+
+// Counts of one tile into its row.  The first pass also zeroes the encoder's
+// look-back words and *reject, and (kOrAnd) records the OR and AND of the
+// tile's keys.
+template <int kBlock, int kItems, int kRounds, class SK>
+__global__ __launch_bounds__(kBlock) void k_rows_count(const SK* __restrict__ keys, uint16_t* __restrict__ rows,
+                                                       uint32_t shift, uint32_t bits, uint32_t n_cap, uint32_t ntiles,
+                                                       uint32_t* __restrict__ reject,
+                                                       const uint64_t* __restrict__ d_n, ClearWords cw) {
+  constexpr int kTile = kBlock * kItems;
+  clear_words(cw);
+  if (reject && blockIdx.x == 0 && threadIdx.x == 0) *reject = 0u;
+  const uint32_t tile = xcd_tile(blockIdx.x, ntiles);
+  uint16_t* const row = rows + ((uint64_t)tile << bits);
+  upsweep_tile<kBlock, kTile, kRounds, false>(
+      keys, shift, tile * kTile, tile_len(tile, kTile, n_cap, d_n),
+      [&](uint32_t d, uint32_t c) {
+        if (d >> bits == 0u) row[d] = (uint16_t)c;
+      },
+      tile, nullptr, (1u << bits) - 1u);
+}
+
+template <int kBlock, int kItems, bool kCheck, int kBits, class SK, class DK>
+__global__ __launch_bounds__(kBlock) void k_rows_scatter(PassIoT<SK, DK> io, const uint16_t* __restrict__ rows,
+                                                         uint32_t shift, uint32_t n_cap, uint32_t ntiles,
+                                                         uint32_t check_shift, uint32_t* __restrict__ reject,
+                                                         const uint64_t* __restrict__ d_n) {
+  constexpr int kTile = kBlock * kItems;
+  __shared__ ScatterLds<kBlock, kItems> L;
+  const uint32_t tile = xcd_tile(blockIdx.x, ntiles);
+  const uint32_t base = tile * kTile;
+  const uint32_t tile_n = tile_len(tile, kTile, n_cap, d_n);
+  if (tile_n == 0) return;  // past a device-resident count
+  uint32_t key[kItems], row[kItems];
+  scatter_load<kBlock, kItems>(io, base, tile_n, key, row);
+  const uint32_t dstart =
+      row_prefix<kBlock, kBits>(rows, ntiles, tile, 0u, reinterpret_cast<uint32_t*>(&L.kr[0]), L.scan);
+  if (tile_n == (uint32_t)kTile)  // uniform: a full tile checks no element against its length
+    scatter_tile<kBlock, kItems, kCheck, false, kBits, true>(L, io, shift, tile_n, dstart, key, row, check_shift,
+                                                             reject);
+  else
+    scatter_tile<kBlock, kItems, kCheck, false, kBits, false>(L, io, shift, tile_n, dstart, key, row, check_shift,
+                                                              reject);
+}
+
+// Plan-driven passes over uint32 keys (8-bit digits).  The first scatter forms
+// the plan from the tiles' OR and AND in every work-group; work-group 0 stores
+// it for the later launches.
+template <bool kFirst, int kBlock, int kItems>
+__global__ __launch_bounds__(kBlock) void k_rows_plan_count(PassBuffers buf, const SortPlan* __restrict__ plan,
+                                                            uint16_t* __restrict__ rows, uint32_t* __restrict__ orand,
+                                                            uint32_t pass, uint32_t n_cap, uint32_t ntiles,
+                                                            const uint64_t* __restrict__ d_n, ClearWords cw) {
+  constexpr int kTile = kBlock * kItems;
+  const uint32_t* keys = buf.keys_in;
+  if (kFirst) clear_words(cw);
+  if (!kFirst) {
+    const uint32_t active = plan->active;
+    if (!((active >> pass) & 1u)) return;  // uniform over the grid
+    keys = pass_io(buf, active, pass).src_keys;
+  }
+  const uint32_t tile = xcd_tile(blockIdx.x, ntiles);
+  uint16_t* const row = rows + (uint64_t)tile * kRadix;
+  upsweep_tile<kBlock, kTile, kFirst ? 1 : -1, kFirst>(
+      keys, pass * kRadixBits, tile * kTile, tile_len(tile, kTile, n_cap, d_n),
+      [&](uint32_t d, uint32_t c) { row[d] = (uint16_t)c; }, tile, orand);
+}
+
+template <bool kFirst, int kBlock, int kItems>
+__global__ __launch_bounds__(kBlock) void k_rows_plan_scatter(PassBuffers buf, SortPlan* __restrict__ plan,
+                                                              const uint16_t* __restrict__ rows,
+                                                              const uint32_t* __restrict__ orand, uint32_t pass,
+                                                              uint32_t n_cap, uint32_t ntiles,
+                                                              const uint64_t* __restrict__ d_n) {
+  constexpr int kTile = kBlock * kItems;
+  __shared__ ScatterLds<kBlock, kItems> L;
+  uint32_t active;
+  if (kFirst) {
+    uint32_t o, a;
+    block_or_and<kBlock>(orand, ntiles, L.scan, reinterpret_cast<uint32_t*>(&L.kr[0]), &o, &a);
+    active = active_passes(o, a);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      plan->active = active;
+      plan->keys_or = o;
+    }
+    __syncthreads();  // L is free again
+  } else {
+    active = plan->active;
+  }
+  if (!((active >> pass) & 1u)) return;
+  const PassIo io = pass_io(buf, active, pass);
+  const uint32_t tile = xcd_tile(blockIdx.x, ntiles);
+  const uint32_t base = tile * kTile;
+  const uint32_t tile_n = tile_len(tile, kTile, n_cap, d_n);
+  if (tile_n == 0) return;  // past a device-resident count
+  uint32_t key[kItems], row[kItems];
+  scatter_load<kBlock, kItems>(io, base, tile_n, key, row);
+  const uint32_t dstart =
+      row_prefix<kBlock, kRadixBits>(rows, ntiles, tile, 0u, reinterpret_cast<uint32_t*>(&L.kr[0]), L.scan);
+  if (tile_n == (uint32_t)kTile)
+    scatter_tile<kBlock, kItems, false, false, kRadixBits, true>(L, io, pass * kRadixBits, tile_n, dstart, key, row);
+  else
+    scatter_tile<kBlock, kItems>(L, io, pass * kRadixBits, tile_n, dstart, key, row);
+}
+
 }  // namespace
 
 namespace {
 
 template <int kBlock, int kItems>
 int sort_with_shape(Env& env, const uint32_t* keys, const uint32_t* rows, uint32_t* skeys, uint32_t* srows,
-                    uint64_t n, const uint64_t* d_n) {
+                    uint64_t n, const uint64_t* d_n, ClearWords cw) {
   constexpr int kTile = kBlock * kItems;
   SortPlan* plan = reinterpret_cast<SortPlan*>(env.arena()->plan);
   const uint32_t ntiles = (uint32_t)((n + kTile - 1) / kTile);
@@ -602,7 +808,7 @@ int sort_with_shape(Env& env, const uint32_t* keys, const uint32_t* rows, uint32
     if (pass == 0) {
       env.prof_begin("radix_upsweep0");
       k_radix_upsweep<true, kTile><<<dim3(g_up0), dim3(kUpBlock), 0, env.stream()>>>(buf, plan, table, orand, pass,
-                                                                                      nn, ntiles, d_n);
+                                                                                      nn, ntiles, d_n, cw);
       env.prof_end("radix_upsweep0");
       int rc = check_launch(env, "radix_upsweep launch");
       if (rc) return rc;
@@ -614,7 +820,7 @@ int sort_with_shape(Env& env, const uint32_t* keys, const uint32_t* rows, uint32
     } else {
       env.prof_begin("radix_upsweep");
       k_radix_upsweep<false, kTile><<<dim3(g_up), dim3(kUpBlock), 0, env.stream()>>>(buf, plan, table, orand,
-                                                                                       pass, nn, ntiles, d_n);
+                                                                                       pass, nn, ntiles, d_n, cw);
       env.prof_end("radix_upsweep");
       int rc = check_launch(env, "radix_upsweep launch");
       if (rc) return rc;
@@ -699,8 +905,9 @@ __global__ __launch_bounds__(kUpBlock) void k_seg_count(const SK* __restrict__ k
   const uint32_t t = xcd_tile(blockIdx.x, ub);
   if (t >= tile_base[nreq]) return;  // uniform over the work-group
   const SegTile s = seg_tile<kTile>(req_off, tile_base, nreq, t);
-  upsweep_tile<kTile, kRounds, false>(keys, shift, s.base, s.len, table, (uint64_t)kRadix * tile_base[s.j] + s.l, s.nt,
-                                      t, nullptr, mask);
+  uint32_t* const part = table + (uint64_t)kRadix * tile_base[s.j] + s.l;
+  upsweep_tile<kUpBlock, kTile, kRounds, false>(
+      keys, shift, s.base, s.len, [&](uint32_t d, uint32_t c) { part[(uint64_t)d * s.nt] = c; }, t, nullptr, mask);
 }
 
 // kCheck (the first pass): a key at or above 2^value_bits flags its request
@@ -797,7 +1004,7 @@ void scatter_fixed(Env& env, uint32_t bits, uint32_t grid, const PassIoT<SK, DK>
 // output is then unspecified.
 template <int kBlock, int kItems>
 int sort16_with_shape(Env& env, const uint32_t* keys, uint16_t* skeys, uint32_t* srows, uint64_t n,
-                      uint32_t value_bits, uint32_t* reject, const uint64_t* d_n) {
+                      uint32_t value_bits, uint32_t* reject, const uint64_t* d_n, ClearWords cw) {
   constexpr int kTile = kBlock * kItems;
   const uint32_t ntiles = (uint32_t)((n + kTile - 1) / kTile);
   const uint32_t nn = (uint32_t)n;
@@ -818,7 +1025,7 @@ int sort16_with_shape(Env& env, const uint32_t* keys, uint16_t* skeys, uint32_t*
   // pass 0: uint32 values in, uint16 keys out
   env.prof_begin("radix_upsweep0");
   k_radix_count<kTile, 1, uint32_t><<<dim3(ntiles), dim3(kUpBlock), 0, env.stream()>>>(
-      keys, table, ds.shift[0], (1u << ds.bits[0]) - 1u, nn, ntiles, reject, d_n);
+      keys, table, ds.shift[0], (1u << ds.bits[0]) - 1u, nn, ntiles, reject, d_n, cw);
   env.prof_end("radix_upsweep0");
   if ((rc = check_launch(env, "radix_count launch"))) return rc;
   if ((rc = launch_exclusive_scan(env, table, offs, tlen, nullptr))) return rc;
@@ -832,7 +1039,7 @@ int sort16_with_shape(Env& env, const uint32_t* keys, uint16_t* skeys, uint32_t*
   // pass 1: uint16 keys in and out
   env.prof_begin("radix_upsweep");
   k_radix_count<kTile, -1, uint16_t><<<dim3(ntiles), dim3(kUpBlock), 0, env.stream()>>>(
-      kb, table, ds.shift[1], (1u << ds.bits[1]) - 1u, nn, ntiles, nullptr, d_n);
+      kb, table, ds.shift[1], (1u << ds.bits[1]) - 1u, nn, ntiles, nullptr, d_n, ClearWords{});
   env.prof_end("radix_upsweep");
   if ((rc = check_launch(env, "radix_count launch"))) return rc;
   if ((rc = launch_exclusive_scan(env, table, offs, tlen, nullptr))) return rc;
@@ -842,6 +1049,122 @@ int sort16_with_shape(Env& env, const uint32_t* keys, uint16_t* skeys, uint32_t*
                                        d_n);
   env.prof_end("radix_scatter");
   return check_launch(env, "radix_scatter launch");
+}
+
+// The narrow-key sort in tile rows (two launches a pass).
+template <int kBlock, int kItems, bool kCheck, class SK, class DK>
+int rows_pass16(Env& env, const PassIoT<SK, DK>& io, uint16_t* rows, uint32_t shift, uint32_t bits, uint32_t nn,
+                uint32_t ntiles, uint32_t check_shift, uint32_t* reject, const uint64_t* d_n, ClearWords cw) {
+  const dim3 g(ntiles), b(kBlock);
+  env.prof_begin(kCheck ? "radix_upsweep0" : "radix_upsweep");
+  k_rows_count<kBlock, kItems, kCheck ? 1 : -1, SK>
+      <<<g, b, 0, env.stream()>>>(io.src_keys, rows, shift, bits, nn, ntiles, reject, d_n, cw);
+  env.prof_end(kCheck ? "radix_upsweep0" : "radix_upsweep");
+  int rc = check_launch(env, "radix_count launch");
+  if (rc) return rc;
+  env.prof_begin("radix_scatter");
+#define KA_ROWS_SCATTER(B)                                 \
+  k_rows_scatter<kBlock, kItems, kCheck, B, SK, DK>        \
+      <<<g, b, 0, env.stream()>>>(io, rows, shift, nn, ntiles, check_shift, reject, d_n)
+  switch (bits) {
+    case 2:
+      KA_ROWS_SCATTER(2);
+      break;
+    case 4:
+      KA_ROWS_SCATTER(4);
+      break;
+    case 6:
+      KA_ROWS_SCATTER(6);
+      break;
+    default:
+      KA_ROWS_SCATTER(8);
+      break;
+  }
+#undef KA_ROWS_SCATTER
+  env.prof_end("radix_scatter");
+  return check_launch(env, "radix_scatter launch");
+}
+
+template <int kBlock, int kItems>
+int rows_sort16(Env& env, const uint32_t* keys, uint16_t* skeys, uint32_t* srows, uint64_t n, uint32_t value_bits,
+                uint32_t* reject, const uint64_t* d_n, ClearWords cw) {
+  constexpr int kTile = kBlock * kItems;
+  const uint32_t ntiles = (uint32_t)((n + kTile - 1) / kTile), nn = (uint32_t)n;
+  const DigitSplit ds = digit_split(value_bits, true);
+  uint16_t* kb = nullptr;
+  uint32_t* rb = nullptr;
+  if (ds.passes > 1) {
+    kb = static_cast<uint16_t*>(env.scratch(n * 2));
+    rb = static_cast<uint32_t*>(env.scratch(n * 4));
+    if (!kb || !rb) return env.fail(kErrOom, "radix_sort16: scratch buffers");
+  }
+  uint16_t* rows = static_cast<uint16_t*>(env.scratch((uint64_t)ntiles * kRadix * 2));
+  if (!rows) return env.fail(kErrOom, "radix_sort16: digit rows");
+  PassIoT<uint32_t, uint16_t> io0{keys, nullptr, ds.passes > 1 ? kb : skeys, ds.passes > 1 ? rb : srows, true};
+  int rc = rows_pass16<kBlock, kItems, true>(env, io0, rows, ds.shift[0], ds.bits[0], nn, ntiles, value_bits, reject,
+                                             d_n, cw);
+  if (rc || ds.passes == 1) return rc;
+  PassIoT<uint16_t, uint16_t> io1{kb, rb, skeys, srows, false};
+  return rows_pass16<kBlock, kItems, false>(env, io1, rows, ds.shift[1], ds.bits[1], nn, ntiles, 32u, nullptr, d_n,
+                                            ClearWords{});
+}
+
+// The plan-driven sort in tile rows.
+template <int kBlock, int kItems>
+int rows_sort32(Env& env, const uint32_t* keys, const uint32_t* rows_in, uint32_t* skeys, uint32_t* srows, uint64_t n,
+                const uint64_t* d_n, ClearWords cw) {
+  constexpr int kTile = kBlock * kItems;
+  SortPlan* plan = reinterpret_cast<SortPlan*>(env.arena()->plan);
+  const uint32_t ntiles = (uint32_t)((n + kTile - 1) / kTile), nn = (uint32_t)n;
+  PassBuffers buf;
+  buf.keys_in = keys;
+  buf.rows_in = rows_in;
+  buf.keys_a = skeys;
+  buf.rows_a = srows;
+  buf.keys_b = static_cast<uint32_t*>(env.scratch(n * 4));
+  buf.rows_b = static_cast<uint32_t*>(env.scratch(n * 4));
+  uint16_t* rows = static_cast<uint16_t*>(env.scratch((uint64_t)ntiles * kRadix * 2));
+  uint32_t* orand = static_cast<uint32_t*>(env.scratch((uint64_t)ntiles * 2 * 4));
+  if (!buf.keys_b || !buf.rows_b || !rows || !orand) return env.fail(kErrOom, "radix_sort: scratch buffers");
+  const dim3 g(ntiles), b(kBlock);
+  for (uint32_t pass = 0; pass < (uint32_t)kPasses; ++pass) {
+    const char* name = pass ? "radix_upsweep" : "radix_upsweep0";
+    env.prof_begin(name);
+    if (pass == 0)
+      k_rows_plan_count<true, kBlock, kItems><<<g, b, 0, env.stream()>>>(buf, plan, rows, orand, pass, nn, ntiles, d_n,
+                                                                         cw);
+    else
+      k_rows_plan_count<false, kBlock, kItems><<<g, b, 0, env.stream()>>>(buf, plan, rows, orand, pass, nn, ntiles,
+                                                                          d_n, cw);
+    env.prof_end(name);
+    int rc = check_launch(env, "radix_upsweep launch");
+    if (rc) return rc;
+    env.prof_begin("radix_scatter");
+    if (pass == 0)
+      k_rows_plan_scatter<true, kBlock, kItems><<<g, b, 0, env.stream()>>>(buf, plan, rows, orand, pass, nn, ntiles,
+                                                                           d_n);
+    else
+      k_rows_plan_scatter<false, kBlock, kItems><<<g, b, 0, env.stream()>>>(buf, plan, rows, orand, pass, nn, ntiles,
+                                                                            d_n);
+    env.prof_end("radix_scatter");
+    if ((rc = check_launch(env, "radix_scatter launch"))) return rc;
+  }
+  return kOk;
+}
+
+// Tile shape of the tile-row sorts by capacity: about one tile per CU, from
+// 1024 keys up; kNone: too many tiles.  An index request, us, scanned table /
+// tile rows: 12-bit values (6-bit digits) 65536 89 / 72, 2^20 96 / 81, 2^21 104
+// / 91, 2^22 118 / 115, 5.2M 132 / 145; 16-bit (8-bit digits) 65536 95 / 72,
+// 2^21 107 / 96, 2^22 126 / 141; any uint32 65536 142 / 93, 2^21 171 / 157, 2^22
+// 204 / 248.
+enum class RowShape { kNone, k1024, k2048, k4096, k8192 };
+RowShape row_shape(uint64_t n, uint32_t bits) {
+  if (n <= 256ull * 1024) return RowShape::k1024;
+  if (n <= 256ull * 2048) return RowShape::k2048;
+  if (n <= 256ull * 4096) return RowShape::k4096;
+  if (n <= (bits > 6 ? 256ull : 512ull) * 8192) return RowShape::k8192;
+  return RowShape::kNone;
 }
 
 // Launch of a segmented scatter for a digit width known at run time.
@@ -955,39 +1278,53 @@ const uint32_t* sort_plan_keys_or(Env& env) {
 }
 
 int launch_radix_sort_rows16(Env& env, const uint32_t* keys, uint16_t* skeys, uint32_t* srows, uint64_t n,
-                             uint32_t value_bits, uint32_t* reject, int shape, const uint64_t* d_n) {
+                             uint32_t value_bits, uint32_t* reject, const uint64_t* d_n, ClearWords cw) {
   if (!reject) return env.fail(kErrArg, "radix_sort16: null reject flag");
   if (value_bits == 0 || value_bits > 16) return env.fail(kErrArg, "radix_sort16: value_bits must be 1..16");
   if (n == 0) return launch_fill_u32(env, reject, 1, 0);
   if (!keys || !skeys || !srows) return env.fail(kErrArg, "radix_sort16: null buffer");
   if (n >= (1ull << 31)) return env.fail(kErrArg, "radix_sort16: n must be below 2^31");
-  switch (shape) {
-    case 0:
-      return sort16_with_shape<kShapes[0].block, kShapes[0].items>(env, keys, skeys, srows, n, value_bits, reject,
-                                                                      d_n);
-    case 1:
-      return sort16_with_shape<kShapes[1].block, kShapes[1].items>(env, keys, skeys, srows, n, value_bits, reject,
-                                                                      d_n);
-    case 2:
-      return sort16_with_shape<kShapes[2].block, kShapes[2].items>(env, keys, skeys, srows, n, value_bits, reject,
-                                                                      d_n);
-    default:
-      return env.fail(kErrArg, "radix_sort16: unknown tile shape");
+  switch (row_shape(n, digit_split(value_bits, true).bits[0])) {
+    case RowShape::k1024:
+      return rows_sort16<256, 4>(env, keys, skeys, srows, n, value_bits, reject, d_n, cw);
+    case RowShape::k2048:
+      return rows_sort16<512, 4>(env, keys, skeys, srows, n, value_bits, reject, d_n, cw);
+    case RowShape::k4096:
+      return rows_sort16<1024, 4>(env, keys, skeys, srows, n, value_bits, reject, d_n, cw);
+    case RowShape::k8192:
+      return rows_sort16<1024, 8>(env, keys, skeys, srows, n, value_bits, reject, d_n, cw);
+    case RowShape::kNone:
+      break;
   }
+  return sort16_with_shape<kShapes[0].block, kShapes[0].items>(env, keys, skeys, srows, n, value_bits, reject, d_n, cw);
 }
 
 int launch_radix_sort_pairs(Env& env, const uint32_t* keys, const uint32_t* rows, uint32_t* skeys,
-                            uint32_t* srows, uint64_t n, int shape, const uint64_t* d_n) {
+                            uint32_t* srows, uint64_t n, int shape, const uint64_t* d_n, ClearWords cw) {
   if (n == 0) return kOk;
   if (!keys || !skeys || !srows) return env.fail(kErrArg, "radix_sort: null buffer");
   if (n >= (1ull << 31)) return env.fail(kErrArg, "radix_sort: n must be below 2^31");
+  if (shape == 0) {
+    switch (row_shape(n, kRadixBits)) {
+      case RowShape::k1024:
+        return rows_sort32<256, 4>(env, keys, rows, skeys, srows, n, d_n, cw);
+      case RowShape::k2048:
+        return rows_sort32<512, 4>(env, keys, rows, skeys, srows, n, d_n, cw);
+      case RowShape::k4096:
+        return rows_sort32<1024, 4>(env, keys, rows, skeys, srows, n, d_n, cw);
+      case RowShape::k8192:
+        return rows_sort32<1024, 8>(env, keys, rows, skeys, srows, n, d_n, cw);
+      case RowShape::kNone:
+        break;
+    }
+  }
   switch (shape) {
     case 0:
-      return sort_with_shape<kShapes[0].block, kShapes[0].items>(env, keys, rows, skeys, srows, n, d_n);
+      return sort_with_shape<kShapes[0].block, kShapes[0].items>(env, keys, rows, skeys, srows, n, d_n, cw);
     case 1:
-      return sort_with_shape<kShapes[1].block, kShapes[1].items>(env, keys, rows, skeys, srows, n, d_n);
+      return sort_with_shape<kShapes[1].block, kShapes[1].items>(env, keys, rows, skeys, srows, n, d_n, cw);
     case 2:
-      return sort_with_shape<kShapes[2].block, kShapes[2].items>(env, keys, rows, skeys, srows, n, d_n);
+      return sort_with_shape<kShapes[2].block, kShapes[2].items>(env, keys, rows, skeys, srows, n, d_n, cw);
     default:
       return env.fail(kErrArg, "radix_sort: unknown tile shape");
   }

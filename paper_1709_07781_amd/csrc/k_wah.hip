@@ -44,6 +44,8 @@
 // dead by then) and written out by consecutive work-items.  Sorted keys are
 // uint32, or uint16 when every value is below 2^16 (the index build's
 // narrow-key sort).
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace ka {
@@ -651,17 +653,34 @@ __global__ void k_wah_clear(uint64_t* __restrict__ status, uint32_t ntiles) {
   if (i < ntiles) status[kLbSpread * i] = 0ull;
 }
 
-template <int kFmt, class KeyT>
-int encode_fmt(Env& env, const KeyT* skeys, const uint32_t* srows, uint32_t n, const IndexOut& out,
-               const EncodeOpts& opt) {
-  constexpr int kBlock = kEncBlock, kTile = EncLds<kBlock, kFmt>::kTile;
-  const uint32_t ntiles = (n + kTile - 1) / kTile;
-  // The (words, values) chain has no epoch: its own status words, zeroed here.
-  uint64_t* status = static_cast<uint64_t*>(env.scratch(8ull * kLbSpread * ntiles));
-  if (!status) return env.fail(kErrOom, "wah encoder: look-back status words");
-  k_wah_clear<<<dim3((ntiles + 255) / 256), dim3(256), 0, env.stream()>>>(status, ntiles);
-  const int rc = check_launch(env, "wah_clear launch");
-  if (rc) return rc;
+// Work-items of the encoder's work-groups by capacity: tiles small enough for
+// about one per CU.
+uint32_t enc_block(uint64_t n) {
+  return n <= 256ull * 2048 ? 256u : n <= 256ull * 4096 ? 512u : (uint32_t)kEncBlock;
+}
+
+uint32_t enc_tiles(uint64_t n) {
+  const uint64_t tile = (uint64_t)enc_block(n) * kEncItems;
+  return (uint32_t)((n + tile - 1) / tile);
+}
+
+template <int kBlock, int kFmt, class KeyT>
+int encode_block(Env& env, const KeyT* skeys, const uint32_t* srows, uint32_t n, const IndexOut& out,
+                 const EncodeOpts& opt) {
+  const uint32_t ntiles = enc_tiles(n);
+  // The (words, values) chain has no epoch: its own status words, zeroed by the
+  // sort before it or here.
+  uint64_t* status = opt.cleared.p;
+  if (!status) {
+    const ClearWords cw = wah_status(env, n);
+    if (!cw.p) return env.fail(kErrOom, "wah encoder: look-back status words");
+    status = cw.p;
+    k_wah_clear<<<dim3((ntiles + 255) / 256), dim3(256), 0, env.stream()>>>(status, ntiles);
+    const int rc = check_launch(env, "wah_clear launch");
+    if (rc) return rc;
+  } else if (opt.cleared.count < ntiles) {
+    return env.fail(kErrArg, "wah encoder: too few look-back status words");
+  }
   constexpr uintptr_t kKeyAlign = sizeof(KeyT) == 4 ? 15u : 7u;
   const bool vec = ((reinterpret_cast<uintptr_t>(skeys) & kKeyAlign) | (reinterpret_cast<uintptr_t>(srows) & 15u)) == 0;
   const BatchRows br{opt.req_base, opt.req_shift};
@@ -675,6 +694,19 @@ int encode_fmt(Env& env, const KeyT* skeys, const uint32_t* srows, uint32_t n, c
         skeys, srows, n, opt.d_n, status, env.spin_limit(), out, br, rej);
   env.prof_end("wah_write");
   return check_launch(env, "wah_write launch");
+}
+
+template <int kFmt, class KeyT>
+int encode_fmt(Env& env, const KeyT* skeys, const uint32_t* srows, uint32_t n, const IndexOut& out,
+               const EncodeOpts& opt) {
+  switch (enc_block(n)) {
+    case 256:
+      return encode_block<256, kFmt>(env, skeys, srows, n, out, opt);
+    case 512:
+      return encode_block<512, kFmt>(env, skeys, srows, n, out, opt);
+    default:
+      return encode_block<kEncBlock, kFmt>(env, skeys, srows, n, out, opt);
+  }
 }
 
 template <int kFmt>
@@ -721,6 +753,13 @@ int encode_impl(Env& env, const KeyT* skeys, const uint32_t* srows, uint64_t n, 
 }
 
 }  // namespace
+
+ClearWords wah_status(Env& env, uint64_t n) {
+  ClearWords cw;
+  cw.count = enc_tiles(n);
+  cw.p = static_cast<uint64_t*>(env.scratch(8ull * kLbSpread * std::max<uint32_t>(cw.count, 1)));
+  return cw;
+}
 
 int launch_wah_encode(Env& env, const uint32_t* skeys, const uint32_t* srows, uint64_t n, const IndexOut& out,
                       const EncodeOpts& opt) {

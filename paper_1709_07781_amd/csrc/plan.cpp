@@ -148,7 +148,7 @@ static int plan_build(ka_system* sys, const uint32_t* req_off, uint64_t n, uint3
   // ---- one allocation: input, table, outputs, look-back state, scratch arena -----------
   const uint64_t n1 = n ? n : 1;
   // the segmented sort cuts tiles at request boundaries: at most one more per request
-  const uint64_t sort_tiles = (n + 8191) / 8192 + nreq, enc_tiles = (n + 4095) / 4096;
+  const uint64_t sort_tiles = (n + 8191) / 8192 + nreq, enc_tiles = (n + 2047) / 2048;
   const uint64_t scan_tiles = 2 * ((256 * sort_tiles + 4095) / 4096) + 2;  // scan tiles hold >= 4096 entries
   // look-back status slots (kLbSpread words each): the encoder's tiles, or the
   // requests of the fused small-request launch

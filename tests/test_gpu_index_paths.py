@@ -103,3 +103,41 @@ def test_small_input_beyond_its_hint(sess, bits):
         sess.wah_index(v, value_bits=bits)
     v[4999] -= 1
     check(sess, v, bits, 0)
+
+
+# capacities where the sort's tile grows (1024, 2048, 4096, 8192 keys) and where its digit table is scanned instead
+# of summed by every tile (by digit width), with the encoder's tiles of 2048, 4096 and 8192 pairs
+SORT_EDGES = [1 << 18, 1 << 19, 1 << 20, 1 << 21, 1 << 22]
+
+
+@pytest.mark.parametrize("n", [SMALL_MAX + 1, 70_001] + [e + d for e in SORT_EDGES for d in (0, 1)])
+def test_sort_tile_shapes(sess, n):
+    """Every digit width (2, 4, 6, 8 bits, one and two passes), skipped passes of unhinted values, skewed values."""
+    u = workloads.u32(n, n)
+    z = workloads.zipf_values(n, n, 1.1, 1 << 16)
+    for bits in (1, 4, 7, 12, 16):
+        check(sess, (u & np.uint32((1 << bits) - 1)), bits, 0)
+    check(sess, z, 16, 0)
+    if n <= (1 << 21) + 1:
+        check(sess, (u & np.uint32(0xFF00FF)), 0, 0)
+        check(sess, z, 20, 2)
+
+
+@pytest.mark.parametrize("cap,n", [(300_000, 299_000), (300_000, 5), (300_000, 0), (6000, 17), (6000, 0)])
+@pytest.mark.parametrize("bits", [0, 12])
+def test_counts_on_the_device(sess, cap, n, bits):
+    """The same paths behind a compaction: the grid covers its capacity, the count is read on the device."""
+    import ctypes
+    import paper_1709_07781_amd as ka
+    x = np.zeros(cap, np.uint32)
+    x[np.sort(workloads.u32(cap + n, cap).argsort(kind="stable")[:n])] = workloads.u32(3, n) % 4095 + 1
+    priv = (ctypes.c_uint32 * 1)(bits)
+    comp = sess.spawn("compact_nonzero_u32", [ka.arg(ka.KA_IN, in_mode=ka.KA_VAL), ka.arg(ka.KA_OUT)])
+    idx = sess.spawn("wah_index", [ka.arg(ka.KA_IN), ka.arg(ka.KA_PRIV, count=1, init=priv)] +
+                     [ka.arg(ka.KA_OUT, out_mode=ka.KA_VAL)] * 3)
+    both = sess.compose(idx, comp)
+    got = sess.request(both, ka.val(x.ctypes.data, x.size), n_out=3)
+    for a in (both, comp, idx):
+        sess.release_actor(a)
+    for g, e in zip(got, oracle.default().wah_index(x[x != 0])):
+        np.testing.assert_array_equal(g, e)
