@@ -174,7 +174,7 @@ int run_wah(Actor* a, uint32_t value_bits, const std::vector<Input>& in, ka_tick
     rc = launch_wah_batch(env, static_cast<uint32_t*>(vals->ptr), n, static_cast<uint32_t*>(roff->ptr), nreq,
                           value_bits, static_cast<uint32_t*>(keys->ptr), static_cast<uint32_t*>(offs->ptr),
                           static_cast<uint32_t*>(words->ptr), static_cast<uint32_t*>(ks->ptr),
-                          static_cast<uint32_t*>(ws->ptr), l, l + 1, l + 2, l + 3, l + 4, 0, biggest,
+                          static_cast<uint32_t*>(ws->ptr), BatchLens{l, l + 1, l + 2, l + 3, l + 4, {}}, 0, biggest,
                           static_cast<uint32_t*>(bad->ptr));
     if (rc) return rc;
   }

@@ -69,7 +69,7 @@ int run_compact(LaunchCtx& c) {
   Bound& out = (*c.args)[1];
   if (c.n > in.cap || c.n > out.cap) return c.env->fail(KA_E_ARG, "compact_nonzero_u32: range exceeds a buffer");
   return launch_compact_nonzero(*c.env, static_cast<const uint32_t*>(in.ptr), static_cast<uint32_t*>(out.ptr), c.n,
-                                c.d_n, const_cast<uint64_t*>(out.d_len));
+                                c.d_n, const_cast<uint64_t*>(out.d_len), out.h_len);
 }
 
 // radix_sort_rows_u32: (in keys; out skeys; out srows)
@@ -103,7 +103,7 @@ int run_wah(LaunchCtx& c) {
     return c.env->fail(KA_E_ARG, "wah_encode_sorted: outputs need capacities n, n+1 and 2n");
   const IndexOut out{static_cast<uint32_t*>(a[2].ptr), static_cast<uint32_t*>(a[3].ptr),
                      static_cast<uint32_t*>(a[4].ptr), const_cast<uint64_t*>(a[2].d_len),
-                     const_cast<uint64_t*>(a[3].d_len), const_cast<uint64_t*>(a[4].d_len)};
+                     const_cast<uint64_t*>(a[3].d_len), const_cast<uint64_t*>(a[4].d_len), a[2].h_len};
   EncodeOpts opt;
   opt.d_n = c.d_n;
   return launch_wah_encode(*c.env, static_cast<const uint32_t*>(a[0].ptr), static_cast<const uint32_t*>(a[1].ptr), c.n,
@@ -131,7 +131,7 @@ int run_wah_index(LaunchCtx& c) {
   const uint32_t* values = static_cast<const uint32_t*>(a[0].ptr);
   const IndexOut out{static_cast<uint32_t*>(a[2].ptr), static_cast<uint32_t*>(a[3].ptr),
                      static_cast<uint32_t*>(a[4].ptr), const_cast<uint64_t*>(a[2].d_len),
-                     const_cast<uint64_t*>(a[3].d_len), const_cast<uint64_t*>(a[4].d_len)};
+                     const_cast<uint64_t*>(a[3].d_len), const_cast<uint64_t*>(a[4].d_len), a[2].h_len};
   EncodeOpts opt;
   opt.format = (uint32_t)a[1].priv[1];
   opt.d_n = c.d_n;  // the count on the device (n is then the capacity)
@@ -194,7 +194,7 @@ int run_decode(LaunchCtx& c) {
   if ((rc = launch_wah_decode(env, static_cast<const uint32_t*>(a[0].ptr), c.n, c.d_n, fmt, (uint32_t)ng,
                               static_cast<uint32_t*>(a[2].ptr), reject)))
     return rc;
-  return launch_len_unless(env, const_cast<uint64_t*>(a[2].d_len), ng, reject);
+  return launch_len_unless(env, const_cast<uint64_t*>(a[2].d_len), a[2].h_len, ng, reject);
 }
 
 // wah_combine: (in a; in b; priv op, in_format, out_format, ngroups; out words)
@@ -215,7 +215,7 @@ int run_combine(LaunchCtx& c) {
   return launch_wah_combine(env, static_cast<const uint32_t*>(a[0].ptr), a[0].d_len ? a[0].cap : a[0].len, a[0].d_len,
                             static_cast<const uint32_t*>(a[1].ptr), a[1].d_len ? a[1].cap : a[1].len, a[1].d_len, fin,
                             (uint32_t)ng, op, fout, static_cast<uint32_t*>(a[3].ptr), const_cast<uint64_t*>(a[3].d_len),
-                            reject);
+                            a[3].h_len, reject);
 }
 
 // wah_index_batch: (in values; in req_off; priv value_bits [, largest request + 1];
@@ -234,9 +234,10 @@ int run_batch(LaunchCtx& c) {
                           nreq, (uint32_t)a[2].priv[0], static_cast<uint32_t*>(a[3].ptr),
                           static_cast<uint32_t*>(a[4].ptr), static_cast<uint32_t*>(a[5].ptr),
                           static_cast<uint32_t*>(a[6].ptr), static_cast<uint32_t*>(a[7].ptr),
-                          const_cast<uint64_t*>(a[3].d_len), const_cast<uint64_t*>(a[4].d_len),
-                          const_cast<uint64_t*>(a[5].d_len), const_cast<uint64_t*>(a[6].d_len),
-                          const_cast<uint64_t*>(a[7].d_len), 0,
+                          BatchLens{const_cast<uint64_t*>(a[3].d_len), const_cast<uint64_t*>(a[4].d_len),
+                                    const_cast<uint64_t*>(a[5].d_len), const_cast<uint64_t*>(a[6].d_len),
+                                    const_cast<uint64_t*>(a[7].d_len), a[3].h_len},
+                          0,
                           a[2].priv[1] ? (uint32_t)(a[2].priv[1] - 1) : kMaxReqUnknown);
 }
 

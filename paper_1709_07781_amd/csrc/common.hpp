@@ -63,6 +63,17 @@ class Env {
   virtual int fail(int code, const char* msg) = 0;
 };
 
+// Where the lengths that a kernel writes are also wanted on the host: pinned
+// memory, one 64-bit word per length in the order of the outputs, each written
+// as tag << 32 | length (lengths are below 2^32).  The host takes a word with
+// the request's tag instead of copying the device's slot back, which took
+// three to five copies and another wait for every index (about 25 us of a
+// request of 72).  Null: not wanted.
+struct LenHost {
+  uint64_t* p = nullptr;
+  uint32_t tag = 0;
+};
+
 // Launchers (one file each).  They queue work on env.stream() and return a
 // KA_* code.  `d_n`, when not null, points to the true element count on the
 // device (at most n_cap), written by an earlier stage.
@@ -73,7 +84,7 @@ int launch_affine(Env& env, uint32_t* x, uint64_t n_cap, const uint64_t* d_n, ui
                   uint32_t b);
 int launch_exclusive_scan(Env& env, const uint32_t* in, uint32_t* out, uint64_t n_cap, const uint64_t* d_n);
 int launch_compact_nonzero(Env& env, const uint32_t* in, uint32_t* out, uint64_t n_cap, const uint64_t* d_n,
-                           uint64_t* d_out_len);
+                           uint64_t* d_out_len, LenHost host = {});
 // Look-back words (count of them, kLbSpread apart) that a sort's first launch
 // zeroes for the encoder after it.
 struct ClearWords {
@@ -114,6 +125,7 @@ int launch_radix_sort_rows16(Env& env, const uint32_t* keys, uint16_t* skeys, ui
 struct IndexOut {
   uint32_t *keys, *offsets, *words;
   uint64_t *len_keys, *len_offsets, *len_words;
+  LenHost host;
 };
 // reject_flag, when given, voids the result (every output length 0) if
 // (*reject_flag >> reject_shift) != 0 once the earlier kernels of the stream
@@ -152,14 +164,14 @@ int launch_wah_decode(Env& env, const uint32_t* words, uint64_t m_cap, const uin
 // out_fmt into words (capacity 2 ngroups), its length in *len_words.
 int launch_wah_combine(Env& env, const uint32_t* a, uint64_t a_cap, const uint64_t* a_len, const uint32_t* b,
                        uint64_t b_cap, const uint64_t* b_len, uint32_t in_fmt, uint32_t ngroups, uint32_t op,
-                       uint32_t out_fmt, uint32_t* words, uint64_t* len_words, uint32_t* reject);
+                       uint32_t out_fmt, uint32_t* words, uint64_t* len_words, LenHost host, uint32_t* reject);
 // slots[i] = d with keys[d] == queries[i], or 0xFFFFFFFF (keys ascending).
 // q_len, when given, is the query count on the device (at most q).
 int launch_wah_lookup(Env& env, const uint32_t* keys, uint64_t d_cap, const uint64_t* d_len, const uint32_t* queries,
                       uint64_t q, uint32_t* slots, const uint64_t* q_len = nullptr);
 int launch_zero_u32(Env& env, uint32_t* p);
 // *len = *reject ? 0 : value.
-int launch_len_unless(Env& env, uint64_t* len, uint64_t value, const uint32_t* reject);
+int launch_len_unless(Env& env, uint64_t* len, LenHost host, uint64_t value, const uint32_t* reject);
 // Batched index build: nreq requests, values concatenated, req_off[j] the
 // first position of request j (req_off[nreq] = n).  max_req: the largest
 // request, when the caller knows it (kMaxReqUnknown otherwise); batches of
@@ -168,10 +180,14 @@ int launch_len_unless(Env& env, uint64_t* len, uint64_t value, const uint32_t* r
 // req_bad (nreq device words), only its own request: req_bad[j] = 1 and that
 // request's slices are unspecified while every other request's are exact.
 constexpr uint32_t kMaxReqUnknown = 0xFFFFFFFFu;
+// The lengths of a batch's five outputs: device-resident, and on the host.
+struct BatchLens {
+  uint64_t *keys, *offsets, *words, *key_start, *word_start;
+  LenHost host;
+};
 int launch_wah_batch(Env& env, const uint32_t* values, uint64_t n, const uint32_t* req_off, uint32_t nreq,
                      uint32_t value_bits, uint32_t* keys, uint32_t* offsets, uint32_t* words, uint32_t* key_start,
-                     uint32_t* word_start, uint64_t* len_keys, uint64_t* len_offsets, uint64_t* len_words,
-                     uint64_t* len_key_start, uint64_t* len_word_start, int sort_shape = 0,
+                     uint32_t* word_start, const BatchLens& lens, int sort_shape = 0,
                      uint32_t max_req = kMaxReqUnknown, uint32_t* req_bad = nullptr,
                      const uint64_t* d_n = nullptr);
 // Exclusive scan of each of nreq requests concatenated in in[0..n) (req_off as
@@ -180,7 +196,7 @@ int launch_segmented_scan(Env& env, const uint32_t* in, uint32_t* out, uint64_t 
                           uint32_t nreq);
 int launch_fill_u64(Env& env, uint64_t* p, uint64_t count, uint64_t value);
 int launch_fill_u32(Env& env, uint32_t* p, uint64_t count, uint32_t value);
-int launch_set_len(Env& env, uint64_t* d_len, uint64_t value);
+int launch_set_len(Env& env, uint64_t* d_len, uint64_t value, LenHost host = {});
 int launch_copy_len(Env& env, uint64_t* dst, const uint64_t* src);
 // *dst = *src (a uint32 count, e.g. a request table's last entry, as a length).
 int launch_len_from_u32(Env& env, uint64_t* dst, const uint32_t* src);
@@ -201,6 +217,13 @@ inline int check_launch(Env& env, const char* what) {
 
 constexpr uint32_t kLbAggregate = 1u;  // status flag: tile total only
 constexpr uint32_t kLbInclusive = 2u;  // status flag: prefix including the tile
+// *dev = v, and word i of the host's lengths.
+__device__ __forceinline__ void put_len(uint64_t* dev, const LenHost& host, int i, uint64_t v) {
+  *dev = v;
+  if (host.p)
+    __hip_atomic_store(host.p + i, (uint64_t)host.tag << 32 | (uint32_t)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
 
 // Native 4 x uint32 vector: one 16-byte global access.

@@ -142,6 +142,16 @@ __global__ __launch_bounds__(kKeyBlock) void k_batch_map(const uint32_t* in, uin
   if (over && bad) *bad = 1u;
 }
 
+// The lengths of a batch of nreq requests with D values and W words (all 0 if
+// it is rejected).
+__device__ __forceinline__ void put_batch_lens(const BatchLens& lens, bool ok, uint32_t D, uint32_t W, uint32_t nreq) {
+  put_len(lens.keys, lens.host, 0, ok ? D : 0u);
+  put_len(lens.offsets, lens.host, 1, ok ? (uint64_t)D + nreq : 0u);
+  put_len(lens.words, lens.host, 2, ok ? W : 0u);
+  put_len(lens.key_start, lens.host, 3, ok ? (uint64_t)nreq + 1 : 0u);
+  put_len(lens.word_start, lens.host, 4, ok ? (uint64_t)nreq + 1 : 0u);
+}
+
 // base[j] = scan[req_off[j]] for every non-empty request.
 __global__ __launch_bounds__(kSplitBlock) void k_batch_bases(const uint32_t* __restrict__ scan, uint32_t n,
                                                              const uint32_t* __restrict__ req_off, uint32_t nreq,
@@ -179,8 +189,7 @@ __global__ __launch_bounds__(kSplitBlock) void k_batch_starts(const uint32_t* __
 __global__ __launch_bounds__(kSplitBlock) void k_batch_tables(
     uint32_t* __restrict__ keys, const uint32_t* __restrict__ g_off, uint32_t nreq, uint32_t value_bits,
     const uint32_t* __restrict__ key_start, const uint32_t* __restrict__ word_start, const uint32_t* __restrict__ bad,
-    uint32_t* __restrict__ offsets, uint64_t* __restrict__ len_keys, uint64_t* __restrict__ len_offsets,
-    uint64_t* __restrict__ len_words, uint64_t* __restrict__ len_key_start, uint64_t* __restrict__ len_word_start) {
+    uint32_t* __restrict__ offsets, BatchLens lens) {
   const uint32_t D = key_start[nreq];
   const uint32_t stride = gridDim.x * kSplitBlock;
   const uint32_t first = blockIdx.x * kSplitBlock + threadIdx.x;
@@ -195,11 +204,7 @@ __global__ __launch_bounds__(kSplitBlock) void k_batch_tables(
   for (uint32_t j = first; j < nreq; j += stride) offsets[key_start[j + 1] + j] = word_start[j + 1] - word_start[j];
   if (first == 0) {
     const bool ok = *bad == 0u;
-    *len_keys = ok ? D : 0u;
-    *len_offsets = ok ? (uint64_t)D + nreq : 0u;
-    *len_words = ok ? word_start[nreq] : 0u;
-    *len_key_start = ok ? (uint64_t)nreq + 1 : 0u;
-    *len_word_start = ok ? (uint64_t)nreq + 1 : 0u;
+    put_batch_lens(lens, ok, D, word_start[nreq], nreq);
   }
 }
 
@@ -237,8 +242,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_fused(
     uint32_t* __restrict__ ticket, uint64_t* __restrict__ status, uint32_t* __restrict__ bad_flag,
     uint32_t* __restrict__ keys, uint32_t* __restrict__ offsets,
     uint32_t* __restrict__ words, uint32_t* __restrict__ key_start, uint32_t* __restrict__ word_start,
-    uint64_t* __restrict__ len_keys, uint64_t* __restrict__ len_offsets, uint64_t* __restrict__ len_words,
-    uint64_t* __restrict__ len_key_start, uint64_t* __restrict__ len_word_start) {
+    BatchLens lens) {
   __shared__ uint32_t s[kSmallMax];
   __shared__ uint32_t s_scan[kSmallBlock / 64];
   __shared__ uint32_t s_j, s_pre[2];
@@ -364,11 +368,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_fused(
         word_start[nreq] = wpre + W;
         __threadfence();
         const bool rejected = __hip_atomic_load(bad_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
-        *len_keys = rejected ? 0u : dpre + D;
-        *len_offsets = rejected ? 0u : (uint64_t)dpre + D + nreq;
-        *len_words = rejected ? 0u : wpre + W;
-        *len_key_start = rejected ? 0u : (uint64_t)nreq + 1;
-        *len_word_start = rejected ? 0u : (uint64_t)nreq + 1;
+        put_batch_lens(lens, !rejected, dpre + D, wpre + W, nreq);
       }
     }
     __syncthreads();  // s, s_j and s_pre are reused by the next request
@@ -495,11 +495,7 @@ constexpr int kStartsBlock = 1024;
 __global__ __launch_bounds__(kStartsBlock) void k_small_starts(const uint32_t* __restrict__ counts, uint32_t nreq,
                                                                uint32_t* __restrict__ key_start,
                                                                uint32_t* __restrict__ word_start,
-                                                               uint64_t* __restrict__ len_keys,
-                                                               uint64_t* __restrict__ len_offsets,
-                                                               uint64_t* __restrict__ len_words,
-                                                               uint64_t* __restrict__ len_key_start,
-                                                               uint64_t* __restrict__ len_word_start,
+                                                               BatchLens lens,
                                                                uint32_t* __restrict__ req_bad) {
   __shared__ uint32_t s_a[kStartsBlock / 64], s_b[kStartsBlock / 64];
   uint32_t wbase = 0, dbase = 0, any_bad = 0;
@@ -527,11 +523,7 @@ __global__ __launch_bounds__(kStartsBlock) void k_small_starts(const uint32_t* _
   if (threadIdx.x == 0) {
     word_start[nreq] = wbase;
     key_start[nreq] = dbase;
-    *len_keys = bad ? 0u : dbase;
-    *len_offsets = bad ? 0u : (uint64_t)dbase + nreq;
-    *len_words = bad ? 0u : wbase;
-    *len_key_start = bad ? 0u : (uint64_t)nreq + 1;
-    *len_word_start = bad ? 0u : (uint64_t)nreq + 1;
+    put_batch_lens(lens, !bad, dbase, wbase, nreq);
   }
 }
 
@@ -556,11 +548,10 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_place(const uint32_t* __r
 
 int launch_wah_batch(Env& env, const uint32_t* values, uint64_t n, const uint32_t* req_off, uint32_t nreq,
                      uint32_t value_bits, uint32_t* keys, uint32_t* offsets, uint32_t* words, uint32_t* key_start,
-                     uint32_t* word_start, uint64_t* len_keys, uint64_t* len_offsets, uint64_t* len_words,
-                     uint64_t* len_key_start, uint64_t* len_word_start, int sort_shape, uint32_t max_req,
+                     uint32_t* word_start, const BatchLens& lens, int sort_shape, uint32_t max_req,
                      uint32_t* req_bad, const uint64_t* d_n) {
-  if (!req_off || !offsets || !key_start || !word_start || !len_keys || !len_offsets || !len_words || !len_key_start ||
-      !len_word_start)
+  if (!req_off || !offsets || !key_start || !word_start || !lens.keys || !lens.offsets || !lens.words ||
+      !lens.key_start || !lens.word_start)
     return env.fail(kErrArg, "wah_index_batch: null buffer");
   if (nreq == 0) return env.fail(kErrArg, "wah_index_batch: no requests");
   if (value_bits == 0 || value_bits > 32) return env.fail(kErrArg, "wah_index_batch: value_bits must be 1..32");
@@ -589,9 +580,8 @@ int launch_wah_batch(Env& env, const uint32_t* values, uint64_t n, const uint32_
     int rc = check_launch(env, "batch_small_index launch");
     if (rc) return rc;
     env.prof_begin("batch_small_place");
-    k_small_starts<<<dim3(1), dim3(kStartsBlock), 0, env.stream()>>>(counts, nreq, key_start, word_start, len_keys,
-                                                                      len_offsets, len_words, len_key_start,
-                                                                      len_word_start, req_bad);
+    k_small_starts<<<dim3(1), dim3(kStartsBlock), 0, env.stream()>>>(counts, nreq, key_start, word_start, lens,
+                                                                      req_bad);
     if ((rc = check_launch(env, "batch_small_starts launch"))) return rc;
     k_small_place<<<dim3(nreq), dim3(kSmallBlock), 0, env.stream()>>>(counts, req_off, wslot, kslot, oslot,
                                                                        key_start, word_start, keys, offsets, words);
@@ -611,7 +601,7 @@ int launch_wah_batch(Env& env, const uint32_t* values, uint64_t n, const uint32_
     env.prof_begin("batch_small_fused");
     k_small_fused<<<dim3(std::min<uint32_t>(nreq, kSmallGrid)), dim3(kSmallBlock), 0, env.stream()>>>(
         values, req_off, nreq, value_bits, ticket, status, ticket + 1, keys, offsets, words, key_start,
-        word_start, len_keys, len_offsets, len_words, len_key_start, len_word_start);
+        word_start, lens);
     env.prof_end("batch_small_fused");
     return check_launch(env, "batch_small_fused launch");
   }
@@ -655,16 +645,15 @@ int launch_wah_batch(Env& env, const uint32_t* values, uint64_t n, const uint32_
     opt.req_base = req_off;
     opt.req_shift = value_bits;
   }
-  if ((rc = launch_wah_encode(env, skeys, srows, n, IndexOut{keys, g_off, words, len_keys, g_len, len_words}, opt)))
+  if ((rc = launch_wah_encode(env, skeys, srows, n, IndexOut{keys, g_off, words, lens.keys, g_len, lens.words, {}}, opt)))
     return rc;
   const uint32_t sgrid = std::min<uint32_t>(kSplitGrid, (nreq + kSplitBlock) / kSplitBlock);
   env.prof_begin("batch_split");
-  k_batch_starts<<<dim3(sgrid), dim3(kSplitBlock), 0, env.stream()>>>(keys, len_keys, g_off, nreq, value_bits,
+  k_batch_starts<<<dim3(sgrid), dim3(kSplitBlock), 0, env.stream()>>>(keys, lens.keys, g_off, nreq, value_bits,
                                                                        key_start, word_start);
   if ((rc = check_launch(env, "batch_starts launch"))) return rc;
   k_batch_tables<<<dim3(kSplitGrid), dim3(kSplitBlock), 0, env.stream()>>>(
-      keys, g_off, nreq, value_bits, key_start, word_start, bad, offsets, len_keys, len_offsets, len_words,
-      len_key_start, len_word_start);
+      keys, g_off, nreq, value_bits, key_start, word_start, bad, offsets, lens);
   env.prof_end("batch_split");
   return check_launch(env, "batch_tables launch");
 }

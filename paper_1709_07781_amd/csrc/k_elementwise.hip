@@ -81,8 +81,8 @@ __global__ __launch_bounds__(256) void k_fill_u32(uint32_t* __restrict__ p, uint
     p[i] = value;
 }
 
-__global__ void k_set_len(uint64_t* d_len, uint64_t value) {
-  if (threadIdx.x == 0) *d_len = value;
+__global__ void k_set_len(uint64_t* d_len, LenHost host, uint64_t value) {
+  if (threadIdx.x == 0) put_len(d_len, host, 0, value);
 }
 
 __global__ void k_copy_len(uint64_t* dst, const uint64_t* src) {
@@ -155,8 +155,8 @@ int launch_fill_u32(Env& env, uint32_t* p, uint64_t count, uint32_t value) {
   return check_launch(env, "fill_u32 launch");
 }
 
-int launch_set_len(Env& env, uint64_t* d_len, uint64_t value) {
-  k_set_len<<<dim3(1), dim3(64), 0, env.stream()>>>(d_len, value);
+int launch_set_len(Env& env, uint64_t* d_len, uint64_t value, LenHost host) {
+  k_set_len<<<dim3(1), dim3(64), 0, env.stream()>>>(d_len, host, value);
   return check_launch(env, "set_len launch");
 }
 

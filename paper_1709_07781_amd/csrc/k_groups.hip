@@ -143,7 +143,7 @@ __global__ __launch_bounds__(kBlock) void k_groups_write(Groups g, uint64_t cap,
                                                          uint32_t* __restrict__ out_words,
                                                          uint64_t* __restrict__ len_keys,
                                                          uint64_t* __restrict__ len_offsets,
-                                                         uint64_t* __restrict__ len_words) {
+                                                         uint64_t* __restrict__ len_words, LenHost host) {
   const uint32_t k = dev_count(cap, k_len);
   const uint32_t first = blockIdx.x * kBlock + threadIdx.x;
   if (k == 0) {
@@ -151,7 +151,7 @@ __global__ __launch_bounds__(kBlock) void k_groups_write(Groups g, uint64_t cap,
       if (out_offsets) out_offsets[0] = 0;
       if (len_keys) *len_keys = 0;
       if (len_offsets) *len_offsets = 1;
-      *len_words = 0;
+      put_len(len_words, host, 0, 0);
     }
     return;
   }
@@ -188,7 +188,7 @@ __global__ __launch_bounds__(kBlock) void k_groups_write(Groups g, uint64_t cap,
       if (out_offsets) out_offsets[D] = W;
       if (len_keys) *len_keys = void_ ? 0u : D;
       if (len_offsets) *len_offsets = void_ ? 0u : (uint64_t)D + 1;
-      *len_words = void_ ? 0u : W;
+      put_len(len_words, host, 0, void_ ? 0u : W);
     }
   }
 }
@@ -303,15 +303,16 @@ __global__ void k_set_zero_u32(uint32_t* p) {
 }
 
 // *len = *reject ? 0 : value.
-__global__ void k_len_unless(uint64_t* __restrict__ len, uint64_t value, const uint32_t* __restrict__ reject) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *len = *reject ? 0u : value;
+__global__ void k_len_unless(uint64_t* __restrict__ len, LenHost host, uint64_t value,
+                             const uint32_t* __restrict__ reject) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) put_len(len, host, 0, *reject ? 0u : value);
 }
 
 // ---- host side --------------------------------------------------------------------------
 template <int kFmt>
 int encode_groups_fmt(Env& env, const Groups& g, uint64_t cap, const uint64_t* k_len, uint32_t* keys,
                       uint32_t* offsets, uint32_t* words, uint64_t* len_keys, uint64_t* len_offsets,
-                      uint64_t* len_words, uint32_t* reject) {
+                      uint64_t* len_words, LenHost host, uint32_t* reject) {
   const uint64_t c = std::max<uint64_t>(cap, 1);
   uint32_t* wc = static_cast<uint32_t*>(env.scratch(4 * c));
   uint32_t* sg = static_cast<uint32_t*>(env.scratch(4 * c));
@@ -332,24 +333,24 @@ int encode_groups_fmt(Env& env, const Groups& g, uint64_t cap, const uint64_t* k
   env.prof_begin("groups_write");
   k_groups_write<kFmt><<<dim3(grid), dim3(kBlock), 0, env.stream()>>>(g, c, k_len, wp, dp, fp, fl, reject, keys,
                                                                        offsets, words, len_keys, len_offsets,
-                                                                       len_words);
+                                                                       len_words, host);
   env.prof_end("groups_write");
   return check_launch(env, "groups_write launch");
 }
 
 int encode_groups(Env& env, uint32_t fmt, const Groups& g, uint64_t cap, const uint64_t* k_len, uint32_t* keys,
                   uint32_t* offsets, uint32_t* words, uint64_t* len_keys, uint64_t* len_offsets, uint64_t* len_words,
-                  uint32_t* reject) {
+                  LenHost host, uint32_t* reject) {
   switch (fmt) {
     case kFmtPaper:
       return encode_groups_fmt<kFmtPaper>(env, g, cap, k_len, keys, offsets, words, len_keys, len_offsets, len_words,
-                                          reject);
+                                          host, reject);
     case kFmtCanonical:
       return encode_groups_fmt<kFmtCanonical>(env, g, cap, k_len, keys, offsets, words, len_keys, len_offsets,
-                                              len_words, reject);
+                                              len_words, host, reject);
     case kFmtPlwah:
       return encode_groups_fmt<kFmtPlwah>(env, g, cap, k_len, keys, offsets, words, len_keys, len_offsets, len_words,
-                                          reject);
+                                          host, reject);
     default:
       return env.fail(kErrArg, "unknown WAH format");
   }
@@ -357,8 +358,8 @@ int encode_groups(Env& env, uint32_t fmt, const Groups& g, uint64_t cap, const u
 
 }  // namespace
 
-int launch_len_unless(Env& env, uint64_t* len, uint64_t value, const uint32_t* reject) {
-  k_len_unless<<<dim3(1), dim3(64), 0, env.stream()>>>(len, value, reject);
+int launch_len_unless(Env& env, uint64_t* len, LenHost host, uint64_t value, const uint32_t* reject) {
+  k_len_unless<<<dim3(1), dim3(64), 0, env.stream()>>>(len, host, value, reject);
   return check_launch(env, "len_unless launch");
 }
 
@@ -393,7 +394,7 @@ int launch_wah_decode(Env& env, const uint32_t* words, uint64_t m_cap, const uin
 
 int launch_wah_combine(Env& env, const uint32_t* a, uint64_t a_cap, const uint64_t* a_len, const uint32_t* b,
                        uint64_t b_cap, const uint64_t* b_len, uint32_t in_fmt, uint32_t ngroups, uint32_t op,
-                       uint32_t out_fmt, uint32_t* words, uint64_t* len_words, uint32_t* reject) {
+                       uint32_t out_fmt, uint32_t* words, uint64_t* len_words, LenHost host, uint32_t* reject) {
   if (op > 1) return env.fail(kErrArg, "wah combine: op must be 0 (AND) or 1 (OR)");
   if (in_fmt > kFmtPlwah || out_fmt > kFmtPlwah) return env.fail(kErrArg, "unknown WAH format");
   if (!words || !len_words || !reject) return env.fail(kErrArg, "wah combine: null buffer");
@@ -420,7 +421,7 @@ int launch_wah_combine(Env& env, const uint32_t* a, uint64_t a_cap, const uint64
   k_nonempty_groups<<<dim3(gg), dim3(kBlock), 0, env.stream()>>>(nz, gc, k_len, lit, chunk, glit);
   if ((rc = check_launch(env, "nonempty_groups launch"))) return rc;
   return encode_groups(env, out_fmt, Groups{nullptr, chunk, glit}, gc, k_len, nullptr, nullptr, words, nullptr,
-                       nullptr, len_words, reject);
+                       nullptr, len_words, host, reject);
 }
 
 int launch_wah_lookup(Env& env, const uint32_t* keys, uint64_t d_cap, const uint64_t* d_len, const uint32_t* queries,

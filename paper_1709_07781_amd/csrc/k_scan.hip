@@ -182,14 +182,14 @@ template <bool kVec>
 __global__ __launch_bounds__(kScanBlock) void k_compact_nonzero_u32(const uint32_t* __restrict__ in,
                                                                     uint32_t* __restrict__ out, uint64_t n_cap,
                                                                     const uint64_t* __restrict__ d_n,
-                                                                    uint64_t* __restrict__ d_out_len, LbArgs lb) {
+                                                                    uint64_t* __restrict__ d_out_len, LenHost host, LbArgs lb) {
   constexpr int R = kCompactRounds, kTile = kTileElems<R>;
   __shared__ uint32_t s_prefix;
   __shared__ uint32_t s_wave[R][kWaves];
   __shared__ __align__(16) uint32_t s_out[kTile];
   const uint64_t n = device_count(n_cap, d_n);
   const uint64_t ntiles = (n + kTile - 1) / kTile;
-  if (n == 0 && blockIdx.x == 0 && threadIdx.x == 0) *d_out_len = 0;  // empty input
+  if (n == 0 && blockIdx.x == 0 && threadIdx.x == 0) put_len(d_out_len, host, 0, 0);  // empty input
   const uint32_t tile = blockIdx.x;
   if (tile >= ntiles) return;
   uint32_t v[R][4];
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(kScanBlock) void k_compact_nonzero_u32(const uint32
   for (uint32_t v = threadIdx.x; v < nv; v += kScanBlock)
     *reinterpret_cast<u32x4w*>(out + dst + 4 * v) = *reinterpret_cast<const u32x4*>(s_out + 4 * v);
   if (threadIdx.x < total - 4 * nv) out[dst + 4 * nv + threadIdx.x] = s_out[4 * nv + threadIdx.x];
-  if (tile == ntiles - 1 && threadIdx.x == 0) *d_out_len = dst + total;
+  if (tile == ntiles - 1 && threadIdx.x == 0) put_len(d_out_len, host, 0, dst + total);
 }
 
 inline bool ranges_overlap(const uint32_t* a, const uint32_t* b, uint64_t n) {
@@ -253,9 +253,9 @@ int launch_exclusive_scan(Env& env, const uint32_t* in, uint32_t* out, uint64_t 
 }
 
 int launch_compact_nonzero(Env& env, const uint32_t* in, uint32_t* out, uint64_t n_cap, const uint64_t* d_n,
-                           uint64_t* d_out_len) {
+                           uint64_t* d_out_len, LenHost host) {
   if (!d_out_len) return env.fail(kErrArg, "compact_nonzero_u32: no length slot");
-  if (n_cap == 0) return launch_set_len(env, d_out_len, 0);
+  if (n_cap == 0) return launch_set_len(env, d_out_len, 0, host);
   if (!in || !out) return env.fail(kErrArg, "compact_nonzero_u32: null buffer");
   if (n_cap > 0xFFFFFFFFull) return env.fail(kErrArg, "compact_nonzero_u32: more than 2^32-1 elements");
   if (ranges_overlap(in, out, n_cap)) return env.fail(kErrArg, "compact_nonzero_u32: in and out overlap");
@@ -266,9 +266,10 @@ int launch_compact_nonzero(Env& env, const uint32_t* in, uint32_t* out, uint64_t
   const bool vec = (reinterpret_cast<uintptr_t>(in) & 15u) == 0;
   env.prof_begin("compact_nonzero_u32");
   if (vec)
-    k_compact_nonzero_u32<true><<<dim3(grid), dim3(kScanBlock), 0, env.stream()>>>(in, out, n_cap, d_n, d_out_len, lb);
+    k_compact_nonzero_u32<true><<<dim3(grid), dim3(kScanBlock), 0, env.stream()>>>(in, out, n_cap, d_n, d_out_len, host,
+                                                                                   lb);
   else
-    k_compact_nonzero_u32<false><<<dim3(grid), dim3(kScanBlock), 0, env.stream()>>>(in, out, n_cap, d_n, d_out_len,
+    k_compact_nonzero_u32<false><<<dim3(grid), dim3(kScanBlock), 0, env.stream()>>>(in, out, n_cap, d_n, d_out_len, host,
                                                                                     lb);
   env.prof_end("compact_nonzero_u32");
   return check_launch(env, "compact_nonzero_u32 launch");

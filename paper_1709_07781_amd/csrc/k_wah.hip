@@ -204,9 +204,9 @@ __device__ LbPairSum wave_tile_count(const KeyT* __restrict__ skeys, const uint3
 // An empty input's index, D = 0, W = 0, offsets = [0], by one work-item.
 __device__ __forceinline__ void write_empty_index(const IndexOut& out) {
   out.offsets[0] = 0;
-  *out.len_keys = 0;
-  *out.len_offsets = 1;
-  *out.len_words = 0;
+  put_len(out.len_keys, out.host, 0, 0);
+  put_len(out.len_offsets, out.host, 1, 1);
+  put_len(out.len_words, out.host, 2, 0);
 }
 
 __global__ void k_wah_empty(IndexOut out) {
@@ -640,9 +640,9 @@ __global__ __launch_bounds__(kBlock, kFmt == kFmtPaper && !kSort ? 8 : 4) void k
     const uint32_t D = dpre + tile_ns, W = wpre + tile_nw;
     out.offsets[D] = W;
     const bool void_ = kSort ? rej.shift < 32 && (small_or >> rej.shift) != 0u : rej();
-    *out.len_keys = void_ ? 0u : D;
-    *out.len_offsets = void_ ? 0u : (uint64_t)D + 1;
-    *out.len_words = void_ ? 0u : W;
+    put_len(out.len_keys, out.host, 0, void_ ? 0u : D);
+    put_len(out.len_offsets, out.host, 1, void_ ? 0u : (uint64_t)D + 1);
+    put_len(out.len_words, out.host, 2, void_ ? 0u : W);
   }
 }
 

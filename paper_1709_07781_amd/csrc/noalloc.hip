@@ -104,7 +104,7 @@ extern "C" KA_API int ka_wah_index_noalloc(const uint32_t* values, uint64_t n, u
     int rc = scratch_address(dev, &base);
     if (rc) return rc;
     NoAllocEnv env(static_cast<char*>(base), static_cast<hipStream_t>(stream));
-    const IndexOut out{keys, offsets, words, lengths, lengths + 1, lengths + 2};
+    const IndexOut out{keys, offsets, words, lengths, lengths + 1, lengths + 2, {}};
     if (n && n <= kSmallIndexMax) return launch_wah_small(env, values, n, 0, out);
     // Status words start at zero in every call (a fill kernel: no memset node
     // if the caller captures the call into a graph).

@@ -229,7 +229,8 @@ static int plan_build(ka_system* sys, const uint32_t* req_off, uint64_t n, uint3
     rc = any_batch ? launch_len_from_u32(e, p->d_n, p->req_off + nreq) : kOk;
     if (!rc)
       rc = launch_wah_batch(e, p->input, n, p->req_off, nreq, value_bits, p->keys, p->offsets, p->words,
-                            p->key_start, p->word_start, p->lens, p->lens + 1, p->lens + 2, p->lens + 3, p->lens + 4,
+                            p->key_start, p->word_start,
+                            BatchLens{p->lens, p->lens + 1, p->lens + 2, p->lens + 3, p->lens + 4, {}},
                             shape, biggest, nullptr, any_batch ? p->d_n : nullptr);
     hipGraph_t g = nullptr;
     const hipError_t ec = hipStreamEndCapture(p->s, &g);

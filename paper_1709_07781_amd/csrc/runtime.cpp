@@ -111,6 +111,7 @@ int System::ensure_init() {
     if (hipMemset(p, 0, kSortPlanBytes) != hipSuccess) return fail(KA_E_DEVICE, "arena clear failed");
     sc->arena.plan = p;
   }
+  if (!len_lines.init()) return fail(KA_E_OOM, "pinned allocation failed");
   init_rc = KA_OK;
   return KA_OK;
 }
@@ -356,6 +357,52 @@ void HostStage::destroy(System* sys) {
 }
 
 // ---------------------------------------------------------------------------------
+// lengths on the host
+// ---------------------------------------------------------------------------------
+bool LenLines::grow_locked() {
+  constexpr size_t kSlab = 64 << 10;
+  void* p = nullptr;
+  if (hipHostMalloc(&p, kSlab, hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  slabs_.push_back(p);
+  uint64_t* w = static_cast<uint64_t*>(p);
+  for (size_t i = 0; i < kSlab / 8; i += kWords) free_.push_back(w + i);
+  return true;
+}
+
+bool LenLines::init() {
+  std::lock_guard<std::mutex> g(mu_);
+  return grow_locked();
+}
+
+LenLine* LenLines::get() {
+  std::lock_guard<std::mutex> g(mu_);
+  if (free_.empty() && !grow_locked()) return nullptr;
+  LenLine* l = new LenLine();
+  l->p = free_.back();
+  free_.pop_back();
+  if (++tag_ == 0) ++tag_;
+  l->tag = tag_;
+  for (uint32_t i = 0; i < kWords; ++i) __atomic_store_n(l->p + i, 0ull, __ATOMIC_RELAXED);
+  return l;
+}
+
+void LenLines::put(LenLine* l) {
+  std::lock_guard<std::mutex> g(mu_);
+  if (!slabs_.empty()) free_.push_back(l->p);  // else the system is gone, and the line with it
+  delete l;
+}
+
+void LenLines::destroy() {
+  std::lock_guard<std::mutex> g(mu_);
+  for (void* p : slabs_) (void)hipHostFree(p);
+  slabs_.clear();
+  free_.clear();
+}
+
+// ---------------------------------------------------------------------------------
 // references
 // ---------------------------------------------------------------------------------
 int ref_create(System* sys, uint32_t dtype, uint64_t count, uint32_t si, bool device_len, Ref** out) {
@@ -390,6 +437,7 @@ void ref_release(Ref* r) {
   System* sys = r->sys;
   if (!r->borrowed && !sys->destroyed.load()) sys->pool.release(r->ptr, r->alloc_bytes, r->home, r->used_mask.load());
   Ref* parent = r->parent;
+  if (r->line && r->line->rc.fetch_sub(1) == 1) sys->len_lines.put(r->line);
   delete static_cast<ka_ref*>(r);
   sys->release();
   if (parent) ref_release(parent);
@@ -427,6 +475,19 @@ int ref_sync(Ref* r) {
   return KA_OK;
 }
 
+bool ref_length_there(Ref* r, uint64_t* len) {
+  if (!r->len_known.load()) {
+    if (!r->line || r->sys->destroyed.load()) return false;
+    const uint64_t w = __atomic_load_n(r->line->p + r->line_i, __ATOMIC_ACQUIRE);
+    if ((uint32_t)(w >> 32) != r->line->tag) return false;
+    r->sys->length_reads.fetch_add(1);
+    r->len = std::min<uint64_t>((uint32_t)w, r->cap);
+    r->len_known.store(true);
+  }
+  *len = r->len;
+  return true;
+}
+
 int ref_length(Ref* r, uint64_t* len) {
   if (r->len_known.load()) {
     *len = r->len;
@@ -434,6 +495,7 @@ int ref_length(Ref* r, uint64_t* len) {
   }
   int rc = ref_sync(r);
   if (rc) return rc;
+  if (ref_length_there(r, len)) return KA_OK;
   r->sys->length_reads.fetch_add(1);
   uint64_t v = 0;
   KA_HIP(hipMemcpy(&v, r->d_len, sizeof(v), hipMemcpyDeviceToHost), "length read-back");
@@ -773,7 +835,8 @@ static int run_kernel_actor(Actor* a, Msg& msg, Msg& out, uint32_t si) {
   // Bind outputs, local and private arguments.
   std::vector<ka_value> cin;
   bool have_cin = false;
-  uint32_t lds_off = 0;
+  uint32_t lds_off = 0, n_lens = 0;
+  LenLine* line = nullptr;  // the data-dependent lengths, on the host too
   for (size_t i = 0; i < a->sig.size(); ++i) {
     const SigArg& s = a->sig[i];
     Bound& b = args[i];
@@ -808,6 +871,16 @@ static int run_kernel_actor(Actor* a, Msg& msg, Msg& out, uint32_t si) {
       b.ptr = r->ptr;
       b.cap = cap;
       b.d_len = dlen ? r->d_len : nullptr;
+      if (a->bk && a->bk->device_len((uint32_t)i) && n_lens < LenLines::kWords) {
+        if (!n_lens) line = sys->len_lines.get();
+        if (line) {
+          if (n_lens) line->rc.fetch_add(1);
+          r->line = line;
+          r->line_i = n_lens;
+          b.h_len = LenHost{line->p + n_lens, line->tag};
+        }
+        ++n_lens;
+      }
     } else if (s.a.dir == KA_LOCAL) {
       b.lds_offset = lds_off;
       lds_off += (uint32_t)((s.a.count * dtype_size(s.a.dtype) + 15) / 16 * 16);
@@ -980,6 +1053,7 @@ KA_API int ka_system_destroy(ka_system* sys) {
       sys->prof_pending.clear();
     }
     sys->stage.destroy(sys);
+    sys->len_lines.destroy();
     for (auto& sc : sys->streams) {
       sc->arena.status = nullptr;  // a pool block, freed with the pool below
       hipFree(sc->arena.plan);
@@ -1536,6 +1610,8 @@ static int wah_actor(ka_system* sys, uint32_t value_bits, uint32_t format, ka_ac
 // so on one stream) in one round trip: three 8-byte copies into pinned memory,
 // one synchronisation.  Each becomes the ref's host-known length.
 static int read_lengths3(System* sys, Ref* const r[3], uint64_t len[3]) {
+  if (ref_length_there(r[0], &len[0]) && ref_length_there(r[1], &len[1]) && ref_length_there(r[2], &len[2]))
+    return KA_OK;
   const uint32_t home = r[0]->home;
   if (r[1]->home != home || r[2]->home != home) {
     for (int i = 0; i < 3; ++i) {
@@ -1760,7 +1836,8 @@ KA_API int ka_wah_batch(ka_system* sys, const uint32_t* values, uint64_t n, cons
   ka_ticket_release(t);
   if (rc) return rc;
   uint64_t len[5] = {};
-  for (int i = 0; i < 5 && !rc; ++i) rc = ref_length(res[i].ref, &len[i]);
+  for (int i = 0; i < 5 && !rc; ++i)  // the response is there, and its lengths with it
+    if (!ref_length_there(res[i].ref, &len[i])) rc = ref_length(res[i].ref, &len[i]);
   if (!rc && len[3] == 0) rc = set_error(KA_E_ARG, "a value is at or above 2^value_bits");
   if (!rc && (len[1] != len[0] + nreq || len[3] != nreq + 1ull || len[4] != nreq + 1ull))
     rc = set_error(KA_E_DEVICE, "inconsistent batch index lengths");

@@ -79,6 +79,33 @@ class HostStage {
   std::unordered_map<void*, uint64_t> sizes_;
 };
 
+// ---- lengths on the host -----------------------------------------------------------
+// The pinned words of one response's data-dependent lengths (see LenHost), one
+// 64-byte line.  Shared by the response's refs; the line is reused when the
+// last of them is gone.  A kernel of an earlier owner may still write its
+// lengths later: they carry that owner's tag, and the new owner's ref then
+// reads its length from the device.
+struct LenLine {
+  uint64_t* p = nullptr;
+  uint32_t tag = 0;
+  std::atomic<int> rc{1};
+};
+class LenLines {
+ public:
+  static constexpr uint32_t kWords = 8;
+  bool init();       // the first lines (with the system: none is pinned under a graph capture)
+  LenLine* get();    // null: none left (lengths are then read from the device)
+  void put(LenLine* l);
+  void destroy();
+
+ private:
+  bool grow_locked();
+  std::mutex mu_;
+  std::vector<void*> slabs_;
+  std::vector<uint64_t*> free_;
+  uint32_t tag_ = 0;
+};
+
 struct StreamCtx {
   hipStream_t s = nullptr;
   bool owned = false;
@@ -105,6 +132,7 @@ struct System {
   std::vector<std::unique_ptr<StreamCtx>> streams;
   Pool pool;
   HostStage stage;
+  LenLines len_lines;
   std::atomic<bool> profile{false};
   std::atomic<uint64_t> length_reads{0};  // device-resident lengths read back on the host (each waits)
   uint32_t lb_spin = kLbSpinLimit;  // look-back spin limit (KA_LOOKBACK_SPIN)
@@ -219,6 +247,8 @@ struct Ref {
   bool borrowed = false;
   uint64_t* d_len = nullptr;  // device-resident length (data-dependent outputs)
   std::atomic<bool> len_known{true};
+  LenLine* line = nullptr;  // the same length on the host, word line_i (+1 held)
+  uint32_t line_i = 0;
   uint64_t len = 0;
   uint32_t home = 0;  // stream of the last writer
   std::atomic<uint64_t> used_mask{0};
@@ -234,6 +264,8 @@ void ref_release(Ref* r);
 int ref_sync(Ref* r);
 // The true length (reads the device slot if needed; waits).
 int ref_length(Ref* r, uint64_t* len);
+// The length if it is on the host already (its producer has run); never waits.
+bool ref_length_there(Ref* r, uint64_t* len);
 // Orders stream si after the last writer of r (and, for a write, after every
 // stream that used r) and records the use.
 int ref_use_on(Ref* r, uint32_t si, bool write);
@@ -247,6 +279,7 @@ struct Bound {  // one signature argument bound for a launch
   uint64_t cap = 0;
   uint64_t len = 0;               // host-known length (inputs), valid when d_len == nullptr
   const uint64_t* d_len = nullptr;  // device length of an input, or slot of an output
+  LenHost h_len;                    // an output's length on the host (later outputs' follow)
   Ref* ref = nullptr;
   uint64_t priv[4] = {0, 0, 0, 0};
   uint32_t lds_offset = 0;

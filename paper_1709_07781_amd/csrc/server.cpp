@@ -372,7 +372,7 @@ Batch* Server::launch(std::vector<SrvReq*>& take, uint64_t bytes) {
     for (auto* r : b->reqs[KA_REQ_WAH]) biggest = std::max<uint32_t>(biggest, (uint32_t)r->n);
     if (rw)
       rc = launch_wah_batch(env, u32(d_vw), nw, u32(d_rw), rw, value_bits, u32(d_keys), u32(d_offs), u32(d_words),
-                            u32(d_ks), u32(d_ws), lens, lens + 1, lens + 2, lens + 3, lens + 4, 0, biggest,
+                            u32(d_ks), u32(d_ws), BatchLens{lens, lens + 1, lens + 2, lens + 3, lens + 4, {}}, 0, biggest,
                             u32(d_bad));
     if (!rc && rs) rc = launch_segmented_scan(env, u32(d_vs), u32(d_scan), ns, u32(d_rs), rs);
     if (!rc && nc)

@@ -141,3 +141,31 @@ def test_counts_on_the_device(sess, cap, n, bits):
         sess.release_actor(a)
     for g, e in zip(got, oracle.default().wah_index(x[x != 0])):
         np.testing.assert_array_equal(g, e)
+
+
+@pytest.mark.parametrize("n", [3000, 40_000])
+def test_lengths_of_requests_in_flight(sess, n):
+    """Lengths that arrive on the host: requests queued before any is received, some dropped unread (their words
+    are reused by later requests while the kernels may still have to write them), lengths read in any order."""
+    import ctypes
+    import paper_1709_07781_amd as ka
+    priv = (ctypes.c_uint32 * 1)(10)
+    idx = sess.spawn("wah_index", [ka.arg(ka.KA_IN), ka.arg(ka.KA_PRIV, count=1, init=priv)] + [ka.arg(ka.KA_OUT)] * 3)
+    cols = [workloads.uniform_values(50 + i, n - 7 * i, 3 + 90 * i) for i in range(9)]
+    dev = [sess.upload(c) for c in cols]
+    refs = [sess.wrap(d) for d in dev]
+    for round_ in range(3):
+        tickets = [sess.send(idx, ka.ref(r)) for r in refs]
+        for i in (0, 3, 4):
+            sess.release_ticket(tickets[i])
+        more = [sess.send(idx, ka.ref(refs[i])) for i in (8, 7, 6)]
+        todo = [(i, tickets[i]) for i in (8, 1, 7, 2, 6, 5)] + list(zip((8, 7, 6), more))
+        for i, t in todo:
+            got = sess.receive(t, 3)
+            sess.release_ticket(t)
+            for g, e in zip(got, oracle.default().wah_index(cols[i])):
+                np.testing.assert_array_equal(sess.read(g), e)
+                sess.release_ref(g)
+    for r in refs:
+        sess.release_ref(r)
+    sess.release_actor(idx)
