@@ -187,14 +187,8 @@ int run_decode(LaunchCtx& c) {
   if (fmt > 2) return env.fail(KA_E_ARG, "wah_decode: format must be 0, 1 or 2");
   if (ng >= (1ull << 32) || ng > a[2].cap) return env.fail(KA_E_ARG, "wah_decode: ngroups exceeds the output");
   if (c.n > a[0].cap) return env.fail(KA_E_ARG, "wah_decode: range exceeds the words");
-  uint32_t* reject = static_cast<uint32_t*>(env.scratch(4));
-  if (!reject) return env.fail(KA_E_OOM, "wah_decode: scratch");
-  int rc;
-  if ((rc = launch_zero_u32(env, reject))) return rc;
-  if ((rc = launch_wah_decode(env, static_cast<const uint32_t*>(a[0].ptr), c.n, c.d_n, fmt, (uint32_t)ng,
-                              static_cast<uint32_t*>(a[2].ptr), reject)))
-    return rc;
-  return launch_len_unless(env, const_cast<uint64_t*>(a[2].d_len), a[2].h_len, ng, reject);
+  return launch_wah_decode(env, static_cast<const uint32_t*>(a[0].ptr), c.n, c.d_n, fmt, (uint32_t)ng,
+                           static_cast<uint32_t*>(a[2].ptr), const_cast<uint64_t*>(a[2].d_len), a[2].h_len);
 }
 
 // wah_combine: (in a; in b; priv op, in_format, out_format, ngroups; out words)
@@ -208,14 +202,10 @@ int run_combine(LaunchCtx& c) {
   if (op > 1 || fin > 2 || fout > 2) return env.fail(KA_E_ARG, "wah_combine: op 0..1, formats 0..2");
   if (ng >= (1ull << 31) || 2 * ng + 1 > a[3].cap) return env.fail(KA_E_ARG, "wah_combine: ngroups exceeds the output");
   if (fout == 2 && ng > 0x1FFFFFFull) return env.fail(KA_E_ARG, "wah_combine: PLWAH fills cover at most 2^25 - 1 groups");
-  uint32_t* reject = static_cast<uint32_t*>(env.scratch(4));
-  if (!reject) return env.fail(KA_E_OOM, "wah_combine: scratch");
-  int rc;
-  if ((rc = launch_zero_u32(env, reject))) return rc;
   return launch_wah_combine(env, static_cast<const uint32_t*>(a[0].ptr), a[0].d_len ? a[0].cap : a[0].len, a[0].d_len,
                             static_cast<const uint32_t*>(a[1].ptr), a[1].d_len ? a[1].cap : a[1].len, a[1].d_len, fin,
                             (uint32_t)ng, op, fout, static_cast<uint32_t*>(a[3].ptr), const_cast<uint64_t*>(a[3].d_len),
-                            a[3].h_len, reject);
+                            a[3].h_len);
 }
 
 // wah_index_batch: (in values; in req_off; priv value_bits [, largest request + 1];

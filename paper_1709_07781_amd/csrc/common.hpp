@@ -83,6 +83,9 @@ int launch_affine_chain(Env& env, uint32_t* x, uint64_t n, const uint32_t* a, co
 int launch_affine(Env& env, uint32_t* x, uint64_t n_cap, const uint64_t* d_n, uint64_t offset, uint32_t a,
                   uint32_t b);
 int launch_exclusive_scan(Env& env, const uint32_t* in, uint32_t* out, uint64_t n_cap, const uint64_t* d_n);
+// start[i] = groups covered by words[0 .. i-1] of a bitmap in word format fmt.
+int launch_exclusive_scan_groups(Env& env, const uint32_t* words, uint32_t* start, uint64_t n_cap,
+                                 const uint64_t* d_n, uint32_t fmt);
 int launch_compact_nonzero(Env& env, const uint32_t* in, uint32_t* out, uint64_t n_cap, const uint64_t* d_n,
                            uint64_t* d_out_len, LenHost host = {});
 // Look-back words (count of them, kLbSpread apart) that a sort's first launch
@@ -157,21 +160,19 @@ int launch_wah_small(Env& env, const uint32_t* values, uint64_t n, uint32_t valu
 int launch_wah_encode16(Env& env, const uint16_t* skeys, const uint32_t* srows, uint64_t n, const IndexOut& out,
                         const EncodeOpts& opt = {});
 // One bitmap (m words, the count on the device when m_len is given) decoded
-// into ngroups 31-bit group words; more groups than ngroups sets *reject.
+// into ngroups 31-bit group words; *len = ngroups, or 0 if it covers more.
 int launch_wah_decode(Env& env, const uint32_t* words, uint64_t m_cap, const uint64_t* m_len, uint32_t fmt,
-                      uint32_t ngroups, uint32_t* groups, uint32_t* reject);
+                      uint32_t ngroups, uint32_t* groups, uint64_t* len, LenHost host);
 // AND (op 0) / OR (op 1) of two bitmaps over ngroups groups, encoded in
-// out_fmt into words (capacity 2 ngroups), its length in *len_words.
+// out_fmt into words (capacity 2 ngroups), its length in *len_words (0 if an
+// input covers more groups).
 int launch_wah_combine(Env& env, const uint32_t* a, uint64_t a_cap, const uint64_t* a_len, const uint32_t* b,
                        uint64_t b_cap, const uint64_t* b_len, uint32_t in_fmt, uint32_t ngroups, uint32_t op,
-                       uint32_t out_fmt, uint32_t* words, uint64_t* len_words, LenHost host, uint32_t* reject);
+                       uint32_t out_fmt, uint32_t* words, uint64_t* len_words, LenHost host);
 // slots[i] = d with keys[d] == queries[i], or 0xFFFFFFFF (keys ascending).
 // q_len, when given, is the query count on the device (at most q).
 int launch_wah_lookup(Env& env, const uint32_t* keys, uint64_t d_cap, const uint64_t* d_len, const uint32_t* queries,
                       uint64_t q, uint32_t* slots, const uint64_t* q_len = nullptr);
-int launch_zero_u32(Env& env, uint32_t* p);
-// *len = *reject ? 0 : value.
-int launch_len_unless(Env& env, uint64_t* len, LenHost host, uint64_t value, const uint32_t* reject);
 // Batched index build: nreq requests, values concatenated, req_off[j] the
 // first position of request j (req_off[nreq] = n).  max_req: the largest
 // request, when the caller knows it (kMaxReqUnknown otherwise); batches of
@@ -242,6 +243,18 @@ __device__ __forceinline__ void load_key4(const uint32_t* __restrict__ p, uint64
 __device__ __forceinline__ void load_key4(const uint16_t* __restrict__ p, uint64_t q, uint32_t (&k)[4]) {
   const u32x2 a = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p) + q);
   k[0] = a.x & 0xFFFFu, k[1] = a.x >> 16, k[2] = a.y & 0xFFFFu, k[3] = a.y >> 16;
+}
+
+// Word formats: 0 the paper's form, 1 canonical WAH with 1-fills, 2 PLWAH.
+enum { kFmtPaper = 0, kFmtCanonical = 1, kFmtPlwah = 2 };
+constexpr uint32_t kPlwahShift = 25;  // PLWAH: bits 29..25 = 1 + the absorbed group's bit
+
+// Groups that one word covers.
+template <int kFmt>
+__device__ __forceinline__ uint32_t word_groups(uint32_t w) {
+  if (!(w & 0x80000000u)) return 1u;
+  if (kFmt == kFmtPlwah) return (w & 0x1FFFFFFu) + (((w >> kPlwahShift) & 31u) ? 1u : 0u);
+  return w & 0x3FFFFFFFu;
 }
 
 // Inclusive wave64 prefix sum: row_shr 1,2,4,8 inside each row of 16 lanes,

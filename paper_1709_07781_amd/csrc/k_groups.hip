@@ -6,31 +6,35 @@
 // lengths; a fill absorbs the group right after it when that differs from the
 // fill's groups in one bit only: bits 29..25 = 1 + that bit's index).
 //
-// AND / OR decodes both bitmaps, combines them group by group and encodes the
-// non-empty result groups, a list of (chunk id, literal), by their flags: what
-// group i emits depends on groups i-1 and i, except for the length of a 1-fill
-// (the run's end, found by binary search over the prefix count of full groups)
-// and its PLWAH position (the group after the run); prefix sums of words and
-// full groups (the look-back scan) then place the words.
+// Decoding is a scan of the words' group counts (the look-back scan, counting
+// as it loads) and a pass over tiles of groups: a tile finds its first and last
+// word by a 64-way search, marks where the words between start, and a running
+// maximum gives every group its word.  AND / OR decodes both bitmaps tile by
+// tile in one pass, which writes the combined groups and each tile's summary,
+// and encodes them in a second: what a group emits depends on it and the group
+// before, a fill's length on the last non-empty group and a 1-fill's on the end
+// of its run, both found in the tile or in the summaries.  Both are bound by
+// latency (the search's dependent loads, about 1 us each): over 645,162 groups
+// a decode takes 7 + 11 us and an OR 2 x 7 + 18 + 6 us, in two and four
+// launches; counting, scanning, searching per group, compacting and encoding
+// through a group list took 27 us in three and 80 us in sixteen.
 //
 // Every count that depends on the data stays on the device; grids are sized
 // by capacities and read the true counts there.
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace ka {
 namespace {
 
-constexpr uint32_t kRows = 31;
 constexpr uint32_t kFillBit = 0x80000000u;
 constexpr uint32_t kOneBit = 0x40000000u;
 constexpr uint32_t kFull = 0x7FFFFFFFu;
 constexpr uint32_t kLen30 = 0x3FFFFFFFu;
-constexpr uint32_t kPlwahShift = 25;
 constexpr uint32_t kLen25 = 0x1FFFFFFu;
 constexpr int kBlock = 256;
 constexpr uint32_t kMaxGrid = 4096;
-
-enum { kFmtPaper = 0, kFmtCanonical = 1, kFmtPlwah = 2 };
 
 __device__ __forceinline__ uint32_t dev_count(uint64_t cap, const uint64_t* d_n) {
   return (uint32_t)device_count(cap, d_n);
@@ -42,236 +46,393 @@ uint32_t grid_for(uint64_t cap) {
 }
 
 // ---------------------------------------------------------------------------------
-// the encoder over k groups (gkey null: one bitmap, key 0)
+// tiles of groups decoded from words
 // ---------------------------------------------------------------------------------
-struct Groups {
-  const uint32_t* key;  // null: all 0
-  const uint32_t* chunk;
-  const uint32_t* lit;
-  __device__ __forceinline__ uint32_t k_of(uint32_t i) const { return key ? key[i] : 0u; }
+constexpr int kPer = 8;                   // consecutive groups per work-item
+constexpr uint32_t kTile = kBlock * kPer;  // 2048 groups
+constexpr int kWaves = kBlock / 64;
+
+// One bitmap: m words (the count on the device) and the scan of their group counts.
+struct Bitmap {
+  const uint32_t* words;
+  const uint32_t* start;
+  uint64_t cap;
+  const uint64_t* len;
+  __device__ __forceinline__ uint32_t count() const { return dev_count(cap, len); }
 };
 
-// What group i emits, from groups i-1 and i.
-struct GroupFlags {
-  bool seg;    // first group of its key
-  bool full;   // all 31 rows
-  bool fill;   // a 0-fill word precedes it (gap > 0), unless absorbed below
-  bool main;   // its literal, or the 1-fill of the run it starts
-  uint32_t gap;
-  uint32_t words;
-};
-
+// Groups that m words cover.
 template <int kFmt>
-__device__ __forceinline__ GroupFlags group_flags(const Groups& g, uint32_t i) {
-  GroupFlags f;
-  const uint32_t lit = g.lit[i], c = g.chunk[i];
-  f.seg = i == 0 || g.k_of(i) != g.k_of(i - 1);
-  const uint32_t pc = f.seg ? 0u : g.chunk[i - 1];
-  f.gap = f.seg ? c : c - pc - 1u;
-  f.full = lit == kFull;
-  bool skip = false, fold1 = false;
-  if (kFmt != kFmtPaper) {
-    const bool pfull = !f.seg && pc + 1u == c && g.lit[i - 1] == kFull;  // the previous group ends a full run
-    skip = f.full && pfull;                                                // inside the run's 1-fill
-    if (kFmt == kFmtPlwah) {
-      const uint32_t pop = (uint32_t)__popc(lit);
-      skip = skip || (!f.full && pfull && pop == 30u);  // absorbed into the run's 1-fill
-      fold1 = !f.full && f.gap > 0u && pop == 1u;       // absorbed into its 0-fill
-    }
-  }
-  f.fill = !skip && f.gap > 0u;
-  f.main = !skip && !fold1;
-  f.words = (f.fill ? 1u : 0u) + (f.main ? 1u : 0u);
-  return f;
+__device__ __forceinline__ uint64_t total_groups(const Bitmap& b, uint32_t m) {
+  return m ? (uint64_t)b.start[m - 1] + word_groups<kFmt>(b.words[m - 1]) : 0u;
 }
 
-// words[i], seg[i] and (formats with 1-fills) full[i] per group; a fill length
-// beyond the format's field sets *reject.
-template <int kFmt>
-__global__ __launch_bounds__(kBlock) void k_groups_flags(Groups g, uint64_t cap, const uint64_t* __restrict__ k_len,
-                                                         uint32_t* __restrict__ words, uint32_t* __restrict__ segs,
-                                                         uint32_t* __restrict__ fulls, uint32_t* __restrict__ reject) {
-  const uint32_t k = dev_count(cap, k_len);
-  const uint32_t lim = kFmt == kFmtPlwah ? kLen25 : kLen30;
-  for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < k; i += gridDim.x * kBlock) {
-    const GroupFlags f = group_flags<kFmt>(g, i);
-    words[i] = f.words;
-    segs[i] = f.seg ? 1u : 0u;
-    if (kFmt != kFmtPaper) fulls[i] = f.full ? 1u : 0u;
-    if (f.fill && f.gap > lim) *reject = 1u;
-  }
-}
-
-// Groups in the run of full groups that starts at i: the largest L with
-// groups i .. i+L-1 of one key, consecutive chunk ids and all full.  The
-// predicate is monotone in L (chunk ids increase within a key, so equal
-// differences of ids and positions mean consecutive ids; the prefix count of
-// full groups, fpos, tells whether all of them are full): exponential then
-// binary search.
-__device__ __forceinline__ uint32_t run_length(const Groups& g, const uint32_t* __restrict__ fpos,
-                                               const uint32_t* __restrict__ fulls, uint32_t k, uint32_t i) {
-  const uint32_t key = g.k_of(i), c = g.chunk[i], f0 = fpos[i];
-  auto ok = [&](uint32_t L) {  // groups i .. i+L-1 form the run's first L groups
-    const uint32_t e = i + L - 1u;
-    return e < k && g.k_of(e) == key && g.chunk[e] - c == L - 1u && fpos[e] + fulls[e] - f0 == L;
-  };
-  uint32_t lo = 1, step = 1;  // ok(lo) holds
-  while (ok(lo + step)) {
-    lo += step;
-    step <<= 1;
-  }
-  uint32_t hi = lo + step;  // ok(hi) fails
+// Last k in [0, m) with start[k] <= g, by one wave (m > 0; start[0] = 0): every
+// step leaves a 64th of the range.
+__device__ __forceinline__ uint32_t wave_last_start(const uint32_t* __restrict__ start, uint32_t m, uint32_t g) {
+  uint32_t lo = 0, hi = m;  // start[lo] <= g < start[hi] (or hi = m)
   while (hi - lo > 1u) {
-    const uint32_t mid = lo + (hi - lo) / 2u;
-    if (ok(mid))
-      lo = mid;
-    else
-      hi = mid;
+    const uint32_t step = (hi - lo + 63u) / 64u;
+    const uint64_t p = (uint64_t)lo + (uint64_t)lane_id() * step;
+    const bool le = p < hi && start[p < hi ? p : lo] <= g;
+    const uint32_t c = (uint32_t)__popcll(__ballot(le || lane_id() == 0));
+    lo += (c - 1u) * step;
+    hi = min(hi, lo + step);
   }
   return lo;
 }
 
+// Group gi of the word w that starts at group s.
 template <int kFmt>
-__global__ __launch_bounds__(kBlock) void k_groups_write(Groups g, uint64_t cap, const uint64_t* __restrict__ k_len,
-                                                         const uint32_t* __restrict__ wpos,
-                                                         const uint32_t* __restrict__ dpos,
-                                                         const uint32_t* __restrict__ fpos,
-                                                         const uint32_t* __restrict__ fulls,
-                                                         const uint32_t* __restrict__ reject,
-                                                         uint32_t* __restrict__ out_keys,
-                                                         uint32_t* __restrict__ out_offsets,
-                                                         uint32_t* __restrict__ out_words,
-                                                         uint64_t* __restrict__ len_keys,
-                                                         uint64_t* __restrict__ len_offsets,
-                                                         uint64_t* __restrict__ len_words, LenHost host) {
-  const uint32_t k = dev_count(cap, k_len);
-  const uint32_t first = blockIdx.x * kBlock + threadIdx.x;
-  if (k == 0) {
-    if (first == 0) {
-      if (out_offsets) out_offsets[0] = 0;
-      if (len_keys) *len_keys = 0;
-      if (len_offsets) *len_offsets = 1;
-      put_len(len_words, host, 0, 0);
-    }
-    return;
+__device__ __forceinline__ uint32_t group_value(uint32_t w, uint32_t s, uint32_t gi) {
+  if (!(w & kFillBit)) return w;
+  const bool one = (w & kOneBit) != 0u;
+  const uint32_t len = kFmt == kFmtPlwah ? (w & kLen25) : (w & kLen30);
+  if (gi - s < len) return one ? kFull : 0u;
+  const uint32_t p = kFmt == kFmtPlwah ? (w >> kPlwahShift) & 31u : 0u;  // the absorbed group after the fill
+  return one ? (kFull & ~(1u << (p - 1u))) : (1u << (p - 1u));
+}
+
+// Largest of the wave's lanes up to this one.
+__device__ __forceinline__ uint32_t wave_incl_max(uint32_t x) {
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t y = (uint32_t)__shfl_up((int)x, off);
+    if ((int)lane_id() >= off) x = max(x, y);
   }
-  for (uint32_t i = first; i < k; i += gridDim.x * kBlock) {
-    const GroupFlags f = group_flags<kFmt>(g, i);
-    uint32_t w = wpos[i];
-    if (f.seg && out_keys) {
-      const uint32_t d = dpos[i];
-      out_keys[d] = g.k_of(i);
-      out_offsets[d] = w;
+  return x;
+}
+
+// Largest of the work-group's work-items before this one (0 for the first) and,
+// in *all, of all of them.  s_wave: kWaves words; one barrier.
+__device__ __forceinline__ uint32_t block_excl_max(uint32_t x, uint32_t* s_wave, uint32_t* all) {
+  const uint32_t inc = wave_incl_max(x), w = threadIdx.x / 64;
+  if (lane_id() == 63) s_wave[w] = inc;
+  uint32_t r = (uint32_t)__shfl_up((int)inc, 1);
+  if (lane_id() == 0) r = 0;
+  __syncthreads();
+  uint32_t t = 0;
+#pragma unroll
+  for (int i = 0; i < kWaves; ++i) {
+    const uint32_t m = s_wave[i];
+    if (i < (int)w) r = max(r, m);
+    t = max(t, m);
+  }
+  *all = t;
+  return r;
+}
+
+// Groups g0 + kPer tid + (0 .. kPer-1) of a bitmap in v (0 past the words and
+// from ngroups on; words that cover 2^32 groups and more give unspecified
+// ones); wl and wr: the words that hold groups g0 and the tile's last
+// one.  s_mark: kTile words.  Starts and ends with a barrier.
+template <int kFmt>
+__device__ __forceinline__ void tile_groups(const Bitmap& b, uint32_t m, uint32_t wl, uint32_t wr, uint32_t g0,
+                                            uint32_t ngroups, uint32_t* s_mark, uint32_t* s_wave,
+                                            uint32_t (&v)[kPer]) {
+  const uint32_t tid = threadIdx.x;
+  const uint64_t total = total_groups<kFmt>(b, m);
+  u32x4* const mine = reinterpret_cast<u32x4*>(s_mark + kPer * tid);
+  const u32x4 zero = {0u, 0u, 0u, 0u};
+  __syncthreads();
+  mine[0] = zero;
+  mine[1] = zero;
+  __syncthreads();
+  // each word marks its first group with its index + 1 (words of no groups: none)
+  if (m) {
+    if (tid == 0) s_mark[0] = wl + 1u;
+    // kPer words per work-item and step, their loads issued together (a word
+    // covers a group at least, so one step is the rule)
+    for (uint64_t k0 = (uint64_t)wl + 1u + tid; k0 <= wr; k0 += kPer * kBlock) {
+      uint32_t at[kPer], w[kPer];
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) {
+        const uint64_t k = k0 + (uint64_t)i * kBlock;
+        at[i] = k <= wr ? b.start[k] - g0 : kTile;
+        w[i] = k <= wr ? b.words[k] : 0u;
+      }
+#pragma unroll
+      for (int i = 0; i < kPer; ++i)
+        if (at[i] < kTile && word_groups<kFmt>(w[i])) s_mark[at[i]] = (uint32_t)k0 + i * kBlock + 1u;
     }
-    const uint32_t lit = g.lit[i];
-    if (f.fill) {
-      uint32_t word = kFillBit | f.gap;
-      if (kFmt == kFmtPlwah && !f.main) word |= (1u + (uint32_t)__builtin_ctz(lit)) << kPlwahShift;
-      out_words[w++] = word;
+  }
+  __syncthreads();
+  uint32_t idx[kPer];
+  {
+    const u32x4 x = mine[0], y = mine[1];
+    idx[0] = x.x, idx[1] = x.y, idx[2] = x.z, idx[3] = x.w;
+    idx[4] = y.x, idx[5] = y.y, idx[6] = y.z, idx[7] = y.w;
+  }
+#pragma unroll
+  for (int i = 1; i < kPer; ++i) idx[i] = max(idx[i], idx[i - 1]);
+  uint32_t all;
+  const uint32_t before = block_excl_max(idx[kPer - 1], s_wave, &all);
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    const uint32_t l = kPer * tid + i, g = g0 + l, k = max(idx[i], before);
+    v[i] = l < ngroups - g0 && g < total ? group_value<kFmt>(b.words[k - 1u], b.start[k - 1u], g) : 0u;
+  }
+  __syncthreads();
+}
+
+// This work-item's kPer words of a tile that holds n at out, in 16-byte stores
+// where all exist.
+__device__ __forceinline__ void store_tile(uint32_t* __restrict__ out, uint32_t n, const uint32_t (&v)[kPer]) {
+  const uint32_t g = kPer * threadIdx.x;
+  if (g + kPer <= n) {
+    u32x4w a, c;
+    a.x = v[0], a.y = v[1], a.z = v[2], a.w = v[3];
+    c.x = v[4], c.y = v[5], c.z = v[6], c.w = v[7];
+    *reinterpret_cast<u32x4w*>(out + g) = a;
+    *reinterpret_cast<u32x4w*>(out + g + 4) = c;
+  } else {
+#pragma unroll
+    for (int i = 0; i < kPer; ++i)
+      if (g + i < n) out[g + i] = v[i];
+  }
+}
+
+// groups[g] for g < ngroups; the output's length is ngroups, or 0 if the words
+// cover more.
+template <int kFmt>
+__global__ __launch_bounds__(kBlock) void k_decode_expand(Bitmap b, uint32_t ngroups, uint32_t* __restrict__ groups,
+                                                          uint64_t* __restrict__ len, LenHost host) {
+  __shared__ __align__(16) uint32_t s_mark[kTile];
+  __shared__ uint32_t s_wave[kWaves], s_at[2];
+  const uint32_t m = b.count(), g0 = blockIdx.x * kTile;
+  if (blockIdx.x == 0 && threadIdx.x == 0)
+    put_len(len, host, 0, total_groups<kFmt>(b, m) > ngroups ? 0u : ngroups);
+  if (g0 >= ngroups) return;
+  if (m && threadIdx.x < 128) {  // wave 0: the first group's word, wave 1: the last one's
+    const uint32_t w = threadIdx.x / 64;
+    const uint32_t k = wave_last_start(b.start, m, w ? g0 + min(kTile, ngroups - g0) - 1u : g0);
+    if (lane_id() == 0) s_at[w] = k;
+  }
+  __syncthreads();
+  uint32_t v[kPer];
+  tile_groups<kFmt>(b, m, m ? s_at[0] : 0u, m ? s_at[1] : 0u, g0, ngroups, s_mark, s_wave, v);
+  store_tile(groups + g0, min(kTile, ngroups - g0), v);
+}
+
+// ---------------------------------------------------------------------------------
+// AND / OR of two bitmaps and the encoding of dense groups
+// ---------------------------------------------------------------------------------
+// What a group x emits after the group p before it (the first group: p = 1, a
+// literal of one row).
+struct DenseEmits {
+  bool fill, main, run;  // a 0-fill for the empty groups before it; a literal or 1-fill; main starts a run of full ones
+};
+template <int kFmt>
+__device__ __forceinline__ DenseEmits dense_emits(uint32_t x, uint32_t p) {
+  DenseEmits e;
+  const bool full = kFmt != kFmtPaper && x == kFull, pfull = kFmt != kFmtPaper && p == kFull;
+  e.fill = x != 0u && p == 0u;
+  bool skip = full && pfull;  // inside the run's 1-fill
+  if (kFmt == kFmtPlwah) {
+    const uint32_t pop = (uint32_t)__popc(x);
+    skip = skip || (pfull && pop == 30u);    // absorbed by the run's 1-fill
+    skip = skip || (e.fill && pop == 1u);  // absorbed by its 0-fill
+  }
+  e.main = x != 0u && !skip;
+  e.run = e.main && full;
+  return e;
+}
+
+// Summary of a tile of groups: the words it emits, its last non-empty group's
+// index + 1 (0: none), its leading full groups.
+struct TileSums {
+  uint32_t *words, *last, *lead;
+};
+
+template <int kFmt, int kOutFmt>
+__global__ __launch_bounds__(kBlock) void k_combine(Bitmap a, Bitmap b, uint32_t ngroups, uint32_t op,
+                                                    uint32_t* __restrict__ dense, TileSums sums) {
+  __shared__ __align__(16) uint32_t s_mark[kTile];
+  __shared__ uint32_t s_wave[kWaves], s_at[4], s_sum[kWaves], s_prev;
+  const uint32_t tid = threadIdx.x, ma = a.count(), mb = b.count(), g0 = blockIdx.x * kTile;
+  {  // a wave each: the words of the tile's first and last group in a and in b
+    const uint32_t w = tid / 64, m = w < 2 ? ma : mb;
+    const uint32_t k = m ? wave_last_start(w < 2 ? a.start : b.start, m, (w & 1u) ? g0 + min(kTile, ngroups - g0) - 1u : g0)
+                         : 0u;
+    if (lane_id() == 0) s_at[w] = k;
+  }
+  __syncthreads();
+  if (tid == 0) {  // the group before the tile
+    uint32_t p = 1u;
+    if (g0) {
+      uint32_t v[2];
+      for (int i = 0; i < 2; ++i) {
+        const Bitmap& t = i ? b : a;
+        const uint32_t m = i ? mb : ma;
+        v[i] = 0;
+        if (g0 - 1u < total_groups<kFmt>(t, m)) {
+          uint32_t k = s_at[2 * i];
+          while (t.start[k] > g0 - 1u) --k;
+          v[i] = group_value<kFmt>(t.words[k], t.start[k], g0 - 1u);
+        }
+      }
+      p = op ? v[0] | v[1] : v[0] & v[1];
     }
-    if (f.main) {
-      if (kFmt != kFmtPaper && f.full) {
-        const uint32_t L = run_length(g, fpos, fulls, k, i);
-        uint32_t word = kFillBit | kOneBit | L;
-        const uint32_t nx = i + L;
-        if (kFmt == kFmtPlwah && nx < k && g.k_of(nx) == g.k_of(i) && g.chunk[nx] == g.chunk[i] + L &&
-            __popc(g.lit[nx]) == 30)
-          word |= (1u + (uint32_t)__builtin_ctz(~g.lit[nx] & kFull)) << kPlwahShift;
-        out_words[w] = word;
-      } else {
-        out_words[w] = lit;
+    s_prev = p;
+  }
+  uint32_t va[kPer], vb[kPer];
+  tile_groups<kFmt>(a, ma, s_at[0], s_at[1], g0, ngroups, s_mark, s_wave, va);
+  tile_groups<kFmt>(b, mb, s_at[2], s_at[3], g0, ngroups, s_mark, s_wave, vb);
+  const uint32_t g = g0 + kPer * tid;
+  uint32_t x[kPer];
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) x[i] = op ? va[i] | vb[i] : va[i] & vb[i];
+  store_tile(dense + g0, min(kTile, ngroups - g0), x);
+  s_mark[tid] = x[kPer - 1];  // the next work-item's group before its first
+  __syncthreads();
+  uint32_t p = tid ? s_mark[tid - 1] : s_prev, words = 0, last = 0, lead = kTile;
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    const DenseEmits e = dense_emits<kOutFmt>(x[i], p);
+    words += (e.fill ? 1u : 0u) + (e.main ? 1u : 0u);
+    if (x[i]) last = g + i + 1u;
+    if (x[i] != kFull && lead == kTile) lead = kPer * tid + i;
+    p = x[i];
+  }
+  uint32_t last_all, nlead_all;
+  (void)block_excl_max(last, s_wave, &last_all);
+  __syncthreads();
+  (void)block_excl_max(kTile - lead, s_wave, &nlead_all);  // the smallest lead
+  const uint32_t wsum = wave_sum(words);
+  if (lane_id() == 0) s_sum[tid / 64] = wsum;
+  __syncthreads();
+  if (tid == 0) {
+    uint32_t t = 0;
+#pragma unroll
+    for (int i = 0; i < kWaves; ++i) t += s_sum[i];
+    sums.words[blockIdx.x] = t;
+    sums.last[blockIdx.x] = last_all;
+    sums.lead[blockIdx.x] = kTile - nlead_all;
+  }
+}
+
+// Words of the tiles before tile t, by one wave.
+__device__ __forceinline__ uint32_t wave_words_before(const uint32_t* __restrict__ words, uint32_t t) {
+  uint32_t s = 0;
+  for (uint32_t i = lane_id(); i < t; i += 64) s += words[i];
+  return wave_sum(s);
+}
+
+// The words of one tile.  first_word: the scan of the tiles' words, or null
+// (every tile then adds up those before it).  The last tile writes the length:
+// the words' count, or 0 if an input covers more than ngroups groups.  A fill
+// beyond its length field sets *reject (given only where one can be).
+template <int kFmt, int kOutFmt>
+__global__ __launch_bounds__(kBlock) void k_dense_encode(Bitmap a, Bitmap b, const uint32_t* __restrict__ dense,
+                                                         uint32_t ngroups, TileSums sums,
+                                                         const uint32_t* __restrict__ first_word,
+                                                         uint32_t* __restrict__ out, uint64_t* __restrict__ len,
+                                                         LenHost host, uint32_t* __restrict__ reject) {
+  __shared__ uint32_t s_words[2 * kTile];
+  __shared__ uint64_t s_full[kTile / 64];  // bit i: group i of the tile is full
+  __shared__ uint32_t s_last[kBlock], s_wave[kWaves], s_scan[kWaves];
+  __shared__ uint32_t s_base, s_carry, s_ext;
+  const uint32_t tid = threadIdx.x, tile = blockIdx.x, ntiles = gridDim.x, g0 = tile * kTile, g = g0 + kPer * tid;
+  uint32_t x[kPer];
+  if (g + kPer <= ngroups) {
+    const u32x4w q = *reinterpret_cast<const u32x4w*>(dense + g), r = *reinterpret_cast<const u32x4w*>(dense + g + 4);
+    x[0] = q.x, x[1] = q.y, x[2] = q.z, x[3] = q.w;
+    x[4] = r.x, x[5] = r.y, x[6] = r.z, x[7] = r.w;
+  } else {
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) x[i] = g + i < ngroups ? dense[g + i] : 0u;
+  }
+  const uint32_t edge = tid == 0 && g0 ? dense[g0 - 1u] : 1u;
+  const uint32_t w = tid / 64;
+  if (w == 0) {  // the tile's first word
+    const uint32_t base = first_word ? first_word[tile] : wave_words_before(sums.words, tile);
+    if (lane_id() == 0) s_base = base;
+  } else if (w == 1) {  // the last non-empty group before the tile
+    uint32_t carry = 0;
+    for (int64_t j = (int64_t)tile - 1; j >= 0; j -= 64) {
+      const int64_t t = j - (int64_t)lane_id();
+      const uint32_t l = t >= 0 ? sums.last[t] : 0u;
+      const uint64_t some = __ballot(l != 0u);
+      if (some) {
+        carry = (uint32_t)__builtin_amdgcn_readlane((int)l, (int)__builtin_ctzll(some));
+        break;
       }
     }
-    if (i == k - 1) {  // the last group: totals and lengths
-      const uint32_t D = dpos[i] + (f.seg ? 1u : 0u), W = wpos[i] + f.words;
-      const bool void_ = reject && *reject;
-      if (out_offsets) out_offsets[D] = W;
-      if (len_keys) *len_keys = void_ ? 0u : D;
-      if (len_offsets) *len_offsets = void_ ? 0u : (uint64_t)D + 1;
-      put_len(len_words, host, 0, void_ ? 0u : W);
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------------
-// decoding one bitmap into one 31-bit word per group
-// ---------------------------------------------------------------------------------
-template <int kFmt>
-__device__ __forceinline__ uint32_t word_groups(uint32_t w) {
-  if (!(w & kFillBit)) return 1u;
-  if (kFmt == kFmtPlwah) return (w & kLen25) + (((w >> kPlwahShift) & 31u) ? 1u : 0u);
-  return w & kLen30;
-}
-
-template <int kFmt>
-__global__ __launch_bounds__(kBlock) void k_decode_counts(const uint32_t* __restrict__ words, uint64_t cap,
-                                                          const uint64_t* __restrict__ m_len,
-                                                          uint32_t* __restrict__ cnt) {
-  const uint32_t m = dev_count(cap, m_len);
-  for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < m; i += gridDim.x * kBlock) cnt[i] = word_groups<kFmt>(words[i]);
-}
-
-// groups[g] for g < ngroups: the word covering g (binary search over the
-// prefix counts), or 0 past the last word; more groups than ngroups sets
-// *reject.
-template <int kFmt>
-__global__ __launch_bounds__(kBlock) void k_decode_expand(const uint32_t* __restrict__ words, uint64_t cap,
-                                                          const uint64_t* __restrict__ m_len,
-                                                          const uint32_t* __restrict__ start, uint32_t ngroups,
-                                                          uint32_t* __restrict__ groups, uint32_t* __restrict__ reject) {
-  const uint32_t m = dev_count(cap, m_len);
-  const uint64_t total = m ? (uint64_t)start[m - 1] + word_groups<kFmt>(words[m - 1]) : 0u;
-  if (blockIdx.x == 0 && threadIdx.x == 0 && total > ngroups && reject) *reject = 1u;
-  for (uint32_t gi = blockIdx.x * kBlock + threadIdx.x; gi < ngroups; gi += gridDim.x * kBlock) {
-    uint32_t v = 0;
-    if (gi < total) {
-      uint32_t lo = 0, hi = m;  // the last word with start <= gi
-      while (hi - lo > 1u) {
-        const uint32_t mid = lo + (hi - lo) / 2u;
-        if (start[mid] <= gi)
-          lo = mid;
-        else
-          hi = mid;
+    if (lane_id() == 0) s_carry = carry;
+  } else if (w == 2) {  // full groups right after the tile
+    uint32_t ext = 0;
+    for (uint64_t j = (uint64_t)tile + 1; j < ntiles; j += 64) {
+      const uint64_t t = j + lane_id();
+      const uint32_t l = t < ntiles ? sums.lead[t] : 0u;
+      const uint64_t stop = __ballot(l != kTile);
+      if (stop) {
+        const uint32_t at = (uint32_t)__builtin_ctzll(stop);
+        ext += at * kTile + (uint32_t)__builtin_amdgcn_readlane((int)l, (int)at);
+        break;
       }
-      const uint32_t w = words[lo];
-      if (!(w & kFillBit)) {
-        v = w;
-      } else {
-        const bool one = (w & kOneBit) != 0u;
-        const uint32_t len = kFmt == kFmtPlwah ? (w & kLen25) : (w & kLen30);
-        const uint32_t p = kFmt == kFmtPlwah ? (w >> kPlwahShift) & 31u : 0u;
-        if (gi - start[lo] < len)
-          v = one ? kFull : 0u;
-        else  // the absorbed group after the fill
-          v = one ? (kFull & ~(1u << (p - 1u))) : (1u << (p - 1u));
-      }
+      ext += 64u * kTile;
     }
-    groups[gi] = v;
+    if (lane_id() == 0) s_ext = ext;
   }
-}
-
-// ---------------------------------------------------------------------------------
-// AND / OR of two decoded bitmaps, and the non-empty groups as a group list
-// ---------------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void k_combine(const uint32_t* __restrict__ a, const uint32_t* __restrict__ b,
-                                                    uint32_t ngroups, uint32_t op, uint32_t* __restrict__ lit,
-                                                    uint32_t* __restrict__ tag) {
-  for (uint32_t gi = blockIdx.x * kBlock + threadIdx.x; gi < ngroups; gi += gridDim.x * kBlock) {
-    const uint32_t x = op ? (a[gi] | b[gi]) : (a[gi] & b[gi]);
-    lit[gi] = x;
-    tag[gi] = x ? gi + 1u : 0u;  // compacted below: the non-empty groups' ids + 1, in order
+  s_last[tid] = x[kPer - 1];
+  uint32_t full = 0, last = 0;
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    full |= (x[i] == kFull ? 1u : 0u) << i;
+    if (x[i]) last = g + i + 1u;
   }
-}
-
-__global__ __launch_bounds__(kBlock) void k_nonempty_groups(const uint32_t* __restrict__ tag, uint64_t cap,
-                                                            const uint64_t* __restrict__ k_len,
-                                                            const uint32_t* __restrict__ dense,
-                                                            uint32_t* __restrict__ chunk, uint32_t* __restrict__ lit) {
-  const uint32_t k = dev_count(cap, k_len);
-  for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < k; i += gridDim.x * kBlock) {
-    const uint32_t c = tag[i] - 1u;
-    chunk[i] = c;
-    lit[i] = dense[c];
+  reinterpret_cast<uint8_t*>(s_full)[tid] = (uint8_t)full;
+  __syncthreads();
+  const uint32_t prev = tid ? s_last[tid - 1] : edge;
+  uint32_t p = prev, words = 0;
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    const DenseEmits e = dense_emits<kOutFmt>(x[i], p);
+    words += (e.fill ? 1u : 0u) + (e.main ? 1u : 0u);
+    p = x[i];
+  }
+  uint32_t total, all;
+  uint32_t at = block_excl_scan<kBlock>(words, s_scan, &total);
+  const uint32_t before = max(block_excl_max(last, s_wave, &all), s_carry);
+  p = prev;
+  uint32_t nz = before;  // index + 1 of the last non-empty group so far
+  bool over = false;
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    const DenseEmits e = dense_emits<kOutFmt>(x[i], p);
+    if (e.fill) {
+      const uint32_t gap = g + i - nz;
+      over = over || gap > kLen30;
+      uint32_t word = kFillBit | gap;
+      if (kOutFmt == kFmtPlwah && !e.main) word |= (1u + (uint32_t)__builtin_ctz(x[i])) << kPlwahShift;
+      s_words[at++] = word;
+    }
+    if (e.main) {
+      uint32_t word = x[i];
+      if (e.run) {  // the run's length: to the next group that is not full
+        const uint32_t l0 = kPer * tid + i;
+        uint32_t j = l0 / 64u;
+        uint64_t rest = ~s_full[j] & (~0ull << (l0 % 64u));
+        while (!rest && ++j < kTile / 64u) rest = ~s_full[j];
+        const uint32_t L = rest ? 64u * j + (uint32_t)__builtin_ctzll(rest) - l0 : kTile - l0 + s_ext;
+        word = kFillBit | kOneBit | L;
+        if (kOutFmt == kFmtPlwah && (uint64_t)g + i + L < ngroups) {
+          const uint32_t y = dense[g + i + L];
+          if (__popc(y) == 30) word |= (1u + (uint32_t)__builtin_ctz(~y & kFull)) << kPlwahShift;
+        }
+      }
+      s_words[at++] = word;
+    }
+    if (x[i]) nz = g + i + 1u;
+    p = x[i];
+  }
+  if (over && reject) *reject = 1u;
+  __syncthreads();
+  const uint32_t base = s_base;
+  for (uint32_t i = tid; i < total; i += kBlock) out[base + i] = s_words[i];
+  if (tile == ntiles - 1 && tid == 0) {
+    const bool more = total_groups<kFmt>(a, a.count()) > ngroups || total_groups<kFmt>(b, b.count()) > ngroups;
+    put_len(len, host, 0, more ? 0u : base + total);
   }
 }
 
@@ -302,126 +463,113 @@ __global__ void k_set_zero_u32(uint32_t* p) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *p = 0u;
 }
 
-// *len = *reject ? 0 : value.
-__global__ void k_len_unless(uint64_t* __restrict__ len, LenHost host, uint64_t value,
-                             const uint32_t* __restrict__ reject) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) put_len(len, host, 0, *reject ? 0u : value);
+// Voids a length (and puts it on the host) if *reject is set.
+__global__ void k_void_len(uint64_t* __restrict__ len, LenHost host, const uint32_t* __restrict__ reject) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) put_len(len, host, 0, *reject ? 0u : *len);
+}
+
+int launch_void_len(Env& env, uint64_t* len, LenHost host, const uint32_t* reject) {
+  k_void_len<<<dim3(1), dim3(64), 0, env.stream()>>>(len, host, reject);
+  return check_launch(env, "void_len launch");
+}
+
+int launch_zero_u32(Env& env, uint32_t* p) {
+  k_set_zero_u32<<<dim3(1), dim3(64), 0, env.stream()>>>(p);
+  return check_launch(env, "zero launch");
 }
 
 // ---- host side --------------------------------------------------------------------------
-template <int kFmt>
-int encode_groups_fmt(Env& env, const Groups& g, uint64_t cap, const uint64_t* k_len, uint32_t* keys,
-                      uint32_t* offsets, uint32_t* words, uint64_t* len_keys, uint64_t* len_offsets,
-                      uint64_t* len_words, LenHost host, uint32_t* reject) {
-  const uint64_t c = std::max<uint64_t>(cap, 1);
-  uint32_t* wc = static_cast<uint32_t*>(env.scratch(4 * c));
-  uint32_t* sg = static_cast<uint32_t*>(env.scratch(4 * c));
-  uint32_t* wp = static_cast<uint32_t*>(env.scratch(4 * c));
-  uint32_t* dp = static_cast<uint32_t*>(env.scratch(4 * c));
-  uint32_t* fl = kFmt != kFmtPaper ? static_cast<uint32_t*>(env.scratch(4 * c)) : nullptr;
-  uint32_t* fp = kFmt != kFmtPaper ? static_cast<uint32_t*>(env.scratch(4 * c)) : nullptr;
-  if (!wc || !sg || !wp || !dp || (kFmt != kFmtPaper && (!fl || !fp))) return env.fail(kErrOom, "group encoder: scratch");
-  const uint32_t grid = grid_for(c);
-  int rc;
-  env.prof_begin("groups_flags");
-  k_groups_flags<kFmt><<<dim3(grid), dim3(kBlock), 0, env.stream()>>>(g, c, k_len, wc, sg, fl, reject);
-  env.prof_end("groups_flags");
-  if ((rc = check_launch(env, "groups_flags launch"))) return rc;
-  if ((rc = launch_exclusive_scan(env, wc, wp, c, k_len))) return rc;
-  if ((rc = launch_exclusive_scan(env, sg, dp, c, k_len))) return rc;
-  if (kFmt != kFmtPaper && (rc = launch_exclusive_scan(env, fl, fp, c, k_len))) return rc;
-  env.prof_begin("groups_write");
-  k_groups_write<kFmt><<<dim3(grid), dim3(kBlock), 0, env.stream()>>>(g, c, k_len, wp, dp, fp, fl, reject, keys,
-                                                                       offsets, words, len_keys, len_offsets,
-                                                                       len_words, host);
-  env.prof_end("groups_write");
-  return check_launch(env, "groups_write launch");
+// The scan of a bitmap's group counts, into scratch.
+int bitmap_starts(Env& env, const uint32_t* words, uint64_t cap, const uint64_t* len, uint32_t fmt, Bitmap* out) {
+  uint32_t* start = static_cast<uint32_t*>(env.scratch(4 * std::max<uint64_t>(cap, 1)));
+  if (!start) return env.fail(kErrOom, "wah query: scratch");
+  *out = Bitmap{words, start, cap, len};
+  return launch_exclusive_scan_groups(env, words, start, cap, len, fmt);
 }
 
-int encode_groups(Env& env, uint32_t fmt, const Groups& g, uint64_t cap, const uint64_t* k_len, uint32_t* keys,
-                  uint32_t* offsets, uint32_t* words, uint64_t* len_keys, uint64_t* len_offsets, uint64_t* len_words,
-                  LenHost host, uint32_t* reject) {
-  switch (fmt) {
-    case kFmtPaper:
-      return encode_groups_fmt<kFmtPaper>(env, g, cap, k_len, keys, offsets, words, len_keys, len_offsets, len_words,
-                                          host, reject);
-    case kFmtCanonical:
-      return encode_groups_fmt<kFmtCanonical>(env, g, cap, k_len, keys, offsets, words, len_keys, len_offsets,
-                                              len_words, host, reject);
-    case kFmtPlwah:
-      return encode_groups_fmt<kFmtPlwah>(env, g, cap, k_len, keys, offsets, words, len_keys, len_offsets, len_words,
-                                          host, reject);
-    default:
-      return env.fail(kErrArg, "unknown WAH format");
-  }
+template <int kFmt, int kOutFmt>
+int combine_fmt(Env& env, const Bitmap& a, const Bitmap& b, uint32_t ngroups, uint32_t op, uint32_t* dense,
+                const TileSums& sums, uint32_t* first_word, uint32_t* words, uint64_t* len, LenHost host,
+                uint32_t* reject) {
+  const uint32_t ntiles = (ngroups + kTile - 1) / kTile;
+  const dim3 grid(ntiles), block(kBlock);
+  env.prof_begin("wah_combine");
+  k_combine<kFmt, kOutFmt><<<grid, block, 0, env.stream()>>>(a, b, ngroups, op, dense, sums);
+  env.prof_end("wah_combine");
+  int rc = check_launch(env, "combine launch");
+  if (rc) return rc;
+  if (first_word && (rc = launch_exclusive_scan(env, sums.words, first_word, ntiles, nullptr))) return rc;
+  if (reject && (rc = launch_zero_u32(env, reject))) return rc;
+  env.prof_begin("dense_encode");
+  k_dense_encode<kFmt, kOutFmt><<<grid, block, 0, env.stream()>>>(a, b, dense, ngroups, sums, first_word, words, len,
+                                                                   reject ? LenHost{} : host, reject);
+  env.prof_end("dense_encode");
+  if ((rc = check_launch(env, "dense_encode launch"))) return rc;
+  return reject ? launch_void_len(env, len, host, reject) : kOk;
 }
 
 }  // namespace
 
-int launch_len_unless(Env& env, uint64_t* len, LenHost host, uint64_t value, const uint32_t* reject) {
-  k_len_unless<<<dim3(1), dim3(64), 0, env.stream()>>>(len, host, value, reject);
-  return check_launch(env, "len_unless launch");
-}
-
 int launch_wah_decode(Env& env, const uint32_t* words, uint64_t m_cap, const uint64_t* m_len, uint32_t fmt,
-                      uint32_t ngroups, uint32_t* groups, uint32_t* reject) {
+                      uint32_t ngroups, uint32_t* groups, uint64_t* len, LenHost host) {
   if (fmt > kFmtPlwah) return env.fail(kErrArg, "unknown WAH format");
-  if (!reject || (ngroups && !groups) || (m_cap && !words)) return env.fail(kErrArg, "wah decode: null buffer");
-  const uint64_t c = std::max<uint64_t>(m_cap, 1);
-  uint32_t* cnt = static_cast<uint32_t*>(env.scratch(4 * c));
-  uint32_t* start = static_cast<uint32_t*>(env.scratch(4 * c));
-  if (!cnt || !start) return env.fail(kErrOom, "wah decode: scratch");
-  int rc;
-  const uint32_t gw = grid_for(c), gg = grid_for(ngroups);
+  if (!len || (ngroups && !groups) || (m_cap && !words)) return env.fail(kErrArg, "wah decode: null buffer");
+  Bitmap b;
+  int rc = bitmap_starts(env, words, m_cap, m_len, fmt, &b);
+  if (rc) return rc;
+  const dim3 grid(std::max<uint32_t>(1, (uint32_t)(((uint64_t)ngroups + kTile - 1) / kTile))), block(kBlock);
   env.prof_begin("wah_decode");
-#define KA_DECODE(F)                                                                                              \
-  k_decode_counts<F><<<dim3(gw), dim3(kBlock), 0, env.stream()>>>(words, m_cap, m_len, cnt);                      \
-  if ((rc = check_launch(env, "decode_counts launch"))) return rc;                                                \
-  if ((rc = launch_exclusive_scan(env, cnt, start, m_cap, m_len))) return rc;                                     \
-  k_decode_expand<F><<<dim3(gg), dim3(kBlock), 0, env.stream()>>>(words, m_cap, m_len, start, ngroups, groups, \
-                                                                  reject);
-  if (fmt == kFmtPaper) {
-    KA_DECODE(kFmtPaper)
-  } else if (fmt == kFmtCanonical) {
-    KA_DECODE(kFmtCanonical)
-  } else {
-    KA_DECODE(kFmtPlwah)
+  switch (fmt) {
+    case kFmtPaper:
+      k_decode_expand<kFmtPaper><<<grid, block, 0, env.stream()>>>(b, ngroups, groups, len, host);
+      break;
+    case kFmtCanonical:
+      k_decode_expand<kFmtCanonical><<<grid, block, 0, env.stream()>>>(b, ngroups, groups, len, host);
+      break;
+    default:
+      k_decode_expand<kFmtPlwah><<<grid, block, 0, env.stream()>>>(b, ngroups, groups, len, host);
+      break;
   }
-#undef KA_DECODE
   env.prof_end("wah_decode");
   return check_launch(env, "decode_expand launch");
 }
 
 int launch_wah_combine(Env& env, const uint32_t* a, uint64_t a_cap, const uint64_t* a_len, const uint32_t* b,
                        uint64_t b_cap, const uint64_t* b_len, uint32_t in_fmt, uint32_t ngroups, uint32_t op,
-                       uint32_t out_fmt, uint32_t* words, uint64_t* len_words, LenHost host, uint32_t* reject) {
+                       uint32_t out_fmt, uint32_t* words, uint64_t* len_words, LenHost host) {
   if (op > 1) return env.fail(kErrArg, "wah combine: op must be 0 (AND) or 1 (OR)");
   if (in_fmt > kFmtPlwah || out_fmt > kFmtPlwah) return env.fail(kErrArg, "unknown WAH format");
-  if (!words || !len_words || !reject) return env.fail(kErrArg, "wah combine: null buffer");
-  const uint64_t gc = std::max<uint64_t>(ngroups, 1);
-  uint32_t* ga = static_cast<uint32_t*>(env.scratch(4 * gc));
-  uint32_t* gb = static_cast<uint32_t*>(env.scratch(4 * gc));
-  uint32_t* lit = static_cast<uint32_t*>(env.scratch(4 * gc));
-  uint32_t* tag = static_cast<uint32_t*>(env.scratch(4 * gc));
-  uint32_t* nz = static_cast<uint32_t*>(env.scratch(4 * gc));
-  uint32_t* chunk = static_cast<uint32_t*>(env.scratch(4 * gc));
-  uint32_t* glit = static_cast<uint32_t*>(env.scratch(4 * gc));
-  uint64_t* k_len = static_cast<uint64_t*>(env.scratch(8));
-  if (!ga || !gb || !lit || !tag || !nz || !chunk || !glit || !k_len) return env.fail(kErrOom, "wah combine: scratch");
+  if (!words || !len_words || (a_cap && !a) || (b_cap && !b)) return env.fail(kErrArg, "wah combine: null buffer");
+  if (ngroups == 0) return launch_set_len(env, len_words, 0, host);
+  const uint32_t ntiles = (ngroups + kTile - 1) / kTile;
+  uint32_t* dense = static_cast<uint32_t*>(env.scratch(4ull * ngroups));
+  uint32_t* sums = static_cast<uint32_t*>(env.scratch(12ull * ntiles));
+  // The tiles' words are scanned in a launch of their own only where every
+  // tile's own sum would read more (2048 tiles: 8 KiB a tile).
+  uint32_t* first_word = ntiles > 2048 ? static_cast<uint32_t*>(env.scratch(4ull * ntiles)) : nullptr;
+  uint32_t* reject = ngroups > kLen30 ? static_cast<uint32_t*>(env.scratch(4)) : nullptr;
+  if (!dense || !sums || (ntiles > 2048 && !first_word) || (ngroups > kLen30 && !reject))
+    return env.fail(kErrOom, "wah combine: scratch");
+  const TileSums ts{sums, sums + ntiles, sums + 2ull * ntiles};
+  Bitmap ba, bb;
   int rc;
-  if ((rc = launch_wah_decode(env, a, a_cap, a_len, in_fmt, ngroups, ga, reject))) return rc;
-  if ((rc = launch_wah_decode(env, b, b_cap, b_len, in_fmt, ngroups, gb, reject))) return rc;
-  const uint32_t gg = grid_for(gc);
-  env.prof_begin("wah_combine");
-  k_combine<<<dim3(gg), dim3(kBlock), 0, env.stream()>>>(ga, gb, ngroups, op, lit, tag);
-  env.prof_end("wah_combine");
-  if ((rc = check_launch(env, "combine launch"))) return rc;
-  if ((rc = launch_set_len(env, k_len, 0))) return rc;
-  if (ngroups && (rc = launch_compact_nonzero(env, tag, nz, ngroups, nullptr, k_len))) return rc;
-  k_nonempty_groups<<<dim3(gg), dim3(kBlock), 0, env.stream()>>>(nz, gc, k_len, lit, chunk, glit);
-  if ((rc = check_launch(env, "nonempty_groups launch"))) return rc;
-  return encode_groups(env, out_fmt, Groups{nullptr, chunk, glit}, gc, k_len, nullptr, nullptr, words, nullptr,
-                       nullptr, len_words, host, reject);
+  if ((rc = bitmap_starts(env, a, a_cap, a_len, in_fmt, &ba))) return rc;
+  if ((rc = bitmap_starts(env, b, b_cap, b_len, in_fmt, &bb))) return rc;
+#define KA_COMBINE(I, O) \
+  return combine_fmt<I, O>(env, ba, bb, ngroups, op, dense, ts, first_word, words, len_words, host, reject)
+#define KA_COMBINE_IN(I)                                    \
+  if (out_fmt == kFmtPaper) KA_COMBINE(I, kFmtPaper);         \
+  if (out_fmt == kFmtCanonical) KA_COMBINE(I, kFmtCanonical); \
+  KA_COMBINE(I, kFmtPlwah)
+  if (in_fmt == kFmtPaper) {
+    KA_COMBINE_IN(kFmtPaper);
+  }
+  if (in_fmt == kFmtCanonical) {
+    KA_COMBINE_IN(kFmtCanonical);
+  }
+  KA_COMBINE_IN(kFmtPlwah);
+#undef KA_COMBINE_IN
+#undef KA_COMBINE
 }
 
 int launch_wah_lookup(Env& env, const uint32_t* keys, uint64_t d_cap, const uint64_t* d_len, const uint32_t* queries,
@@ -434,11 +582,6 @@ int launch_wah_lookup(Env& env, const uint32_t* keys, uint64_t d_cap, const uint
                                                                          slots);
   env.prof_end("wah_lookup");
   return check_launch(env, "lookup launch");
-}
-
-int launch_zero_u32(Env& env, uint32_t* p) {
-  k_set_zero_u32<<<dim3(1), dim3(64), 0, env.stream()>>>(p);
-  return check_launch(env, "zero launch");
 }
 
 }  // namespace ka

@@ -139,9 +139,21 @@ __device__ __forceinline__ void load_tile(const uint32_t* __restrict__ in, uint6
   for (int r = 0; r < R; ++r) load4<kVec>(in, base + ((uint64_t)r * kScanBlock + threadIdx.x) * 4, n, v[r]);
 }
 
+// What an element adds: itself, or the groups that it covers as a word of a
+// bitmap (the count fused into the scan: no array of counts).
+struct AddSelf {
+  static constexpr bool kSelf = true;
+  __device__ __forceinline__ uint32_t operator()(uint32_t x) const { return x; }
+};
+template <int kFmt>
+struct AddGroups {
+  static constexpr bool kSelf = false;
+  __device__ __forceinline__ uint32_t operator()(uint32_t x) const { return word_groups<kFmt>(x); }
+};
+
 // One tile per work-group.  The grid is the tile count of n_cap; with a
 // smaller device-resident count the surplus work-groups leave at once.
-template <int R, bool kVec>
+template <int R, bool kVec, class Op>
 __global__ __launch_bounds__(kScanBlock) void k_exclusive_scan_u32(const uint32_t* __restrict__ in,
                                                                    uint32_t* __restrict__ out, uint64_t n_cap,
                                                                    const uint64_t* __restrict__ d_n, LbArgs lb) {
@@ -155,13 +167,20 @@ __global__ __launch_bounds__(kScanBlock) void k_exclusive_scan_u32(const uint32_
   const uint64_t base = (uint64_t)tile * kTile;
   uint32_t v[R][4];
   load_tile<R, kVec>(in, tile, n, v);
+  if (!Op::kSelf) {  // elements past the end add nothing
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        v[r][j] = base + ((uint64_t)r * kScanBlock + threadIdx.x) * 4 + j < n ? Op()(v[r][j]) : 0u;
+  }
   uint32_t s[R], pre[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) s[r] = v[r][0] + v[r][1] + v[r][2] + v[r][3];
   uint32_t total;
   tile_scan<R>(s, pre, &total, s_wave);
   tile_lookback(lb, tile, total, &s_prefix, [&](uint32_t u) {
-    return wave_tile_total<R, kVec>(in, u, n, [](uint32_t x) { return x; });
+    return wave_tile_total<R, kVec>(in, u, n, Op());  // an earlier tile: every element exists
   });
   const uint32_t tp = s_prefix;
 #pragma unroll
@@ -223,7 +242,7 @@ inline bool ranges_overlap(const uint32_t* a, const uint32_t* b, uint64_t n) {
   return x < y + 4 * n && y < x + 4 * n;
 }
 
-template <int R>
+template <int R, class Op>
 int scan_launch(Env& env, const uint32_t* in, uint32_t* out, uint64_t n_cap, const uint64_t* d_n) {
   const uint32_t grid = (uint32_t)((n_cap + kTileElems<R> - 1) / kTileElems<R>);
   LbArgs lb;
@@ -233,9 +252,9 @@ int scan_launch(Env& env, const uint32_t* in, uint32_t* out, uint64_t n_cap, con
   const dim3 g(grid), b(kScanBlock);
   env.prof_begin("exclusive_scan_u32");
   if (vec)
-    k_exclusive_scan_u32<R, true><<<g, b, 0, env.stream()>>>(in, out, n_cap, d_n, lb);
+    k_exclusive_scan_u32<R, true, Op><<<g, b, 0, env.stream()>>>(in, out, n_cap, d_n, lb);
   else
-    k_exclusive_scan_u32<R, false><<<g, b, 0, env.stream()>>>(in, out, n_cap, d_n, lb);
+    k_exclusive_scan_u32<R, false, Op><<<g, b, 0, env.stream()>>>(in, out, n_cap, d_n, lb);
   env.prof_end("exclusive_scan_u32");
   return check_launch(env, "exclusive_scan_u32 launch");
 }
@@ -243,13 +262,32 @@ int scan_launch(Env& env, const uint32_t* in, uint32_t* out, uint64_t n_cap, con
 }  // namespace
 
 // in and out must not overlap.
-int launch_exclusive_scan(Env& env, const uint32_t* in, uint32_t* out, uint64_t n_cap, const uint64_t* d_n) {
+template <class Op>
+static int scan_any(Env& env, const uint32_t* in, uint32_t* out, uint64_t n_cap, const uint64_t* d_n) {
   if (n_cap == 0) return kOk;
   if (!in || !out) return env.fail(kErrArg, "exclusive_scan_u32: null buffer");
   if (n_cap > 0xFFFFFFFFull) return env.fail(kErrArg, "exclusive_scan_u32: more than 2^32-1 elements");
   if (ranges_overlap(in, out, n_cap)) return env.fail(kErrArg, "exclusive_scan_u32: in and out overlap");
-  return n_cap > kLargeScan ? scan_launch<kLargeRounds>(env, in, out, n_cap, d_n)
-                            : scan_launch<kSmallRounds>(env, in, out, n_cap, d_n);
+  return n_cap > kLargeScan ? scan_launch<kLargeRounds, Op>(env, in, out, n_cap, d_n)
+                            : scan_launch<kSmallRounds, Op>(env, in, out, n_cap, d_n);
+}
+
+int launch_exclusive_scan(Env& env, const uint32_t* in, uint32_t* out, uint64_t n_cap, const uint64_t* d_n) {
+  return scan_any<AddSelf>(env, in, out, n_cap, d_n);
+}
+
+int launch_exclusive_scan_groups(Env& env, const uint32_t* words, uint32_t* start, uint64_t n_cap,
+                                 const uint64_t* d_n, uint32_t fmt) {
+  switch (fmt) {
+    case kFmtPaper:
+      return scan_any<AddGroups<kFmtPaper>>(env, words, start, n_cap, d_n);
+    case kFmtCanonical:
+      return scan_any<AddGroups<kFmtCanonical>>(env, words, start, n_cap, d_n);
+    case kFmtPlwah:
+      return scan_any<AddGroups<kFmtPlwah>>(env, words, start, n_cap, d_n);
+    default:
+      return env.fail(kErrArg, "unknown WAH format");
+  }
 }
 
 int launch_compact_nonzero(Env& env, const uint32_t* in, uint32_t* out, uint64_t n_cap, const uint64_t* d_n,

@@ -67,8 +67,6 @@ constexpr int kLook = 32;             // >= 30 elements of look-ahead
 constexpr uint32_t kGroupRows = 31;
 constexpr uint32_t kFill = 0x80000000u;
 constexpr uint32_t kOnes = 0x40000000u;      // fill bit of a 1-fill
-constexpr uint32_t kPlwahShift = 25;         // PLWAH: bits 29..25 = 1 + the absorbed group's bit
-enum { kFmtPaper = 0, kFmtCanonical = 1, kFmtPlwah = 2 };
 
 // Padded LDS index: four spare words after every 64 elements.  Groups of 4
 // elements stay 16-byte aligned, so the tile is staged with conflict-free

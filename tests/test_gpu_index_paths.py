@@ -169,3 +169,85 @@ def test_lengths_of_requests_in_flight(sess, n):
     for r in refs:
         sess.release_ref(r)
     sess.release_actor(idx)
+
+
+GROUP_TILE = 2048  # groups per tile of the decoder and of the AND / OR
+
+
+def bitmap(groups, fmt):
+    """The words of a bitmap given as 31-bit groups, by the oracle's own encoder."""
+    bits = ((groups[:, None] >> np.arange(31, dtype=np.uint32)) & 1).astype(np.uint32).ravel()
+    bits = np.append(bits, np.uint32(0))  # value 0 exists too: it sorts first
+    keys, off, words = expected(bits, fmt)
+    d = int(np.searchsorted(keys, 1))
+    return words[off[d]:off[d + 1]].copy() if d < keys.size and keys[d] == 1 else np.zeros(0, np.uint32)
+
+
+def group_patterns(ng):
+    """Bitmaps with fills and runs of full groups longer than tiles, ending and starting at their edges, groups of 30
+    rows after runs and of one row after gaps."""
+    full, i = np.uint32(0x7FFFFFFF), np.arange(ng)
+    sparse = np.zeros(ng, np.uint32)
+    sparse[[0, ng // 2, ng - 1]] = [1, 1 << 30, 6]
+    runs = np.where((i // (GROUP_TILE + 1)) % 2 == 0, full, 0).astype(np.uint32)
+    runs[GROUP_TILE - 1::GROUP_TILE] = full ^ np.uint32(1 << 7)
+    ones = np.full(ng, full)
+    mixed = workloads.u32(ng, ng) & full
+    mixed[(i % 7) < 4] = 0
+    mixed[(i % 53) > 40] = full
+    mixed[(i % 53) == 52] = full ^ np.uint32(1)
+    return [sparse, runs, ones, mixed]
+
+
+@pytest.mark.parametrize("fmt", [0, 1, 2])
+@pytest.mark.parametrize("ng", [1, 7, GROUP_TILE - 1, GROUP_TILE + 1, 5 * GROUP_TILE, 70 * GROUP_TILE + 9])
+def test_bitmap_queries_around_tiles(sess, fmt, ng):
+    """Decode, AND and OR of bitmaps around the tile of groups; 70 tiles: more than one window of summaries."""
+    import ctypes
+    import paper_1709_07781_amd as ka
+    pats = group_patterns(ng)
+    words = [bitmap(p, fmt) for p in pats]
+    val = lambda w: ka.val(w.ctypes.data if w.size else None, w.size)  # noqa: E731
+    dec = sess.spawn("wah_decode", [ka.arg(ka.KA_IN, in_mode=ka.KA_VAL),
+                                    ka.arg(ka.KA_PRIV, count=2, init=(ctypes.c_uint32 * 2)(fmt, ng)),
+                                    ka.arg(ka.KA_OUT, out_mode=ka.KA_VAL)])
+    for p, w in zip(pats, words):
+        (g,) = sess.request(dec, val(w), n_out=1)
+        np.testing.assert_array_equal(g, p)
+    sess.release_actor(dec)
+    for op in (0, 1):
+        for fout in (0, 1, 2):
+            act = sess.spawn("wah_combine", [ka.arg(ka.KA_IN, in_mode=ka.KA_VAL), ka.arg(ka.KA_IN, in_mode=ka.KA_VAL),
+                                             ka.arg(ka.KA_PRIV, count=4, init=(ctypes.c_uint32 * 4)(op, fmt, fout, ng)),
+                                             ka.arg(ka.KA_OUT, out_mode=ka.KA_VAL)])
+            for i, j in ((0, 1), (1, 2), (3, 1), (3, 0), (2, 2), (3, 3)):
+                (o,) = sess.request(act, val(words[i]), val(words[j]), n_out=1)
+                want = bitmap(pats[i] | pats[j] if op else pats[i] & pats[j], fout)
+                np.testing.assert_array_equal(o, want, err_msg=f"op={op} out={fout} {i},{j}")
+            sess.release_actor(act)
+
+
+def test_combine_scans_many_tiles(sess):
+    """More tiles than one work-group sums up: their words are scanned in a launch of their own."""
+    import ctypes
+    import paper_1709_07781_amd as ka
+    ng = 2048 * GROUP_TILE + 77
+    a, b = (workloads.u32(k, ng) & np.uint32(0x7FFFFFFF) for k in (1, 2))
+    a[np.arange(ng) % 3 == 0] = 0
+    act = sess.spawn("wah_combine", [ka.arg(ka.KA_IN, in_mode=ka.KA_VAL), ka.arg(ka.KA_IN, in_mode=ka.KA_VAL),
+                                     ka.arg(ka.KA_PRIV, count=4, init=(ctypes.c_uint32 * 4)(0, 0, 0, ng)),
+                                     ka.arg(ka.KA_OUT, out_mode=ka.KA_VAL)])
+
+    def paper(x):  # literals with a fill before each that follows empty groups
+        at = np.flatnonzero(x)
+        gap = np.diff(np.concatenate([[-1], at])) - 1
+        w = np.zeros(at.size + int((gap > 0).sum()), np.uint32)
+        end = np.cumsum(1 + (gap > 0))
+        w[end - 1] = x[at]
+        w[end[gap > 0] - 2] = np.uint32(0x80000000) | gap[gap > 0].astype(np.uint32)
+        return w
+
+    wa, wb = paper(a), paper(b)
+    (o,) = sess.request(act, ka.val(wa.ctypes.data, wa.size), ka.val(wb.ctypes.data, wb.size), n_out=1)
+    sess.release_actor(act)
+    np.testing.assert_array_equal(o, paper(a & b))
