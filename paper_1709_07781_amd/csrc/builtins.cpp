@@ -49,6 +49,9 @@ int run_affine(LaunchCtx& c) {
   Bound& x = (*c.args)[0];
   const uint64_t off = c.range ? c.range->offset[0] : 0;
   if (off > x.cap || c.n > x.cap - off) return c.env->fail(KA_E_ARG, "affine_u32: range exceeds the buffer");
+  if (c.stages)
+    return launch_affine_chain(*c.env, static_cast<uint32_t*>(x.ptr) + off, c.n, c.stages->a.data(), c.stages->b.data(),
+                               (uint32_t)c.stages->a.size(), c.d_n);
   return launch_affine(*c.env, static_cast<uint32_t*>(x.ptr), c.n, c.d_n, off, (uint32_t)(*c.args)[1].priv[0],
                        (uint32_t)(*c.args)[2].priv[0]);
 }

@@ -118,7 +118,8 @@ int launch_affine(Env& env, uint32_t* x, uint64_t n_cap, const uint64_t* d_n, ui
   return check_launch(env, "affine_u32 launch");
 }
 
-int launch_affine_chain(Env& env, uint32_t* x, uint64_t n, const uint32_t* a, const uint32_t* b, uint32_t len) {
+int launch_affine_chain(Env& env, uint32_t* x, uint64_t n, const uint32_t* a, const uint32_t* b, uint32_t len,
+                        const uint64_t* d_n) {
   if (n == 0 || len == 0) return kOk;
   if (!x || !a || !b) return env.fail(kErrArg, "affine chain: null buffer");
   const uint64_t grid = (n + kAffTile - 1) / kAffTile;
@@ -133,9 +134,9 @@ int launch_affine_chain(Env& env, uint32_t* x, uint64_t n, const uint32_t* a, co
     }
     env.prof_begin("affine_chain_u32");
     if (vec)
-      k_affine_u32<true><<<dim3((uint32_t)grid), dim3(kAffBlock), 0, env.stream()>>>(x, n, nullptr, op);
+      k_affine_u32<true><<<dim3((uint32_t)grid), dim3(kAffBlock), 0, env.stream()>>>(x, n, d_n, op);
     else
-      k_affine_u32<false><<<dim3((uint32_t)grid), dim3(kAffBlock), 0, env.stream()>>>(x, n, nullptr, op);
+      k_affine_u32<false><<<dim3((uint32_t)grid), dim3(kAffBlock), 0, env.stream()>>>(x, n, d_n, op);
     env.prof_end("affine_chain_u32");
     const int rc = check_launch(env, "affine chain launch");
     if (rc) return rc;

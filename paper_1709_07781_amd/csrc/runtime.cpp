@@ -737,9 +737,9 @@ static int launch_module(Actor* a, CmdEnv& env, std::vector<Bound>& args, uint64
   return KA_OK;
 }
 
-static int run_kernel_actor(Actor* a, Msg& msg, Msg& out, uint32_t si) {
+// The caller holds a->mu.
+static int run_kernel_actor(Actor* a, Msg& msg, Msg& out, uint32_t si, const AffineStages* stages = nullptr) {
   System* sys = a->sys;
-  std::lock_guard<std::mutex> lock(a->mu);
   int rc = KA_OK;
   if (a->pre && (rc = apply_map(a->pre, a->map_ud, msg))) return rc;
 
@@ -898,7 +898,7 @@ static int run_kernel_actor(Actor* a, Msg& msg, Msg& out, uint32_t si) {
   {
     CmdEnv env(sys, si);
     if (a->bk) {
-      LaunchCtx c{&env, n, d_n, &a->range, &args};
+      LaunchCtx c{&env, n, d_n, &a->range, &args, stages};
       rc = a->bk->launch(c);
       // Default-sized outputs of a device-counted range get the same count.
       if (!rc && d_n) {
@@ -935,21 +935,83 @@ static int run_kernel_actor(Actor* a, Msg& msg, Msg& out, uint32_t si) {
   return KA_OK;
 }
 
+// The stages of a composed actor in order; an inner composition without
+// mapping functions counts as its own stages.
+static void flat_stages(Actor* c, std::vector<Actor*>& out) {
+  for (Actor* st : c->stages) {
+    if (st->composed && !st->pre && !st->post)
+      flat_stages(st, out);
+    else
+      out.push_back(st);
+  }
+}
+
+// An affine stage over a reference, in place, with nothing between it and its
+// neighbours.
+static bool plain_affine(const Actor* a) {
+  return !a->composed && a->bk && !a->pre && !a->post && a->kernel == "affine_u32" && a->sig[0].a.in_mode == KA_REF &&
+         a->sig[0].a.out_mode == KA_REF && a->sig[1].init.size() >= 4 && a->sig[2].init.size() >= 4;
+}
+
+// Takes the run of affine stages over one index space that starts at stage i:
+// each actor's lock (none is waited for: an actor that is busy ends the run)
+// and its parameters.  Returns the run's length; below 2 nothing is taken.
+static size_t affine_run(const std::vector<Actor*>& st, size_t i, std::vector<std::unique_lock<std::mutex>>& locks,
+                         AffineStages& stages) {
+  size_t n = 0;
+  for (; i + n < st.size(); ++n) {
+    Actor* a = st[i + n];
+    if (a->composed) break;
+    bool held = false;
+    for (size_t j = i; j < i + n; ++j) held = held || st[j] == a;
+    std::unique_lock<std::mutex> l;
+    if (!held) {
+      l = std::unique_lock<std::mutex>(a->mu, std::try_to_lock);
+      if (!l.owns_lock()) break;
+    }
+    const ka_nd_range &r = a->range, &r0 = st[i]->range;
+    if (!plain_affine(a) || r.global[0] != r0.global[0] || r.offset[0] != r0.offset[0]) break;
+    if (!held) locks.push_back(std::move(l));
+    uint32_t p[2];
+    std::memcpy(&p[0], a->sig[1].init.data(), 4);
+    std::memcpy(&p[1], a->sig[2].init.data(), 4);
+    stages.a.push_back(p[0]);
+    stages.b.push_back(p[1]);
+  }
+  if (n < 2) locks.clear();
+  return n;
+}
+
 int actor_run(Actor* a, Msg& in, Msg& out, uint32_t si) {
-  if (!a->composed) return run_kernel_actor(a, in, out, si);
+  if (!a->composed) {
+    std::lock_guard<std::mutex> lock(a->mu);
+    return run_kernel_actor(a, in, out, si);
+  }
   int rc = KA_OK;
   if (a->pre && (rc = apply_map(a->pre, a->map_ud, in))) return rc;
   Msg cur = std::move(in);
   in.clear();
-  for (Actor* st : a->stages) {
+  std::vector<Actor*> stages;
+  flat_stages(a, stages);
+  for (size_t i = 0; i < stages.size();) {
     Msg next;
-    rc = actor_run(st, cur, next, si);
+    std::vector<std::unique_lock<std::mutex>> locks;
+    AffineStages run;
+    size_t n = affine_run(stages, i, locks, run);
+    if (n >= 2) {
+      rc = run_kernel_actor(stages[i], cur, next, si, &run);
+      locks.clear();
+    } else {
+      n = 1;
+      rc = actor_run(stages[i], cur, next, si);
+    }
     msg_clear(cur);
     if (rc) {
       msg_clear(next);
       return rc;
     }
     cur = std::move(next);
+    i += n;
   }
   out = std::move(cur);
   if (a->post && (rc = apply_map(a->post, a->map_ud, out))) return rc;

@@ -285,12 +285,18 @@ struct Bound {  // one signature argument bound for a launch
   uint32_t lds_offset = 0;
 };
 
+// Affine stages that one launch applies in turn.
+struct AffineStages {
+  std::vector<uint32_t> a, b;
+};
+
 struct LaunchCtx {
   Env* env;
   uint64_t n;               // work-items (host-known upper bound)
   const uint64_t* d_n;      // device-resident work-item count, or null
   const ka_nd_range* range;
   std::vector<Bound>* args;
+  const AffineStages* stages = nullptr;  // affine_u32: these instead of the actor's own parameters
 };
 
 struct BuiltinKernel {
