@@ -108,15 +108,16 @@ int sort_shape_count();
 // batch of small requests takes its own path: variant 1 the persistent fused
 // launch, the others the three-launch form.
 int batch_variant_count();
+constexpr uint32_t kMaxReqUnknown = 0xFFFFFFFFu;
 // Sort of a batch of requests (request j: values[req_off[j] .. req_off[j+1]),
 // all below 2^value_bits, value_bits 1..16) by value inside each request,
 // stable: skeys[i] = j << value_bits | value, srows[i] = the position inside
 // the request, request j's pairs at [req_off[j], req_off[j+1]).  A value at or
-// above 2^value_bits sets req_bad[j] (or *bad without req_bad); the caller
-// clears them.
+// above 2^value_bits sets req_bad[j] (or *bad without req_bad), which the sort
+// clears first.  max_req: the largest request, or kMaxReqUnknown.
 int launch_radix_sort_segments(Env& env, const uint32_t* values, uint64_t n, const uint32_t* req_off, uint32_t nreq,
                                uint32_t value_bits, uint32_t* skeys, uint32_t* srows, uint32_t* bad,
-                               uint32_t* req_bad, bool even_split = true);
+                               uint32_t* req_bad, bool even_split, uint32_t max_req, ClearWords cw);
 // Device address of the OR of all keys of the last launch_radix_sort_pairs on
 // this stream (valid once that sort has run, for n > 0).
 const uint32_t* sort_plan_keys_or(Env& env);
@@ -182,7 +183,6 @@ int launch_wah_lookup(Env& env, const uint32_t* keys, uint64_t d_cap, const uint
 // 2^value_bits rejects the whole batch (every output length 0), or, with
 // req_bad (nreq device words), only its own request: req_bad[j] = 1 and that
 // request's slices are unspecified while every other request's are exact.
-constexpr uint32_t kMaxReqUnknown = 0xFFFFFFFFu;
 // The lengths of a batch's five outputs: device-resident, and on the host.
 struct BatchLens {
   uint64_t *keys, *offsets, *words, *key_start, *word_start;

@@ -24,6 +24,7 @@
 #include <algorithm>
 
 #include "common.hpp"
+#include "lds_sort.hpp"
 
 namespace ka {
 namespace {
@@ -167,19 +168,30 @@ __global__ __launch_bounds__(kSplitBlock) void k_batch_starts(const uint32_t* __
                                                               const uint32_t* __restrict__ g_off, uint32_t nreq,
                                                               uint32_t value_bits, uint32_t* __restrict__ key_start,
                                                               uint32_t* __restrict__ word_start) {
-  const uint32_t D = (uint32_t)*d_len_keys;
-  for (uint32_t j = blockIdx.x * kSplitBlock + threadIdx.x; j <= nreq; j += gridDim.x * kSplitBlock) {
-    uint32_t lo = 0, hi = D;  // first d in [0, D] with request(d) >= j
+  // A wave per request: every step of its search leaves a 64th of the range (a
+  // work-item's binary search took 20 dependent loads, 11 us, over 8 10^5 entries).
+  const uint32_t D = (uint32_t)*d_len_keys, lane = lane_id();
+  const uint32_t first = (blockIdx.x * kSplitBlock + threadIdx.x) / 64, stride = gridDim.x * (kSplitBlock / 64);
+  for (uint32_t j = first; j <= nreq; j += stride) {
+    uint32_t lo = 0, hi = D;  // the first d with request(d) >= j is in [lo, hi]
     while (lo < hi) {
-      const uint32_t mid = (lo + hi) / 2;
-      const uint32_t r = tag_shift_ok(value_bits) ? tkeys[mid] >> value_bits : 0u;
-      if (r < j)
-        lo = mid + 1;
-      else
-        hi = mid;
+      const uint32_t step = (hi - lo + 63u) / 64u;
+      const uint64_t p = (uint64_t)lo + (uint64_t)lane * step;  // probes lo, lo + step, ...
+      uint32_t r = ~0u;
+      if (p < hi) r = tag_shift_ok(value_bits) ? tkeys[p] >> value_bits : 0u;
+      const uint32_t c = (uint32_t)__popcll(__ballot(p < hi && r < j));  // the first c probes are below j
+      if (c == 0) {
+        hi = lo;
+      } else {
+        const uint32_t at = lo + (c - 1u) * step;  // the last probe below j
+        hi = min(hi, at + step);
+        lo = at + 1u;
+      }
     }
-    key_start[j] = lo;
-    word_start[j] = g_off[lo];  // g_off[D] = W
+    if (lane == 0) {
+      key_start[j] = lo;
+      word_start[j] = g_off[lo];  // g_off[D] = W
+    }
   }
 }
 
@@ -215,8 +227,8 @@ __global__ __launch_bounds__(kSplitBlock) void k_batch_tables(
 // 32 - kSmallRowBits bits, the whole batch is one persistent launch,
 // k_small_fused: each work-group takes the next request in order from a
 // ticket counter and
-//   * sorts value << kSmallRowBits | row in LDS (a bitonic sort; the row bits
-//     make equal values keep their order) and marks value, group and fill
+//   * sorts value << kSmallRowBits | row in LDS (equal values keep their order)
+//     and marks value, group and fill
 //     heads as the encoder does (Sec. 4.1 parts 3-5);
 //   * publishes the request's word and value counts, and finds those of all
 //     earlier requests by decoupled look-back over the requests' status words;
@@ -237,6 +249,33 @@ constexpr uint32_t kSmallRows = 31, kSmallFill = 0x80000000u;
 constexpr uint32_t kSmallGrid = 2048;               // persistent work-groups (8 per CU)
 static_assert((1 << kSmallRowBits) == kSmallMax, "row bits cover a request");
 
+// Sorted pairs packed in one word each: value << kSmallRowBits | row.
+struct PackedPairs {
+  uint32_t* s;
+  __device__ __forceinline__ void put(uint32_t i, uint32_t key, uint32_t row) const { s[i] = key << kSmallRowBits | row; }
+  __device__ __forceinline__ void get(uint32_t i, uint32_t& key, uint32_t& row) const {
+    key = s[i] >> kSmallRowBits;
+    row = s[i] & (kSmallMax - 1);
+  }
+};
+
+// The n <= kSmallMax values of a request sorted into s (packed pairs); whether
+// a value is at or above 2^value_bits (value_bits <= 32 - kSmallRowBits).
+// Starts and ends with a barrier.  (A radix sort by two 8-bit digits; the 55
+// compare-exchange steps of a bitonic sort, a barrier each, took 32 us of a
+// batch of 256 requests.)
+__device__ __forceinline__ bool sort_request(const uint32_t* __restrict__ values, uint32_t n, uint32_t* s,
+                                             LdsSort<kSmallBlock>& S, uint32_t value_bits) {
+  __syncthreads();
+  if (n == 0) return false;  // uniform over the work-group
+  uint32_t keys_or;
+  if (n <= (uint32_t)kSmallBlock)  // a ranking step per value and work-item
+    keys_or = lds_sort<kSmallBlock, 1>(values, n, PackedPairs{s}, S);
+  else
+    keys_or = lds_sort<kSmallBlock, kSmallPer>(values, n, PackedPairs{s}, S);
+  return (keys_or >> value_bits) != 0u;
+}
+
 __global__ __launch_bounds__(kSmallBlock) void k_small_fused(
     const uint32_t* __restrict__ values, const uint32_t* __restrict__ req_off, uint32_t nreq, uint32_t value_bits,
     uint32_t* __restrict__ ticket, uint64_t* __restrict__ status, uint32_t* __restrict__ bad_flag,
@@ -245,6 +284,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_fused(
     BatchLens lens) {
   __shared__ uint32_t s[kSmallMax];
   __shared__ uint32_t s_scan[kSmallBlock / 64];
+  __shared__ LdsSort<kSmallBlock> S;
   __shared__ uint32_t s_j, s_pre[2];
   const uint32_t tid = threadIdx.x;
   for (;;) {
@@ -257,37 +297,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_fused(
     // out-of-range value; only its first kSmallMax values are touched.
     const uint32_t n_req = req_off[j + 1] - b;
     const uint32_t n = min(n_req, (uint32_t)kSmallMax);
-    uint32_t over = n_req > (uint32_t)kSmallMax ? 1u : 0u;
-#pragma unroll
-    for (int q = 0; q < kSmallPer; ++q) {
-      const uint32_t i = q * kSmallBlock + tid;
-      uint32_t c = 0xFFFFFFFFu;  // padding sorts last
-      if (i < n) {
-        const uint32_t v = values[b + i];
-        over |= v >> value_bits;  // value_bits <= 32 - kSmallRowBits here
-        c = (v << kSmallRowBits) | i;
-      }
-      s[i] = c;
-    }
-    const bool bad = __syncthreads_or(over != 0u);
-    // bitonic sort of the first m = 2^ceil(log2 n) entries, ascending
-    uint32_t m = 1;
-    while (m < n) m <<= 1;
-    for (uint32_t k = 2; k <= m; k <<= 1) {
-      for (uint32_t h = k >> 1; h > 0; h >>= 1) {
-        for (uint32_t i = tid; i < m; i += kSmallBlock) {
-          const uint32_t l = i ^ h;
-          if (l > i) {
-            const uint32_t x = s[i], y = s[l];
-            if ((x > y) == ((i & k) == 0u)) {
-              s[i] = y;
-              s[l] = x;
-            }
-          }
-        }
-        __syncthreads();
-      }
-    }
+    const bool bad = sort_request(values + b, n, s, S, value_bits) || n_req > (uint32_t)kSmallMax;
     // heads of values, groups and fills, as in the encoder
     const uint32_t e0 = tid * kSmallPer;
     uint32_t heads = 0, segs = 0, gaps = 0;
@@ -393,43 +403,14 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_index(const uint32_t* __r
                                                              uint32_t* __restrict__ counts) {
   __shared__ uint32_t s[kSmallMax];
   __shared__ uint32_t s_scan[kSmallBlock / 64];
+  __shared__ LdsSort<kSmallBlock> S;
   const uint32_t j = blockIdx.x, tid = threadIdx.x;
   const uint32_t b = req_off[j];
   // A request above kSmallMax (a wrong size hint) fails the batch like an
   // out-of-range value; only its first kSmallMax values are touched.
   const uint32_t n_req = req_off[j + 1] - b;
   const uint32_t n = min(n_req, (uint32_t)kSmallMax);
-  uint32_t over = n_req > (uint32_t)kSmallMax ? 1u : 0u;
-#pragma unroll
-  for (int q = 0; q < kSmallPer; ++q) {
-    const uint32_t i = q * kSmallBlock + tid;
-    uint32_t c = 0xFFFFFFFFu;  // padding sorts last
-    if (i < n) {
-      const uint32_t v = values[b + i];
-      over |= v >> value_bits;  // value_bits <= 32 - kSmallRowBits here
-      c = (v << kSmallRowBits) | i;
-    }
-    s[i] = c;
-  }
-  const bool bad = __syncthreads_or(over != 0u);
-  // bitonic sort of the first m = 2^ceil(log2 n) entries, ascending
-  uint32_t m = 1;
-  while (m < n) m <<= 1;
-  for (uint32_t k = 2; k <= m; k <<= 1) {
-    for (uint32_t h = k >> 1; h > 0; h >>= 1) {
-      for (uint32_t i = tid; i < m; i += kSmallBlock) {
-        const uint32_t l = i ^ h;
-        if (l > i) {
-          const uint32_t x = s[i], y = s[l];
-          if ((x > y) == ((i & k) == 0u)) {
-            s[i] = y;
-            s[l] = x;
-          }
-        }
-      }
-      __syncthreads();
-    }
-  }
+  const bool bad = sort_request(values + b, n, s, S, value_bits) || n_req > (uint32_t)kSmallMax;
   // heads of values, groups and fills, as in the encoder (Sec. 4.1 parts 3-5)
   const uint32_t e0 = tid * kSmallPer;
   uint32_t heads = 0, segs = 0, gaps = 0;
@@ -614,9 +595,14 @@ int launch_wah_batch(Env& env, const uint32_t* values, uint64_t n, const uint32_
   uint32_t* g_off = static_cast<uint32_t*>(env.scratch(4 * (n + 1)));
   uint64_t* g_len = static_cast<uint64_t*>(env.scratch(8));
   if (!bad || !tkeys || !skeys || !srows || !g_off || !g_len) return env.fail(kErrOom, "wah_index_batch: scratch");
-  int rc = launch_fill_u32(env, bad, 1, 0);
-  if (rc) return rc;
-  if (req_bad && (rc = launch_fill_u32(env, req_bad, nreq, 0))) return rc;
+  EncodeOpts opt;
+  opt.cleared = wah_status(env, n);
+  if (!opt.cleared.p) return env.fail(kErrOom, "wah_index_batch: scratch");
+  int rc;
+  if (!(segmented && n)) {  // the segmented sort clears the flags itself
+    if ((rc = launch_fill_u32(env, bad, 1, 0))) return rc;
+    if (req_bad && (rc = launch_fill_u32(env, req_bad, nreq, 0))) return rc;
+  }
   // Values of at most 16 bits: the segmented sort orders each request by value
   // in ceil(value_bits / 8) passes over 16-bit keys and makes request-relative
   // rows; wider values: every value tagged with its request in the key's high
@@ -625,7 +611,7 @@ int launch_wah_batch(Env& env, const uint32_t* values, uint64_t n, const uint32_
   if (n) {
     if (segmented) {
       if ((rc = launch_radix_sort_segments(env, values, n, req_off, nreq, value_bits, skeys, srows, bad, req_bad,
-                                           sort_shape != 3)))
+                                           sort_shape != 3, max_req, opt.cleared)))
         return rc;
     } else {
       const uint64_t blocks = (n + kKeyTile - 1) / kKeyTile;
@@ -634,12 +620,12 @@ int launch_wah_batch(Env& env, const uint32_t* values, uint64_t n, const uint32_
           values, tkeys, nn, req_off, nreq, TagOp{value_bits, req_bad}, bad, d_n);
       env.prof_end("batch_keys");
       if ((rc = check_launch(env, "batch_keys launch"))) return rc;
-      if ((rc = launch_radix_sort_pairs(env, tkeys, nullptr, skeys, srows, n, sort_shape == 3 ? 0 : sort_shape, d_n)))
+      if ((rc = launch_radix_sort_pairs(env, tkeys, nullptr, skeys, srows, n, sort_shape == 3 ? 0 : sort_shape, d_n,
+                                        opt.cleared)))
         return rc;
     }
   }
   // The tagged keys are the encoder's keys; rows are (or become) request-relative.
-  EncodeOpts opt;
   opt.d_n = d_n;
   if (!segmented) {
     opt.req_base = req_off;
@@ -647,7 +633,7 @@ int launch_wah_batch(Env& env, const uint32_t* values, uint64_t n, const uint32_
   }
   if ((rc = launch_wah_encode(env, skeys, srows, n, IndexOut{keys, g_off, words, lens.keys, g_len, lens.words, {}}, opt)))
     return rc;
-  const uint32_t sgrid = std::min<uint32_t>(kSplitGrid, (nreq + kSplitBlock) / kSplitBlock);
+  const uint32_t sgrid = std::min<uint32_t>(4 * kSplitGrid, nreq / (kSplitBlock / 64) + 1);
   env.prof_begin("batch_split");
   k_batch_starts<<<dim3(sgrid), dim3(kSplitBlock), 0, env.stream()>>>(keys, lens.keys, g_off, nreq, value_bits,
                                                                        key_start, word_start);

@@ -389,7 +389,9 @@ struct ScatterLds {
   uint2 kr[kTile];  // reorder buffer: key and row of each element (the rank masks before)
   uint16_t wcnt[kWaves][kRadix];  // per-wave digit counts, then each wave's start of each digit in the tile
   uint32_t dbase[kRadix];         // global start minus tile-local start
-  uint32_t scan[kWaves];
+  uint32_t before[kRadix];        // tile rows: digit counts of the tiles before this one
+  uint32_t from[kRadix];          // and of this one and the later ones
+  uint32_t scan[kWaves], scan2[kWaves];
 };
 
 // The tile's keys and rows: wave w owns 64*kItems consecutive elements, lane
@@ -423,17 +425,67 @@ __device__ __forceinline__ void scatter_load(const IO& io, uint32_t base, uint32
   }
 }
 
+// Where a tile's runs go, from tile rows (see k_rows_count): T rows of counts,
+// this tile's is row `tile`; `origin` is the first position of all.  T = 0: the
+// start of each digit is given instead.
+struct TileRows {
+  const uint16_t* rows = nullptr;
+  uint32_t T = 0, tile = 0, origin = 0;
+};
+
+// Adds the rows' counts to before and from (LDS, zeroed): a wave reads 512
+// bytes of rows at a time.
+template <int kBlock, int kItems, int kBits>
+__device__ __forceinline__ void add_rows(const TileRows& tr, ScatterLds<kBlock, kItems>& L) {
+  constexpr uint32_t kD = 1u << kBits, kWaves = kBlock / 64;
+  constexpr uint32_t kLanes = kD / 4, kRowsPer = 64 / kLanes;  // lanes per row, rows per wave and step
+  const uint32_t w = threadIdx.x / 64, lane = lane_id();
+  const uint32_t col = lane % kLanes, sub = lane / kLanes;
+  uint32_t bef[4] = {0, 0, 0, 0}, aft[4] = {0, 0, 0, 0};
+  const uint2* src = reinterpret_cast<const uint2*>(tr.rows) + col;
+#pragma unroll 4
+  for (uint32_t r0 = w * kRowsPer; r0 < tr.T; r0 += kWaves * kRowsPer) {
+    const uint32_t r = r0 + sub;
+    uint2 v = make_uint2(0u, 0u);
+    if (r < tr.T) v = src[(uint64_t)r * kLanes];
+    const uint32_t c[4] = {v.x & 0xFFFFu, v.x >> 16, v.y & 0xFFFFu, v.y >> 16};
+    const bool b = r < tr.tile;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      bef[i] += b ? c[i] : 0u;
+      aft[i] += b ? 0u : c[i];
+    }
+  }
+#pragma unroll
+  for (uint32_t off = kLanes; off < 64; off <<= 1) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      bef[i] += (uint32_t)__shfl_xor((int)bef[i], (int)off);
+      aft[i] += (uint32_t)__shfl_xor((int)aft[i], (int)off);
+    }
+  }
+  if (lane < kLanes && w * kRowsPer < tr.T) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      atomicAdd(&L.before[4 * col + i], bef[i]);
+      atomicAdd(&L.from[4 * col + i], aft[i]);
+    }
+  }
+}
+
 // Ranks, reorders and writes one tile whose keys and rows are in registers
 // (their loads may still be in flight); dstart = the table entry of digit
 // threadIdx.x for this tile.  Starts and ends with a barrier.  With kCheck a
 // key at or above 2^check_shift sets *reject to 1.  With kFull the tile is
 // full (tile_n = kBlock * kItems) and no element is checked against tile_n.
+// With kRows dstart is not used: the starts come from the tile rows, which are
+// read while the keys are on their way and added up beside the ranking.
 template <int kBlock, int kItems, bool kCheck = false, bool kTag = false, int kBits = kRadixBits, bool kFull = false,
-          class IO>
+          bool kRows = false, class IO>
 __device__ __forceinline__ void scatter_tile(ScatterLds<kBlock, kItems>& L, const IO& io, uint32_t shift,
                                              uint32_t tile_n, uint32_t dstart, const uint32_t (&key)[kItems],
                                              const uint32_t (&row)[kItems], uint32_t check_shift = 32,
-                                             uint32_t* reject = nullptr) {
+                                             uint32_t* reject = nullptr, const TileRows& tr = {}) {
   constexpr int kWaves = kBlock / 64;
   static_assert(kBits >= 2 && kBits <= kRadixBits && kBits % 2 == 0, "digit widths 2, 4, 6, 8");
   constexpr uint32_t kMask = (1u << kBits) - 1u;
@@ -447,7 +499,9 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<kBlock, kItems>& L, cons
   uint64_t* dmask = reinterpret_cast<uint64_t*>(&L.kr[0]) + w * kRadix;
   if (kMaskRank)
     for (int j = lane; j < kRadix; j += 64) dmask[j] = 0ull;
+  if (kRows && tid < kRadix) L.before[tid] = L.from[tid] = 0u;
   __syncthreads();
+  if (kRows) add_rows<kBlock, kItems, kBits>(tr, L);
 
   // ---- rank inside the wave: peers = lanes with the same digit ----------------
   // 8-bit digits: digits 0 and 1, the most frequent ones on small values, by
@@ -516,6 +570,10 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<kBlock, kItems>& L, cons
     }
   }
   uint32_t total;
+  if (kRows) {  // the digits' starts: their totals scanned, then this tile's share of its digit
+    const uint32_t bef = tid < (1u << kBits) ? L.before[tid] : 0u, from = tid < (1u << kBits) ? L.from[tid] : 0u;
+    dstart = tr.origin + bef + block_excl_scan<kBlock>(bef + from, L.scan2, &total);
+  }
   const uint32_t loff = block_excl_scan<kBlock>(tid < kRadix ? tile_count : 0u, L.scan, &total);
   // Each wave's start of each digit in the tile: the digit's tile-local start
   // added to its per-wave offsets here, once per (wave, digit), so the reorder
@@ -613,64 +671,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter_fixed(PassIoT<SK, DK> 
 // way.  A pass is two launches instead of three, and the tile shrinks with the
 // input so that there are about as many work-groups as CUs.  What bounds it is
 // the rows' traffic, tiles^2 * digits * 2 bytes out of L2, so wide digits stop
-// at 256 tiles and narrow ones at 512 (see row_shape).
-
-// This tile's output position of digit threadIdx.x (below kRadix): T rows of
-// 1 << kBits counts, this tile's is row `tile`; `origin` is added.  A wave
-// reads 512 bytes of rows at a time.  s_mem: 2 * kBlock / 64 * (1 << kBits)
-// words.  Ends with a barrier.
-template <int kBlock, int kBits>
-__device__ __forceinline__ uint32_t row_prefix(const uint16_t* __restrict__ rows, uint32_t T, uint32_t tile,
-                                               uint32_t origin, uint32_t* s_mem, uint32_t* s_scan) {
-  constexpr uint32_t kD = 1u << kBits, kWaves = kBlock / 64;
-  constexpr uint32_t kLanes = kD / 4, kRowsPer = 64 / kLanes;  // lanes per row, rows per wave and step
-  const uint32_t tid = threadIdx.x, w = tid / 64, lane = lane_id();
-  const uint32_t col = lane % kLanes, sub = lane / kLanes;
-  uint32_t bef[4] = {0, 0, 0, 0}, aft[4] = {0, 0, 0, 0};
-  const uint2* src = reinterpret_cast<const uint2*>(rows) + col;
-#pragma unroll 8
-  for (uint32_t r0 = w * kRowsPer; r0 < T; r0 += kWaves * kRowsPer) {
-    const uint32_t r = r0 + sub;
-    uint2 v = make_uint2(0u, 0u);
-    if (r < T) v = src[(uint64_t)r * kLanes];
-    const uint32_t c[4] = {v.x & 0xFFFFu, v.x >> 16, v.y & 0xFFFFu, v.y >> 16};
-    const bool b = r < tile;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      bef[i] += b ? c[i] : 0u;
-      aft[i] += b ? 0u : c[i];
-    }
-  }
-#pragma unroll
-  for (uint32_t off = kLanes; off < 64; off <<= 1) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      bef[i] += (uint32_t)__shfl_xor((int)bef[i], (int)off);
-      aft[i] += (uint32_t)__shfl_xor((int)aft[i], (int)off);
-    }
-  }
-  if (lane < kLanes) {
-    u32x4 b, a;
-    b.x = bef[0], b.y = bef[1], b.z = bef[2], b.w = bef[3];
-    a.x = aft[0], a.y = aft[1], a.z = aft[2], a.w = aft[3];
-    reinterpret_cast<u32x4*>(s_mem)[w * kLanes + col] = b;
-    reinterpret_cast<u32x4*>(s_mem)[(kWaves + w) * kLanes + col] = a;
-  }
-  __syncthreads();
-  uint32_t before = 0, total = 0;
-  if (tid < kD) {
-#pragma unroll
-    for (uint32_t ww = 0; ww < kWaves; ++ww) {
-      before += s_mem[ww * kD + tid];
-      total += s_mem[(kWaves + ww) * kD + tid];
-    }
-    total += before;
-  }
-  uint32_t all;
-  const uint32_t first = block_excl_scan<kBlock>(total, s_scan, &all);
-  __syncthreads();
-  return origin + first + before;
-}
+// at 384 tiles and narrow ones at 512 (see row_shape).
 
 // Counts of one tile into its row.  The first pass also zeroes the encoder's
 // look-back words and *reject, and (kOrAnd) records the OR and AND of the
@@ -694,7 +695,7 @@ __global__ __launch_bounds__(kBlock) void k_rows_count(const SK* __restrict__ ke
 }
 
 template <int kBlock, int kItems, bool kCheck, int kBits, class SK, class DK>
-__global__ __launch_bounds__(kBlock) void k_rows_scatter(PassIoT<SK, DK> io, const uint16_t* __restrict__ rows,
+__global__ __launch_bounds__(kBlock, 8) void k_rows_scatter(PassIoT<SK, DK> io, const uint16_t* __restrict__ rows,
                                                          uint32_t shift, uint32_t n_cap, uint32_t ntiles,
                                                          uint32_t check_shift, uint32_t* __restrict__ reject,
                                                          const uint64_t* __restrict__ d_n) {
@@ -706,14 +707,13 @@ __global__ __launch_bounds__(kBlock) void k_rows_scatter(PassIoT<SK, DK> io, con
   if (tile_n == 0) return;  // past a device-resident count
   uint32_t key[kItems], row[kItems];
   scatter_load<kBlock, kItems>(io, base, tile_n, key, row);
-  const uint32_t dstart =
-      row_prefix<kBlock, kBits>(rows, ntiles, tile, 0u, reinterpret_cast<uint32_t*>(&L.kr[0]), L.scan);
+  const TileRows tr{rows, ntiles, tile, 0u};
   if (tile_n == (uint32_t)kTile)  // uniform: a full tile checks no element against its length
-    scatter_tile<kBlock, kItems, kCheck, false, kBits, true>(L, io, shift, tile_n, dstart, key, row, check_shift,
-                                                             reject);
+    scatter_tile<kBlock, kItems, kCheck, false, kBits, true, true>(L, io, shift, tile_n, 0u, key, row, check_shift,
+                                                                   reject, tr);
   else
-    scatter_tile<kBlock, kItems, kCheck, false, kBits, false>(L, io, shift, tile_n, dstart, key, row, check_shift,
-                                                              reject);
+    scatter_tile<kBlock, kItems, kCheck, false, kBits, false, true>(L, io, shift, tile_n, 0u, key, row, check_shift,
+                                                                    reject, tr);
 }
 
 // Plan-driven passes over uint32 keys (8-bit digits).  The first scatter forms
@@ -740,7 +740,7 @@ __global__ __launch_bounds__(kBlock) void k_rows_plan_count(PassBuffers buf, con
 }
 
 template <bool kFirst, int kBlock, int kItems>
-__global__ __launch_bounds__(kBlock) void k_rows_plan_scatter(PassBuffers buf, SortPlan* __restrict__ plan,
+__global__ __launch_bounds__(kBlock, 8) void k_rows_plan_scatter(PassBuffers buf, SortPlan* __restrict__ plan,
                                                               const uint16_t* __restrict__ rows,
                                                               const uint32_t* __restrict__ orand, uint32_t pass,
                                                               uint32_t n_cap, uint32_t ntiles,
@@ -768,12 +768,13 @@ __global__ __launch_bounds__(kBlock) void k_rows_plan_scatter(PassBuffers buf, S
   if (tile_n == 0) return;  // past a device-resident count
   uint32_t key[kItems], row[kItems];
   scatter_load<kBlock, kItems>(io, base, tile_n, key, row);
-  const uint32_t dstart =
-      row_prefix<kBlock, kRadixBits>(rows, ntiles, tile, 0u, reinterpret_cast<uint32_t*>(&L.kr[0]), L.scan);
+  const TileRows tr{rows, ntiles, tile, 0u};
   if (tile_n == (uint32_t)kTile)
-    scatter_tile<kBlock, kItems, false, false, kRadixBits, true>(L, io, pass * kRadixBits, tile_n, dstart, key, row);
+    scatter_tile<kBlock, kItems, false, false, kRadixBits, true, true>(L, io, pass * kRadixBits, tile_n, 0u, key, row,
+                                                                       32u, nullptr, tr);
   else
-    scatter_tile<kBlock, kItems>(L, io, pass * kRadixBits, tile_n, dstart, key, row);
+    scatter_tile<kBlock, kItems, false, false, kRadixBits, false, true>(L, io, pass * kRadixBits, tile_n, 0u, key, row,
+                                                                        32u, nullptr, tr);
 }
 
 }  // namespace
@@ -847,97 +848,164 @@ int sort_with_shape(Env& env, const uint32_t* keys, const uint32_t* rows, uint32
 // positions cut at the multiples of kTile, so tile l of request j covers
 // [max(req_off[j], (c0 + l) kTile), min(req_off[j+1], (c0 + l + 1) kTile)) with
 // c0 = req_off[j] / kTile (whole tiles stay aligned).  tile_base[j] is the
-// number of tiles of the requests before j.  The digit table holds request j's
-// counts at 256 tile_base[j] + d ntiles_j + l: scanned in that order, each
-// entry is the position in the batch of the tile's first key with digit d, and
-// no key leaves its request.  Rows are made relative to the request's first
-// position; the last pass writes the key tagged with its request (j <<
-// value_bits | key), which is what the encoder and the per-request split read.
+// number of tiles of the requests before j, tile_req[t] the request of tile t
+// (~0 from the last tile on; looking it up by search in every work-group and
+// launch took 9 dependent loads of 192 requests).  The digit counts are kept
+//  * as a table, request j's at 256 tile_base[j] + d ntiles_j + l: scanned in
+//    that order, each entry is the position in the batch of the tile's first
+//    key with digit d, and no key leaves its request; or
+//  * in batches of few tiles as rows (see k_rows_count), of which a tile sums
+//    its own request's.
+// Rows are made relative to the request's first position; the last pass writes
+// the key tagged with its request (j << value_bits | key), which is what the
+// encoder and the per-request split read.
+template <int kTile>
+__device__ __forceinline__ uint32_t request_tiles(const uint32_t* __restrict__ req_off, uint32_t j) {
+  const uint32_t r0 = req_off[j], r1 = req_off[j + 1];
+  return r1 > r0 ? (r1 + (uint32_t)kTile - 1u) / (uint32_t)kTile - r0 / (uint32_t)kTile : 0u;
+}
+
+// The layout of up to kSegLayoutMax requests by one work-group: tile_base,
+// tile_req (ub entries), the table's length, the cleared flags.
+constexpr uint32_t kSegLayoutMax = 16384;
+template <int kTile>
+__global__ __launch_bounds__(1024) void k_seg_layout(const uint32_t* __restrict__ req_off, uint32_t nreq, uint32_t ub,
+                                                     uint32_t* __restrict__ tile_base, uint32_t* __restrict__ tile_req,
+                                                     uint64_t* __restrict__ tlen, uint32_t* __restrict__ bad,
+                                                     uint32_t* __restrict__ req_bad) {
+  __shared__ uint32_t s_scan[16], s_base[1025];
+  const uint32_t tid = threadIdx.x, w = tid / 64, lane = lane_id();
+  uint32_t run = 0;
+  for (uint32_t c0 = 0; c0 < nreq; c0 += 1024) {
+    const uint32_t j = c0 + tid;
+    uint32_t nt = 0;
+    if (j < nreq) {
+      nt = request_tiles<kTile>(req_off, j);
+      if (req_bad) req_bad[j] = 0u;
+    }
+    uint32_t total;
+    const uint32_t base = run + block_excl_scan<1024>(nt, s_scan, &total);
+    if (j < nreq) tile_base[j] = base;
+    s_base[tid] = base;
+    if (tid == 0) s_base[1024] = run + total;
+    __syncthreads();
+    for (uint32_t q = w; q < min(1024u, nreq - c0); q += 16)  // a wave per request
+      for (uint32_t t = s_base[q] + lane; t < min(s_base[q + 1], ub); t += 64) tile_req[t] = c0 + q;
+    run += total;
+    __syncthreads();
+  }
+  if (tid == 0) {
+    tile_base[nreq] = run;
+    *tlen = (uint64_t)kRadix * run;
+    *bad = 0u;
+  }
+  for (uint32_t t = run + tid; t < ub; t += 1024) tile_req[t] = ~0u;
+}
+
+// The same for more requests: the tile counts (scanned by the launch between),
+// then a wave per request.
 template <int kTile>
 __global__ __launch_bounds__(256) void k_seg_tiles(const uint32_t* __restrict__ req_off, uint32_t nreq,
                                                    uint32_t* __restrict__ ntiles) {
-  for (uint32_t j = blockIdx.x * 256 + threadIdx.x; j <= nreq; j += gridDim.x * 256) {
-    uint32_t nt = 0;
-    if (j < nreq && req_off[j + 1] > req_off[j])
-      nt = (req_off[j + 1] + (uint32_t)kTile - 1u) / (uint32_t)kTile - req_off[j] / (uint32_t)kTile;
-    ntiles[j] = nt;
-  }
+  for (uint32_t j = blockIdx.x * 256 + threadIdx.x; j <= nreq; j += gridDim.x * 256)
+    ntiles[j] = j < nreq ? request_tiles<kTile>(req_off, j) : 0u;
 }
 
-// The table's length for its scan: 256 entries per tile of the batch.
-__global__ void k_seg_table_len(const uint32_t* __restrict__ tile_base, uint32_t nreq, uint64_t* __restrict__ len) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) *len = (uint64_t)kRadix * tile_base[nreq];
+__global__ __launch_bounds__(256) void k_seg_map(const uint32_t* __restrict__ tile_base, uint32_t nreq, uint32_t ub,
+                                                 uint32_t* __restrict__ tile_req, uint64_t* __restrict__ tlen,
+                                                 uint32_t* __restrict__ bad, uint32_t* __restrict__ req_bad) {
+  const uint32_t first = blockIdx.x * 256 + threadIdx.x, stride = gridDim.x * 256;
+  for (uint32_t j = first / 64; j < nreq; j += stride / 64) {
+    const uint32_t t1 = min(tile_base[j + 1], ub);
+    for (uint32_t t = tile_base[j] + lane_id(); t < t1; t += 64) tile_req[t] = j;
+    if (req_bad && lane_id() == 0) req_bad[j] = 0u;
+  }
+  const uint32_t all = tile_base[nreq];
+  for (uint64_t t = (uint64_t)all + first; t < ub; t += stride) tile_req[t] = ~0u;
+  if (first == 0) {
+    *tlen = (uint64_t)kRadix * all;
+    *bad = 0u;
+  }
 }
 
 struct SegTile {
   uint32_t j, l, base, len, nt;
 };
 
-// Request and place of tile t < tile_base[nreq]: the last request j with
-// tile_base[j] <= t (empty requests share their successor's base).
+// Tile t of request j.
 template <int kTile>
 __device__ __forceinline__ SegTile seg_tile(const uint32_t* __restrict__ req_off, const uint32_t* __restrict__ tile_base,
-                                            uint32_t nreq, uint32_t t) {
-  uint32_t lo = 0, hi = nreq;
-  while (hi - lo > 1u) {
-    const uint32_t mid = (lo + hi) / 2u;
-    if (tile_base[mid] <= t)
-      lo = mid;
-    else
-      hi = mid;
-  }
+                                            uint32_t j, uint32_t t) {
   SegTile s;
-  s.j = lo;
-  s.l = t - tile_base[lo];
-  s.nt = tile_base[lo + 1] - tile_base[lo];
-  const uint32_t r0 = req_off[lo], r1 = req_off[lo + 1], c0 = r0 / (uint32_t)kTile;
+  s.j = j;
+  s.l = t - tile_base[j];
+  s.nt = tile_base[j + 1] - tile_base[j];
+  const uint32_t r0 = req_off[j], r1 = req_off[j + 1], c0 = r0 / (uint32_t)kTile;
   s.base = max(r0, (c0 + s.l) * (uint32_t)kTile);
   s.len = min(r1, (c0 + s.l + 1u) * (uint32_t)kTile) - s.base;
   return s;
 }
 
-template <int kTile, int kRounds, class SK>
-__global__ __launch_bounds__(kUpBlock) void k_seg_count(const SK* __restrict__ keys, uint32_t* __restrict__ table,
-                                                        uint32_t shift, uint32_t mask,
-                                                        const uint32_t* __restrict__ req_off,
-                                                        const uint32_t* __restrict__ tile_base, uint32_t nreq,
-                                                        uint32_t ub) {
-  const uint32_t t = xcd_tile(blockIdx.x, ub);
-  if (t >= tile_base[nreq]) return;  // uniform over the work-group
-  const SegTile s = seg_tile<kTile>(req_off, tile_base, nreq, t);
-  uint32_t* const part = table + (uint64_t)kRadix * tile_base[s.j] + s.l;
+// The batch's tiles on the device, and where the counts are (one of the two).
+struct Segments {
+  const uint32_t *req_off, *tile_base, *tile_req;
+  uint32_t ub;        // tiles at most
+  uint32_t* table;    // digit-major per request
+  uint16_t* rows;     // 1 << bits counts per tile
+};
+
+template <int kTile, int kRounds, bool kRows, class SK>
+__global__ __launch_bounds__(kUpBlock) void k_seg_count(const SK* __restrict__ keys, Segments sg, uint32_t shift,
+                                                        uint32_t bits, ClearWords cw) {
+  clear_words(cw);
+  const uint32_t t = xcd_tile(blockIdx.x, sg.ub), j = sg.tile_req[t];
+  if (j == ~0u) return;  // uniform over the work-group
+  const SegTile s = seg_tile<kTile>(sg.req_off, sg.tile_base, j, t);
+  uint32_t* const part = sg.table + (uint64_t)kRadix * (t - s.l) + s.l;
+  uint16_t* const row = sg.rows + ((uint64_t)t << bits);
   upsweep_tile<kUpBlock, kTile, kRounds, false>(
-      keys, shift, s.base, s.len, [&](uint32_t d, uint32_t c) { part[(uint64_t)d * s.nt] = c; }, t, nullptr, mask);
+      keys, shift, s.base, s.len,
+      [&](uint32_t d, uint32_t c) {
+        if (!kRows)
+          part[(uint64_t)d * s.nt] = c;
+        else if (d >> bits == 0u)
+          row[d] = (uint16_t)c;
+      },
+      t, nullptr, (1u << bits) - 1u);
 }
 
-// kCheck (the first pass): a key at or above 2^value_bits flags its request
-// (req_bad[j]) or, without req_bad, the batch (*bad).  kTag (the last pass):
-// keys are written as j << value_bits | key.
-template <int kBlock, int kItems, bool kCheck, bool kTag, int kBits, class SK, class DK>
-__global__ __launch_bounds__(kBlock) void k_seg_scatter(PassIoT<SK, DK> io, const uint32_t* __restrict__ table,
-                                                        uint32_t shift, const uint32_t* __restrict__ req_off,
-                                                        const uint32_t* __restrict__ tile_base, uint32_t nreq,
-                                                        uint32_t ub, uint32_t value_bits, uint32_t* __restrict__ bad,
-                                                        uint32_t* __restrict__ req_bad) {
+// offs: the scanned table (not with kRows).  kCheck (the first pass): a key at
+// or above 2^value_bits flags its request (req_bad[j]) or, without req_bad, the
+// batch (*bad).  kTag (the last pass): keys are written as j << value_bits |
+// key.
+template <int kBlock, int kItems, bool kCheck, bool kTag, bool kRows, int kBits, class SK, class DK>
+__global__ __launch_bounds__(kBlock, 8) void k_seg_scatter(PassIoT<SK, DK> io, Segments sg,
+                                                           const uint32_t* __restrict__ offs, uint32_t shift,
+                                                           uint32_t value_bits, uint32_t* __restrict__ bad,
+                                                           uint32_t* __restrict__ req_bad) {
   constexpr int kTile = kBlock * kItems;
   __shared__ ScatterLds<kBlock, kItems> L;
-  const uint32_t t = xcd_tile(blockIdx.x, ub);
-  if (t >= tile_base[nreq]) return;  // uniform over the work-group
-  const SegTile s = seg_tile<kTile>(req_off, tile_base, nreq, t);
-  const uint32_t dstart =
-      threadIdx.x < kRadix ? table[(uint64_t)kRadix * tile_base[s.j] + (uint64_t)threadIdx.x * s.nt + s.l] : 0u;
-  io.row_origin = req_off[s.j];
+  const uint32_t t = xcd_tile(blockIdx.x, sg.ub), j = sg.tile_req[t];
+  if (j == ~0u) return;  // uniform over the work-group
+  const SegTile s = seg_tile<kTile>(sg.req_off, sg.tile_base, j, t);
+  const uint32_t dstart = !kRows && threadIdx.x < kRadix
+                              ? offs[(uint64_t)kRadix * (t - s.l) + (uint64_t)threadIdx.x * s.nt + s.l]
+                              : 0u;
+  io.row_origin = sg.req_off[j];
   if (kTag) {
     io.key_and = value_bits < 32 ? (1u << value_bits) - 1u : ~0u;
-    io.key_or = value_bits < 32 ? s.j << value_bits : 0u;
+    io.key_or = value_bits < 32 ? j << value_bits : 0u;
   }
   uint32_t key[kItems], row[kItems];
   scatter_load<kBlock, kItems>(io, s.base, s.len, key, row);
-  uint32_t* const flag = req_bad ? req_bad + s.j : bad;
+  uint32_t* const flag = req_bad ? req_bad + j : bad;
+  const TileRows tr{sg.rows + ((uint64_t)(t - s.l) << kBits), s.nt, s.l, io.row_origin};
   if (s.len == (uint32_t)kTile)  // uniform: a full tile checks no element against its length
-    scatter_tile<kBlock, kItems, kCheck, kTag, kBits, true>(L, io, shift, s.len, dstart, key, row, value_bits, flag);
+    scatter_tile<kBlock, kItems, kCheck, kTag, kBits, true, kRows>(L, io, shift, s.len, dstart, key, row, value_bits,
+                                                                   flag, tr);
   else
-    scatter_tile<kBlock, kItems, kCheck, kTag, kBits, false>(L, io, shift, s.len, dstart, key, row, value_bits, flag);
+    scatter_tile<kBlock, kItems, kCheck, kTag, kBits, false, kRows>(L, io, shift, s.len, dstart, key, row, value_bits,
+                                                                    flag, tr);
 }
 
 // Digits of a fixed-pass sort of values below 2^value_bits (value_bits 1..16):
@@ -1153,28 +1221,37 @@ int rows_sort32(Env& env, const uint32_t* keys, const uint32_t* rows_in, uint32_
 }
 
 // Tile shape of the tile-row sorts by capacity: about one tile per CU, from
-// 1024 keys up; kNone: too many tiles.  An index request, us, scanned table /
-// tile rows: 12-bit values (6-bit digits) 65536 89 / 72, 2^20 96 / 81, 2^21 104
-// / 91, 2^22 118 / 115, 5.2M 132 / 145; 16-bit (8-bit digits) 65536 95 / 72,
-// 2^21 107 / 96, 2^22 126 / 141; any uint32 65536 142 / 93, 2^21 171 / 157, 2^22
-// 204 / 248.
+// 1024 keys up; kNone: too many tiles.  An index request, us, by the scanned
+// table / by tile rows: 12-bit values (6-bit digits) 65536 89 / 72 and 2^20 96 /
+// 81 (both before the lengths came to the host by themselves), 3M 82 / 72, 2^22 85
+// / 77, 5M 97 / 98, 6M 101 / 103; 16-bit (8-bit digits) 65536 95 / 72, 3M 88 / 84,
+// 2^22 91 / 94; any uint32 65536 142 / 93, 3M 162 / 154, 2^22 184 / 209.
 enum class RowShape { kNone, k1024, k2048, k4096, k8192 };
+constexpr uint64_t row_tiles_max(uint32_t bits) { return bits > 6 ? 384 : 512; }
 RowShape row_shape(uint64_t n, uint32_t bits) {
   if (n <= 256ull * 1024) return RowShape::k1024;
   if (n <= 256ull * 2048) return RowShape::k2048;
   if (n <= 256ull * 4096) return RowShape::k4096;
-  if (n <= (bits > 6 ? 256ull : 512ull) * 8192) return RowShape::k8192;
+  if (n <= row_tiles_max(bits) * 8192) return RowShape::k8192;
   return RowShape::kNone;
 }
 
-// Launch of a segmented scatter for a digit width known at run time.
-template <int kBlock, int kItems, bool kCheck, bool kTag, class SK, class DK>
-void seg_scatter(Env& env, uint32_t bits, uint32_t grid, const PassIoT<SK, DK>& io, const uint32_t* offs,
-                 uint32_t shift, const uint32_t* req_off, const uint32_t* tile_base, uint32_t nreq, uint32_t ub,
-                 uint32_t value_bits, uint32_t* bad, uint32_t* req_bad) {
-#define KA_SEG_SCATTER(B)                                                                                   \
-  k_seg_scatter<kBlock, kItems, kCheck, kTag, B><<<dim3(grid), dim3(kBlock), 0, env.stream()>>>(          \
-      io, offs, shift, req_off, tile_base, nreq, ub, value_bits, bad, req_bad)
+// One pass of the segmented sort.
+template <bool kCheck, bool kTag, bool kRows, class SK, class DK>
+int seg_pass(Env& env, const PassIoT<SK, DK>& io, const Segments& sg, uint32_t* offs, const uint64_t* tlen,
+             uint32_t shift, uint32_t bits, uint32_t value_bits, uint32_t* bad, uint32_t* req_bad, ClearWords cw) {
+  constexpr int kBlock = kShapes[0].block, kItems = kShapes[0].items, kTile = kBlock * kItems;
+  env.prof_begin(kCheck ? "radix_upsweep0" : "radix_upsweep");
+  k_seg_count<kTile, kCheck ? 1 : -1, kRows, SK><<<dim3(sg.ub), dim3(kUpBlock), 0, env.stream()>>>(io.src_keys, sg,
+                                                                                                  shift, bits, cw);
+  env.prof_end(kCheck ? "radix_upsweep0" : "radix_upsweep");
+  int rc = check_launch(env, "seg_count launch");
+  if (rc) return rc;
+  if (!kRows && (rc = launch_exclusive_scan(env, sg.table, offs, (uint64_t)kRadix * sg.ub, tlen))) return rc;
+  env.prof_begin("radix_scatter");
+#define KA_SEG_SCATTER(B)                                                                                             \
+  k_seg_scatter<kBlock, kItems, kCheck, kTag, kRows, B, SK, DK><<<dim3(sg.ub), dim3(kBlock), 0, env.stream()>>>(       \
+      io, sg, offs, shift, value_bits, bad, req_bad)
   switch (bits) {
     case 2:
       KA_SEG_SCATTER(2);
@@ -1190,71 +1267,83 @@ void seg_scatter(Env& env, uint32_t bits, uint32_t grid, const PassIoT<SK, DK>& 
       break;
   }
 #undef KA_SEG_SCATTER
+  env.prof_end("radix_scatter");
+  return check_launch(env, "seg_scatter launch");
+}
+
+template <bool kRows>
+int seg_passes(Env& env, const uint32_t* values, const DigitSplit& ds, const Segments& sg, uint32_t* offs,
+               const uint64_t* tlen, uint32_t value_bits, uint16_t* kb, uint32_t* rb, uint32_t* skeys, uint32_t* srows,
+               uint32_t* bad, uint32_t* req_bad, ClearWords cw) {
+  // pass 0: uint32 values in (checked), uint16 keys out -- or tagged keys if it is the only pass
+  if (ds.passes == 1)
+    return seg_pass<true, true, kRows>(env, PassIoT<uint32_t, uint32_t>{values, nullptr, skeys, srows, true}, sg, offs,
+                                       tlen, ds.shift[0], ds.bits[0], value_bits, bad, req_bad, cw);
+  const int rc =
+      seg_pass<true, false, kRows>(env, PassIoT<uint32_t, uint16_t>{values, nullptr, kb, rb, true}, sg, offs, tlen,
+                                   ds.shift[0], ds.bits[0], value_bits, bad, req_bad, cw);
+  if (rc) return rc;
+  // pass 1: uint16 keys in, tagged uint32 keys out
+  return seg_pass<false, true, kRows>(env, PassIoT<uint16_t, uint32_t>{kb, rb, skeys, srows, false}, sg, offs, tlen,
+                                      ds.shift[1], ds.bits[1], value_bits, bad, req_bad, ClearWords{});
 }
 
 // The segmented sort of a batch (values below 2^value_bits, value_bits <= 16):
 // uint16 keys between passes, request-relative rows, tagged uint32 keys out;
 // the byte or the even digit split.
 int seg_sort(Env& env, const uint32_t* values, uint64_t n, const uint32_t* req_off, uint32_t nreq,
-             uint32_t value_bits, uint32_t* skeys, uint32_t* srows, uint32_t* bad, uint32_t* req_bad, bool even) {
-  constexpr int kBlock = kShapes[0].block, kItems = kShapes[0].items, kTile = kBlock * kItems;
+             uint32_t value_bits, uint32_t* skeys, uint32_t* srows, uint32_t* bad, uint32_t* req_bad, bool even,
+             uint32_t max_req, ClearWords cw) {
+  constexpr int kTile = kShapes[0].block * kShapes[0].items;
   const DigitSplit ds = digit_split(value_bits, even);
-  const uint32_t passes = ds.passes;
   const uint64_t ub64 = (n + kTile - 1) / kTile + nreq;  // tiles: at most one more per request
   if (ub64 >= (1ull << 31)) return env.fail(kErrArg, "segmented sort: too many tiles");
-  const uint32_t ub = (uint32_t)ub64;
-  uint32_t* ntiles = static_cast<uint32_t*>(env.scratch(4ull * (nreq + 1)));
+  Segments sg{};
+  sg.ub = (uint32_t)ub64;
+  sg.req_off = req_off;
+  // Rows unless a request has too many tiles to sum (or may have, and the batch
+  // has).  12-bit values, us a batch by the scanned table / by rows: requests of
+  // 20,000 values 10^5 84 / 71, 4 10^6 133 / 111, 1.6 10^7 286 / 262; of 200,000
+  // values 10^6 94 / 76, 2.8 10^7 343 / 320.
+  const bool use_rows = sg.ub <= 384 || max_req <= 128ull * kTile;
   uint32_t* tile_base = static_cast<uint32_t*>(env.scratch(4ull * (nreq + 1)));
+  uint32_t* tile_req = static_cast<uint32_t*>(env.scratch(4ull * sg.ub));
   uint64_t* tlen = static_cast<uint64_t*>(env.scratch(8));
-  uint32_t* table = static_cast<uint32_t*>(env.scratch((uint64_t)kRadix * ub * 4));
-  uint32_t* offs = static_cast<uint32_t*>(env.scratch((uint64_t)kRadix * ub * 4));
-  uint16_t* kb = passes > 1 ? static_cast<uint16_t*>(env.scratch(2 * n)) : nullptr;
-  uint32_t* rb = passes > 1 ? static_cast<uint32_t*>(env.scratch(4 * n)) : nullptr;
-  if (!ntiles || !tile_base || !tlen || !table || !offs || (passes > 1 && (!kb || !rb)))
+  uint32_t* offs = nullptr;
+  if (use_rows) {
+    sg.rows = static_cast<uint16_t*>(env.scratch(2ull * kRadix * sg.ub));
+  } else {
+    sg.table = static_cast<uint32_t*>(env.scratch((uint64_t)kRadix * sg.ub * 4));
+    offs = static_cast<uint32_t*>(env.scratch((uint64_t)kRadix * sg.ub * 4));
+  }
+  uint16_t* kb = ds.passes > 1 ? static_cast<uint16_t*>(env.scratch(2 * n)) : nullptr;
+  uint32_t* rb = ds.passes > 1 ? static_cast<uint32_t*>(env.scratch(4 * n)) : nullptr;
+  if (!tile_base || !tile_req || !tlen || (use_rows ? !sg.rows : !sg.table || !offs) || (ds.passes > 1 && (!kb || !rb)))
     return env.fail(kErrOom, "segmented sort: scratch");
+  sg.tile_base = tile_base;
+  sg.tile_req = tile_req;
   int rc;
   env.prof_begin("seg_tiles");
-  k_seg_tiles<kTile><<<dim3(std::min<uint32_t>((nreq + 256) / 256, 1024)), dim3(256), 0, env.stream()>>>(req_off, nreq,
-                                                                                                      ntiles);
-  env.prof_end("seg_tiles");
-  if ((rc = check_launch(env, "seg_tiles launch"))) return rc;
-  if ((rc = launch_exclusive_scan(env, ntiles, tile_base, nreq + 1ull, nullptr))) return rc;
-  k_seg_table_len<<<dim3(1), dim3(64), 0, env.stream()>>>(tile_base, nreq, tlen);
-  if ((rc = check_launch(env, "seg_table_len launch"))) return rc;
-  const uint64_t tcap = (uint64_t)kRadix * ub;
-  // pass 0: uint32 values in (checked), uint16 keys out -- or tagged keys if it is the only pass
-  env.prof_begin("radix_upsweep0");
-  k_seg_count<kTile, 1, uint32_t><<<dim3(ub), dim3(kUpBlock), 0, env.stream()>>>(
-      values, table, ds.shift[0], (1u << ds.bits[0]) - 1u, req_off, tile_base, nreq, ub);
-  env.prof_end("radix_upsweep0");
-  if ((rc = check_launch(env, "seg_count launch"))) return rc;
-  if ((rc = launch_exclusive_scan(env, table, offs, tcap, tlen))) return rc;
-  env.prof_begin("radix_scatter");
-  if (passes == 1) {
-    PassIoT<uint32_t, uint32_t> io{values, nullptr, skeys, srows, true};
-    seg_scatter<kBlock, kItems, true, true>(env, ds.bits[0], ub, io, offs, ds.shift[0], req_off, tile_base, nreq, ub,
-                                            value_bits, bad, req_bad);
+  if (nreq <= kSegLayoutMax) {
+    k_seg_layout<kTile><<<dim3(1), dim3(1024), 0, env.stream()>>>(req_off, nreq, sg.ub, tile_base, tile_req, tlen, bad,
+                                                                  req_bad);
+    env.prof_end("seg_tiles");
+    if ((rc = check_launch(env, "seg_layout launch"))) return rc;
   } else {
-    PassIoT<uint32_t, uint16_t> io{values, nullptr, kb, rb, true};
-    seg_scatter<kBlock, kItems, true, false>(env, ds.bits[0], ub, io, offs, ds.shift[0], req_off, tile_base, nreq, ub,
-                                             value_bits, bad, req_bad);
+    uint32_t* ntiles = static_cast<uint32_t*>(env.scratch(4ull * (nreq + 1)));
+    if (!ntiles) return env.fail(kErrOom, "segmented sort: scratch");
+    k_seg_tiles<kTile><<<dim3(std::min<uint32_t>((nreq + 256) / 256, 1024)), dim3(256), 0, env.stream()>>>(req_off, nreq,
+                                                                                                        ntiles);
+    env.prof_end("seg_tiles");
+    if ((rc = check_launch(env, "seg_tiles launch"))) return rc;
+    if ((rc = launch_exclusive_scan(env, ntiles, tile_base, nreq + 1ull, nullptr))) return rc;
+    k_seg_map<<<dim3(std::min<uint32_t>(nreq / 4 + 1, 4096)), dim3(256), 0, env.stream()>>>(tile_base, nreq, sg.ub,
+                                                                                         tile_req, tlen, bad, req_bad);
+    if ((rc = check_launch(env, "seg_map launch"))) return rc;
   }
-  env.prof_end("radix_scatter");
-  if ((rc = check_launch(env, "seg_scatter launch"))) return rc;
-  if (passes == 1) return kOk;
-  // pass 1: uint16 keys in, tagged uint32 keys out
-  env.prof_begin("radix_upsweep");
-  k_seg_count<kTile, -1, uint16_t><<<dim3(ub), dim3(kUpBlock), 0, env.stream()>>>(
-      kb, table, ds.shift[1], (1u << ds.bits[1]) - 1u, req_off, tile_base, nreq, ub);
-  env.prof_end("radix_upsweep");
-  if ((rc = check_launch(env, "seg_count launch"))) return rc;
-  if ((rc = launch_exclusive_scan(env, table, offs, tcap, tlen))) return rc;
-  PassIoT<uint16_t, uint32_t> io1{kb, rb, skeys, srows, false};
-  env.prof_begin("radix_scatter");
-  seg_scatter<kBlock, kItems, false, true>(env, ds.bits[1], ub, io1, offs, ds.shift[1], req_off, tile_base, nreq, ub,
-                                           value_bits, bad, req_bad);
-  env.prof_end("radix_scatter");
-  return check_launch(env, "seg_scatter launch");
+  return use_rows ? seg_passes<true>(env, values, ds, sg, offs, tlen, value_bits, kb, rb, skeys, srows, bad, req_bad, cw)
+                  : seg_passes<false>(env, values, ds, sg, offs, tlen, value_bits, kb, rb, skeys, srows, bad, req_bad,
+                                      cw);
 }
 
 }  // namespace
@@ -1264,13 +1353,13 @@ int batch_variant_count() { return kNumShapes + 1; }
 
 int launch_radix_sort_segments(Env& env, const uint32_t* values, uint64_t n, const uint32_t* req_off, uint32_t nreq,
                                uint32_t value_bits, uint32_t* skeys, uint32_t* srows, uint32_t* bad,
-                               uint32_t* req_bad, bool even_split) {
+                               uint32_t* req_bad, bool even_split, uint32_t max_req, ClearWords cw) {
   if (n == 0) return kOk;
   if (!values || !req_off || !skeys || !srows || !bad || nreq == 0)
     return env.fail(kErrArg, "segmented sort: null buffer");
   if (value_bits == 0 || value_bits > 16) return env.fail(kErrArg, "segmented sort: value_bits must be 1..16");
   if (n >= (1ull << 31)) return env.fail(kErrArg, "segmented sort: n must be below 2^31");
-  return seg_sort(env, values, n, req_off, nreq, value_bits, skeys, srows, bad, req_bad, even_split);
+  return seg_sort(env, values, n, req_off, nreq, value_bits, skeys, srows, bad, req_bad, even_split, max_req, cw);
 }
 
 const uint32_t* sort_plan_keys_or(Env& env) {

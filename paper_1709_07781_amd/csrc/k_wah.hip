@@ -47,6 +47,7 @@
 #include <algorithm>
 
 #include "common.hpp"
+#include "lds_sort.hpp"
 
 namespace ka {
 namespace {
@@ -220,118 +221,20 @@ struct Reject {
   __device__ __forceinline__ bool operator()() const { return flag && shift < 32 && (*flag >> shift) != 0u; }
 };
 
-// ---------------------------------------------------------------------------------
-// the sort of a small input inside one work-group
-// ---------------------------------------------------------------------------------
-// n <= 1024 * kItems values: sorted by value, equal values in row order, into
-// s_k (values) and s_r (rows) at their padded places; wave w owns 64 kItems
-// consecutive elements.  8-bit digits over the bits that differ between the
-// values at all, ranked inside each wave by ballots.  Returns the OR of the
-// values.  Ends with a barrier.
-constexpr int kSmallBlock = 1024;
-constexpr int kSmallWaves = kSmallBlock / 64;
-template <int kItems>
-__device__ __forceinline__ uint32_t small_sort(const uint32_t* __restrict__ values, uint32_t n, uint32_t* s_k,
-                                               uint32_t* s_r, uint16_t (*s_cnt)[256], uint32_t* s_scan,
-                                               uint32_t* s_or, uint32_t* s_and) {
-  const uint32_t tid = threadIdx.x, w = tid / 64, lane = lane_id();
-  const uint32_t i0 = w * 64 * kItems + lane;  // elements i0 + 64 i
-  uint32_t key[kItems], row[kItems];
-#pragma unroll
-  for (int i = 0; i < kItems; ++i) {
-    row[i] = i0 + 64 * i;
-    key[i] = row[i] < n ? values[row[i]] : 0u;
+constexpr int kSmallBlock = 1024;  // the work-group that sorts and encodes a small input
+
+// Pairs at their padded places in the encoder's stage.
+struct StagedPairs {
+  uint32_t *k, *r;
+  __device__ __forceinline__ void put(uint32_t i, uint32_t key, uint32_t row) const {
+    k[pidx(i)] = key;
+    r[pidx(i)] = row;
   }
-  uint32_t o = 0, a = ~0u;
-#pragma unroll
-  for (int i = 0; i < kItems; ++i) {
-    o |= key[i];
-    if (row[i] < n) a &= key[i];
+  __device__ __forceinline__ void get(uint32_t i, uint32_t& key, uint32_t& row) const {
+    key = k[pidx(i)];
+    row = r[pidx(i)];
   }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    o |= (uint32_t)__shfl_xor((int)o, off);
-    a &= (uint32_t)__shfl_xor((int)a, off);
-  }
-  if (lane == 0) {
-    s_or[w] = o;
-    s_and[w] = a;
-  }
-  __syncthreads();
-  o = 0, a = ~0u;
-#pragma unroll
-  for (int ww = 0; ww < kSmallWaves; ++ww) {
-    o |= s_or[ww];
-    a &= s_and[ww];
-  }
-  const uint32_t diff = (uint32_t)__builtin_amdgcn_readfirstlane((int)(o ^ a));  // bits in which values differ
-  const uint32_t lo = diff ? (uint32_t)__builtin_ctz(diff) : 32u, hi = diff ? 32u - (uint32_t)__builtin_clz(diff) : 0u;
-  if (!diff) {  // all values equal: in order already
-#pragma unroll
-    for (int i = 0; i < kItems; ++i)
-      if (row[i] < n) {
-        s_k[pidx(row[i])] = key[i];
-        s_r[pidx(row[i])] = row[i];
-      }
-  }
-  for (uint32_t shift = lo; shift < hi; shift += 8) {
-    for (int i = tid; i < kSmallWaves * 256 / 2; i += kSmallBlock) reinterpret_cast<uint32_t*>(&s_cnt[0][0])[i] = 0u;
-    if (shift != lo) {  // what the pass before has placed
-#pragma unroll
-      for (int i = 0; i < kItems; ++i)
-        if (i0 + 64 * i < n) {
-          key[i] = s_k[pidx(i0 + 64 * i)];
-          row[i] = s_r[pidx(i0 + 64 * i)];
-        }
-    }
-    __syncthreads();
-    uint32_t rank[kItems];
-#pragma unroll
-    for (int i = 0; i < kItems; ++i) {
-      const bool valid = i0 + 64 * i < n;
-      const uint32_t d = (key[i] >> shift) & 255u;
-      uint32_t dl = 0, dh = 0;
-      differing_lanes<0>(d, dl, dh);
-      differing_lanes<2>(d, dl, dh);
-      differing_lanes<4>(d, dl, dh);
-      differing_lanes<6>(d, dl, dh);
-      const uint64_t peers = __builtin_amdgcn_ballot_w64(valid) & ~(((uint64_t)dh << 32) | dl);
-      rank[i] = 0;
-      if (valid) {
-        const uint32_t below =
-            __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0u));
-        const uint32_t old = s_cnt[w][d];
-        if (below == 0) s_cnt[w][d] = (uint16_t)(old + (uint32_t)__popcll(peers));
-        rank[i] = old + below;
-      }
-    }
-    __syncthreads();
-    uint32_t cnt[kSmallWaves], total = 0, all;
-    if (tid < 256) {
-#pragma unroll
-      for (int ww = 0; ww < kSmallWaves; ++ww) {
-        cnt[ww] = total;
-        total += s_cnt[ww][tid];
-      }
-    }
-    const uint32_t start = block_excl_scan<kSmallBlock>(total, s_scan, &all);
-    if (tid < 256) {
-#pragma unroll
-      for (int ww = 0; ww < kSmallWaves; ++ww) s_cnt[ww][tid] = (uint16_t)(start + cnt[ww]);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kItems; ++i)
-      if (i0 + 64 * i < n) {
-        const uint32_t p = pidx(s_cnt[w][(key[i] >> shift) & 255u] + rank[i]);
-        s_k[p] = key[i];
-        s_r[p] = row[i];
-      }
-    __syncthreads();
-  }
-  __syncthreads();
-  return o;
-}
+};
 
 // ---------------------------------------------------------------------------------
 // write: literals, fills and lookup-table entries of one tile
@@ -372,9 +275,8 @@ __global__ __launch_bounds__(kBlock, kFmt == kFmtPaper && !kSort ? 8 : 4) void k
   const uint32_t avail = min((uint32_t)(kTile + kLook), n - base);  // readable from base on
 
   if constexpr (kSort > 0) {
-    __shared__ __align__(16) uint16_t s_cnt[kSmallWaves][256];
-    __shared__ uint32_t s_or[kSmallWaves], s_and[kSmallWaves];
-    small_or = small_sort<kSort>(skeys, n, s_k, s_r, s_cnt, L.scan, s_or, s_and);
+    __shared__ LdsSort<kBlock> S;
+    small_or = lds_sort<kBlock, kSort>(skeys, n, StagedPairs{s_k, s_r}, S);
   }
   // ---- stage elements base .. base+kTile+kLook-1 into slots 0.. ---------------
   // Work-items 64.. also load the look-ahead (slots kTile ..) and the kBehind

@@ -107,7 +107,7 @@ def test_small_input_beyond_its_hint(sess, bits):
 
 # capacities where the sort's tile grows (1024, 2048, 4096, 8192 keys) and where its digit table is scanned instead
 # of summed by every tile (by digit width), with the encoder's tiles of 2048, 4096 and 8192 pairs
-SORT_EDGES = [1 << 18, 1 << 19, 1 << 20, 1 << 21, 1 << 22]
+SORT_EDGES = [1 << 18, 1 << 19, 1 << 20, 384 << 13, 1 << 22]
 
 
 @pytest.mark.parametrize("n", [SMALL_MAX + 1, 70_001] + [e + d for e in SORT_EDGES for d in (0, 1)])
@@ -251,3 +251,42 @@ def test_combine_scans_many_tiles(sess):
     (o,) = sess.request(act, ka.val(wa.ctypes.data, wa.size), ka.val(wb.ctypes.data, wb.size), n_out=1)
     sess.release_actor(act)
     np.testing.assert_array_equal(o, paper(a & b))
+
+
+@pytest.mark.parametrize("sizes", [[3000] * 400, [1 << 20, 0, 5, (1 << 20) - 1, 1] + [9000] * 20,
+                                   [(1 << 20) + 1] * 4, [0, 0, 8192, 8193, 0, 77] * 3, [2] * 17_000 + [1500]])
+@pytest.mark.parametrize("bits", [3, 12, 16])
+def test_batch_tile_layouts(sess, sizes, bits):
+    """Rows and table, requests that share tiles, empty ones, more requests than one work-group lays out; a batch in
+    which some value exceeds its hint is refused."""
+    from paper_1709_07781_amd import KaError
+    if bits == 16 and len(sizes) > 1 << 16:
+        pytest.skip("request ids and values exceed 32 bits")
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.uint32)
+    v = workloads.u32(len(sizes), int(off[-1])) & np.uint32((1 << bits) - 1)
+    got = sess.wah_batch(sess.upload(v), off, bits)
+    some = range(len(sizes)) if len(sizes) < 500 else list(range(0, len(sizes), 997)) + [len(sizes) - 1]
+    for j in some:
+        for g, e in zip(got[j], oracle.default().wah_index(v[off[j]:off[j + 1]])):
+            np.testing.assert_array_equal(g, e, err_msg=f"request {j}")
+    v[int(off[-1]) // 2] = 1 << bits
+    with pytest.raises(KaError):
+        sess.wah_batch(sess.upload(v), off, bits)
+
+
+@pytest.mark.parametrize("variant", [0, 1])
+@pytest.mark.parametrize("size", [1, 255, 256, 257, 1023, 1024])
+def test_small_requests_of_a_batch(sess, size, variant):
+    """The small-request forms' sort: one and four values per work-item, values of 1 to 22 bits, equal and distinct."""
+    from paper_1709_07781_amd.session import BatchPlan
+    for bits in (1, 8, 12, 22):
+        sizes = [size, 0, size, 1, size]
+        off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.uint32)
+        v = workloads.u32(size + bits, int(off[-1])) & np.uint32((1 << bits) - 1)
+        v[off[2]:off[3]] = (1 << bits) - 1
+        plan = BatchPlan(sess, off, bits, shape=variant)
+        plan.run(v)
+        for j, got in enumerate(plan.result()):
+            for g, e in zip(got, oracle.default().wah_index(v[off[j]:off[j + 1]])):
+                np.testing.assert_array_equal(g, e)
+        plan.close()
