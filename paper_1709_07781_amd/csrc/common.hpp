@@ -197,6 +197,29 @@ int launch_wah_batch(Env& env, const uint32_t* values, uint64_t n, const uint32_
 // for the batched index).
 int launch_segmented_scan(Env& env, const uint32_t* in, uint32_t* out, uint64_t n, const uint32_t* req_off,
                           uint32_t nreq);
+// Copies of 32-bit words between device memory and pinned host memory (or
+// inside either), all in one launch: segment i's words count is `words`, or the
+// smaller of it and the device's *d_words.
+struct CopySeg {
+  const uint32_t* src;
+  uint32_t* dst;
+  uint64_t words;
+  const uint64_t* d_words;
+};
+constexpr uint32_t kCopySegs = 10;
+struct CopyList {
+  CopySeg seg[kCopySegs];
+  uint32_t n = 0;
+  uint64_t most = 0;  // words of the longest segment
+  void add(const uint32_t* src, uint32_t* dst, uint64_t words, const uint64_t* d_words = nullptr) {
+    seg[n++] = {src, dst, words, d_words};
+    most = words > most ? words : most;
+  }
+};
+int launch_copy(Env& env, const CopyList& list);
+// The same for n segments listed in pinned or device memory; most: the words of
+// the longest one.
+int launch_copy_many(Env& env, const CopySeg* segs, uint32_t n, uint64_t most);
 int launch_fill_u64(Env& env, uint64_t* p, uint64_t count, uint64_t value);
 int launch_fill_u32(Env& env, uint32_t* p, uint64_t count, uint32_t value);
 int launch_set_len(Env& env, uint64_t* d_len, uint64_t value, LenHost host = {});

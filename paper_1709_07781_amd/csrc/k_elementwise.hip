@@ -81,6 +81,35 @@ __global__ __launch_bounds__(256) void k_fill_u32(uint32_t* __restrict__ p, uint
     p[i] = value;
 }
 
+// blockIdx.y: the segment.  Over PCIe a kernel reads or writes pinned memory at
+// the link's rate once a few thousand 16-byte accesses are in flight; one
+// launch then replaces a copy command per piece (about 5 us each on the device,
+// and as much on the host).
+constexpr uint32_t kCopyGrid = 64;  // work-groups per segment at most
+__device__ __forceinline__ void copy_segment(const CopySeg& s) {
+  const uint64_t n = device_count(s.words, s.d_words);
+  const uint64_t step = (uint64_t)gridDim.x * 256, nv = n / 4;
+  const uint64_t i0 = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+  const u32x4w* src = reinterpret_cast<const u32x4w*>(s.src);
+  u32x4w* dst = reinterpret_cast<u32x4w*>(s.dst);
+  for (uint64_t i = i0; i < nv; i += 4 * step) {
+    u32x4w v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (i + k * step < nv) v[k] = src[i + k * step];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (i + k * step < nv) dst[i + k * step] = v[k];
+  }
+  if (i0 < n - 4 * nv) s.dst[4 * nv + i0] = s.src[4 * nv + i0];
+}
+
+__global__ __launch_bounds__(256) void k_copy(CopyList list) { copy_segment(list.seg[blockIdx.y]); }
+
+__global__ __launch_bounds__(256) void k_copy_many(const CopySeg* __restrict__ segs) {
+  copy_segment(segs[blockIdx.y]);
+}
+
 __global__ void k_set_len(uint64_t* d_len, LenHost host, uint64_t value) {
   if (threadIdx.x == 0) put_len(d_len, host, 0, value);
 }
@@ -139,6 +168,29 @@ int launch_affine_chain(Env& env, uint32_t* x, uint64_t n, const uint32_t* a, co
       k_affine_u32<false><<<dim3((uint32_t)grid), dim3(kAffBlock), 0, env.stream()>>>(x, n, d_n, op);
     env.prof_end("affine_chain_u32");
     const int rc = check_launch(env, "affine chain launch");
+    if (rc) return rc;
+  }
+  return kOk;
+}
+
+static uint32_t copy_grid(uint64_t most) {
+  return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(kCopyGrid, (most / 4 + 255) / 256));
+}
+
+int launch_copy(Env& env, const CopyList& list) {
+  if (list.n == 0 || list.most == 0) return kOk;
+  if (list.n > kCopySegs) return env.fail(kErrArg, "copy: too many segments");
+  k_copy<<<dim3(copy_grid(list.most), list.n), dim3(256), 0, env.stream()>>>(list);
+  return check_launch(env, "copy launch");
+}
+
+int launch_copy_many(Env& env, const CopySeg* segs, uint32_t n, uint64_t most) {
+  if (n == 0 || most == 0) return kOk;
+  if (!segs) return env.fail(kErrArg, "copy: segment list");
+  constexpr uint32_t kMost = 32768;  // segments per launch (a grid's y extent is 16 bits)
+  for (uint32_t i = 0; i < n; i += kMost) {
+    k_copy_many<<<dim3(copy_grid(most), std::min(kMost, n - i)), dim3(256), 0, env.stream()>>>(segs + i);
+    const int rc = check_launch(env, "copy launch");
     if (rc) return rc;
   }
   return kOk;

@@ -294,17 +294,48 @@ KA_API int ka_batch_plan_stream(ka_batch_plan* plan, void** stream) {
   return KA_OK;
 }
 
-KA_API int ka_batch_plan_run(ka_batch_plan* plan, const uint32_t* values, uint32_t flags) {
-  if (!plan) return set_error(KA_E_ARG, "null plan");
-  int rc = plan->sys->use_device();
-  if (rc) return rc;
-  if (values && plan->n &&
-      hipMemcpyAsync(plan->input, values, 4 * plan->n,
-                     (flags & KA_WAH_INPUT_DEVICE) ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
-                     plan->s) != hipSuccess) {
+// Values (and, of an any-batch plan, the table in t) to the plan's buffers.
+// Small ones from the host go through pinned memory and one kernel, larger ones
+// by copy commands.
+constexpr uint64_t kPlanStaged = 8ull << 20;
+static int plan_upload(ka_batch_plan* plan, const uint32_t* values, uint32_t flags, const uint32_t* t) {
+  System* sys = plan->sys;
+  const uint64_t bytes = values ? 4 * plan->n : 0, tab = t ? 4 * (plan->nreq_cap + 1ull) : 0;
+  if (!(flags & KA_WAH_INPUT_DEVICE) && bytes + tab <= kPlanStaged) {
+    CopyList l;
+    if (t) l.add(t, plan->req_off, plan->nreq_cap + 1ull);
+    void* st = nullptr;
+    if (bytes && (st = sys->stage.get(sys, bytes))) {
+      std::memcpy(st, values, bytes);
+      l.add(static_cast<const uint32_t*>(st), plan->input, plan->n);
+    }
+    if (!bytes || st) {
+      int rc = launch_copy(plan->env, l);
+      if (st) {
+        hipEvent_t e = sys->get_event();
+        if (e && hipEventRecord(e, plan->s) == hipSuccess) {
+          sys->stage.retire(sys, st, e);
+        } else {
+          (void)hipGetLastError();
+          (void)hipStreamSynchronize(plan->s);
+          if (e) sys->put_event(e);
+          sys->stage.give_back(st);
+        }
+      }
+      return rc;
+    }
+  }
+  if ((t && hipMemcpyAsync(plan->req_off, t, tab, hipMemcpyHostToDevice, plan->s) != hipSuccess) ||
+      (bytes && hipMemcpyAsync(plan->input, values, bytes,
+                               (flags & KA_WAH_INPUT_DEVICE) ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
+                               plan->s) != hipSuccess)) {
     (void)hipGetLastError();
     return set_error(KA_E_DEVICE, "plan: input copy");
   }
+  return KA_OK;
+}
+
+static int plan_replay(ka_batch_plan* plan) {
   if (plan->chosen < 0) {
     // Autotuning: the first run times every recorded shape on these values
     // (each leaves the same outputs) and keeps the fastest for later runs.
@@ -348,6 +379,16 @@ KA_API int ka_batch_plan_run(ka_batch_plan* plan, const uint32_t* values, uint32
   return KA_OK;
 }
 
+KA_API int ka_batch_plan_run(ka_batch_plan* plan, const uint32_t* values, uint32_t flags) {
+  KA_GUARD_BEGIN
+  if (!plan) return set_error(KA_E_ARG, "null plan");
+  int rc = plan->sys->use_device();
+  if (rc) return rc;
+  if ((rc = plan_upload(plan, values, flags, nullptr))) return rc;
+  return plan_replay(plan);
+  KA_GUARD_END
+}
+
 KA_API int ka_batch_plan_run_batch(ka_batch_plan* plan, const uint32_t* values, const uint32_t* req_off,
                                    uint32_t nreq, uint32_t flags) {
   KA_GUARD_BEGIN
@@ -374,15 +415,15 @@ KA_API int ka_batch_plan_run_batch(ka_batch_plan* plan, const uint32_t* values, 
   uint32_t* t = plan->h_tab[k];
   std::memcpy(t, req_off, 4 * (nreq + 1ull));
   for (uint32_t j = nreq + 1; j <= plan->nreq_cap; ++j) t[j] = (uint32_t)n;
-  if (hipMemcpyAsync(plan->req_off, t, 4 * (plan->nreq_cap + 1ull), hipMemcpyHostToDevice, plan->s) != hipSuccess ||
-      hipEventRecord(plan->tab_done[k], plan->s) != hipSuccess) {
+  plan->n = n;
+  plan->nreq = nreq;
+  if ((rc = plan_upload(plan, values, flags, t))) return rc;
+  if (hipEventRecord(plan->tab_done[k], plan->s) != hipSuccess) {
     (void)hipGetLastError();
     return set_error(KA_E_DEVICE, "plan: table upload");
   }
   plan->tab_next = k ^ 1;
-  plan->n = n;
-  plan->nreq = nreq;
-  return ka_batch_plan_run(plan, values, flags);
+  return plan_replay(plan);
   KA_GUARD_END
 }
 
@@ -399,11 +440,37 @@ KA_API int ka_batch_plan_result(ka_batch_plan* plan, ka_wah_batch_result* out) {
   int rc = plan->sys->use_device();
   if (rc) return rc;
   uint64_t len[5];
+  const uint32_t* src[5] = {plan->keys, plan->offsets, plan->words, plan->key_start, plan->word_start};
+  // Small results: one kernel behind the run copies lengths and outputs, as long
+  // as the device says they are, into pinned memory at their capacities' places.
+  const uint64_t dcap = plan->value_bits < 32 ? std::min<uint64_t>(plan->n, (uint64_t)plan->nreq << plan->value_bits)
+                                              : plan->n;
+  const uint64_t tab = plan->nreq_cap + 1ull, cap[5] = {dcap, dcap + plan->nreq_cap, 2 * plan->n, tab, tab};
+  uint64_t at[5], total = 64;
+  for (int i = 0; i < 5; ++i) {
+    at[i] = total;
+    total += (4 * cap[i] + 63) / 64 * 64;
+  }
+  struct Pinned {
+    System* sys;
+    char* p;
+    ~Pinned() {
+      if (p) sys->stage.give_back(p);
+    }
+  } st{plan->sys, total <= kPlanStaged ? static_cast<char*>(plan->sys->stage.get(plan->sys, total)) : nullptr};
+  if (st.p) {
+    CopyList l;
+    l.add(reinterpret_cast<const uint32_t*>(plan->lens), reinterpret_cast<uint32_t*>(st.p), 10);
+    for (int i = 0; i < 5; ++i)
+      if (cap[i]) l.add(src[i], reinterpret_cast<uint32_t*>(st.p + at[i]), cap[i], plan->lens + i);
+    if ((rc = launch_copy(plan->env, l))) return rc;
+  }
   if (hipStreamSynchronize(plan->s) != hipSuccess ||
-      hipMemcpy(len, plan->lens, sizeof(len), hipMemcpyDeviceToHost) != hipSuccess) {
+      (!st.p && hipMemcpy(len, plan->lens, sizeof(len), hipMemcpyDeviceToHost) != hipSuccess)) {
     (void)hipGetLastError();
     return set_error(KA_E_DEVICE, "plan: synchronisation");
   }
+  if (st.p) std::memcpy(len, st.p, sizeof(len));
   if (len[3] == 0) return set_error(KA_E_ARG, "a value is at or above 2^value_bits");
   // an any-batch plan's padding (empty requests after the real ones) adds one
   // offsets entry and one table entry each, at the ends
@@ -416,12 +483,13 @@ KA_API int ka_batch_plan_result(ka_batch_plan* plan, ka_wah_batch_result* out) {
   r.n = plan->n;
   r.D = len[0];
   r.W = len[2];
-  const uint32_t* src[5] = {plan->keys, plan->offsets, plan->words, plan->key_start, plan->word_start};
   uint32_t** dst[5] = {&r.keys, &r.offsets, &r.words, &r.key_start, &r.word_start};
   for (int i = 0; i < 5 && !rc; ++i) {
     *dst[i] = static_cast<uint32_t*>(std::malloc(std::max<uint64_t>(len[i], 1) * 4));
     if (!*dst[i]) {
       rc = set_error(KA_E_OOM, "host allocation failed");
+    } else if (st.p) {
+      std::memcpy(*dst[i], st.p + at[i], 4 * len[i]);
     } else if (len[i] && hipMemcpy(*dst[i], src[i], 4 * len[i], hipMemcpyDeviceToHost) != hipSuccess) {
       (void)hipGetLastError();
       rc = set_error(KA_E_DEVICE, "plan: result copy");

@@ -35,6 +35,12 @@ static int hip_fail(hipError_t e, const char* what) {
     if (_e != hipSuccess) return hip_fail(_e, what); \
   } while (0)
 
+#define KA_HIP_RC(rc, expr, what)                  \
+  do {                                             \
+    hipError_t _e = (expr);                        \
+    if (_e != hipSuccess) rc = hip_fail(_e, what); \
+  } while (0)
+
 uint32_t dtype_size(uint32_t dtype) {
   switch (dtype) {
     case KA_U32:
@@ -1710,43 +1716,57 @@ static int read_lengths3(System* sys, Ref* const r[3], uint64_t len[3]) {
   return KA_OK;
 }
 
-// Host copies of three outputs of one stream after their lengths are known:
-// through one pinned staging buffer and one synchronisation when they are
-// small, else one blocking copy each.
-static int read_outputs3(System* sys, Ref* const r[3], void* const dst[3], const uint64_t bytes[3]) {
-  constexpr uint64_t kStagedMax = 8ull << 20;
-  const uint64_t total = bytes[0] + bytes[1] + bytes[2];
-  const uint32_t home = r[0]->home;
-  if (total == 0) return KA_OK;
-  if (total > kStagedMax || r[1]->home != home || r[2]->home != home) {
-    for (int i = 0; i < 3; ++i) {
-      int rc = bytes[i] ? ka_ref_read(static_cast<ka_ref*>(r[i]), dst[i], bytes[i]) : KA_OK;
-      if (rc) return rc;
+// Small host outputs of a request are copied into pinned memory by a kernel
+// queued behind the ones that make them, which reads the lengths on the device:
+// the host waits once for the whole request.  (Lengths, then a copy each, took two
+// waits and three copy commands.)  Their places are those of the capacities, so
+// only outputs up to this many bytes in all go this way.
+constexpr uint64_t kStagedMax = 8ull << 20;
+struct StagedOutputs {
+  System* sys = nullptr;
+  char* p = nullptr;
+  uint64_t off[8] = {};
+  hipEvent_t done = nullptr;
+  ~StagedOutputs() {
+    if (done) {
+      (void)hipEventSynchronize(done);  // the kernel writes into p
+      sys->put_event(done);
     }
-    return KA_OK;
+    if (p) sys->stage.give_back(p);
   }
-  char* st = static_cast<char*>(sys->stage.get(sys, total));
-  if (!st) return set_error(KA_E_OOM, "pinned staging");
-  hipStream_t s = sys->streams[home]->s;
-  hipError_t e = hipSuccess;
-  uint64_t off = 0;
-  for (int i = 0; i < 3 && e == hipSuccess; ++i) {
-    if (bytes[i]) e = hipMemcpyAsync(st + off, r[i]->ptr, bytes[i], hipMemcpyDeviceToHost, s);
-    off += bytes[i];
+};
+
+// Queues the copy of refs[0 .. n-1] (uint32 outputs of one stream, at most caps[i]
+// words each); false: not staged (too large, or out of pinned memory).
+static bool stage_outputs(System* sys, Ref* const* refs, const uint64_t* caps, uint32_t n, uint32_t si,
+                          StagedOutputs* so) {
+  uint64_t total = 0;
+  for (uint32_t i = 0; i < n; ++i) {
+    if (refs[i]->home != si) return false;
+    so->off[i] = total;
+    total += (4 * std::min(caps[i], refs[i]->cap) + 63) / 64 * 64;
   }
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e != hipSuccess) {
+  if (!total || total > kStagedMax) return false;
+  so->sys = sys;
+  so->p = static_cast<char*>(sys->stage.get(sys, total));
+  if (!so->p) return false;
+  CopyList l;
+  for (uint32_t i = 0; i < n; ++i) {
+    const bool known = refs[i]->len_known.load();
+    l.add(static_cast<const uint32_t*>(refs[i]->ptr), reinterpret_cast<uint32_t*>(so->p + so->off[i]),
+          std::min(known ? refs[i]->len : caps[i], refs[i]->cap), known ? nullptr : refs[i]->d_len);
+  }
+  CmdEnv env(sys, si);
+  if (launch_copy(env, l) != kOk) return false;
+  so->done = sys->get_event();
+  if (!so->done || hipEventRecord(so->done, env.stream()) != hipSuccess) {
     (void)hipGetLastError();
-    sys->stage.give_back(st);
-    return set_error(KA_E_DEVICE, "result read-back");
+    (void)hipStreamSynchronize(env.stream());
+    if (so->done) sys->put_event(so->done);
+    so->done = nullptr;
+    return false;
   }
-  off = 0;
-  for (int i = 0; i < 3; ++i) {
-    if (bytes[i]) std::memcpy(dst[i], st + off, bytes[i]);
-    off += bytes[i];
-  }
-  sys->stage.give_back(st);
-  return KA_OK;
+  return true;
 }
 
 KA_API int ka_wah_index(ka_system* sys, const uint32_t* values, uint64_t n, uint32_t flags, ka_wah_result* out) {
@@ -1782,6 +1802,15 @@ KA_API int ka_wah_index(ka_system* sys, const uint32_t* values, uint64_t n, uint
   rc = ka_send(act, &msg, 1, &t);
   ka_ref_release(in);
   if (rc) return rc;
+  StagedOutputs so;
+  bool staged = false;
+  if (!(flags & KA_WAH_OUTPUT_REFS)) {
+    // a hint that holds bounds the distinct values; a larger index is refused below
+    const uint64_t dcap = value_bits && value_bits < 32 ? std::min<uint64_t>(n, 1ull << value_bits) : n;
+    Ref* const outs[3] = {t->outs[0].ref, t->outs[1].ref, t->outs[2].ref};
+    const uint64_t caps[3] = {dcap, dcap + 1, 2 * n};
+    staged = stage_outputs(sys, outs, caps, 3, act->stream, &so);
+  }
   ka_value res[3] = {};
   rc = ka_receive(t, res, 3, -1);
   ka_ticket_release(t);
@@ -1811,7 +1840,13 @@ KA_API int ka_wah_index(ka_system* sys, const uint32_t* values, uint64_t n, uint
     if (!rc) {
       void* const dst[3] = {r.keys, r.offsets, r.words};
       const uint64_t bytes[3] = {D * 4, (D + 1) * 4, W * 4};
-      rc = read_outputs3(sys, outs, dst, bytes);
+      if (staged) KA_HIP_RC(rc, hipEventSynchronize(so.done), "result read-back");
+      for (int i = 0; i < 3 && !rc; ++i) {
+        if (staged)
+          std::memcpy(dst[i], so.p + so.off[i], bytes[i]);
+        else if (bytes[i])
+          rc = ka_ref_read(static_cast<ka_ref*>(outs[i]), dst[i], bytes[i]);
+      }
     }
   }
   for (auto& v : res)
@@ -1891,8 +1926,18 @@ KA_API int ka_wah_batch(ka_system* sys, const uint32_t* values, uint64_t n, cons
   ka_ticket* t = nullptr;
   rc = ka_send(act, msg, 2, &t);
   ka_ref_release(in);
+  const uint32_t si = act->stream;
   ka_actor_release(act);
   if (rc) return rc;
+  StagedOutputs so;
+  bool staged = false;
+  if (!(flags & KA_WAH_OUTPUT_REFS)) {
+    Ref* outs[5];
+    for (int i = 0; i < 5; ++i) outs[i] = t->outs[i].ref;
+    const uint64_t dcap = value_bits < 32 ? std::min<uint64_t>(n, (uint64_t)nreq << value_bits) : n;
+    const uint64_t caps[5] = {dcap, dcap + nreq, 2 * n, nreq + 1ull, nreq + 1ull};
+    staged = stage_outputs(sys, outs, caps, 5, si, &so);
+  }
   ka_value res[5] = {};
   rc = ka_receive(t, res, 5, -1);
   ka_ticket_release(t);
@@ -1919,10 +1964,13 @@ KA_API int ka_wah_batch(ka_system* sys, const uint32_t* values, uint64_t n, cons
       return KA_OK;
     }
     uint32_t** dst[5] = {&br.keys, &br.offsets, &br.words, &br.key_start, &br.word_start};
+    if (staged) KA_HIP_RC(rc, hipEventSynchronize(so.done), "result read-back");
     for (int i = 0; i < 5 && !rc; ++i) {
       *dst[i] = static_cast<uint32_t*>(std::malloc(std::max<uint64_t>(len[i], 1) * 4));
       if (!*dst[i])
         rc = set_error(KA_E_OOM, "host allocation failed");
+      else if (staged)
+        std::memcpy(*dst[i], so.p + so.off[i], len[i] * 4);
       else
         rc = ka_ref_read(res[i].ref, *dst[i], len[i] * 4);
     }

@@ -313,7 +313,9 @@ Batch* Server::launch(std::vector<SrvReq*>& take, uint64_t bytes) {
     b->rc = rc;
     return b;
   }
-  b->h_tab = sys->stage.get(sys, 4 * (rw + 1ull) + 4 * (rs + 1ull));
+  // pinned: the request tables, then the list of the inputs' copies
+  const uint64_t tab_bytes = align_up(4 * (rw + 1ull) + 4 * (rs + 1ull));
+  b->h_tab = sys->stage.get(sys, tab_bytes + sizeof(CopySeg) * (take.size() + 2));
   b->out = new OutBuf();
   b->out->sys = sys;
   b->out->p = sys->stage.get(sys, std::max<uint64_t>(out_bytes, 4));
@@ -340,28 +342,41 @@ Batch* Server::launch(std::vector<SrvReq*>& take, uint64_t bytes) {
   {
     CmdEnv env(sys, b->si);
     hipStream_t s = env.stream();
-    // each request's data from its pinned buffer to its place; then the tables
+    // Each request's data from its pinned buffer (or device reference) to its
+    // place, and the tables: one kernel reads all the small ones over the link, a
+    // large one has its copy command (whose cost is little to it).
+    constexpr uint64_t kLarge = (1ull << 20) / 4;  // values
+    CopySeg* const segs = reinterpret_cast<CopySeg*>(static_cast<char*>(b->h_tab) + tab_bytes);
+    uint32_t nsegs = 0;
+    uint64_t most = std::max<uint64_t>(rw, rs) + 1;
     hipError_t e = hipSuccess;
     const uint64_t kind_off[3] = {d_vw, d_vs, d_vc};
     for (int k = 0; k < 3 && e == hipSuccess; ++k) {
       uint64_t pos = 0;
       for (auto* r : b->reqs[k]) {
         if (r->n && e == hipSuccess) {
-          if (r->dref) {  // device input: ordered after its writer, copied on the device
-            if ((rc = ref_use_on(r->dref, b->si, false))) {
-              b->rc = rc;
-              return b;
-            }
-            e = hipMemcpyAsync(dev + kind_off[k] + 4 * pos, r->dref->ptr, 4 * r->n, hipMemcpyDeviceToDevice, s);
+          if (r->dref && (rc = ref_use_on(r->dref, b->si, false))) {  // ordered after its writer
+            b->rc = rc;
+            return b;
+          }
+          uint32_t* const at = u32(kind_off[k] + 4 * pos);
+          const void* const from = r->dref ? r->dref->ptr : r->pin;
+          if (r->n < kLarge) {
+            segs[nsegs++] = {static_cast<const uint32_t*>(from), at, r->n, nullptr};
+            most = std::max(most, r->n);
           } else {
-            e = hipMemcpyAsync(dev + kind_off[k] + 4 * pos, r->pin, 4 * r->n, hipMemcpyHostToDevice, s);
+            e = hipMemcpyAsync(at, from, 4 * r->n, r->dref ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s);
           }
         }
         pos += r->n;
       }
     }
-    if (e == hipSuccess) e = hipMemcpyAsync(dev + d_rw, tab, 4 * (rw + 1ull), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(dev + d_rs, tab + rw + 1, 4 * (rs + 1ull), hipMemcpyHostToDevice, s);
+    segs[nsegs++] = {tab, u32(d_rw), rw + 1ull, nullptr};
+    segs[nsegs++] = {tab + rw + 1, u32(d_rs), rs + 1ull, nullptr};
+    if (e == hipSuccess && (rc = launch_copy_many(env, segs, nsegs, most))) {
+      b->rc = rc;
+      return b;
+    }
     if (e != hipSuccess) {
       (void)hipGetLastError();
       b->rc = set_error(KA_E_DEVICE, "server: input copy");
@@ -381,10 +396,33 @@ Batch* Server::launch(std::vector<SrvReq*>& take, uint64_t bytes) {
       b->rc = rc;
       return b;
     }
-    // outputs back: the WAH and scan region in one copy, the chain region in another
-    e = hipMemcpyAsync(b->out->p, dev + d_keys, b->o_chain, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess && nc)
-      e = hipMemcpyAsync(static_cast<char*>(b->out->p) + b->o_chain, dev + d_vc, 4 * nc, hipMemcpyDeviceToHost, s);
+    // Outputs back: small ones by one kernel, the index's as long as the device
+    // says they are; else the WAH and scan region in one copy, the chain region in
+    // another.
+    if (out_bytes <= (8ull << 20)) {
+      char* const ho = static_cast<char*>(b->out->p);
+      auto hu32 = [&](uint64_t o) { return reinterpret_cast<uint32_t*>(ho + o); };
+      CopyList l;
+      if (rw) {
+        l.add(u32(d_keys), hu32(b->o_keys), dcap, lens);
+        l.add(u32(d_offs), hu32(b->o_offs), dcap + rw, lens + 1);
+        l.add(u32(d_words), hu32(b->o_words), 2 * nw, lens + 2);
+        l.add(u32(d_ks), hu32(b->o_ks), rw + 1ull);
+        l.add(u32(d_ws), hu32(b->o_ws), rw + 1ull);
+        l.add(u32(d_lens), hu32(b->o_lens), 10);
+        l.add(u32(d_bad), hu32(b->o_bad), rw);
+      }
+      if (ns) l.add(u32(d_scan), hu32(b->o_scan), ns);
+      if (nc) l.add(u32(d_vc), hu32(b->o_chain), nc);
+      if ((rc = launch_copy(env, l))) {
+        b->rc = rc;
+        return b;
+      }
+    } else {
+      e = hipMemcpyAsync(b->out->p, dev + d_keys, b->o_chain, hipMemcpyDeviceToHost, s);
+      if (e == hipSuccess && nc)
+        e = hipMemcpyAsync(static_cast<char*>(b->out->p) + b->o_chain, dev + d_vc, 4 * nc, hipMemcpyDeviceToHost, s);
+    }
     if (e == hipSuccess) {
       b->done = sys->get_event(false);
       e = b->done ? hipEventRecord(b->done, s) : hipErrorOutOfMemory;

@@ -15,6 +15,13 @@ from . import (ka_wah_batch_result, KA_IN, KA_IN_OUT, KA_OUT, KA_PRIV, KA_REF, K
                nd_range, ref, sig, val, values)
 
 
+def _per_request(keys, offs, words, ks: list, ws: list):
+    """(keys, offsets, words) of each request of a batch: slices of the batch's arrays at the lookup-entry and word
+    starts (lists: indexing numpy scalars one by one took most of a small batch's time here)."""
+    return [(keys[k0:k1], offs[k0 + j:k1 + j + 1], words[w0:w1])
+            for j, (k0, k1, w0, w1) in enumerate(zip(ks, ks[1:], ws, ws[1:]))]
+
+
 class Session:
     """One kernel-actor system on device 0 plus its built-in program."""
 
@@ -198,14 +205,10 @@ class Session:
         keys = np.ctypeslib.as_array(res.keys, shape=(max(D, 1),))[:D].copy()
         offs = np.ctypeslib.as_array(res.offsets, shape=(D + nreq,)).copy()
         words = np.ctypeslib.as_array(res.words, shape=(max(W, 1),))[:W].copy()
-        ks = np.ctypeslib.as_array(res.key_start, shape=(nreq + 1,)).copy()
-        ws = np.ctypeslib.as_array(res.word_start, shape=(nreq + 1,)).copy()
+        ks = np.ctypeslib.as_array(res.key_start, shape=(nreq + 1,)).tolist()
+        ws = np.ctypeslib.as_array(res.word_start, shape=(nreq + 1,)).tolist()
         check(lib.ka_wah_batch_result_free(byref(res)), "ka_wah_batch_result_free")
-        out = []
-        for j in range(nreq):
-            k0, k1, w0, w1 = int(ks[j]), int(ks[j + 1]), int(ws[j]), int(ws[j + 1])
-            out.append((keys[k0:k1], offs[k0 + j:k1 + j + 1], words[w0:w1]))
-        return out
+        return _per_request(keys, offs, words, ks, ws)
 
     def stream_handle(self, i: int = 0) -> int:
         s = c_void_p()
@@ -407,11 +410,10 @@ class BatchPlan:
         keys = np.ctypeslib.as_array(res.keys, shape=(max(D, 1),))[:D].copy()
         offs = np.ctypeslib.as_array(res.offsets, shape=(D + nreq,)).copy()
         words = np.ctypeslib.as_array(res.words, shape=(max(W, 1),))[:W].copy()
-        ks = np.ctypeslib.as_array(res.key_start, shape=(nreq + 1,)).copy()
-        ws = np.ctypeslib.as_array(res.word_start, shape=(nreq + 1,)).copy()
+        ks = np.ctypeslib.as_array(res.key_start, shape=(nreq + 1,)).tolist()
+        ws = np.ctypeslib.as_array(res.word_start, shape=(nreq + 1,)).tolist()
         check(lib.ka_wah_batch_result_free(byref(res)), "ka_wah_batch_result_free")
-        return [(keys[ks[j]:ks[j + 1]], offs[ks[j] + j:ks[j + 1] + j + 1], words[ws[j]:ws[j + 1]])
-                for j in range(nreq)]
+        return _per_request(keys, offs, words, ks, ws)
 
     def close(self):
         if self.plan:

@@ -290,3 +290,32 @@ def test_small_requests_of_a_batch(sess, size, variant):
             for g, e in zip(got, oracle.default().wah_index(v[off[j]:off[j + 1]])):
                 np.testing.assert_array_equal(g, e)
         plan.close()
+
+
+@pytest.mark.parametrize("n,bits", [(1, 10), (31_337, 10), (1_030_000, 10), (1_060_000, 10), (300_000, 0)])
+def test_host_outputs_of_every_size(sess, n, bits):
+    """Results copied by a kernel behind the request, and those too large for it, of an index and of a batch."""
+    v = workloads.u32(n, n) & np.uint32((1 << bits) - 1 if bits else 0xFFFFFFFF)
+    for g, e in zip(sess.wah_index(v, value_bits=bits), oracle.default().wah_index(v)):
+        np.testing.assert_array_equal(g, e)
+    if not bits:
+        return
+    off = np.array([0, n // 3, n // 3, n], np.uint32)
+    for j, got in enumerate(sess.wah_batch(v, off, bits)):
+        for g, e in zip(got, oracle.default().wah_index(v[off[j]:off[j + 1]])):
+            np.testing.assert_array_equal(g, e)
+
+
+@pytest.mark.parametrize("n", [40, 70_000, 900_000])
+def test_plan_results_of_every_size(sess, n):
+    """One plan for any batch, host and device values, batches that grow and shrink."""
+    from paper_1709_07781_amd.session import BatchPlan
+    plan = BatchPlan(sess, None, 9, any_batch=(n, 8, 0))
+    for k, m in enumerate((n, n // 2, 0, n)):
+        off = np.array([0, m // 4, m // 4, m], np.uint32)
+        v = workloads.u32(n + k, m) & np.uint32(511)
+        plan.run_batch(sess.upload(v) if k % 2 else v, off)
+        for j, got in enumerate(plan.result()):
+            for g, e in zip(got, oracle.default().wah_index(v[off[j]:off[j + 1]])):
+                np.testing.assert_array_equal(g, e)
+    plan.close()
