@@ -146,7 +146,7 @@ int run_wah_index(LaunchCtx& c) {
   // general path and by this one, 10-bit values: 300 71 / 40, 8192 78 / 50; any uint32: 8192 130 / 67).
   if (n <= kSmallIndexMax) return launch_wah_small(env, values, n, bits, out, opt);
   int rc;
-  opt.cleared = wah_status(env, n);
+  opt.cleared = wah_status(env, n, opt.format);
   if (!opt.cleared.p) return env.fail(KA_E_OOM, "wah_index: scratch");
   uint32_t* sr = static_cast<uint32_t*>(env.scratch(4 * n));
   if (bits >= 1 && bits <= 16) {

@@ -149,7 +149,7 @@ struct EncodeOpts {
 };
 // The encoder's look-back words for n pairs (from env's scratch; p null if
 // that is exhausted), to be zeroed by the sort before it.
-ClearWords wah_status(Env& env, uint64_t n);
+ClearWords wah_status(Env& env, uint64_t n, uint32_t format = 0);
 // WAH encoder over sorted pairs.
 int launch_wah_encode(Env& env, const uint32_t* skeys, const uint32_t* srows, uint64_t n, const IndexOut& out,
                       const EncodeOpts& opt = {});

@@ -216,7 +216,43 @@ __device__ __forceinline__ void upsweep_tile(const SK* __restrict__ keys, uint32
   // more there (measured on 16-bit Zipf keys: 62 -> 42 us; uniform keys 51 ->
   // 44 us).
   uint32_t c0 = 0, ch = 0;
+  // Clustered keys (most work-items' four neighbouring keys share a digit): a
+  // work-item's four are added as one, and the wave's equal digits in one add each.
+  const uint32_t da = (k[0][0] >> shift) & mask, db = (k[0][3] >> shift) & mask;
+  const uint32_t df = (uint32_t)__builtin_amdgcn_readfirstlane((int)da);
+  bool clustered = __popcll(__ballot(da == db)) >= 48 && len == (uint32_t)kTile;  // uniform over the wave
+  if (kRounds < 0)  // not those that sit in the two digits counted in registers
+    clustered = clustered && __popcll(__ballot(da == df || da == 0u)) < 40;
+  if (clustered) {
+#pragma unroll
+    for (int j = 0; j < kUpVecs; ++j) {
+      uint32_t d[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        d[c] = (k[j][c] >> shift) & mask;
+        if (kOrAnd) {
+          kor |= k[j][c];
+          kand &= k[j][c];
+        }
+      }
+      const bool same = d[0] == d[1] && d[0] == d[2] && d[0] == d[3];
+      uint64_t rest = __ballot(same);
+      for (int round = 0; round < 3 && rest; ++round) {
+        const uint32_t first_lane = (uint32_t)__builtin_ctzll(rest);
+        const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d[0], (int)first_lane);
+        const uint64_t eq = __ballot(same && d[0] == d0);
+        if (lane_id() == first_lane) atomicAdd(&s_hist[w][d0], 4u * (uint32_t)__popcll(eq));
+        rest &= ~eq;
+      }
+      if ((rest >> lane_id()) & 1ull)
+        atomicAdd(&s_hist[w][d[0]], 4u);
+      else if (!same)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) atomicAdd(&s_hist[w][d[c]], 1u);
+    }
+  }
   const uint32_t hot = (uint32_t)__builtin_amdgcn_readfirstlane((int)((k[0][0] >> shift) & mask));
+  if (!clustered)
 #pragma unroll
   for (int j = 0; j < kUpVecs; ++j)
 #pragma unroll
@@ -240,7 +276,7 @@ __device__ __forceinline__ void upsweep_tile(const SK* __restrict__ keys, uint32
         kand &= k[j][c];
       }
     }
-  if (kRounds < 0) {
+  if (kRounds < 0 && !clustered) {
     const uint32_t z = wave_sum(c0), h = wave_sum(ch);
     if (lane_id() == 0) {
       if (z) atomicAdd(&s_hist[w][0], z);
@@ -516,6 +552,12 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<kBlock, kItems>& L, cons
   // cheaper there: the batched build's 6-bit passes ran 1.3% slower with the
   // masks.
   const uint64_t mybit = 1ull << lane;
+  // Clustered keys: many lanes that OR one mask are served one by one (6,000,011
+  // clustered 16-bit values: 35 us a pass, 21 with the digits of runs taken by
+  // ballot).  Seen by the wave's first two steps (later ones would hold the
+  // ranking up for their loads), whose first lane's digit then fills a quarter of
+  // the wave or more.
+  bool clustered = false;
   uint32_t rank[kItems];
 #pragma unroll
   for (int i = 0; i < kItems; ++i) {
@@ -527,7 +569,24 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<kBlock, kItems>& L, cons
       const uint64_t b0 = __builtin_amdgcn_ballot_w64(valid && d == 0u);
       const uint64_t b1 = __builtin_amdgcn_ballot_w64(valid && d == 1u);
       peers = d == 0u ? b0 : b1;
-      if (valid && d > 1u) {
+      uint64_t rest = ~0ull;  // lanes left to the masks
+      if (i < 2) {
+        const uint32_t df = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
+        clustered = clustered || (df > 1u && __popcll(__builtin_amdgcn_ballot_w64(d == df)) >= 16);
+      }
+      if (clustered) {  // uniform: two digits, the first lane's and the next one's, by ballot as well
+        const uint32_t df = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
+        const uint64_t bf = __builtin_amdgcn_ballot_w64(valid && d == df);
+        rest = __builtin_amdgcn_ballot_w64(valid && d > 1u) & ~bf;
+        if (d == df) peers = bf;
+        if (rest) {
+          const uint32_t dn = (uint32_t)__builtin_amdgcn_readlane((int)d, (int)__builtin_ctzll(rest));
+          const uint64_t bn = __builtin_amdgcn_ballot_w64(valid && d == dn);
+          if (d == dn) peers = bn;
+          rest &= ~bn;
+        }
+      }
+      if (valid && d > 1u && ((rest >> lane) & 1ull)) {
         __hip_atomic_fetch_or(&dmask[d], mybit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
         peers = __hip_atomic_load(&dmask[d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
         __hip_atomic_store(&dmask[d], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);

@@ -555,24 +555,24 @@ __global__ void k_wah_clear(uint64_t* __restrict__ status, uint32_t ntiles) {
 
 // Work-items of the encoder's work-groups by capacity: tiles small enough for
 // about one per CU.
-uint32_t enc_block(uint64_t n) {
-  return n <= 256ull * 2048 ? 256u : n <= 256ull * 4096 ? 512u : (uint32_t)kEncBlock;
+uint32_t enc_block(uint64_t n, uint32_t format) {
+  return n <= 256ull * 2048 ? 256u : n <= 256ull * 4096 || format != kFmtPaper ? 512u : (uint32_t)kEncBlock;
 }
 
-uint32_t enc_tiles(uint64_t n) {
-  const uint64_t tile = (uint64_t)enc_block(n) * kEncItems;
+uint32_t enc_tiles(uint64_t n, uint32_t format) {
+  const uint64_t tile = (uint64_t)enc_block(n, format) * kEncItems;
   return (uint32_t)((n + tile - 1) / tile);
 }
 
 template <int kBlock, int kFmt, class KeyT>
 int encode_block(Env& env, const KeyT* skeys, const uint32_t* srows, uint32_t n, const IndexOut& out,
                  const EncodeOpts& opt) {
-  const uint32_t ntiles = enc_tiles(n);
+  const uint32_t ntiles = enc_tiles(n, kFmt);
   // The (words, values) chain has no epoch: its own status words, zeroed by the
   // sort before it or here.
   uint64_t* status = opt.cleared.p;
   if (!status) {
-    const ClearWords cw = wah_status(env, n);
+    const ClearWords cw = wah_status(env, n, kFmt);
     if (!cw.p) return env.fail(kErrOom, "wah encoder: look-back status words");
     status = cw.p;
     k_wah_clear<<<dim3((ntiles + 255) / 256), dim3(256), 0, env.stream()>>>(status, ntiles);
@@ -599,7 +599,7 @@ int encode_block(Env& env, const KeyT* skeys, const uint32_t* srows, uint32_t n,
 template <int kFmt, class KeyT>
 int encode_fmt(Env& env, const KeyT* skeys, const uint32_t* srows, uint32_t n, const IndexOut& out,
                const EncodeOpts& opt) {
-  switch (enc_block(n)) {
+  switch (enc_block(n, kFmt)) {
     case 256:
       return encode_block<256, kFmt>(env, skeys, srows, n, out, opt);
     case 512:
@@ -654,9 +654,9 @@ int encode_impl(Env& env, const KeyT* skeys, const uint32_t* srows, uint64_t n, 
 
 }  // namespace
 
-ClearWords wah_status(Env& env, uint64_t n) {
+ClearWords wah_status(Env& env, uint64_t n, uint32_t format) {
   ClearWords cw;
-  cw.count = enc_tiles(n);
+  cw.count = enc_tiles(n, format);
   cw.p = static_cast<uint64_t*>(env.scratch(8ull * kLbSpread * std::max<uint32_t>(cw.count, 1)));
   return cw;
 }
