@@ -82,6 +82,8 @@ struct PassBuffers {
 // narrow-key sort.
 template <class SK, class DK>
 struct PassIoT {
+  // uint32 values in, uint16 keys out: the first pass, whose rows are positions
+  static constexpr bool kPacked = sizeof(SK) == 4 && sizeof(DK) == 2;
   const SK* src_keys;
   const uint32_t* src_rows;
   DK* dst_keys;
@@ -418,11 +420,22 @@ __global__ __launch_bounds__(kPlanBlock) void k_radix_plan(const uint32_t* __res
 // ---------------------------------------------------------------------------------
 // scatter: one tile, ranked in LDS, written to its offsets
 // ---------------------------------------------------------------------------------
-template <int kBlock, int kItems>
+// kPacked (the first pass over values of at most 16 bits): an element is
+// reordered as one word, its key and its place in the tile, from which the row
+// follows; half the LDS traffic and conflicts of (key, row) pairs: 178 -> 162 us
+// for 2^26 Zipf values, 96 -> 86 for a batch of 2.8 10^7.  (512 x 16 work-groups,
+// of which four then fit a CU: 193 us, the ranking's 16 steps are too long.
+// Stores by 32-bit offsets: no change.)
+template <int kBlock, int kItems, bool kPacked = false>
 struct ScatterLds {
   static constexpr int kWaves = kBlock / 64;
   static constexpr int kTile = kBlock * kItems;
-  uint2 kr[kTile];  // reorder buffer: key and row of each element (the rank masks before)
+  static constexpr int kBytes = kPacked ? 4 * kTile : 8 * kTile;
+  static constexpr int kMaskBytes = 8 * kWaves * kRadix;
+  // reorder buffer (the rank masks before)
+  __align__(16) unsigned char kr[kBytes > kMaskBytes ? kBytes : kMaskBytes];
+  __device__ __forceinline__ uint2* pairs() { return reinterpret_cast<uint2*>(kr); }
+  __device__ __forceinline__ uint32_t* words() { return reinterpret_cast<uint32_t*>(kr); }
   uint16_t wcnt[kWaves][kRadix];  // per-wave digit counts, then each wave's start of each digit in the tile
   uint32_t dbase[kRadix];         // global start minus tile-local start
   uint32_t before[kRadix];        // tile rows: digit counts of the tiles before this one
@@ -441,7 +454,10 @@ __device__ __forceinline__ void scatter_load(const IO& io, uint32_t base, uint32
   if (tile_n == (uint32_t)kTile) {  // uniform: every load of a full tile is issued unconditionally
 #pragma unroll
     for (int i = 0; i < kItems; ++i) key[i] = __builtin_nontemporal_load(io.src_keys + base + wbase + i * 64 + lane);
-    if (io.implicit_rows) {
+    if (IO::kPacked) {
+#pragma unroll
+      for (int i = 0; i < kItems; ++i) row[i] = 0u;  // made when written
+    } else if (io.implicit_rows) {
 #pragma unroll
       for (int i = 0; i < kItems; ++i) row[i] = base + wbase + i * 64 + lane - io.row_origin;
     } else {
@@ -471,8 +487,8 @@ struct TileRows {
 
 // Adds the rows' counts to before and from (LDS, zeroed): a wave reads 512
 // bytes of rows at a time.
-template <int kBlock, int kItems, int kBits>
-__device__ __forceinline__ void add_rows(const TileRows& tr, ScatterLds<kBlock, kItems>& L) {
+template <int kBlock, int kBits, class Lds>
+__device__ __forceinline__ void add_rows(const TileRows& tr, Lds& L) {
   constexpr uint32_t kD = 1u << kBits, kWaves = kBlock / 64;
   constexpr uint32_t kLanes = kD / 4, kRowsPer = 64 / kLanes;  // lanes per row, rows per wave and step
   const uint32_t w = threadIdx.x / 64, lane = lane_id();
@@ -514,11 +530,14 @@ __device__ __forceinline__ void add_rows(const TileRows& tr, ScatterLds<kBlock, 
 // threadIdx.x for this tile.  Starts and ends with a barrier.  With kCheck a
 // key at or above 2^check_shift sets *reject to 1.  With kFull the tile is
 // full (tile_n = kBlock * kItems) and no element is checked against tile_n.
+// io.kPacked: no rows are given, an element's row is its position less
+// io.row_origin, `base` the tile's first.
 // With kRows dstart is not used: the starts come from the tile rows, which are
 // read while the keys are on their way and added up beside the ranking.
 template <int kBlock, int kItems, bool kCheck = false, bool kTag = false, int kBits = kRadixBits, bool kFull = false,
           bool kRows = false, class IO>
-__device__ __forceinline__ void scatter_tile(ScatterLds<kBlock, kItems>& L, const IO& io, uint32_t shift,
+__device__ __forceinline__ void scatter_tile(ScatterLds<kBlock, kItems, IO::kPacked>& L, const IO& io, uint32_t base,
+                                             uint32_t shift,
                                              uint32_t tile_n, uint32_t dstart, const uint32_t (&key)[kItems],
                                              const uint32_t (&row)[kItems], uint32_t check_shift = 32,
                                              uint32_t* reject = nullptr, const TileRows& tr = {}) {
@@ -531,13 +550,12 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<kBlock, kItems>& L, cons
   // 8-bit digits: per-wave digit masks, in the reorder buffer (unused until
   // the reorder).
   constexpr bool kMaskRank = kBits == kRadixBits;
-  static_assert(kBlock * kItems >= kWaves * kRadix, "digit masks fit the reorder buffer");
   uint64_t* dmask = reinterpret_cast<uint64_t*>(&L.kr[0]) + w * kRadix;
   if (kMaskRank)
     for (int j = lane; j < kRadix; j += 64) dmask[j] = 0ull;
   if (kRows && tid < kRadix) L.before[tid] = L.from[tid] = 0u;
   __syncthreads();
-  if (kRows) add_rows<kBlock, kItems, kBits>(tr, L);
+  if (kRows) add_rows<kBlock, kBits>(tr, L);
 
   // ---- rank inside the wave: peers = lanes with the same digit ----------------
   // 8-bit digits: digits 0 and 1, the most frequent ones on small values, by
@@ -554,13 +572,12 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<kBlock, kItems>& L, cons
   const uint64_t mybit = 1ull << lane;
   // Clustered keys: many lanes that OR one mask are served one by one (6,000,011
   // clustered 16-bit values: 35 us a pass, 21 with the digits of runs taken by
-  // ballot).  Seen by the wave's first two steps (later ones would hold the
-  // ranking up for their loads), whose first lane's digit then fills a quarter of
-  // the wave or more.
-  bool clustered = false;
+  // ballot).  Seen by the wave's first step, whose first lane's digit then fills
+  // a quarter of the wave or more; a step of theirs takes two digits, its first
+  // lane's and the next one's, by ballot as well.  (Two loops: a branch in every
+  // step of one cost random keys 2% of the pass.)
   uint32_t rank[kItems];
-#pragma unroll
-  for (int i = 0; i < kItems; ++i) {
+  auto rank_step = [&](int i, bool clustered) __attribute__((always_inline)) {
     const bool valid = (kFull || wbase + i * 64 + lane < tile_n);
     const uint32_t d = (key[i] >> shift) & kMask;
     uint32_t r = 0;
@@ -569,15 +586,11 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<kBlock, kItems>& L, cons
       const uint64_t b0 = __builtin_amdgcn_ballot_w64(valid && d == 0u);
       const uint64_t b1 = __builtin_amdgcn_ballot_w64(valid && d == 1u);
       peers = d == 0u ? b0 : b1;
-      uint64_t rest = ~0ull;  // lanes left to the masks
-      if (i < 2) {
-        const uint32_t df = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
-        clustered = clustered || (df > 1u && __popcll(__builtin_amdgcn_ballot_w64(d == df)) >= 16);
-      }
-      if (clustered) {  // uniform: two digits, the first lane's and the next one's, by ballot as well
+      bool masked = valid && d > 1u;
+      if (clustered) {
         const uint32_t df = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
         const uint64_t bf = __builtin_amdgcn_ballot_w64(valid && d == df);
-        rest = __builtin_amdgcn_ballot_w64(valid && d > 1u) & ~bf;
+        uint64_t rest = __builtin_amdgcn_ballot_w64(masked) & ~bf;
         if (d == df) peers = bf;
         if (rest) {
           const uint32_t dn = (uint32_t)__builtin_amdgcn_readlane((int)d, (int)__builtin_ctzll(rest));
@@ -585,8 +598,9 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<kBlock, kItems>& L, cons
           if (d == dn) peers = bn;
           rest &= ~bn;
         }
+        masked = (rest >> lane) & 1ull;
       }
-      if (valid && d > 1u && ((rest >> lane) & 1ull)) {
+      if (masked) {
         __hip_atomic_fetch_or(&dmask[d], mybit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
         peers = __hip_atomic_load(&dmask[d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
         __hip_atomic_store(&dmask[d], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
@@ -608,6 +622,18 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<kBlock, kItems>& L, cons
       r = old + below;
     }
     rank[i] = r;
+  };
+  bool clustered = false;
+  if (kMaskRank) {
+    const uint32_t d0 = (key[0] >> shift) & kMask, df = (uint32_t)__builtin_amdgcn_readfirstlane((int)d0);
+    clustered = df > 1u && __popcll(__builtin_amdgcn_ballot_w64(d0 == df)) >= 16;  // uniform
+  }
+  if (kMaskRank && clustered) {
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) rank_step(i, true);
+  } else {
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) rank_step(i, false);
   }
   if (kCheck) {
     uint32_t over = 0;
@@ -650,7 +676,10 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<kBlock, kItems>& L, cons
     if ((kFull || wbase + i * 64 + lane < tile_n)) {
       const uint32_t d = (key[i] >> shift) & kMask;
       const uint32_t pos = L.wcnt[w][d] + rank[i];
-      L.kr[pos] = make_uint2(key[i], row[i]);
+      if (IO::kPacked)
+        L.words()[pos] = key[i] << 16 | (wbase + i * 64 + lane);  // a key above 16 bits voids the result
+      else
+        L.pairs()[pos] = make_uint2(key[i], row[i]);
     }
   }
   __syncthreads();
@@ -660,11 +689,19 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<kBlock, kItems>& L, cons
   for (int i = 0; i < kItems; ++i) {
     const uint32_t p = i * kBlock + tid;
     if (kFull || p < tile_n) {
-      const uint2 v = L.kr[p];
-      const uint32_t k = v.x;
+      uint32_t k, r;
+      if (IO::kPacked) {
+        const uint32_t v = L.words()[p];
+        k = v >> 16;
+        r = base - io.row_origin + (v & 0xFFFFu);
+      } else {
+        const uint2 v = L.pairs()[p];
+        k = v.x;
+        r = v.y;
+      }
       const uint32_t g = L.dbase[(k >> shift) & kMask] + p;
       io.dst_keys[g] = (std::remove_pointer_t<decltype(io.dst_keys)>)(kTag ? (k & io.key_and) | io.key_or : k);
-      io.dst_rows[g] = v.y;
+      io.dst_rows[g] = r;
     }
   }
   __syncthreads();  // the LDS buffers are free again
@@ -690,9 +727,9 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(PassBuffers buf, const
   uint32_t key[kItems], row[kItems];
   scatter_load<kBlock, kItems>(io, base, tile_n, key, row);
   if (tile_n == (uint32_t)kTile)  // uniform: a full tile checks no element against its length
-    scatter_tile<kBlock, kItems, false, false, kRadixBits, true>(L, io, pass * kRadixBits, tile_n, dstart, key, row);
+    scatter_tile<kBlock, kItems, false, false, kRadixBits, true>(L, io, base, pass * kRadixBits, tile_n, dstart, key, row);
   else
-    scatter_tile<kBlock, kItems>(L, io, pass * kRadixBits, tile_n, dstart, key, row);
+    scatter_tile<kBlock, kItems>(L, io, base, pass * kRadixBits, tile_n, dstart, key, row);
 }
 
 // Scatter of a fixed pass (no plan): keys uint32 or uint16 on either side.
@@ -704,7 +741,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter_fixed(PassIoT<SK, DK> 
                                                                 uint32_t check_shift, uint32_t* __restrict__ reject,
                                                                 const uint64_t* __restrict__ d_n) {
   constexpr int kTile = kBlock * kItems;
-  __shared__ ScatterLds<kBlock, kItems> L;
+  __shared__ ScatterLds<kBlock, kItems, PassIoT<SK, DK>::kPacked> L;
   const uint32_t tile = xcd_tile(blockIdx.x, ntiles);
   const uint32_t base = tile * kTile;
   const uint32_t tile_n = tile_len(tile, kTile, n_cap, d_n);
@@ -713,10 +750,10 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter_fixed(PassIoT<SK, DK> 
   uint32_t key[kItems], row[kItems];
   scatter_load<kBlock, kItems>(io, base, tile_n, key, row);
   if (tile_n == (uint32_t)kTile)  // uniform: a full tile checks no element against its length
-    scatter_tile<kBlock, kItems, kCheck, false, kBits, true>(L, io, shift, tile_n, dstart, key, row, check_shift,
+    scatter_tile<kBlock, kItems, kCheck, false, kBits, true>(L, io, base, shift, tile_n, dstart, key, row, check_shift,
                                                              reject);
   else
-    scatter_tile<kBlock, kItems, kCheck, false, kBits, false>(L, io, shift, tile_n, dstart, key, row, check_shift,
+    scatter_tile<kBlock, kItems, kCheck, false, kBits, false>(L, io, base, shift, tile_n, dstart, key, row, check_shift,
                                                               reject);
 }
 
@@ -759,7 +796,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_rows_scatter(PassIoT<SK, DK> io, 
                                                          uint32_t check_shift, uint32_t* __restrict__ reject,
                                                          const uint64_t* __restrict__ d_n) {
   constexpr int kTile = kBlock * kItems;
-  __shared__ ScatterLds<kBlock, kItems> L;
+  __shared__ ScatterLds<kBlock, kItems, PassIoT<SK, DK>::kPacked> L;
   const uint32_t tile = xcd_tile(blockIdx.x, ntiles);
   const uint32_t base = tile * kTile;
   const uint32_t tile_n = tile_len(tile, kTile, n_cap, d_n);
@@ -768,10 +805,10 @@ __global__ __launch_bounds__(kBlock, 8) void k_rows_scatter(PassIoT<SK, DK> io, 
   scatter_load<kBlock, kItems>(io, base, tile_n, key, row);
   const TileRows tr{rows, ntiles, tile, 0u};
   if (tile_n == (uint32_t)kTile)  // uniform: a full tile checks no element against its length
-    scatter_tile<kBlock, kItems, kCheck, false, kBits, true, true>(L, io, shift, tile_n, 0u, key, row, check_shift,
+    scatter_tile<kBlock, kItems, kCheck, false, kBits, true, true>(L, io, base, shift, tile_n, 0u, key, row, check_shift,
                                                                    reject, tr);
   else
-    scatter_tile<kBlock, kItems, kCheck, false, kBits, false, true>(L, io, shift, tile_n, 0u, key, row, check_shift,
+    scatter_tile<kBlock, kItems, kCheck, false, kBits, false, true>(L, io, base, shift, tile_n, 0u, key, row, check_shift,
                                                                     reject, tr);
 }
 
@@ -829,10 +866,10 @@ __global__ __launch_bounds__(kBlock, 8) void k_rows_plan_scatter(PassBuffers buf
   scatter_load<kBlock, kItems>(io, base, tile_n, key, row);
   const TileRows tr{rows, ntiles, tile, 0u};
   if (tile_n == (uint32_t)kTile)
-    scatter_tile<kBlock, kItems, false, false, kRadixBits, true, true>(L, io, pass * kRadixBits, tile_n, 0u, key, row,
+    scatter_tile<kBlock, kItems, false, false, kRadixBits, true, true>(L, io, base, pass * kRadixBits, tile_n, 0u, key, row,
                                                                        32u, nullptr, tr);
   else
-    scatter_tile<kBlock, kItems, false, false, kRadixBits, false, true>(L, io, pass * kRadixBits, tile_n, 0u, key, row,
+    scatter_tile<kBlock, kItems, false, false, kRadixBits, false, true>(L, io, base, pass * kRadixBits, tile_n, 0u, key, row,
                                                                         32u, nullptr, tr);
 }
 
@@ -1043,7 +1080,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_seg_scatter(PassIoT<SK, DK> io, S
                                                            uint32_t value_bits, uint32_t* __restrict__ bad,
                                                            uint32_t* __restrict__ req_bad) {
   constexpr int kTile = kBlock * kItems;
-  __shared__ ScatterLds<kBlock, kItems> L;
+  __shared__ ScatterLds<kBlock, kItems, PassIoT<SK, DK>::kPacked> L;
   const uint32_t t = xcd_tile(blockIdx.x, sg.ub), j = sg.tile_req[t];
   if (j == ~0u) return;  // uniform over the work-group
   const SegTile s = seg_tile<kTile>(sg.req_off, sg.tile_base, j, t);
@@ -1060,10 +1097,10 @@ __global__ __launch_bounds__(kBlock, 8) void k_seg_scatter(PassIoT<SK, DK> io, S
   uint32_t* const flag = req_bad ? req_bad + j : bad;
   const TileRows tr{sg.rows + ((uint64_t)(t - s.l) << kBits), s.nt, s.l, io.row_origin};
   if (s.len == (uint32_t)kTile)  // uniform: a full tile checks no element against its length
-    scatter_tile<kBlock, kItems, kCheck, kTag, kBits, true, kRows>(L, io, shift, s.len, dstart, key, row, value_bits,
+    scatter_tile<kBlock, kItems, kCheck, kTag, kBits, true, kRows>(L, io, s.base, shift, s.len, dstart, key, row, value_bits,
                                                                    flag, tr);
   else
-    scatter_tile<kBlock, kItems, kCheck, kTag, kBits, false, kRows>(L, io, shift, s.len, dstart, key, row, value_bits,
+    scatter_tile<kBlock, kItems, kCheck, kTag, kBits, false, kRows>(L, io, s.base, shift, s.len, dstart, key, row, value_bits,
                                                                     flag, tr);
 }
 
