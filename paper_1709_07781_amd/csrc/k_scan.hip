@@ -18,10 +18,11 @@
 // tile_base + 4 (r * BLOCK + t), so every global access is a coalesced
 // 16-byte load or store; element order inside the tile is (round, thread, lane
 // of the vector).  The number of rounds R is chosen per launch: 8 (8192
-// elements per tile) up to 2^23 elements, where the look-back's latency
-// dominates, 16 above, where fewer tiles mean fewer look-backs per byte
-// (measured at 2^26: 138 us at 16 rounds, 193 us at 8; at 2^21, 8.7 us at 8
-// and 10.5 us at 16).
+// elements per tile) up to a capacity, where the look-back's latency dominates,
+// 16 above, where fewer tiles mean fewer look-backs per byte.  Scans, us a
+// request with 8 / 16 rounds: 4 10^6 values 21.4 / 21.7, 8 10^6 29.6 / 24.8, 1.6
+// 10^7 43 / 37.  Compactions, whose tile is staged in LDS (32 / 64 KiB: four or
+// two work-groups per CU): 1.6 10^7 42 / 44, 3 10^7 75 / 74, 6 10^7 121 / 110.
 #include "common.hpp"
 
 namespace ka {
@@ -30,8 +31,7 @@ namespace {
 constexpr int kScanBlock = 256;
 constexpr int kWaves = kScanBlock / 64;
 constexpr int kSmallRounds = 8, kLargeRounds = 16;
-constexpr uint64_t kLargeScan = 1ull << 23;  // capacities above this use kLargeRounds
-constexpr int kCompactRounds = 8;            // the compaction stages a tile in LDS (32 KiB)
+constexpr uint64_t kLargeScan = 1ull << 22, kLargeCompact = 1ull << 25;  // capacities above use kLargeRounds
 template <int R>
 constexpr int kTileElems = kScanBlock * R * 4;
 
@@ -197,12 +197,12 @@ __global__ __launch_bounds__(kScanBlock) void k_exclusive_scan_u32(const uint32_
 
 // Kept elements are staged in LDS at their tile-local positions, then copied
 // to out[prefix ...] with consecutive work-items writing consecutive words.
-template <bool kVec>
+template <int R, bool kVec>
 __global__ __launch_bounds__(kScanBlock) void k_compact_nonzero_u32(const uint32_t* __restrict__ in,
                                                                     uint32_t* __restrict__ out, uint64_t n_cap,
                                                                     const uint64_t* __restrict__ d_n,
                                                                     uint64_t* __restrict__ d_out_len, LenHost host, LbArgs lb) {
-  constexpr int R = kCompactRounds, kTile = kTileElems<R>;
+  constexpr int kTile = kTileElems<R>;
   __shared__ uint32_t s_prefix;
   __shared__ uint32_t s_wave[R][kWaves];
   __shared__ __align__(16) uint32_t s_out[kTile];
@@ -290,6 +290,25 @@ int launch_exclusive_scan_groups(Env& env, const uint32_t* words, uint32_t* star
   }
 }
 
+template <int R>
+static int compact_launch(Env& env, const uint32_t* in, uint32_t* out, uint64_t n_cap, const uint64_t* d_n,
+                          uint64_t* d_out_len, LenHost host) {
+  const uint32_t grid = (uint32_t)((n_cap + kTileElems<R> - 1) / kTileElems<R>);
+  LbArgs lb;
+  if (!env.lookback((uint64_t)kLbSpread * grid, &lb))
+    return env.fail(kErrOom, "compact_nonzero_u32: look-back state");
+  const bool vec = (reinterpret_cast<uintptr_t>(in) & 15u) == 0;
+  env.prof_begin("compact_nonzero_u32");
+  if (vec)
+    k_compact_nonzero_u32<R, true><<<dim3(grid), dim3(kScanBlock), 0, env.stream()>>>(in, out, n_cap, d_n, d_out_len, host,
+                                                                                   lb);
+  else
+    k_compact_nonzero_u32<R, false><<<dim3(grid), dim3(kScanBlock), 0, env.stream()>>>(in, out, n_cap, d_n, d_out_len, host,
+                                                                                    lb);
+  env.prof_end("compact_nonzero_u32");
+  return check_launch(env, "compact_nonzero_u32 launch");
+}
+
 int launch_compact_nonzero(Env& env, const uint32_t* in, uint32_t* out, uint64_t n_cap, const uint64_t* d_n,
                            uint64_t* d_out_len, LenHost host) {
   if (!d_out_len) return env.fail(kErrArg, "compact_nonzero_u32: no length slot");
@@ -297,20 +316,8 @@ int launch_compact_nonzero(Env& env, const uint32_t* in, uint32_t* out, uint64_t
   if (!in || !out) return env.fail(kErrArg, "compact_nonzero_u32: null buffer");
   if (n_cap > 0xFFFFFFFFull) return env.fail(kErrArg, "compact_nonzero_u32: more than 2^32-1 elements");
   if (ranges_overlap(in, out, n_cap)) return env.fail(kErrArg, "compact_nonzero_u32: in and out overlap");
-  const uint32_t grid = (uint32_t)((n_cap + kTileElems<kCompactRounds> - 1) / kTileElems<kCompactRounds>);
-  LbArgs lb;
-  if (!env.lookback((uint64_t)kLbSpread * grid, &lb))
-    return env.fail(kErrOom, "compact_nonzero_u32: look-back state");
-  const bool vec = (reinterpret_cast<uintptr_t>(in) & 15u) == 0;
-  env.prof_begin("compact_nonzero_u32");
-  if (vec)
-    k_compact_nonzero_u32<true><<<dim3(grid), dim3(kScanBlock), 0, env.stream()>>>(in, out, n_cap, d_n, d_out_len, host,
-                                                                                   lb);
-  else
-    k_compact_nonzero_u32<false><<<dim3(grid), dim3(kScanBlock), 0, env.stream()>>>(in, out, n_cap, d_n, d_out_len, host,
-                                                                                    lb);
-  env.prof_end("compact_nonzero_u32");
-  return check_launch(env, "compact_nonzero_u32 launch");
+  return n_cap > kLargeCompact ? compact_launch<kLargeRounds>(env, in, out, n_cap, d_n, d_out_len, host)
+                               : compact_launch<kSmallRounds>(env, in, out, n_cap, d_n, d_out_len, host);
 }
 
 }  // namespace ka

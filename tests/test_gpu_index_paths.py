@@ -319,3 +319,22 @@ def test_plan_results_of_every_size(sess, n):
             for g, e in zip(got, oracle.default().wah_index(v[off[j]:off[j + 1]])):
                 np.testing.assert_array_equal(g, e)
     plan.close()
+
+
+@pytest.mark.parametrize("n", [1 << 22, (1 << 22) + 1, 1 << 25, (1 << 25) + 16384 * 3 + 5])
+def test_scan_and_compaction_tile_sizes(sess, impatient, n):
+    """Where the scan's and the compaction's tiles double, with and without the look-back's fallback."""
+    import paper_1709_07781_amd as ka
+    x = workloads.u32(n, n)
+    x[workloads.u32(n + 1, n) % 3 == 0] = 0
+    for s in (sess, impatient):
+        t = s.upload(x)
+        r = s.wrap(t)
+        for kernel, want in (("exclusive_scan_u32", np.concatenate([[0], np.cumsum(x[:-1], dtype=np.uint32)])),
+                             ("compact_nonzero_u32", x[x != 0])):
+            act = s.spawn(kernel, [ka.arg(ka.KA_IN), ka.arg(ka.KA_OUT)])
+            (o,) = s.request(act, ka.ref(r), n_out=1)
+            np.testing.assert_array_equal(s.read(o), want.astype(np.uint32))
+            s.release_ref(o)
+            s.release_actor(act)
+        s.release_ref(r)
