@@ -28,7 +28,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, GB/s
-SORT_KERNELS = ("radix_upsweep0", "radix_plan", "radix_upsweep", "exclusive_scan_u32", "radix_scatter")
+SORT_KERNELS = ("radix_upsweep0", "radix_upsweep", "radix_rows_scan", "exclusive_scan_u32", "radix_scatter")
 ENCODE_KERNELS = ("wah_write",)
 KERNELS = SORT_KERNELS + ENCODE_KERNELS
 # Counter summary of the dominant kernel (FETCH_SIZE / WRITE_SIZE runs of this

@@ -2,28 +2,31 @@
 // and 2 of the WAH index build (Sec. 4.1: tag every value with its input
 // position, then sort by value; Sec. 4.2 sorts with a radix sort).
 //
-// 8-bit digits, up to four passes, each a reduce-then-scan over tiles of
-// kTile keys -- no work-group ever waits for another one:
-//  * k_radix_upsweep (one work-group per tile) counts the tile's digits into a
-//    digit-major table; the pass-0 instance also records the OR and the AND of
-//    the tile's keys, from which k_radix_plan forms the sort plan: a pass whose
-//    digit is the same in every key (equal in the OR and the AND) is the
-//    identity of a stable sort and is skipped, so 16-bit keys cost two passes.
-//  * the exclusive scan of the table (the look-back scan kernel, into a
-//    second table) turns every count into the output position of the tile's
-//    first key with that digit.
-//  * k_radix_scatter (one work-group per tile) ranks its keys by digit inside
+// Up to four passes of 8-bit digits (or, for values known to be below 2^16, one
+// or two of 2 to 8 bits), each a count of every tile and a scatter; no
+// work-group waits for another one:
+//  * the count (one work-group per tile) writes the tile's digit counts as a row
+//    of uint16; the pass-0 instance for any uint32 keys also records the OR and
+//    the AND of the tile's keys, from which the sort plan is formed: a pass whose
+//    digit is the same in every key (equal in the OR and the AND) is the identity
+//    of a stable sort and is skipped, so 16-bit keys cost two passes;
+//  * inputs of few tiles: every scatter work-group adds up the rows before its
+//    own, and all of them for the digits' totals, while its keys are on their
+//    way; more tiles: k_rows_scan first forms the digits' totals and, down every
+//    column, the rows' prefixes;
+//  * the scatter (one work-group per tile) ranks its keys by digit inside
 //    each wave -- the lanes holding the same digit are found by OR-ing each
 //    lane's bit into a per-digit mask in LDS (8-bit digits; digits 0 and 1 by a
 //    ballot each) or with one ballot per digit bit (narrower digits), and a
 //    key's rank is the number of such lanes below it plus the wave's earlier
 //    count of that digit, so equal keys keep their order -- reorders the tile by
-//    digit in LDS and writes each digit's run to its offset from the table,
-//    consecutive work-items writing consecutive addresses.
+//    digit in LDS and writes each digit's run to its place, consecutive
+//    work-items writing consecutive addresses.
 // Tiles are taken in an XCD-aware order (see xcd_tile).
 // The first active pass reads the input (and makes row ids 0..n-1 when no rows
 // are given), later ones read the previous active pass's output, and the last
-// active pass writes the caller's buffers.
+// active pass writes the caller's buffers.  A batch of requests is sorted inside
+// every request (the segmented sort below).
 #include <algorithm>
 #include <cstddef>
 #include <type_traits>
@@ -37,12 +40,6 @@ constexpr int kRadixBits = 8;
 constexpr int kRadix = 1 << kRadixBits;
 constexpr int kPasses = 32 / kRadixBits;
 
-#ifndef KA_SORT_BLOCK
-#define KA_SORT_BLOCK 1024
-#endif
-#ifndef KA_SORT_ITEMS
-#define KA_SORT_ITEMS 8
-#endif
 #ifndef KA_XCD_MAP
 #define KA_XCD_MAP 1
 #endif
@@ -54,16 +51,15 @@ constexpr int kPasses = 32 / kRadixBits;
 struct SortShape {
   int block, items;
 };
-constexpr SortShape kShapes[] = {{KA_SORT_BLOCK, KA_SORT_ITEMS}, {512, 16}, {512, 8}};
+constexpr SortShape kShapes[] = {{1024, 8}, {512, 16}, {512, 8}};
 constexpr int kNumShapes = sizeof(kShapes) / sizeof(kShapes[0]);
 
 }  // namespace
 
-// The sort plan, written by the pass-0 count kernel.
+// The sort plan, written between the first count and the first scatter.
 struct SortPlan {
   uint32_t active;               // bit p: pass p moves data
   uint32_t keys_or;              // OR of all keys
-  uint64_t scan_len[kPasses];    // entries of pass p's table scan (0 when skipped)
 };
 static_assert(sizeof(SortPlan) <= kSortPlanBytes, "plan storage");
 
@@ -155,19 +151,14 @@ __device__ __forceinline__ uint32_t tile_len(uint32_t tile, uint32_t kTile, uint
 }
 
 // ---------------------------------------------------------------------------------
-// upsweep: digit counts of one tile into the digit-major table
+// upsweep: digit counts of one tile
 // ---------------------------------------------------------------------------------
 constexpr int kUpBlock = kRadix;  // one work-item per digit when the counts are written
 
-// table[d * ntiles + tile] = number of keys of the tile with digit d.  The
-// exclusive scan of the table in this digit-major order is, entry by entry,
-// the position in the pass's output of the tile's first key with digit d.
 // All of a work-item's loads are issued before the first key is counted; with
 // kOrAnd the OR and the AND of the tile's keys are written too.
-// The tile is keys[base, base + len); store(d, c) gets digit d's count (the
-// digit-major table: table[d * stride + col], the plan-driven and fixed sorts
-// with stride = tile count and col = tile, the segmented sort in its request's
-// part of the table; the tile-row sorts: rows[tile][d]).
+// The tile is keys[base, base + len); store(d, c) gets digit d's count: rows[tile][d],
+// or the segmented sort's table.
 template <int kUpBlock, int kTile, int kRounds, bool kOrAnd, class SK, class Store>
 __device__ __forceinline__ void upsweep_tile(const SK* __restrict__ keys, uint32_t shift, uint32_t base, uint32_t len,
                                              Store&& store, uint32_t tile, uint32_t* __restrict__ orand,
@@ -322,41 +313,6 @@ __device__ __forceinline__ void clear_words(const ClearWords& cw) {
     for (uint32_t i = blockIdx.x; i < cw.count; i += gridDim.x) cw.p[kLbSpread * i] = 0ull;
 }
 
-// Plan-driven upsweep of pass `pass`; the pass-0 instance also writes the OR
-// and the AND of the tile's keys for the plan.
-template <bool kFirst, int kTile>
-__global__ __launch_bounds__(kUpBlock) void k_radix_upsweep(PassBuffers buf, const SortPlan* __restrict__ plan,
-                                                            uint32_t* __restrict__ table, uint32_t* __restrict__ orand,
-                                                            uint32_t pass, uint32_t n_cap, uint32_t ntiles,
-                                                            const uint64_t* __restrict__ d_n, ClearWords cw) {
-  const uint32_t* keys = buf.keys_in;
-  if (kFirst) clear_words(cw);
-  if (!kFirst) {
-    const uint32_t active = plan->active;
-    if (!((active >> pass) & 1u)) return;  // uniform over the grid
-    keys = pass_io(buf, active, pass).src_keys;
-  }
-  const uint32_t tile = xcd_tile(blockIdx.x, ntiles);
-  upsweep_tile<kUpBlock, kTile, kFirst ? 1 : -1, kFirst>(
-      keys, pass * kRadixBits, tile * kTile, tile_len(tile, kTile, n_cap, d_n),
-      [&](uint32_t d, uint32_t c) { table[(uint64_t)d * ntiles + tile] = c; }, tile, orand);
-}
-
-// Upsweep of a fixed pass (no plan) over uint32 or uint16 keys.  Work-group 0
-// of the first pass clears *reject.
-template <int kTile, int kRounds, class SK>
-__global__ __launch_bounds__(kUpBlock) void k_radix_count(const SK* __restrict__ keys, uint32_t* __restrict__ table,
-                                                          uint32_t shift, uint32_t mask, uint32_t n_cap,
-                                                          uint32_t ntiles, uint32_t* __restrict__ reject,
-                                                          const uint64_t* __restrict__ d_n, ClearWords cw) {
-  clear_words(cw);
-  if (reject && blockIdx.x == 0 && threadIdx.x == 0) *reject = 0u;
-  const uint32_t tile = xcd_tile(blockIdx.x, ntiles);
-  upsweep_tile<kUpBlock, kTile, kRounds, false>(
-      keys, shift, tile * kTile, tile_len(tile, kTile, n_cap, d_n),
-      [&](uint32_t d, uint32_t c) { table[(uint64_t)d * ntiles + tile] = c; }, tile, nullptr, mask);
-}
-
 // Passes that move data: those whose digit is not the same in every key, i.e.
 // differs between the OR and the AND of the keys (all keys equal: one pass
 // still moves them).
@@ -399,24 +355,6 @@ __device__ __forceinline__ void block_or_and(const uint32_t* __restrict__ orand,
   *keys_and = a;
 }
 
-// The sort plan from the OR and the AND of every tile's keys: a pass moves
-// data unless its digit is the same in every key, i.e. the same in the OR and
-// the AND.  Also the length of each pass's table scan: the full table for an
-// active pass, 0 (nothing to scan) for a skipped one.  One work-group.
-constexpr int kPlanBlock = 1024;
-__global__ __launch_bounds__(kPlanBlock) void k_radix_plan(const uint32_t* __restrict__ orand, uint32_t ntiles,
-                                                           SortPlan* __restrict__ plan) {
-  __shared__ uint32_t s_or[kPlanBlock / 64], s_and[kPlanBlock / 64];
-  uint32_t o, a;
-  block_or_and<kPlanBlock>(orand, ntiles, s_or, s_and, &o, &a);
-  if (threadIdx.x == 0) {
-    const uint32_t act = active_passes(o, a);
-    plan->active = act;
-    plan->keys_or = o;
-    for (int p = 0; p < kPasses; ++p) plan->scan_len[p] = ((act >> p) & 1u) ? (uint64_t)ntiles * kRadix : 0u;
-  }
-}
-
 // ---------------------------------------------------------------------------------
 // scatter: one tile, ranked in LDS, written to its offsets
 // ---------------------------------------------------------------------------------
@@ -442,6 +380,16 @@ struct ScatterLds {
   uint32_t from[kRadix];          // and of this one and the later ones
   uint32_t scan[kWaves], scan2[kWaves];
 };
+
+// Where a scatter's starts come from: sums of the rows by every work-group
+// (kSum), whose traffic out of L2 is tiles^2 * digits * 2 bytes, or the rows'
+// prefixes (kScanned), one launch more a pass.
+enum Starts { kGiven, kSum, kScanned };
+// k_rows_scan writes the prefix of every kRowGroup-th row, and a scatter
+// work-group adds the up to three rows after it to that (uint16 loads that
+// arrive behind its keys): at 8192 tiles the scan took 17.2 / 12.6 / 12.0 us with
+// 1 / 4 / 8 rows and the scatters 162 + 176 / 158 + 177 / 167 + 183.
+constexpr uint32_t kRowGroup = 4;
 
 // The tile's keys and rows: wave w owns 64*kItems consecutive elements, lane
 // l the elements w*64*kItems + i*64 + l.
@@ -477,12 +425,12 @@ __device__ __forceinline__ void scatter_load(const IO& io, uint32_t base, uint32
   }
 }
 
-// Where a tile's runs go, from tile rows (see k_rows_count): T rows of counts,
-// this tile's is row `tile`; `origin` is the first position of all.  T = 0: the
-// start of each digit is given instead.
+// Where a tile's runs go, from tile rows (see k_radix_count_fixed): T rows of counts,
+// this tile's is row `tile`; `origin` is the first position of all.
 struct TileRows {
   const uint16_t* rows = nullptr;
   uint32_t T = 0, tile = 0, origin = 0;
+  uint32_t before = 0, total = 0;  // kScanned: of digit threadIdx.x, in the tiles before this one and in all
 };
 
 // Adds the rows' counts to before and from (LDS, zeroed): a wave reads 512
@@ -532,10 +480,10 @@ __device__ __forceinline__ void add_rows(const TileRows& tr, Lds& L) {
 // full (tile_n = kBlock * kItems) and no element is checked against tile_n.
 // io.kPacked: no rows are given, an element's row is its position less
 // io.row_origin, `base` the tile's first.
-// With kRows dstart is not used: the starts come from the tile rows, which are
-// read while the keys are on their way and added up beside the ranking.
+// kStarts (see Starts): kGiven uses dstart; kSum adds up the tile rows while the
+// keys are on their way, beside the ranking; kScanned has the sums in tr.
 template <int kBlock, int kItems, bool kCheck = false, bool kTag = false, int kBits = kRadixBits, bool kFull = false,
-          bool kRows = false, class IO>
+          int kStarts = 0, class IO>
 __device__ __forceinline__ void scatter_tile(ScatterLds<kBlock, kItems, IO::kPacked>& L, const IO& io, uint32_t base,
                                              uint32_t shift,
                                              uint32_t tile_n, uint32_t dstart, const uint32_t (&key)[kItems],
@@ -553,9 +501,15 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<kBlock, kItems, IO::kPac
   uint64_t* dmask = reinterpret_cast<uint64_t*>(&L.kr[0]) + w * kRadix;
   if (kMaskRank)
     for (int j = lane; j < kRadix; j += 64) dmask[j] = 0ull;
-  if (kRows && tid < kRadix) L.before[tid] = L.from[tid] = 0u;
+  if (kStarts == kSum && tid < kRadix) L.before[tid] = L.from[tid] = 0u;
   __syncthreads();
-  if (kRows) add_rows<kBlock, kBits>(tr, L);
+  if (kStarts == kSum) add_rows<kBlock, kBits>(tr, L);
+  uint32_t before = tr.before;
+  if (kStarts == kScanned && tid < (1u << kBits)) {  // the rows between the scanned one and this tile's
+#pragma unroll
+    for (uint32_t r = 0; r + 1 < kRowGroup; ++r)
+      if (r < tr.T) before += tr.rows[(r << kBits) + tid];
+  }
 
   // ---- rank inside the wave: peers = lanes with the same digit ----------------
   // 8-bit digits: digits 0 and 1, the most frequent ones on small values, by
@@ -655,9 +609,13 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<kBlock, kItems, IO::kPac
     }
   }
   uint32_t total;
-  if (kRows) {  // the digits' starts: their totals scanned, then this tile's share of its digit
-    const uint32_t bef = tid < (1u << kBits) ? L.before[tid] : 0u, from = tid < (1u << kBits) ? L.from[tid] : 0u;
-    dstart = tr.origin + bef + block_excl_scan<kBlock>(bef + from, L.scan2, &total);
+  if (kStarts != kGiven) {  // the digits' starts: their totals scanned, then this tile's share of its digit
+    uint32_t bef = before, all = tr.total;
+    if (kStarts == kSum) {
+      bef = tid < (1u << kBits) ? L.before[tid] : 0u;
+      all = bef + (tid < (1u << kBits) ? L.from[tid] : 0u);
+    }
+    dstart = tr.origin + bef + block_excl_scan<kBlock>(all, L.scan2, &total);
   }
   const uint32_t loff = block_excl_scan<kBlock>(tid < kRadix ? tile_count : 0u, L.scan, &total);
   // Each wave's start of each digit in the tile: the digit's tile-local start
@@ -707,73 +665,118 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<kBlock, kItems, IO::kPac
   __syncthreads();  // the LDS buffers are free again
 }
 
-// One work-group per tile.
-template <int kBlock, int kItems>
-__global__ __launch_bounds__(kBlock) void k_radix_scatter(PassBuffers buf, const SortPlan* __restrict__ plan,
-                                                          const uint32_t* __restrict__ table, uint32_t pass,
-                                                          uint32_t n_cap, uint32_t ntiles,
-                                                          const uint64_t* __restrict__ d_n) {
-  constexpr int kTile = kBlock * kItems;
-  __shared__ ScatterLds<kBlock, kItems> L;
-  const uint32_t active = plan->active;
-  if (!((active >> pass) & 1u)) return;
-  const PassIo io = pass_io(buf, active, pass);
-  const uint32_t tile = xcd_tile(blockIdx.x, ntiles);
-  const uint32_t base = tile * kTile;
-  const uint32_t tile_n = tile_len(tile, kTile, n_cap, d_n);
-  if (tile_n == 0) return;  // past a device-resident count
-  // This tile's output position for each digit: loaded first, used last.
-  const uint32_t dstart = threadIdx.x < kRadix ? table[(uint64_t)threadIdx.x * ntiles + tile] : 0u;
-  uint32_t key[kItems], row[kItems];
-  scatter_load<kBlock, kItems>(io, base, tile_n, key, row);
-  if (tile_n == (uint32_t)kTile)  // uniform: a full tile checks no element against its length
-    scatter_tile<kBlock, kItems, false, false, kRadixBits, true>(L, io, base, pass * kRadixBits, tile_n, dstart, key, row);
-  else
-    scatter_tile<kBlock, kItems>(L, io, base, pass * kRadixBits, tile_n, dstart, key, row);
+// ---------------------------------------------------------------------------------
+// the kernels of a pass
+// ---------------------------------------------------------------------------------
+// Column prefixes of the rows: pre[t / kRowGroup][d] = the counts of digit d in
+// the tiles before t, totals[d] those in all T.  Bound by latency: a work-group
+// takes 4 kCols digits, a work-item four of them in a kChunks-th part of the
+// rows -- it adds them up, the sums are scanned over the parts in LDS, and it
+// writes its prefixes, from the rows it holds (the first kHeld) or reads again.
+// With plan a skipped pass leaves at once; with plan_out (the first pass)
+// work-group 0 forms the plan from the tiles' OR and AND.
+// Against a digit-major table (a strided write by every count, a look-back scan
+// of 256 entries per tile, a gather by every scatter), us per request: 4,200,000
+// values of 12 bits, kernels 81.5 -> 75.7, of 31 bits 181.9 -> 173.7 (count 10.0
+// -> 10.1, plan 2.4 -> none, scan 5.0 -> 4.8, scatter 20.9 -> 20.6); 2^25 of 12
+// bits 329.5 -> 319.6; 2^26 of 16 bits 689 -> 686 (counts 51.1 + 42.1 -> 45.2 +
+// 35.6, scan 7.0 -> 12.6, scatters 162.7 + 180.0 -> 158.5 + 177.1).
+template <int kBits, int kCols>
+__global__ __launch_bounds__(1024) void k_rows_scan(const uint16_t* __restrict__ rows, uint32_t T,
+                                                    uint32_t* __restrict__ pre, uint32_t* __restrict__ totals,
+                                                    const SortPlan* __restrict__ plan, uint32_t pass,
+                                                    const uint32_t* __restrict__ orand, SortPlan* __restrict__ plan_out) {
+  constexpr uint32_t kD = 1u << kBits, kChunks = 1024 / kCols, kGroups = kD / 4 / kCols, kHeld = 8;
+  __shared__ uint32_t s_sum[4 * kCols][kChunks];
+  __shared__ uint32_t s_or[16], s_and[16];
+  const uint32_t tid = threadIdx.x, w = tid / 64, lane = lane_id();
+  if (plan && !((plan->active >> pass) & 1u)) return;
+  if (plan_out && blockIdx.x == 0) {
+    uint32_t o, a;
+    block_or_and<1024>(orand, T, s_or, s_and, &o, &a);
+    if (tid == 0) {
+      plan_out->active = active_passes(o, a);
+      plan_out->keys_or = o;
+    }
+  }
+  // work-groups of one XCD take neighbouring digits, so that they share lines in its L2
+  const uint32_t wg = kGroups >= 8 ? blockIdx.x % 8 * (kGroups / 8) + blockIdx.x / 8 : blockIdx.x;
+  const uint32_t c = tid % kCols, chunk = tid / kCols, col = wg * kCols + c;
+  const uint32_t per = (T + kChunks - 1) / kChunks, r0 = min(T, chunk * per), r1 = min(T, r0 + per);
+  const uint2* src = reinterpret_cast<const uint2*>(rows) + col;
+  uint32_t sum[4] = {0, 0, 0, 0};
+  uint2 held[kHeld];
+#pragma unroll
+  for (uint32_t i = 0; i < kHeld; ++i) held[i] = r0 + i < r1 ? src[(uint64_t)(r0 + i) * (kD / 4)] : uint2{0u, 0u};
+#pragma unroll
+  for (uint32_t i = 0; i < kHeld; ++i) {
+    const uint2 v = held[i];
+    sum[0] += v.x & 0xFFFFu, sum[1] += v.x >> 16, sum[2] += v.y & 0xFFFFu, sum[3] += v.y >> 16;
+  }
+#pragma unroll 8
+  for (uint32_t r = r0 + kHeld; r < r1; ++r) {
+    const uint2 v = src[(uint64_t)r * (kD / 4)];
+    sum[0] += v.x & 0xFFFFu, sum[1] += v.x >> 16, sum[2] += v.y & 0xFFFFu, sum[3] += v.y >> 16;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) s_sum[4 * c + i][chunk] = sum[i];
+  __syncthreads();
+  if (w < 4 * kCols) {  // a wave per digit
+    constexpr uint32_t kLane = kChunks / 64;
+    uint32_t x[kLane], t = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < kLane; ++i) {
+      x[i] = t;
+      t += s_sum[w][lane * kLane + i];
+    }
+    const uint32_t inc = wave_incl_scan(t);
+#pragma unroll
+    for (uint32_t i = 0; i < kLane; ++i) s_sum[w][lane * kLane + i] = inc - t + x[i];
+    if (lane == 63) totals[wg * 4 * kCols + w] = inc;
+  }
+  __syncthreads();
+  u32x4 run;
+  run.x = s_sum[4 * c][chunk], run.y = s_sum[4 * c + 1][chunk];
+  run.z = s_sum[4 * c + 2][chunk], run.w = s_sum[4 * c + 3][chunk];
+  u32x4* dst = reinterpret_cast<u32x4*>(pre) + col;
+#pragma unroll
+  for (uint32_t i = 0; i < kHeld; ++i) {
+    const uint2 v = held[i];
+    if (r0 + i < r1 && (r0 + i) % kRowGroup == 0) dst[(uint64_t)((r0 + i) / kRowGroup) * (kD / 4)] = run;
+    run.x += v.x & 0xFFFFu, run.y += v.x >> 16, run.z += v.y & 0xFFFFu, run.w += v.y >> 16;
+  }
+#pragma unroll 8
+  for (uint32_t r = r0 + kHeld; r < r1; ++r) {
+    const uint2 v = src[(uint64_t)r * (kD / 4)];
+    if (r % kRowGroup == 0) dst[(uint64_t)(r / kRowGroup) * (kD / 4)] = run;
+    run.x += v.x & 0xFFFFu, run.y += v.x >> 16, run.z += v.y & 0xFFFFu, run.w += v.y >> 16;
+  }
 }
 
-// Scatter of a fixed pass (no plan): keys uint32 or uint16 on either side.
-// With kCheck (the first pass of the narrow-key sort) a key at or above
-// 2^check_shift sets *reject.
-template <int kBlock, int kItems, bool kCheck, int kBits, class SK, class DK>
-__global__ __launch_bounds__(kBlock) void k_radix_scatter_fixed(PassIoT<SK, DK> io, const uint32_t* __restrict__ table,
-                                                                uint32_t shift, uint32_t n_cap, uint32_t ntiles,
-                                                                uint32_t check_shift, uint32_t* __restrict__ reject,
-                                                                const uint64_t* __restrict__ d_n) {
-  constexpr int kTile = kBlock * kItems;
-  __shared__ ScatterLds<kBlock, kItems, PassIoT<SK, DK>::kPacked> L;
-  const uint32_t tile = xcd_tile(blockIdx.x, ntiles);
-  const uint32_t base = tile * kTile;
-  const uint32_t tile_n = tile_len(tile, kTile, n_cap, d_n);
-  if (tile_n == 0) return;  // past a device-resident count
-  const uint32_t dstart = threadIdx.x < kRadix ? table[(uint64_t)threadIdx.x * ntiles + tile] : 0u;
-  uint32_t key[kItems], row[kItems];
-  scatter_load<kBlock, kItems>(io, base, tile_n, key, row);
-  if (tile_n == (uint32_t)kTile)  // uniform: a full tile checks no element against its length
-    scatter_tile<kBlock, kItems, kCheck, false, kBits, true>(L, io, base, shift, tile_n, dstart, key, row, check_shift,
-                                                             reject);
-  else
-    scatter_tile<kBlock, kItems, kCheck, false, kBits, false>(L, io, base, shift, tile_n, dstart, key, row, check_shift,
-                                                              reject);
-}
+// A pass's rows and, with kScanned, their prefixes and totals.
+struct RowTable {
+  const uint16_t* rows;
+  const uint32_t *pre, *totals;
+};
 
-// ---------------------------------------------------------------------------------
-// tile-row sorts: inputs of few tiles
-// ---------------------------------------------------------------------------------
-// With few tiles the scan of the digit table costs more as a launch of its own
-// than as a sum in every scatter work-group: the counts are kept tile by tile
-// (rows[tile][digit], uint16), and a scatter work-group adds up the rows before
-// its own, and all of them for the digits' totals, while its keys are on their
-// way.  A pass is two launches instead of three, and the tile shrinks with the
-// input so that there are about as many work-groups as CUs.  What bounds it is
-// the rows' traffic, tiles^2 * digits * 2 bytes out of L2, so wide digits stop
-// at 384 tiles and narrow ones at 512 (see row_shape).
+// This tile's part of it.
+template <int kStarts, int kBits>
+__device__ __forceinline__ TileRows tile_rows(const RowTable& rt, uint32_t ntiles, uint32_t tile) {
+  if (kStarts == kSum) return TileRows{rt.rows, ntiles, tile, 0u, 0u, 0u};
+  const uint32_t group = tile / kRowGroup;
+  TileRows tr{rt.rows + ((uint64_t)group * kRowGroup << kBits), tile % kRowGroup, tile, 0u, 0u, 0u};
+  if (threadIdx.x < (1u << kBits)) {
+    tr.before = rt.pre[((uint64_t)group << kBits) + threadIdx.x];
+    tr.total = rt.totals[threadIdx.x];
+  }
+  return tr;
+}
 
 // Counts of one tile into its row.  The first pass also zeroes the encoder's
 // look-back words and *reject, and (kOrAnd) records the OR and AND of the
 // tile's keys.
 template <int kBlock, int kItems, int kRounds, class SK>
-__global__ __launch_bounds__(kBlock) void k_rows_count(const SK* __restrict__ keys, uint16_t* __restrict__ rows,
+__global__ __launch_bounds__(kBlock) void k_radix_count_fixed(const SK* __restrict__ keys, uint16_t* __restrict__ rows,
                                                        uint32_t shift, uint32_t bits, uint32_t n_cap, uint32_t ntiles,
                                                        uint32_t* __restrict__ reject,
                                                        const uint64_t* __restrict__ d_n, ClearWords cw) {
@@ -790,8 +793,8 @@ __global__ __launch_bounds__(kBlock) void k_rows_count(const SK* __restrict__ ke
       tile, nullptr, (1u << bits) - 1u);
 }
 
-template <int kBlock, int kItems, bool kCheck, int kBits, class SK, class DK>
-__global__ __launch_bounds__(kBlock, 8) void k_rows_scatter(PassIoT<SK, DK> io, const uint16_t* __restrict__ rows,
+template <int kBlock, int kItems, int kStarts, bool kCheck, int kBits, class SK, class DK>
+__global__ __launch_bounds__(kBlock, 8) void k_radix_scatter_fixed(PassIoT<SK, DK> io, RowTable rt,
                                                          uint32_t shift, uint32_t n_cap, uint32_t ntiles,
                                                          uint32_t check_shift, uint32_t* __restrict__ reject,
                                                          const uint64_t* __restrict__ d_n) {
@@ -801,22 +804,22 @@ __global__ __launch_bounds__(kBlock, 8) void k_rows_scatter(PassIoT<SK, DK> io, 
   const uint32_t base = tile * kTile;
   const uint32_t tile_n = tile_len(tile, kTile, n_cap, d_n);
   if (tile_n == 0) return;  // past a device-resident count
+  const TileRows tr = tile_rows<kStarts, kBits>(rt, ntiles, tile);
   uint32_t key[kItems], row[kItems];
   scatter_load<kBlock, kItems>(io, base, tile_n, key, row);
-  const TileRows tr{rows, ntiles, tile, 0u};
   if (tile_n == (uint32_t)kTile)  // uniform: a full tile checks no element against its length
-    scatter_tile<kBlock, kItems, kCheck, false, kBits, true, true>(L, io, base, shift, tile_n, 0u, key, row, check_shift,
+    scatter_tile<kBlock, kItems, kCheck, false, kBits, true, kStarts>(L, io, base, shift, tile_n, 0u, key, row, check_shift,
                                                                    reject, tr);
   else
-    scatter_tile<kBlock, kItems, kCheck, false, kBits, false, true>(L, io, base, shift, tile_n, 0u, key, row, check_shift,
+    scatter_tile<kBlock, kItems, kCheck, false, kBits, false, kStarts>(L, io, base, shift, tile_n, 0u, key, row, check_shift,
                                                                     reject, tr);
 }
 
-// Plan-driven passes over uint32 keys (8-bit digits).  The first scatter forms
-// the plan from the tiles' OR and AND in every work-group; work-group 0 stores
-// it for the later launches.
+// Plan-driven passes over uint32 keys (8-bit digits).  With kSum the first
+// scatter forms the plan from the tiles' OR and AND in every work-group, and
+// work-group 0 stores it for the later launches.
 template <bool kFirst, int kBlock, int kItems>
-__global__ __launch_bounds__(kBlock) void k_rows_plan_count(PassBuffers buf, const SortPlan* __restrict__ plan,
+__global__ __launch_bounds__(kBlock) void k_radix_count(PassBuffers buf, const SortPlan* __restrict__ plan,
                                                             uint16_t* __restrict__ rows, uint32_t* __restrict__ orand,
                                                             uint32_t pass, uint32_t n_cap, uint32_t ntiles,
                                                             const uint64_t* __restrict__ d_n, ClearWords cw) {
@@ -835,16 +838,14 @@ __global__ __launch_bounds__(kBlock) void k_rows_plan_count(PassBuffers buf, con
       [&](uint32_t d, uint32_t c) { row[d] = (uint16_t)c; }, tile, orand);
 }
 
-template <bool kFirst, int kBlock, int kItems>
-__global__ __launch_bounds__(kBlock, 8) void k_rows_plan_scatter(PassBuffers buf, SortPlan* __restrict__ plan,
-                                                              const uint16_t* __restrict__ rows,
-                                                              const uint32_t* __restrict__ orand, uint32_t pass,
-                                                              uint32_t n_cap, uint32_t ntiles,
-                                                              const uint64_t* __restrict__ d_n) {
+template <bool kFirst, int kStarts, int kBlock, int kItems>
+__global__ __launch_bounds__(kBlock, kItems <= 8 ? 8 : 4) void k_radix_scatter(
+    PassBuffers buf, SortPlan* __restrict__ plan, RowTable rt, const uint32_t* __restrict__ orand, uint32_t pass,
+    uint32_t n_cap, uint32_t ntiles, const uint64_t* __restrict__ d_n) {
   constexpr int kTile = kBlock * kItems;
   __shared__ ScatterLds<kBlock, kItems> L;
   uint32_t active;
-  if (kFirst) {
+  if (kFirst && kStarts == kSum) {
     uint32_t o, a;
     block_or_and<kBlock>(orand, ntiles, L.scan, reinterpret_cast<uint32_t*>(&L.kr[0]), &o, &a);
     active = active_passes(o, a);
@@ -862,80 +863,20 @@ __global__ __launch_bounds__(kBlock, 8) void k_rows_plan_scatter(PassBuffers buf
   const uint32_t base = tile * kTile;
   const uint32_t tile_n = tile_len(tile, kTile, n_cap, d_n);
   if (tile_n == 0) return;  // past a device-resident count
+  const TileRows tr = tile_rows<kStarts, kRadixBits>(rt, ntiles, tile);
   uint32_t key[kItems], row[kItems];
   scatter_load<kBlock, kItems>(io, base, tile_n, key, row);
-  const TileRows tr{rows, ntiles, tile, 0u};
   if (tile_n == (uint32_t)kTile)
-    scatter_tile<kBlock, kItems, false, false, kRadixBits, true, true>(L, io, base, pass * kRadixBits, tile_n, 0u, key, row,
+    scatter_tile<kBlock, kItems, false, false, kRadixBits, true, kStarts>(L, io, base, pass * kRadixBits, tile_n, 0u, key, row,
                                                                        32u, nullptr, tr);
   else
-    scatter_tile<kBlock, kItems, false, false, kRadixBits, false, true>(L, io, base, pass * kRadixBits, tile_n, 0u, key, row,
+    scatter_tile<kBlock, kItems, false, false, kRadixBits, false, kStarts>(L, io, base, pass * kRadixBits, tile_n, 0u, key, row,
                                                                         32u, nullptr, tr);
 }
 
 }  // namespace
 
 namespace {
-
-template <int kBlock, int kItems>
-int sort_with_shape(Env& env, const uint32_t* keys, const uint32_t* rows, uint32_t* skeys, uint32_t* srows,
-                    uint64_t n, const uint64_t* d_n, ClearWords cw) {
-  constexpr int kTile = kBlock * kItems;
-  SortPlan* plan = reinterpret_cast<SortPlan*>(env.arena()->plan);
-  const uint32_t ntiles = (uint32_t)((n + kTile - 1) / kTile);
-  const uint32_t nn = (uint32_t)n;
-
-  PassBuffers buf;
-  buf.keys_in = keys;
-  buf.rows_in = rows;
-  buf.keys_a = skeys;
-  buf.rows_a = srows;
-  buf.keys_b = static_cast<uint32_t*>(env.scratch(n * 4));
-  buf.rows_b = static_cast<uint32_t*>(env.scratch(n * 4));
-  uint32_t* table = static_cast<uint32_t*>(env.scratch((uint64_t)ntiles * kRadix * 4));
-  uint32_t* offs = static_cast<uint32_t*>(env.scratch((uint64_t)ntiles * kRadix * 4));
-  uint32_t* orand = static_cast<uint32_t*>(env.scratch((uint64_t)ntiles * 2 * 4));
-  if (!buf.keys_b || !buf.rows_b || !table || !offs || !orand)
-    return env.fail(kErrOom, "radix_sort: scratch buffers");
-  // One work-group per tile.  (Grid-stride versions with occupancy-sized
-  // grids made skipped passes cheaper but active scatters 50% slower: the two
-  // work-groups of a CU then run their phases in step instead of interleaved.)
-  const uint32_t g_up0 = ntiles, g_up = ntiles, g_sc = ntiles;
-  for (uint32_t pass = 0; pass < (uint32_t)kPasses; ++pass) {
-    if (pass == 0) {
-      env.prof_begin("radix_upsweep0");
-      k_radix_upsweep<true, kTile><<<dim3(g_up0), dim3(kUpBlock), 0, env.stream()>>>(buf, plan, table, orand, pass,
-                                                                                      nn, ntiles, d_n, cw);
-      env.prof_end("radix_upsweep0");
-      int rc = check_launch(env, "radix_upsweep launch");
-      if (rc) return rc;
-      env.prof_begin("radix_plan");
-      k_radix_plan<<<dim3(1), dim3(kPlanBlock), 0, env.stream()>>>(orand, ntiles, plan);
-      env.prof_end("radix_plan");
-      rc = check_launch(env, "radix_plan launch");
-      if (rc) return rc;
-    } else {
-      env.prof_begin("radix_upsweep");
-      k_radix_upsweep<false, kTile><<<dim3(g_up), dim3(kUpBlock), 0, env.stream()>>>(buf, plan, table, orand,
-                                                                                       pass, nn, ntiles, d_n, cw);
-      env.prof_end("radix_upsweep");
-      int rc = check_launch(env, "radix_upsweep launch");
-      if (rc) return rc;
-    }
-    // Offsets: exclusive scan of the digit-major table into offs (the scan's
-    // input and output must not overlap); the plan gives a skipped pass a
-    // scan of length 0.
-    int rc = launch_exclusive_scan(env, table, offs, (uint64_t)ntiles * kRadix, &plan->scan_len[pass]);
-    if (rc) return rc;
-    env.prof_begin("radix_scatter");
-    k_radix_scatter<kBlock, kItems><<<dim3(g_sc), dim3(kBlock), 0, env.stream()>>>(
-        buf, static_cast<const SortPlan*>(plan), offs, pass, nn, ntiles, d_n);
-    env.prof_end("radix_scatter");
-    rc = check_launch(env, "radix_scatter launch");
-    if (rc) return rc;
-  }
-  return kOk;
-}
 
 // ---------------------------------------------------------------------------------
 // the segmented sort: a batch of requests, keys sorted inside each request
@@ -950,7 +891,7 @@ int sort_with_shape(Env& env, const uint32_t* keys, const uint32_t* rows, uint32
 //  * as a table, request j's at 256 tile_base[j] + d ntiles_j + l: scanned in
 //    that order, each entry is the position in the batch of the tile's first
 //    key with digit d, and no key leaves its request; or
-//  * in batches of few tiles as rows (see k_rows_count), of which a tile sums
+//  * in batches of few tiles as rows (see k_radix_count_fixed), of which a tile sums
 //    its own request's.
 // Rows are made relative to the request's first position; the last pass writes
 // the key tagged with its request (j << value_bits | key), which is what the
@@ -1095,12 +1036,12 @@ __global__ __launch_bounds__(kBlock, 8) void k_seg_scatter(PassIoT<SK, DK> io, S
   uint32_t key[kItems], row[kItems];
   scatter_load<kBlock, kItems>(io, s.base, s.len, key, row);
   uint32_t* const flag = req_bad ? req_bad + j : bad;
-  const TileRows tr{sg.rows + ((uint64_t)(t - s.l) << kBits), s.nt, s.l, io.row_origin};
+  const TileRows tr{sg.rows + ((uint64_t)(t - s.l) << kBits), s.nt, s.l, io.row_origin, 0u, 0u};
   if (s.len == (uint32_t)kTile)  // uniform: a full tile checks no element against its length
-    scatter_tile<kBlock, kItems, kCheck, kTag, kBits, true, kRows>(L, io, s.base, shift, s.len, dstart, key, row, value_bits,
+    scatter_tile<kBlock, kItems, kCheck, kTag, kBits, true, kRows ? kSum : kGiven>(L, io, s.base, shift, s.len, dstart, key, row, value_bits,
                                                                    flag, tr);
   else
-    scatter_tile<kBlock, kItems, kCheck, kTag, kBits, false, kRows>(L, io, s.base, shift, s.len, dstart, key, row, value_bits,
+    scatter_tile<kBlock, kItems, kCheck, kTag, kBits, false, kRows ? kSum : kGiven>(L, io, s.base, shift, s.len, dstart, key, row, value_bits,
                                                                     flag, tr);
 }
 
@@ -1132,104 +1073,73 @@ DigitSplit digit_split(uint32_t value_bits, bool even) {
   return d;
 }
 
-// Launch of a fixed-pass scatter for a digit width known at run time.
-template <int kBits, int kBlock, int kItems, bool kCheck, class SK, class DK>
-void scatter_fixed_bits(Env& env, uint32_t grid, const PassIoT<SK, DK>& io, const uint32_t* offs, uint32_t shift,
-                        uint32_t nn, uint32_t ntiles, uint32_t check_shift, uint32_t* reject, const uint64_t* d_n) {
-  k_radix_scatter_fixed<kBlock, kItems, kCheck, kBits><<<dim3(grid), dim3(kBlock), 0, env.stream()>>>(
-      io, offs, shift, nn, ntiles, check_shift, reject, d_n);
-}
+// Scratch of a pass's rows; the prefixes too if they are scanned.
+struct RowScratch {
+  uint16_t* rows = nullptr;
+  uint32_t *pre = nullptr, *totals = nullptr;
+  bool ok = false;
+  RowScratch(Env& env, uint32_t ntiles, bool scanned) {
+    rows = static_cast<uint16_t*>(env.scratch((uint64_t)ntiles * kRadix * 2));
+    if (scanned) {
+      pre = static_cast<uint32_t*>(env.scratch(((uint64_t)ntiles + kRowGroup - 1) / kRowGroup * kRadix * 4));
+      totals = static_cast<uint32_t*>(env.scratch(kRadix * 4));
+    }
+    ok = rows && (!scanned || (pre && totals));
+  }
+  RowTable table() const { return {rows, pre, totals}; }
+};
 
-template <int kBlock, int kItems, bool kCheck, class SK, class DK>
-void scatter_fixed(Env& env, uint32_t bits, uint32_t grid, const PassIoT<SK, DK>& io, const uint32_t* offs,
-                   uint32_t shift, uint32_t nn, uint32_t ntiles, uint32_t check_shift, uint32_t* reject,
-                   const uint64_t* d_n) {
+// Beyond 2048 tiles a work-group takes 4 digits instead of 16 (4096 tiles of
+// 6-bit digits 8.9 -> 7.6 us, 8192 of 8-bit ones 17.7 -> 12.0; the same at 2048).
+int scan_rows(Env& env, const RowScratch& rs, uint32_t bits, uint32_t ntiles, const SortPlan* plan, uint32_t pass,
+              const uint32_t* orand, SortPlan* plan_out) {
+  env.prof_begin("radix_rows_scan");
+#define KA_ROWS_SCAN(B, C) \
+  k_rows_scan<B, C><<<dim3((1u << B) / 4 / C), dim3(1024), 0, env.stream()>>>(rs.rows, ntiles, rs.pre, \
+                                                                              rs.totals, plan, pass, orand, plan_out)
   switch (bits) {
     case 2:
-      return scatter_fixed_bits<2, kBlock, kItems, kCheck>(env, grid, io, offs, shift, nn, ntiles, check_shift, reject,
-                                                            d_n);
+      KA_ROWS_SCAN(2, 1);
+      break;
     case 4:
-      return scatter_fixed_bits<4, kBlock, kItems, kCheck>(env, grid, io, offs, shift, nn, ntiles, check_shift, reject,
-                                                            d_n);
+      KA_ROWS_SCAN(4, 4);
+      break;
     case 6:
-      return scatter_fixed_bits<6, kBlock, kItems, kCheck>(env, grid, io, offs, shift, nn, ntiles, check_shift, reject,
-                                                            d_n);
+      if (ntiles <= 2048)
+        KA_ROWS_SCAN(6, 4);
+      else
+        KA_ROWS_SCAN(6, 1);
+      break;
     default:
-      return scatter_fixed_bits<8, kBlock, kItems, kCheck>(env, grid, io, offs, shift, nn, ntiles, check_shift, reject,
-                                                            d_n);
+      if (ntiles <= 2048)
+        KA_ROWS_SCAN(8, 4);
+      else
+        KA_ROWS_SCAN(8, 1);
+      break;
   }
+#undef KA_ROWS_SCAN
+  env.prof_end("radix_rows_scan");
+  return check_launch(env, "radix_rows_scan launch");
 }
 
-// The narrow-key sort: keys below 2^value_bits, value_bits <= 16, rows
-// 0..n-1.  ceil(value_bits / 8) fixed passes (no plan, no skipped launches)
-// with the even split of digit_split; from the first pass on the keys are
-// stored as uint16 (6 bytes per pair instead of 8).  The first pass flags a
-// key at or above 2^value_bits in *reject (cleared by its upsweep); the sort's
-// output is then unspecified.
-template <int kBlock, int kItems>
-int sort16_with_shape(Env& env, const uint32_t* keys, uint16_t* skeys, uint32_t* srows, uint64_t n,
-                      uint32_t value_bits, uint32_t* reject, const uint64_t* d_n, ClearWords cw) {
-  constexpr int kTile = kBlock * kItems;
-  const uint32_t ntiles = (uint32_t)((n + kTile - 1) / kTile);
-  const uint32_t nn = (uint32_t)n;
-  const DigitSplit ds = digit_split(value_bits, true);
-  const uint32_t passes = ds.passes;
-  uint16_t* kb = nullptr;
-  uint32_t* rb = nullptr;
-  if (passes > 1) {
-    kb = static_cast<uint16_t*>(env.scratch(n * 2));
-    rb = static_cast<uint32_t*>(env.scratch(n * 4));
-    if (!kb || !rb) return env.fail(kErrOom, "radix_sort16: scratch buffers");
-  }
-  uint32_t* table = static_cast<uint32_t*>(env.scratch((uint64_t)ntiles * kRadix * 4));
-  uint32_t* offs = static_cast<uint32_t*>(env.scratch((uint64_t)ntiles * kRadix * 4));
-  if (!table || !offs) return env.fail(kErrOom, "radix_sort16: digit tables");
-  const uint64_t tlen = (uint64_t)ntiles * kRadix;
-  int rc;
-  // pass 0: uint32 values in, uint16 keys out
-  env.prof_begin("radix_upsweep0");
-  k_radix_count<kTile, 1, uint32_t><<<dim3(ntiles), dim3(kUpBlock), 0, env.stream()>>>(
-      keys, table, ds.shift[0], (1u << ds.bits[0]) - 1u, nn, ntiles, reject, d_n, cw);
-  env.prof_end("radix_upsweep0");
-  if ((rc = check_launch(env, "radix_count launch"))) return rc;
-  if ((rc = launch_exclusive_scan(env, table, offs, tlen, nullptr))) return rc;
-  PassIoT<uint32_t, uint16_t> io0{keys, nullptr, passes > 1 ? kb : skeys, passes > 1 ? rb : srows, true};
-  env.prof_begin("radix_scatter");
-  scatter_fixed<kBlock, kItems, true>(env, ds.bits[0], ntiles, io0, offs, ds.shift[0], nn, ntiles, value_bits, reject,
-                                      d_n);
-  env.prof_end("radix_scatter");
-  if ((rc = check_launch(env, "radix_scatter launch"))) return rc;
-  if (passes == 1) return kOk;
-  // pass 1: uint16 keys in and out
-  env.prof_begin("radix_upsweep");
-  k_radix_count<kTile, -1, uint16_t><<<dim3(ntiles), dim3(kUpBlock), 0, env.stream()>>>(
-      kb, table, ds.shift[1], (1u << ds.bits[1]) - 1u, nn, ntiles, nullptr, d_n, ClearWords{});
-  env.prof_end("radix_upsweep");
-  if ((rc = check_launch(env, "radix_count launch"))) return rc;
-  if ((rc = launch_exclusive_scan(env, table, offs, tlen, nullptr))) return rc;
-  PassIoT<uint16_t, uint16_t> io1{kb, rb, skeys, srows, false};
-  env.prof_begin("radix_scatter");
-  scatter_fixed<kBlock, kItems, false>(env, ds.bits[1], ntiles, io1, offs, ds.shift[1], nn, ntiles, 32u, nullptr,
-                                       d_n);
-  env.prof_end("radix_scatter");
-  return check_launch(env, "radix_scatter launch");
-}
-
-// The narrow-key sort in tile rows (two launches a pass).
-template <int kBlock, int kItems, bool kCheck, class SK, class DK>
-int rows_pass16(Env& env, const PassIoT<SK, DK>& io, uint16_t* rows, uint32_t shift, uint32_t bits, uint32_t nn,
+// One pass of the narrow-key sort.  A scanned sort's counts come from 256
+// work-items a tile: they stream, where those of few tiles wait.
+template <int kBlock, int kItems, int kStarts, bool kCheck, class SK, class DK>
+int rows_pass16(Env& env, const PassIoT<SK, DK>& io, const RowScratch& rs, uint32_t shift, uint32_t bits, uint32_t nn,
                 uint32_t ntiles, uint32_t check_shift, uint32_t* reject, const uint64_t* d_n, ClearWords cw) {
+  constexpr int kCount = kStarts == kScanned ? 256 : kBlock;
   const dim3 g(ntiles), b(kBlock);
   env.prof_begin(kCheck ? "radix_upsweep0" : "radix_upsweep");
-  k_rows_count<kBlock, kItems, kCheck ? 1 : -1, SK>
-      <<<g, b, 0, env.stream()>>>(io.src_keys, rows, shift, bits, nn, ntiles, reject, d_n, cw);
+  k_radix_count_fixed<kCount, kBlock * kItems / kCount, kCheck ? 1 : -1, SK>
+      <<<g, dim3(kCount), 0, env.stream()>>>(io.src_keys, rs.rows, shift, bits, nn, ntiles, reject, d_n, cw);
   env.prof_end(kCheck ? "radix_upsweep0" : "radix_upsweep");
   int rc = check_launch(env, "radix_count launch");
   if (rc) return rc;
+  if (kStarts == kScanned && (rc = scan_rows(env, rs, bits, ntiles, nullptr, 0, nullptr, nullptr))) return rc;
   env.prof_begin("radix_scatter");
-#define KA_ROWS_SCATTER(B)                                 \
-  k_rows_scatter<kBlock, kItems, kCheck, B, SK, DK>        \
-      <<<g, b, 0, env.stream()>>>(io, rows, shift, nn, ntiles, check_shift, reject, d_n)
+#define KA_ROWS_SCATTER(B)                                     \
+  k_radix_scatter_fixed<kBlock, kItems, kStarts, kCheck, B, SK, DK>   \
+      <<<g, b, 0, env.stream()>>>(io, rs.table(), shift, nn, ntiles, check_shift, reject, d_n)
   switch (bits) {
     case 2:
       KA_ROWS_SCATTER(2);
@@ -1249,7 +1159,13 @@ int rows_pass16(Env& env, const PassIoT<SK, DK>& io, uint16_t* rows, uint32_t sh
   return check_launch(env, "radix_scatter launch");
 }
 
-template <int kBlock, int kItems>
+// The narrow-key sort: keys below 2^value_bits, value_bits <= 16, rows
+// 0..n-1.  ceil(value_bits / 8) fixed passes (no plan, no skipped launches)
+// with the even split of digit_split; from the first pass on the keys are
+// stored as uint16 (6 bytes per pair instead of 8).  The first pass flags a
+// key at or above 2^value_bits in *reject (cleared by its count); the sort's
+// output is then unspecified.
+template <int kBlock, int kItems, int kStarts>
 int rows_sort16(Env& env, const uint32_t* keys, uint16_t* skeys, uint32_t* srows, uint64_t n, uint32_t value_bits,
                 uint32_t* reject, const uint64_t* d_n, ClearWords cw) {
   constexpr int kTile = kBlock * kItems;
@@ -1262,22 +1178,22 @@ int rows_sort16(Env& env, const uint32_t* keys, uint16_t* skeys, uint32_t* srows
     rb = static_cast<uint32_t*>(env.scratch(n * 4));
     if (!kb || !rb) return env.fail(kErrOom, "radix_sort16: scratch buffers");
   }
-  uint16_t* rows = static_cast<uint16_t*>(env.scratch((uint64_t)ntiles * kRadix * 2));
-  if (!rows) return env.fail(kErrOom, "radix_sort16: digit rows");
+  const RowScratch rs(env, ntiles, kStarts == kScanned);
+  if (!rs.ok) return env.fail(kErrOom, "radix_sort16: digit rows");
   PassIoT<uint32_t, uint16_t> io0{keys, nullptr, ds.passes > 1 ? kb : skeys, ds.passes > 1 ? rb : srows, true};
-  int rc = rows_pass16<kBlock, kItems, true>(env, io0, rows, ds.shift[0], ds.bits[0], nn, ntiles, value_bits, reject,
-                                             d_n, cw);
+  int rc = rows_pass16<kBlock, kItems, kStarts, true>(env, io0, rs, ds.shift[0], ds.bits[0], nn, ntiles, value_bits,
+                                                      reject, d_n, cw);
   if (rc || ds.passes == 1) return rc;
   PassIoT<uint16_t, uint16_t> io1{kb, rb, skeys, srows, false};
-  return rows_pass16<kBlock, kItems, false>(env, io1, rows, ds.shift[1], ds.bits[1], nn, ntiles, 32u, nullptr, d_n,
-                                            ClearWords{});
+  return rows_pass16<kBlock, kItems, kStarts, false>(env, io1, rs, ds.shift[1], ds.bits[1], nn, ntiles, 32u, nullptr,
+                                                     d_n, ClearWords{});
 }
 
-// The plan-driven sort in tile rows.
-template <int kBlock, int kItems>
+// The plan-driven sort of uint32 keys.
+template <int kBlock, int kItems, int kStarts>
 int rows_sort32(Env& env, const uint32_t* keys, const uint32_t* rows_in, uint32_t* skeys, uint32_t* srows, uint64_t n,
                 const uint64_t* d_n, ClearWords cw) {
-  constexpr int kTile = kBlock * kItems;
+  constexpr int kTile = kBlock * kItems, kCount = kStarts == kScanned ? 256 : kBlock;
   SortPlan* plan = reinterpret_cast<SortPlan*>(env.arena()->plan);
   const uint32_t ntiles = (uint32_t)((n + kTile - 1) / kTile), nn = (uint32_t)n;
   PassBuffers buf;
@@ -1287,43 +1203,47 @@ int rows_sort32(Env& env, const uint32_t* keys, const uint32_t* rows_in, uint32_
   buf.rows_a = srows;
   buf.keys_b = static_cast<uint32_t*>(env.scratch(n * 4));
   buf.rows_b = static_cast<uint32_t*>(env.scratch(n * 4));
-  uint16_t* rows = static_cast<uint16_t*>(env.scratch((uint64_t)ntiles * kRadix * 2));
   uint32_t* orand = static_cast<uint32_t*>(env.scratch((uint64_t)ntiles * 2 * 4));
-  if (!buf.keys_b || !buf.rows_b || !rows || !orand) return env.fail(kErrOom, "radix_sort: scratch buffers");
-  const dim3 g(ntiles), b(kBlock);
+  const RowScratch rs(env, ntiles, kStarts == kScanned);
+  if (!buf.keys_b || !buf.rows_b || !orand || !rs.ok) return env.fail(kErrOom, "radix_sort: scratch buffers");
+  const dim3 g(ntiles), b(kBlock), bc(kCount);
   for (uint32_t pass = 0; pass < (uint32_t)kPasses; ++pass) {
     const char* name = pass ? "radix_upsweep" : "radix_upsweep0";
     env.prof_begin(name);
     if (pass == 0)
-      k_rows_plan_count<true, kBlock, kItems><<<g, b, 0, env.stream()>>>(buf, plan, rows, orand, pass, nn, ntiles, d_n,
-                                                                         cw);
+      k_radix_count<true, kCount, kTile / kCount><<<g, bc, 0, env.stream()>>>(buf, plan, rs.rows, orand, pass, nn,
+                                                                                  ntiles, d_n, cw);
     else
-      k_rows_plan_count<false, kBlock, kItems><<<g, b, 0, env.stream()>>>(buf, plan, rows, orand, pass, nn, ntiles,
-                                                                          d_n, cw);
+      k_radix_count<false, kCount, kTile / kCount><<<g, bc, 0, env.stream()>>>(buf, plan, rs.rows, orand, pass, nn,
+                                                                                   ntiles, d_n, cw);
     env.prof_end(name);
     int rc = check_launch(env, "radix_upsweep launch");
     if (rc) return rc;
+    if (kStarts == kScanned &&
+        (rc = scan_rows(env, rs, kRadixBits, ntiles, pass ? plan : nullptr, pass, orand, pass ? nullptr : plan)))
+      return rc;
     env.prof_begin("radix_scatter");
     if (pass == 0)
-      k_rows_plan_scatter<true, kBlock, kItems><<<g, b, 0, env.stream()>>>(buf, plan, rows, orand, pass, nn, ntiles,
-                                                                           d_n);
+      k_radix_scatter<true, kStarts, kBlock, kItems><<<g, b, 0, env.stream()>>>(buf, plan, rs.table(), orand, pass,
+                                                                                    nn, ntiles, d_n);
     else
-      k_rows_plan_scatter<false, kBlock, kItems><<<g, b, 0, env.stream()>>>(buf, plan, rows, orand, pass, nn, ntiles,
-                                                                            d_n);
+      k_radix_scatter<false, kStarts, kBlock, kItems><<<g, b, 0, env.stream()>>>(buf, plan, rs.table(), orand, pass,
+                                                                                     nn, ntiles, d_n);
     env.prof_end("radix_scatter");
     if ((rc = check_launch(env, "radix_scatter launch"))) return rc;
   }
   return kOk;
 }
 
-// Tile shape of the tile-row sorts by capacity: about one tile per CU, from
-// 1024 keys up; kNone: too many tiles.  An index request, us, by the scanned
-// table / by tile rows: 12-bit values (6-bit digits) 65536 89 / 72 and 2^20 96 /
-// 81 (both before the lengths came to the host by themselves), 3M 82 / 72, 2^22 85
-// / 77, 5M 97 / 98, 6M 101 / 103; 16-bit (8-bit digits) 65536 95 / 72, 3M 88 / 84,
-// 2^22 91 / 94; any uint32 65536 142 / 93, 3M 162 / 154, 2^22 184 / 209.
+// Tile shape by capacity: about one tile per CU, from 1024 keys up; kNone: the
+// rows are scanned.  A scan is two launches and 4 us a pass (three or more a
+// request), sums by every tile grow with the square of their number.  An index
+// request, us, scanned / summed: 12-bit values (6-bit digits) 2,000,000 63 / 56,
+// 3,100,000 74 / 72, 4,100,000 77 / 75, 5,242,880 93 / 97; 16-bit (8-bit digits)
+// 2,000,000 67 / 64, 3,100,000 83 / 84, 4,194,304 87 / 94; any uint32 2,000,000
+// 125 / 120, 2,500,000 151 / 149, 3,100,000 152 / 157, 4,194,304 161 / 178.
 enum class RowShape { kNone, k1024, k2048, k4096, k8192 };
-constexpr uint64_t row_tiles_max(uint32_t bits) { return bits > 6 ? 384 : 512; }
+constexpr uint64_t row_tiles_max(uint32_t bits) { return bits > 6 ? 352 : 512; }
 RowShape row_shape(uint64_t n, uint32_t bits) {
   if (n <= 256ull * 1024) return RowShape::k1024;
   if (n <= 256ull * 2048) return RowShape::k2048;
@@ -1471,17 +1391,17 @@ int launch_radix_sort_rows16(Env& env, const uint32_t* keys, uint16_t* skeys, ui
   if (n >= (1ull << 31)) return env.fail(kErrArg, "radix_sort16: n must be below 2^31");
   switch (row_shape(n, digit_split(value_bits, true).bits[0])) {
     case RowShape::k1024:
-      return rows_sort16<256, 4>(env, keys, skeys, srows, n, value_bits, reject, d_n, cw);
+      return rows_sort16<256, 4, kSum>(env, keys, skeys, srows, n, value_bits, reject, d_n, cw);
     case RowShape::k2048:
-      return rows_sort16<512, 4>(env, keys, skeys, srows, n, value_bits, reject, d_n, cw);
+      return rows_sort16<512, 4, kSum>(env, keys, skeys, srows, n, value_bits, reject, d_n, cw);
     case RowShape::k4096:
-      return rows_sort16<1024, 4>(env, keys, skeys, srows, n, value_bits, reject, d_n, cw);
+      return rows_sort16<1024, 4, kSum>(env, keys, skeys, srows, n, value_bits, reject, d_n, cw);
     case RowShape::k8192:
-      return rows_sort16<1024, 8>(env, keys, skeys, srows, n, value_bits, reject, d_n, cw);
+      return rows_sort16<1024, 8, kSum>(env, keys, skeys, srows, n, value_bits, reject, d_n, cw);
     case RowShape::kNone:
       break;
   }
-  return sort16_with_shape<kShapes[0].block, kShapes[0].items>(env, keys, skeys, srows, n, value_bits, reject, d_n, cw);
+  return rows_sort16<1024, 8, kScanned>(env, keys, skeys, srows, n, value_bits, reject, d_n, cw);
 }
 
 int launch_radix_sort_pairs(Env& env, const uint32_t* keys, const uint32_t* rows, uint32_t* skeys,
@@ -1492,24 +1412,24 @@ int launch_radix_sort_pairs(Env& env, const uint32_t* keys, const uint32_t* rows
   if (shape == 0) {
     switch (row_shape(n, kRadixBits)) {
       case RowShape::k1024:
-        return rows_sort32<256, 4>(env, keys, rows, skeys, srows, n, d_n, cw);
+        return rows_sort32<256, 4, kSum>(env, keys, rows, skeys, srows, n, d_n, cw);
       case RowShape::k2048:
-        return rows_sort32<512, 4>(env, keys, rows, skeys, srows, n, d_n, cw);
+        return rows_sort32<512, 4, kSum>(env, keys, rows, skeys, srows, n, d_n, cw);
       case RowShape::k4096:
-        return rows_sort32<1024, 4>(env, keys, rows, skeys, srows, n, d_n, cw);
+        return rows_sort32<1024, 4, kSum>(env, keys, rows, skeys, srows, n, d_n, cw);
       case RowShape::k8192:
-        return rows_sort32<1024, 8>(env, keys, rows, skeys, srows, n, d_n, cw);
+        return rows_sort32<1024, 8, kSum>(env, keys, rows, skeys, srows, n, d_n, cw);
       case RowShape::kNone:
         break;
     }
   }
   switch (shape) {
     case 0:
-      return sort_with_shape<kShapes[0].block, kShapes[0].items>(env, keys, rows, skeys, srows, n, d_n, cw);
+      return rows_sort32<kShapes[0].block, kShapes[0].items, kScanned>(env, keys, rows, skeys, srows, n, d_n, cw);
     case 1:
-      return sort_with_shape<kShapes[1].block, kShapes[1].items>(env, keys, rows, skeys, srows, n, d_n, cw);
+      return rows_sort32<kShapes[1].block, kShapes[1].items, kScanned>(env, keys, rows, skeys, srows, n, d_n, cw);
     case 2:
-      return sort_with_shape<kShapes[2].block, kShapes[2].items>(env, keys, rows, skeys, srows, n, d_n, cw);
+      return rows_sort32<kShapes[2].block, kShapes[2].items, kScanned>(env, keys, rows, skeys, srows, n, d_n, cw);
     default:
       return env.fail(kErrArg, "radix_sort: unknown tile shape");
   }

@@ -2,8 +2,8 @@
 // pairs, then the WAH encoder) for callers that cannot allocate device memory.
 //
 // Every scratch buffer the kernels need -- the sorted pairs, the sort's
-// ping-pong pair, its digit tables and plan, the look-back status words of its
-// table scans and the encoder's tile counts -- is carved out of one
+// ping-pong pair, its digit rows and plan, the look-back status words of the
+// encoder and its tile counts -- is carved out of one
 // file-scope device array, `scratch`, whose device address is looked up once
 // per device.  Nothing here calls hipMalloc, hipFree, hipMemset or any other
 // allocating routine; the kernels are the same ones ka_wah_index launches.
@@ -20,10 +20,10 @@ namespace {
 
 constexpr uint64_t kAlign = 256;
 constexpr uint64_t kMaxN = KA_NOALLOC_MAX_N;
-constexpr uint64_t kStatusWords = 8192;  // look-back status words of the table scans (kLbSpread per tile)
+constexpr uint64_t kStatusWords = 8192;  // look-back status words (kLbSpread per tile)
 constexpr uint64_t kStatusBytes = kStatusWords * 8;
 constexpr uint64_t kPairBytes = kMaxN * 4;               // one uint32 array of kMaxN elements
-constexpr uint64_t kTableBytes = (kMaxN / 4096 + 1) * 256 * 4;  // digit table at the smallest sort tile
+constexpr uint64_t kTableBytes = (kMaxN / 4096 + 1) * 256 * 4;  // digit counts, 4 bytes each, at a tile of 4096
 constexpr uint64_t kTileBytes = (kMaxN / 4096 + 1) * 8 + 4096;  // orand, encoder tile counts, group totals
 constexpr uint64_t kEncStatusBytes = (kMaxN / 4096 + 1) * 8 * kLbSpread;  // encoder status slots
 constexpr uint64_t kScratchBytes =

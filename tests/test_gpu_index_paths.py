@@ -105,9 +105,9 @@ def test_small_input_beyond_its_hint(sess, bits):
     check(sess, v, bits, 0)
 
 
-# capacities where the sort's tile grows (1024, 2048, 4096, 8192 keys) and where its digit table is scanned instead
+# capacities where the sort's tile grows (1024, 2048, 4096, 8192 keys) and where its digit counts are scanned instead
 # of summed by every tile (by digit width), with the encoder's tiles of 2048, 4096 and 8192 pairs
-SORT_EDGES = [1 << 18, 1 << 19, 1 << 20, 384 << 13, 1 << 22]
+SORT_EDGES = [1 << 18, 1 << 19, 1 << 20, 352 << 13, 1 << 22]
 
 
 @pytest.mark.parametrize("n", [SMALL_MAX + 1, 70_001] + [e + d for e in SORT_EDGES for d in (0, 1)])
@@ -123,7 +123,16 @@ def test_sort_tile_shapes(sess, n):
         check(sess, z, 20, 2)
 
 
-@pytest.mark.parametrize("cap,n", [(300_000, 299_000), (300_000, 5), (300_000, 0), (6000, 17), (6000, 0)])
+@pytest.mark.parametrize("n", [513 * 8192 + 1, 2050 * 8192 - 5])
+def test_scanned_digit_rows(sess, n):
+    """Tiles whose row is the scanned one or up to three after it, both widths of the scan, and skipped passes."""
+    u = workloads.u32(n, n)
+    check(sess, u & np.uint32(0xFFF), 12, 0)
+    check(sess, u & np.uint32(0x3FF00FF), 0, 0)
+    check(sess, np.where(u % 64 == 0, u & np.uint32(0xFFFF), np.uint32(7)), 16, 0)
+
+
+@pytest.mark.parametrize("cap,n", [(4_300_000, 4_200_001), (4_300_000, 9), (300_000, 299_000), (300_000, 5), (300_000, 0), (6000, 17), (6000, 0)])
 @pytest.mark.parametrize("bits", [0, 12])
 def test_counts_on_the_device(sess, cap, n, bits):
     """The same paths behind a compaction: the grid covers its capacity, the count is read on the device."""
