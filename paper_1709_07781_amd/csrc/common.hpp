@@ -85,9 +85,15 @@ int launch_affine_chain(Env& env, uint32_t* x, uint64_t n, const uint32_t* a, co
 int launch_affine(Env& env, uint32_t* x, uint64_t n_cap, const uint64_t* d_n, uint64_t offset, uint32_t a,
                   uint32_t b);
 int launch_exclusive_scan(Env& env, const uint32_t* in, uint32_t* out, uint64_t n_cap, const uint64_t* d_n);
-// start[i] = groups covered by words[0 .. i-1] of a bitmap in word format fmt.
-int launch_exclusive_scan_groups(Env& env, const uint32_t* words, uint32_t* start, uint64_t n_cap,
-                                 const uint64_t* d_n, uint32_t fmt);
+struct ScanJob {
+  const uint32_t* in;
+  uint32_t* out;
+  uint64_t n_cap;
+  const uint64_t* d_n;
+};
+// out[i] = groups covered by in[0 .. i-1], words of a bitmap in word format fmt;
+// b, when not null: a second bitmap in the same launch.
+int launch_exclusive_scan_groups(Env& env, const ScanJob& a, const ScanJob* b, uint32_t fmt);
 int launch_compact_nonzero(Env& env, const uint32_t* in, uint32_t* out, uint64_t n_cap, const uint64_t* d_n,
                            uint64_t* d_out_len, LenHost host = {});
 // Look-back words (count of them, kLbSpread apart) that a sort's first launch

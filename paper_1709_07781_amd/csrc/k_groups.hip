@@ -15,8 +15,8 @@
 // before, a fill's length on the last non-empty group and a 1-fill's on the end
 // of its run, both found in the tile or in the summaries.  Both are bound by
 // latency (the search's dependent loads, about 1 us each): over 645,162 groups
-// a decode takes 7 + 11 us and an OR 2 x 7 + 18 + 6 us, in two and four
-// launches; counting, scanning, searching per group, compacting and encoding
+// a decode takes 7 + 10 us and an OR 8 + 17 + 6 us, in two and three launches
+// (both bitmaps' scans in one: 13.4 us and a launch's gap before); counting, scanning, searching per group, compacting and encoding
 // through a group list took 27 us in three and 80 us in sixteen.
 //
 // Every count that depends on the data stays on the device; grids are sized
@@ -122,57 +122,62 @@ __device__ __forceinline__ uint32_t block_excl_max(uint32_t x, uint32_t* s_wave,
   return r;
 }
 
-// Groups g0 + kPer tid + (0 .. kPer-1) of a bitmap in v (0 past the words and
-// from ngroups on; words that cover 2^32 groups and more give unspecified
-// ones); wl and wr: the words that hold groups g0 and the tile's last
-// one.  s_mark: kTile words.  Starts and ends with a barrier.
+// Every word after wl up to wr (the words that hold group g0 and the tile's last
+// one) marks its first group in s_mark (kTile words, zeroed, a barrier since)
+// with its index + 1, wl the tile's first group; words of no groups mark none.
 template <int kFmt>
-__device__ __forceinline__ void tile_groups(const Bitmap& b, uint32_t m, uint32_t wl, uint32_t wr, uint32_t g0,
-                                            uint32_t ngroups, uint32_t* s_mark, uint32_t* s_wave,
-                                            uint32_t (&v)[kPer]) {
+__device__ __forceinline__ void mark_words(const Bitmap& b, uint32_t m, uint32_t wl, uint32_t wr, uint32_t g0,
+                                           uint32_t* s_mark) {
   const uint32_t tid = threadIdx.x;
-  const uint64_t total = total_groups<kFmt>(b, m);
-  u32x4* const mine = reinterpret_cast<u32x4*>(s_mark + kPer * tid);
-  const u32x4 zero = {0u, 0u, 0u, 0u};
-  __syncthreads();
-  mine[0] = zero;
-  mine[1] = zero;
-  __syncthreads();
-  // each word marks its first group with its index + 1 (words of no groups: none)
-  if (m) {
-    if (tid == 0) s_mark[0] = wl + 1u;
-    // kPer words per work-item and step, their loads issued together (a word
-    // covers a group at least, so one step is the rule)
-    for (uint64_t k0 = (uint64_t)wl + 1u + tid; k0 <= wr; k0 += kPer * kBlock) {
-      uint32_t at[kPer], w[kPer];
+  if (!m) return;
+  if (tid == 0) s_mark[0] = wl + 1u;
+  // kPer words per work-item and step, their loads issued together (a word
+  // covers a group at least, so one step is the rule)
+  for (uint64_t k0 = (uint64_t)wl + 1u + tid; k0 <= wr; k0 += kPer * kBlock) {
+    uint32_t at[kPer], w[kPer];
 #pragma unroll
-      for (int i = 0; i < kPer; ++i) {
-        const uint64_t k = k0 + (uint64_t)i * kBlock;
-        at[i] = k <= wr ? b.start[k] - g0 : kTile;
-        w[i] = k <= wr ? b.words[k] : 0u;
-      }
-#pragma unroll
-      for (int i = 0; i < kPer; ++i)
-        if (at[i] < kTile && word_groups<kFmt>(w[i])) s_mark[at[i]] = (uint32_t)k0 + i * kBlock + 1u;
+    for (int i = 0; i < kPer; ++i) {
+      const uint64_t k = k0 + (uint64_t)i * kBlock;
+      at[i] = k <= wr ? b.start[k] - g0 : kTile;
+      w[i] = k <= wr ? b.words[k] : 0u;
     }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i)
+      if (at[i] < kTile && word_groups<kFmt>(w[i])) s_mark[at[i]] = (uint32_t)k0 + i * kBlock + 1u;
   }
-  __syncthreads();
-  uint32_t idx[kPer];
-  {
-    const u32x4 x = mine[0], y = mine[1];
-    idx[0] = x.x, idx[1] = x.y, idx[2] = x.z, idx[3] = x.w;
-    idx[4] = y.x, idx[5] = y.y, idx[6] = y.z, idx[7] = y.w;
-  }
+}
+
+// The index + 1 of the word of each of this work-item's groups, from the marks.
+__device__ __forceinline__ void marked_words(const uint32_t* s_mark, uint32_t* s_wave, uint32_t (&idx)[kPer]) {
+  const u32x4* const mine = reinterpret_cast<const u32x4*>(s_mark + kPer * threadIdx.x);
+  const u32x4 x = mine[0], y = mine[1];
+  idx[0] = x.x, idx[1] = x.y, idx[2] = x.z, idx[3] = x.w;
+  idx[4] = y.x, idx[5] = y.y, idx[6] = y.z, idx[7] = y.w;
 #pragma unroll
   for (int i = 1; i < kPer; ++i) idx[i] = max(idx[i], idx[i - 1]);
   uint32_t all;
   const uint32_t before = block_excl_max(idx[kPer - 1], s_wave, &all);
 #pragma unroll
+  for (int i = 0; i < kPer; ++i) idx[i] = max(idx[i], before);
+}
+
+// Groups g0 + kPer tid + (0 .. kPer-1) of a bitmap in v (0 past its total and
+// from ngroups on; words that cover 2^32 groups and more give unspecified ones).
+template <int kFmt>
+__device__ __forceinline__ void word_values(const Bitmap& b, uint64_t total, uint32_t g0, uint32_t ngroups,
+                                            const uint32_t (&idx)[kPer], uint32_t (&v)[kPer]) {
+#pragma unroll
   for (int i = 0; i < kPer; ++i) {
-    const uint32_t l = kPer * tid + i, g = g0 + l, k = max(idx[i], before);
-    v[i] = l < ngroups - g0 && g < total ? group_value<kFmt>(b.words[k - 1u], b.start[k - 1u], g) : 0u;
+    const uint32_t l = kPer * threadIdx.x + i, g = g0 + l;
+    v[i] = l < ngroups - g0 && g < total ? group_value<kFmt>(b.words[idx[i] - 1u], b.start[idx[i] - 1u], g) : 0u;
   }
-  __syncthreads();
+}
+
+__device__ __forceinline__ void zero_marks(uint32_t* s_mark) {
+  const u32x4 zero = {0u, 0u, 0u, 0u};
+  u32x4* const mine = reinterpret_cast<u32x4*>(s_mark + kPer * threadIdx.x);
+  mine[0] = zero;
+  mine[1] = zero;
 }
 
 // This work-item's kPer words of a tile that holds n at out, in 16-byte stores
@@ -200,17 +205,21 @@ __global__ __launch_bounds__(kBlock) void k_decode_expand(Bitmap b, uint32_t ngr
   __shared__ __align__(16) uint32_t s_mark[kTile];
   __shared__ uint32_t s_wave[kWaves], s_at[2];
   const uint32_t m = b.count(), g0 = blockIdx.x * kTile;
-  if (blockIdx.x == 0 && threadIdx.x == 0)
-    put_len(len, host, 0, total_groups<kFmt>(b, m) > ngroups ? 0u : ngroups);
+  const uint64_t total = total_groups<kFmt>(b, m);
+  if (blockIdx.x == 0 && threadIdx.x == 0) put_len(len, host, 0, total > ngroups ? 0u : ngroups);
   if (g0 >= ngroups) return;
+  zero_marks(s_mark);
   if (m && threadIdx.x < 128) {  // wave 0: the first group's word, wave 1: the last one's
     const uint32_t w = threadIdx.x / 64;
     const uint32_t k = wave_last_start(b.start, m, w ? g0 + min(kTile, ngroups - g0) - 1u : g0);
     if (lane_id() == 0) s_at[w] = k;
   }
   __syncthreads();
-  uint32_t v[kPer];
-  tile_groups<kFmt>(b, m, m ? s_at[0] : 0u, m ? s_at[1] : 0u, g0, ngroups, s_mark, s_wave, v);
+  if (m) mark_words<kFmt>(b, m, s_at[0], s_at[1], g0, s_mark);
+  __syncthreads();
+  uint32_t idx[kPer], v[kPer];
+  marked_words(s_mark, s_wave, idx);
+  word_values<kFmt>(b, total, g0, ngroups, idx, v);
   store_tile(groups + g0, min(kTile, ngroups - g0), v);
 }
 
@@ -247,45 +256,53 @@ struct TileSums {
 template <int kFmt, int kOutFmt>
 __global__ __launch_bounds__(kBlock) void k_combine(Bitmap a, Bitmap b, uint32_t ngroups, uint32_t op,
                                                     uint32_t* __restrict__ dense, TileSums sums) {
-  __shared__ __align__(16) uint32_t s_mark[kTile];
-  __shared__ uint32_t s_wave[kWaves], s_at[4], s_sum[kWaves], s_prev;
+  __shared__ __align__(16) uint32_t s_mark[2][kTile];
+  __shared__ uint32_t s_wave[2][kWaves], s_at[4], s_prev[2], s_sum[kWaves];
   const uint32_t tid = threadIdx.x, ma = a.count(), mb = b.count(), g0 = blockIdx.x * kTile;
+  zero_marks(s_mark[0]);
+  zero_marks(s_mark[1]);
+  const uint64_t ta = total_groups<kFmt>(a, ma), tb = total_groups<kFmt>(b, mb);
   {  // a wave each: the words of the tile's first and last group in a and in b
-    const uint32_t w = tid / 64, m = w < 2 ? ma : mb;
-    const uint32_t k = m ? wave_last_start(w < 2 ? a.start : b.start, m, (w & 1u) ? g0 + min(kTile, ngroups - g0) - 1u : g0)
-                         : 0u;
-    if (lane_id() == 0) s_at[w] = k;
+    const uint32_t w = tid / 64, lane = lane_id();
+    const bool first = !(w & 1u);
+    const Bitmap& t = w < 2 ? a : b;
+    const uint32_t m = w < 2 ? ma : mb, last = g0 + min(kTile, ngroups - g0) - 1u;
+    uint32_t k = m ? wave_last_start(t.start, m, first ? g0 - (g0 ? 1u : 0u) : last) : 0u;
+    if (first) {
+      if (lane == 0)  // the group before the tile
+        s_prev[w / 2] = g0 && g0 - 1u < (w < 2 ? ta : tb) ? group_value<kFmt>(t.words[k], t.start[k], g0 - 1u) : 0u;
+      // on to the tile's first group: one word at most, but for words of no groups
+      for (uint32_t step = 64; m && step == 64;) {
+        const uint64_t p = (uint64_t)k + 1u + lane;
+        const uint64_t past = __ballot(!(p < m && t.start[p] <= g0));
+        step = past ? (uint32_t)__builtin_ctzll(past) : 64u;
+        k += step;
+      }
+    }
+    if (lane == 0) s_at[w] = k;
   }
   __syncthreads();
-  if (tid == 0) {  // the group before the tile
-    uint32_t p = 1u;
-    if (g0) {
-      uint32_t v[2];
-      for (int i = 0; i < 2; ++i) {
-        const Bitmap& t = i ? b : a;
-        const uint32_t m = i ? mb : ma;
-        v[i] = 0;
-        if (g0 - 1u < total_groups<kFmt>(t, m)) {
-          uint32_t k = s_at[2 * i];
-          while (t.start[k] > g0 - 1u) --k;
-          v[i] = group_value<kFmt>(t.words[k], t.start[k], g0 - 1u);
-        }
-      }
-      p = op ? v[0] | v[1] : v[0] & v[1];
-    }
-    s_prev = p;
-  }
-  uint32_t va[kPer], vb[kPer];
-  tile_groups<kFmt>(a, ma, s_at[0], s_at[1], g0, ngroups, s_mark, s_wave, va);
-  tile_groups<kFmt>(b, mb, s_at[2], s_at[3], g0, ngroups, s_mark, s_wave, vb);
+  mark_words<kFmt>(a, ma, s_at[0], s_at[1], g0, s_mark[0]);
+  mark_words<kFmt>(b, mb, s_at[2], s_at[3], g0, s_mark[1]);
+  __syncthreads();
+  uint32_t ia[kPer], ib[kPer], va[kPer], vb[kPer];
+  marked_words(s_mark[0], s_wave[0], ia);
+  marked_words(s_mark[1], s_wave[1], ib);
+  word_values<kFmt>(a, ta, g0, ngroups, ia, va);
+  word_values<kFmt>(b, tb, g0, ngroups, ib, vb);
   const uint32_t g = g0 + kPer * tid;
   uint32_t x[kPer];
 #pragma unroll
   for (int i = 0; i < kPer; ++i) x[i] = op ? va[i] | vb[i] : va[i] & vb[i];
   store_tile(dense + g0, min(kTile, ngroups - g0), x);
-  s_mark[tid] = x[kPer - 1];  // the next work-item's group before its first
   __syncthreads();
-  uint32_t p = tid ? s_mark[tid - 1] : s_prev, words = 0, last = 0, lead = kTile;
+  s_mark[0][tid] = x[kPer - 1];  // the next work-item's group before its first
+  __syncthreads();
+  uint32_t p = 1u, words = 0, last = 0, lead = kTile;
+  if (tid)
+    p = s_mark[0][tid - 1];
+  else if (g0)
+    p = op ? s_prev[0] | s_prev[1] : s_prev[0] & s_prev[1];
 #pragma unroll
   for (int i = 0; i < kPer; ++i) {
     const DenseEmits e = dense_emits<kOutFmt>(x[i], p);
@@ -295,9 +312,8 @@ __global__ __launch_bounds__(kBlock) void k_combine(Bitmap a, Bitmap b, uint32_t
     p = x[i];
   }
   uint32_t last_all, nlead_all;
-  (void)block_excl_max(last, s_wave, &last_all);
-  __syncthreads();
-  (void)block_excl_max(kTile - lead, s_wave, &nlead_all);  // the smallest lead
+  (void)block_excl_max(last, s_wave[0], &last_all);
+  (void)block_excl_max(kTile - lead, s_wave[1], &nlead_all);  // the smallest lead
   const uint32_t wsum = wave_sum(words);
   if (lane_id() == 0) s_sum[tid / 64] = wsum;
   __syncthreads();
@@ -479,12 +495,12 @@ int launch_zero_u32(Env& env, uint32_t* p) {
 }
 
 // ---- host side --------------------------------------------------------------------------
-// The scan of a bitmap's group counts, into scratch.
-int bitmap_starts(Env& env, const uint32_t* words, uint64_t cap, const uint64_t* len, uint32_t fmt, Bitmap* out) {
+// A bitmap with room for the scan of its group counts.
+bool make_bitmap(Env& env, const uint32_t* words, uint64_t cap, const uint64_t* len, Bitmap* out, ScanJob* job) {
   uint32_t* start = static_cast<uint32_t*>(env.scratch(4 * std::max<uint64_t>(cap, 1)));
-  if (!start) return env.fail(kErrOom, "wah query: scratch");
   *out = Bitmap{words, start, cap, len};
-  return launch_exclusive_scan_groups(env, words, start, cap, len, fmt);
+  *job = ScanJob{words, start, cap, len};
+  return start != nullptr;
 }
 
 template <int kFmt, int kOutFmt>
@@ -515,7 +531,9 @@ int launch_wah_decode(Env& env, const uint32_t* words, uint64_t m_cap, const uin
   if (fmt > kFmtPlwah) return env.fail(kErrArg, "unknown WAH format");
   if (!len || (ngroups && !groups) || (m_cap && !words)) return env.fail(kErrArg, "wah decode: null buffer");
   Bitmap b;
-  int rc = bitmap_starts(env, words, m_cap, m_len, fmt, &b);
+  ScanJob job;
+  if (!make_bitmap(env, words, m_cap, m_len, &b, &job)) return env.fail(kErrOom, "wah decode: scratch");
+  const int rc = launch_exclusive_scan_groups(env, job, nullptr, fmt);
   if (rc) return rc;
   const dim3 grid(std::max<uint32_t>(1, (uint32_t)(((uint64_t)ngroups + kTile - 1) / kTile))), block(kBlock);
   env.prof_begin("wah_decode");
@@ -552,9 +570,11 @@ int launch_wah_combine(Env& env, const uint32_t* a, uint64_t a_cap, const uint64
     return env.fail(kErrOom, "wah combine: scratch");
   const TileSums ts{sums, sums + ntiles, sums + 2ull * ntiles};
   Bitmap ba, bb;
-  int rc;
-  if ((rc = bitmap_starts(env, a, a_cap, a_len, in_fmt, &ba))) return rc;
-  if ((rc = bitmap_starts(env, b, b_cap, b_len, in_fmt, &bb))) return rc;
+  ScanJob ja, jb;
+  if (!make_bitmap(env, a, a_cap, a_len, &ba, &ja) || !make_bitmap(env, b, b_cap, b_len, &bb, &jb))
+    return env.fail(kErrOom, "wah combine: scratch");
+  const int rc = launch_exclusive_scan_groups(env, ja, &jb, in_fmt);
+  if (rc) return rc;
 #define KA_COMBINE(I, O) \
   return combine_fmt<I, O>(env, ba, bb, ngroups, op, dense, ts, first_word, words, len_words, host, reject)
 #define KA_COMBINE_IN(I)                                    \

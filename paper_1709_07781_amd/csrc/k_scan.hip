@@ -23,6 +23,8 @@
 // request with 8 / 16 rounds: 4 10^6 values 21.4 / 21.7, 8 10^6 29.6 / 24.8, 1.6
 // 10^7 43 / 37.  Compactions, whose tile is staged in LDS (32 / 64 KiB: four or
 // two work-groups per CU): 1.6 10^7 42 / 44, 3 10^7 75 / 74, 6 10^7 121 / 110.
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace ka {
@@ -152,17 +154,23 @@ struct AddGroups {
 };
 
 // One tile per work-group.  The grid is the tile count of n_cap; with a
-// smaller device-resident count the surplus work-groups leave at once.
-template <int R, bool kVec, class Op>
-__global__ __launch_bounds__(kScanBlock) void k_exclusive_scan_u32(const uint32_t* __restrict__ in,
-                                                                   uint32_t* __restrict__ out, uint64_t n_cap,
-                                                                   const uint64_t* __restrict__ d_n, LbArgs lb) {
+// smaller device-resident count the surplus work-groups leave at once.  kPair:
+// two arrays, the second's tiles from work-group first_b on, its status words
+// from there on too (two bitmaps of a 2 10^7-row column: 2 x 6.7 us and the
+// gap between two launches -> 8.0 us).
+template <int R, bool kVec, class Op, bool kPair>
+__global__ __launch_bounds__(kScanBlock) void k_exclusive_scan_u32(ScanJob a, ScanJob b, uint32_t first_b, LbArgs lb) {
   constexpr int kTile = kTileElems<R>;
   __shared__ uint32_t s_prefix;
   __shared__ uint32_t s_wave[R][kWaves];
-  const uint64_t n = device_count(n_cap, d_n);
+  const bool second = kPair && blockIdx.x >= first_b;
+  const ScanJob job = second ? b : a;
+  const uint32_t* __restrict__ in = job.in;
+  uint32_t* __restrict__ out = job.out;
+  const uint64_t n = device_count(job.n_cap, job.d_n);
   const uint64_t ntiles = (n + kTile - 1) / kTile;
-  const uint32_t tile = blockIdx.x;
+  const uint32_t tile = second ? blockIdx.x - first_b : blockIdx.x;
+  if (second) lb.status += (uint64_t)kLbSpread * first_b;
   if (tile >= ntiles) return;
   const uint64_t base = (uint64_t)tile * kTile;
   uint32_t v[R][4];
@@ -242,49 +250,71 @@ inline bool ranges_overlap(const uint32_t* a, const uint32_t* b, uint64_t n) {
   return x < y + 4 * n && y < x + 4 * n;
 }
 
-template <int R, class Op>
-int scan_launch(Env& env, const uint32_t* in, uint32_t* out, uint64_t n_cap, const uint64_t* d_n) {
-  const uint32_t grid = (uint32_t)((n_cap + kTileElems<R> - 1) / kTileElems<R>);
+template <int R, class Op, bool kPair>
+int scan_launch(Env& env, const ScanJob& a, const ScanJob& b) {
+  const auto tiles = [](const ScanJob& j) { return (uint32_t)((j.n_cap + kTileElems<R> - 1) / kTileElems<R>); };
+  const uint32_t first_b = tiles(a), grid = first_b + (kPair ? tiles(b) : 0u);
   LbArgs lb;
   if (!env.lookback((uint64_t)kLbSpread * grid, &lb))
     return env.fail(kErrOom, "exclusive_scan_u32: look-back state");
-  const bool vec = ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15u) == 0;
-  const dim3 g(grid), b(kScanBlock);
+  uintptr_t at = reinterpret_cast<uintptr_t>(a.in) | reinterpret_cast<uintptr_t>(a.out);
+  if (kPair) at |= reinterpret_cast<uintptr_t>(b.in) | reinterpret_cast<uintptr_t>(b.out);
+  const dim3 g(grid), block(kScanBlock);
   env.prof_begin("exclusive_scan_u32");
-  if (vec)
-    k_exclusive_scan_u32<R, true, Op><<<g, b, 0, env.stream()>>>(in, out, n_cap, d_n, lb);
+  if ((at & 15u) == 0)
+    k_exclusive_scan_u32<R, true, Op, kPair><<<g, block, 0, env.stream()>>>(a, b, first_b, lb);
   else
-    k_exclusive_scan_u32<R, false, Op><<<g, b, 0, env.stream()>>>(in, out, n_cap, d_n, lb);
+    k_exclusive_scan_u32<R, false, Op, kPair><<<g, block, 0, env.stream()>>>(a, b, first_b, lb);
   env.prof_end("exclusive_scan_u32");
   return check_launch(env, "exclusive_scan_u32 launch");
+}
+
+int check_scan(Env& env, const ScanJob& j) {
+  if (!j.in || !j.out) return env.fail(kErrArg, "exclusive_scan_u32: null buffer");
+  if (j.n_cap > 0xFFFFFFFFull) return env.fail(kErrArg, "exclusive_scan_u32: more than 2^32-1 elements");
+  if (ranges_overlap(j.in, j.out, j.n_cap)) return env.fail(kErrArg, "exclusive_scan_u32: in and out overlap");
+  return kOk;
+}
+
+template <class Op>
+int scan_any(Env& env, const ScanJob& j) {
+  if (j.n_cap == 0) return kOk;
+  const int rc = check_scan(env, j);
+  if (rc) return rc;
+  return j.n_cap > kLargeScan ? scan_launch<kLargeRounds, Op, false>(env, j, j)
+                              : scan_launch<kSmallRounds, Op, false>(env, j, j);
+}
+
+template <class Op>
+int scan_pair(Env& env, const ScanJob& a, const ScanJob& b) {
+  if (a.n_cap == 0) return scan_any<Op>(env, b);
+  if (b.n_cap == 0) return scan_any<Op>(env, a);
+  int rc = check_scan(env, a);
+  if (rc || (rc = check_scan(env, b))) return rc;
+  return std::max(a.n_cap, b.n_cap) > kLargeScan ? scan_launch<kLargeRounds, Op, true>(env, a, b)
+                                                 : scan_launch<kSmallRounds, Op, true>(env, a, b);
+}
+
+template <class Op>
+int scan_groups(Env& env, const ScanJob& a, const ScanJob* b) {
+  return b ? scan_pair<Op>(env, a, *b) : scan_any<Op>(env, a);
 }
 
 }  // namespace
 
 // in and out must not overlap.
-template <class Op>
-static int scan_any(Env& env, const uint32_t* in, uint32_t* out, uint64_t n_cap, const uint64_t* d_n) {
-  if (n_cap == 0) return kOk;
-  if (!in || !out) return env.fail(kErrArg, "exclusive_scan_u32: null buffer");
-  if (n_cap > 0xFFFFFFFFull) return env.fail(kErrArg, "exclusive_scan_u32: more than 2^32-1 elements");
-  if (ranges_overlap(in, out, n_cap)) return env.fail(kErrArg, "exclusive_scan_u32: in and out overlap");
-  return n_cap > kLargeScan ? scan_launch<kLargeRounds, Op>(env, in, out, n_cap, d_n)
-                            : scan_launch<kSmallRounds, Op>(env, in, out, n_cap, d_n);
-}
-
 int launch_exclusive_scan(Env& env, const uint32_t* in, uint32_t* out, uint64_t n_cap, const uint64_t* d_n) {
-  return scan_any<AddSelf>(env, in, out, n_cap, d_n);
+  return scan_any<AddSelf>(env, ScanJob{in, out, n_cap, d_n});
 }
 
-int launch_exclusive_scan_groups(Env& env, const uint32_t* words, uint32_t* start, uint64_t n_cap,
-                                 const uint64_t* d_n, uint32_t fmt) {
+int launch_exclusive_scan_groups(Env& env, const ScanJob& a, const ScanJob* b, uint32_t fmt) {
   switch (fmt) {
     case kFmtPaper:
-      return scan_any<AddGroups<kFmtPaper>>(env, words, start, n_cap, d_n);
+      return scan_groups<AddGroups<kFmtPaper>>(env, a, b);
     case kFmtCanonical:
-      return scan_any<AddGroups<kFmtCanonical>>(env, words, start, n_cap, d_n);
+      return scan_groups<AddGroups<kFmtCanonical>>(env, a, b);
     case kFmtPlwah:
-      return scan_any<AddGroups<kFmtPlwah>>(env, words, start, n_cap, d_n);
+      return scan_groups<AddGroups<kFmtPlwah>>(env, a, b);
     default:
       return env.fail(kErrArg, "unknown WAH format");
   }

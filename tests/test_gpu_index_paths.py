@@ -236,6 +236,26 @@ def test_bitmap_queries_around_tiles(sess, fmt, ng):
             sess.release_actor(act)
 
 
+@pytest.mark.parametrize("fmt", [0, 2])
+def test_bitmaps_of_unlike_sizes(sess, impatient, fmt):
+    """Both bitmaps' words are scanned in one launch: one tile and several, in both orders, with the fallback too."""
+    import ctypes
+    import paper_1709_07781_amd as ka
+    ng = 40 * GROUP_TILE + 3
+    pats = group_patterns(ng)
+    words = [bitmap(p, fmt) for p in pats]
+    assert words[0].size < 10 and words[3].size > 3 * ENC_TILE
+    for s in (sess, impatient):
+        act = s.spawn("wah_combine", [ka.arg(ka.KA_IN, in_mode=ka.KA_VAL), ka.arg(ka.KA_IN, in_mode=ka.KA_VAL),
+                                      ka.arg(ka.KA_PRIV, count=4, init=(ctypes.c_uint32 * 4)(1, fmt, fmt, ng)),
+                                      ka.arg(ka.KA_OUT, out_mode=ka.KA_VAL)])
+        for i, j in ((0, 3), (3, 0), (3, 3)):
+            (o,) = s.request(act, ka.val(words[i].ctypes.data, words[i].size),
+                             ka.val(words[j].ctypes.data, words[j].size), n_out=1)
+            np.testing.assert_array_equal(o, bitmap(pats[i] | pats[j], fmt))
+        s.release_actor(act)
+
+
 def test_combine_scans_many_tiles(sess):
     """More tiles than one work-group sums up: their words are scanned in a launch of their own."""
     import ctypes
