@@ -16,8 +16,9 @@
 // of its run, both found in the tile or in the summaries.  Both are bound by
 // latency (the search's dependent loads, about 1 us each): over 645,162 groups
 // a decode takes 7 + 10 us and an OR 8 + 17 + 6 us, in two and three launches
-// (both bitmaps' scans in one: 13.4 us and a launch's gap before); counting, scanning, searching per group, compacting and encoding
-// through a group list took 27 us in three and 80 us in sixteen.
+// (both bitmaps' scans in one: 13.4 us and a launch's gap before); counting,
+// scanning, searching per group, compacting and encoding through a group list
+// took 27 us in three and 80 us in sixteen.
 //
 // Every count that depends on the data stays on the device; grids are sized
 // by capacities and read the true counts there.

@@ -14,16 +14,24 @@
 // order; its phases "count per group", "scan of the group counts" and "move
 // the valid elements" run in one kernel.
 //
-// Tile layout: round r of thread t holds the 4 consecutive elements starting at
-// tile_base + 4 (r * BLOCK + t), so every global access is a coalesced
-// 16-byte load or store; element order inside the tile is (round, thread, lane
-// of the vector).  The number of rounds R is chosen per launch: 8 (8192
+// Tile layout: round r of lane l of wave w holds the 4 consecutive elements
+// starting at tile_base + 4 (64 (w R + r) + l), so every global access is a
+// coalesced 16-byte load or store, and a wave's elements are consecutive: its
+// rounds' sums are carried along in a scalar, only one sum per wave goes through
+// LDS, and a full tile's rounds check no end.  (Rounds over the whole
+// work-group, a sum per wave and round: 229 registers for 122 in the scan.)  Us
+// before / now: scans of 10^6 values 5.9 / 5.4, 8 10^6 12.1 / 10.8, 6.7 10^7 121 /
+// 90; compactions of 10^6 7.4 / 6.6, 8 10^6 15.4 / 14.3, 2.4 10^7 39.7 / 33.3, 6.7
+// 10^7 97 / 91 (with the cached loads of load4).
+//
+// The number of rounds R is chosen per launch: 8 (8192
 // elements per tile) up to a capacity, where the look-back's latency dominates,
 // 16 above, where fewer tiles mean fewer look-backs per byte.  Scans, us a
 // request with 8 / 16 rounds: 4 10^6 values 21.4 / 21.7, 8 10^6 29.6 / 24.8, 1.6
 // 10^7 43 / 37.  Compactions, whose tile is staged in LDS (32 / 64 KiB: four or
 // two work-groups per CU): 1.6 10^7 42 / 44, 3 10^7 75 / 74, 6 10^7 121 / 110.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 
@@ -37,10 +45,16 @@ constexpr uint64_t kLargeScan = 1ull << 22, kLargeCompact = 1ull << 25;  // capa
 template <int R>
 constexpr int kTileElems = kScanBlock * R * 4;
 
-template <bool kVec>
+// Loads are kept in the caches (kStream: not).  The 256 MB behind the L2 hold an
+// input of up to that size for what reads it next: a scan and a compaction of
+// the same 30,000,003 values 67 + 41 us streamed, 48 + 37 us cached.  Only the
+// compactions of kLargeRounds stream: their inputs begin at half of it (6.7 10^7
+// values 91 / 101 us streamed / cached).  Stores are streamed.
+template <bool kVec, bool kFull, bool kStream>
 __device__ __forceinline__ void load4(const uint32_t* __restrict__ p, uint64_t e, uint64_t n, uint32_t v[4]) {
-  if (kVec && e + 4 <= n) {
-    const u32x4 q = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p + e));
+  if (kVec && (kFull || e + 4 <= n)) {
+    const u32x4* const src = reinterpret_cast<const u32x4*>(p + e);
+    const u32x4 q = kStream ? __builtin_nontemporal_load(src) : *src;
     v[0] = q.x;
     v[1] = q.y;
     v[2] = q.z;
@@ -51,9 +65,9 @@ __device__ __forceinline__ void load4(const uint32_t* __restrict__ p, uint64_t e
   }
 }
 
-template <bool kVec>
+template <bool kVec, bool kFull = false>
 __device__ __forceinline__ void store4(uint32_t* __restrict__ p, uint64_t e, uint64_t n, const uint32_t v[4]) {
-  if (kVec && e + 4 <= n) {
+  if (kVec && (kFull || e + 4 <= n)) {
     u32x4 q;
     q.x = v[0];
     q.y = v[1];
@@ -67,33 +81,31 @@ __device__ __forceinline__ void store4(uint32_t* __restrict__ p, uint64_t e, uin
   }
 }
 
-// Exclusive prefix of each thread's round sums over (round, thread) order,
-// plus the tile total.  One barrier.
+// Exclusive prefix of each lane's round sums over (wave, round, lane) order, plus
+// the tile total.  One barrier.
 template <int R>
 __device__ __forceinline__ void tile_scan(const uint32_t (&s)[R], uint32_t (&pre)[R], uint32_t* tile_total,
-                                          uint32_t (*s_wave)[kWaves]) {
+                                          uint32_t* s_wave) {
   const uint32_t w = threadIdx.x / 64;
-  uint32_t inc[R];
+  uint32_t run = 0;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    inc[r] = wave_incl_scan(s[r]);
-    if (lane_id() == 63) s_wave[r][w] = inc[r];
+    const uint32_t inc = wave_incl_scan(s[r]);
+    pre[r] = run + inc - s[r];
+    run += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
   }
+  if (lane_id() == 0) s_wave[w] = run;
   __syncthreads();
-  uint32_t round_base = 0;
+  uint32_t before = 0, total = 0;
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    uint32_t before = 0, tot = 0;
-#pragma unroll
-    for (int i = 0; i < kWaves; ++i) {
-      const uint32_t t = s_wave[r][i];
-      before += (i < (int)w) ? t : 0u;
-      tot += t;
-    }
-    pre[r] = round_base + before + inc[r] - s[r];
-    round_base += tot;
+  for (int i = 0; i < kWaves; ++i) {
+    const uint32_t t = s_wave[i];
+    before += (i < (int)w) ? t : 0u;
+    total += t;
   }
-  *tile_total = round_base;
+#pragma unroll
+  for (int r = 0; r < R; ++r) pre[r] += before;
+  *tile_total = total;
 }
 
 // Wave 0 publishes the tile total, looks back, publishes the inclusive prefix
@@ -127,18 +139,29 @@ __device__ __forceinline__ uint32_t wave_tile_total(const uint32_t* in, uint32_t
 #pragma unroll 4
   for (int i = 0; i < kTileElems<R> / 256; ++i) {
     uint32_t q[4];
-    load4<kVec>(in, b + 4 * ((uint64_t)i * 64 + lane_id()), n, q);
+    load4<kVec, false, false>(in, b + 4 * ((uint64_t)i * 64 + lane_id()), n, q);
     acc += op(q[0]) + op(q[1]) + op(q[2]) + op(q[3]);
   }
   return wave_sum(acc);
 }
 
-template <int R, bool kVec>
+// The first of the 4 elements of round r of this work-item in its tile.
+template <int R>
+__device__ __forceinline__ uint32_t round_elem(int r) {
+  return 4u * ((threadIdx.x / 64u * R + r) * 64u + lane_id());
+}
+
+template <int R, bool kVec, bool kStream>
 __device__ __forceinline__ void load_tile(const uint32_t* __restrict__ in, uint64_t tile, uint64_t n,
                                           uint32_t (&v)[R][4]) {
   const uint64_t base = tile * kTileElems<R>;
+  if (kVec && base + kTileElems<R> <= n) {  // uniform: no round checks the end
 #pragma unroll
-  for (int r = 0; r < R; ++r) load4<kVec>(in, base + ((uint64_t)r * kScanBlock + threadIdx.x) * 4, n, v[r]);
+    for (int r = 0; r < R; ++r) load4<kVec, true, kStream>(in, base + round_elem<R>(r), n, v[r]);
+  } else {
+#pragma unroll
+    for (int r = 0; r < R; ++r) load4<kVec, false, kStream>(in, base + round_elem<R>(r), n, v[r]);
+  }
 }
 
 // What an element adds: itself, or the groups that it covers as a word of a
@@ -158,11 +181,15 @@ struct AddGroups {
 // two arrays, the second's tiles from work-group first_b on, its status words
 // from there on too (two bitmaps of a 2 10^7-row column: 2 x 6.7 us and the
 // gap between two launches -> 8.0 us).
+// Two work-groups per CU are enough with 16 rounds (32 KB of loads each), and more
+// of them spread the chip over more of the arrays: 3.3 10^7 values 51 us with
+// three, 46 with two; 6.7 10^7 96 / 90.
 template <int R, bool kVec, class Op, bool kPair>
-__global__ __launch_bounds__(kScanBlock) void k_exclusive_scan_u32(ScanJob a, ScanJob b, uint32_t first_b, LbArgs lb) {
+__global__ __launch_bounds__(kScanBlock)
+__attribute__((amdgpu_waves_per_eu(2, R == kLargeRounds ? 2 : 8))) void k_exclusive_scan_u32(ScanJob a, ScanJob b, uint32_t first_b, LbArgs lb) {
   constexpr int kTile = kTileElems<R>;
   __shared__ uint32_t s_prefix;
-  __shared__ uint32_t s_wave[R][kWaves];
+  __shared__ uint32_t s_wave[kWaves];
   const bool second = kPair && blockIdx.x >= first_b;
   const ScanJob job = second ? b : a;
   const uint32_t* __restrict__ in = job.in;
@@ -174,13 +201,13 @@ __global__ __launch_bounds__(kScanBlock) void k_exclusive_scan_u32(ScanJob a, Sc
   if (tile >= ntiles) return;
   const uint64_t base = (uint64_t)tile * kTile;
   uint32_t v[R][4];
-  load_tile<R, kVec>(in, tile, n, v);
+  load_tile<R, kVec, false>(in, tile, n, v);
   if (!Op::kSelf) {  // elements past the end add nothing
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        v[r][j] = base + ((uint64_t)r * kScanBlock + threadIdx.x) * 4 + j < n ? Op()(v[r][j]) : 0u;
+        v[r][j] = base + round_elem<R>(r) + j < n ? Op()(v[r][j]) : 0u;
   }
   uint32_t s[R], pre[R];
 #pragma unroll
@@ -191,16 +218,22 @@ __global__ __launch_bounds__(kScanBlock) void k_exclusive_scan_u32(ScanJob a, Sc
     return wave_tile_total<R, kVec>(in, u, n, Op());  // an earlier tile: every element exists
   });
   const uint32_t tp = s_prefix;
+  const auto write = [&](auto full) {
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    uint32_t acc = tp + pre[r], o[4];
+    for (int r = 0; r < R; ++r) {
+      uint32_t acc = tp + pre[r], o[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      o[j] = acc;
-      acc += v[r][j];
+      for (int j = 0; j < 4; ++j) {
+        o[j] = acc;
+        acc += v[r][j];
+      }
+      store4<kVec, decltype(full)::value>(out, base + round_elem<R>(r), n, o);
     }
-    store4<kVec>(out, base + ((uint64_t)r * kScanBlock + threadIdx.x) * 4, n, o);
-  }
+  };
+  if (kVec && base + kTile <= n)
+    write(std::true_type());
+  else
+    write(std::false_type());
 }
 
 // Kept elements are staged in LDS at their tile-local positions, then copied
@@ -212,7 +245,7 @@ __global__ __launch_bounds__(kScanBlock) void k_compact_nonzero_u32(const uint32
                                                                     uint64_t* __restrict__ d_out_len, LenHost host, LbArgs lb) {
   constexpr int kTile = kTileElems<R>;
   __shared__ uint32_t s_prefix;
-  __shared__ uint32_t s_wave[R][kWaves];
+  __shared__ uint32_t s_wave[kWaves];
   __shared__ __align__(16) uint32_t s_out[kTile];
   const uint64_t n = device_count(n_cap, d_n);
   const uint64_t ntiles = (n + kTile - 1) / kTile;
@@ -220,7 +253,7 @@ __global__ __launch_bounds__(kScanBlock) void k_compact_nonzero_u32(const uint32
   const uint32_t tile = blockIdx.x;
   if (tile >= ntiles) return;
   uint32_t v[R][4];
-  load_tile<R, kVec>(in, tile, n, v);
+  load_tile<R, kVec, R == kLargeRounds>(in, tile, n, v);
   uint32_t s[R], pre[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) s[r] = (v[r][0] != 0) + (v[r][1] != 0) + (v[r][2] != 0) + (v[r][3] != 0);
