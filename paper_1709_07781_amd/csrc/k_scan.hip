@@ -47,7 +47,7 @@ constexpr int kTileElems = kScanBlock * R * 4;
 
 // Loads are kept in the caches (kStream: not).  The 256 MB behind the L2 hold an
 // input of up to that size for what reads it next: a scan and a compaction of
-// the same 30,000,003 values 67 + 41 us streamed, 48 + 37 us cached.  Only the
+// the same 30,000,001 values 67 + 41 us streamed, 48 + 37 us cached.  Only the
 // compactions of kLargeRounds stream: their inputs begin at half of it (6.7 10^7
 // values 91 / 101 us streamed / cached).  Stores are streamed.
 template <bool kVec, bool kFull, bool kStream>

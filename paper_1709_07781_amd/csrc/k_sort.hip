@@ -387,9 +387,14 @@ struct ScatterLds {
 enum Starts { kGiven, kSum, kScanned };
 // k_rows_scan writes the prefix of every kRowGroup-th row, and a scatter
 // work-group adds the up to three rows after it to that (uint16 loads that
-// arrive behind its keys): at 8192 tiles the scan took 17.2 / 12.6 / 12.0 us with
-// 1 / 4 / 8 rows and the scatters 162 + 176 / 158 + 177 / 167 + 183.
+// arrive behind its keys): at 8192 tiles the scatters took 162 + 176 / 158 + 177 /
+// 167 + 183 us with 1 / 4 / 8 rows, the scan the least with 4 or more.
 constexpr uint32_t kRowGroup = 4;
+// Scanned rows are stored by groups of kRowGroup, four digits of each row beside
+// those of the next one: the place of digit d in the row of tile `tile`.
+__device__ __forceinline__ uint32_t grouped_digit(uint32_t tile, uint32_t d) {
+  return d / 4u * (4u * kRowGroup) + tile % kRowGroup * 4u + d % 4u;
+}
 
 // The tile's keys and rows: wave w owns 64*kItems consecutive elements, lane
 // l the elements w*64*kItems + i*64 + l.
@@ -508,7 +513,7 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<kBlock, kItems, IO::kPac
   if (kStarts == kScanned && tid < (1u << kBits)) {  // the rows between the scanned one and this tile's
 #pragma unroll
     for (uint32_t r = 0; r + 1 < kRowGroup; ++r)
-      if (r < tr.T) before += tr.rows[(r << kBits) + tid];
+      if (r < tr.T) before += tr.rows[grouped_digit(r, tid)];
   }
 
   // ---- rank inside the wave: peers = lanes with the same digit ----------------
@@ -669,24 +674,27 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<kBlock, kItems, IO::kPac
 // the kernels of a pass
 // ---------------------------------------------------------------------------------
 // Column prefixes of the rows: pre[t / kRowGroup][d] = the counts of digit d in
-// the tiles before t, totals[d] those in all T.  Bound by latency: a work-group
-// takes 4 kCols digits, a work-item four of them in a kChunks-th part of the
-// rows -- it adds them up, the sums are scanned over the parts in LDS, and it
-// writes its prefixes, from the rows it holds (the first kHeld) or reads again.
+// the tiles before t, totals[d] those in all T.  Bound by latency, and with many
+// tiles by the work-items' scattered loads: a work-group takes 4 kCols digits, a
+// work-item four of them in a kChunks-th part of the groups -- two 16-byte loads
+// a group -- which it adds up, the sums are scanned over the parts in LDS, and it
+// writes its prefixes, from the groups it holds (the first kHeld) or reads again.
+// With rows one after the other (an 8-byte load a row) 8192 tiles took 12.8 us
+// instead of 6.8, and any other number 0.2 to 2 us more.
 // With plan a skipped pass leaves at once; with plan_out (the first pass)
 // work-group 0 forms the plan from the tiles' OR and AND.
 // Against a digit-major table (a strided write by every count, a look-back scan
-// of 256 entries per tile, a gather by every scatter), us per request: 4,200,000
-// values of 12 bits, kernels 81.5 -> 75.7, of 31 bits 181.9 -> 173.7 (count 10.0
-// -> 10.1, plan 2.4 -> none, scan 5.0 -> 4.8, scatter 20.9 -> 20.6); 2^25 of 12
-// bits 329.5 -> 319.6; 2^26 of 16 bits 689 -> 686 (counts 51.1 + 42.1 -> 45.2 +
-// 35.6, scan 7.0 -> 12.6, scatters 162.7 + 180.0 -> 158.5 + 177.1).
+// of 256 entries per tile, a gather by every scatter, a launch for the plan), us
+// of kernels a request: 4,200,000 values of 12 bits 81.5 -> 74.5, of 31 bits 181.9
+// -> 172.5; 2^24 of 12 bits 182.0 -> 174.8; 2^26 of 16 bits 689 -> 671 (counts
+// 51.1 + 42.1 -> 45.4 + 35.8, scan 7.0 -> 6.8, scatters 162.7 + 180.0 -> 156.9 +
+// 179.4).
 template <int kBits, int kCols>
 __global__ __launch_bounds__(1024) void k_rows_scan(const uint16_t* __restrict__ rows, uint32_t T,
                                                     uint32_t* __restrict__ pre, uint32_t* __restrict__ totals,
                                                     const SortPlan* __restrict__ plan, uint32_t pass,
                                                     const uint32_t* __restrict__ orand, SortPlan* __restrict__ plan_out) {
-  constexpr uint32_t kD = 1u << kBits, kChunks = 1024 / kCols, kGroups = kD / 4 / kCols, kHeld = 8;
+  constexpr uint32_t kD = 1u << kBits, kChunks = 1024 / kCols, kGroups = kD / 4 / kCols, kHeld = 2;
   __shared__ uint32_t s_sum[4 * kCols][kChunks];
   __shared__ uint32_t s_or[16], s_and[16];
   const uint32_t tid = threadIdx.x, w = tid / 64, lane = lane_id();
@@ -702,20 +710,32 @@ __global__ __launch_bounds__(1024) void k_rows_scan(const uint16_t* __restrict__
   // work-groups of one XCD take neighbouring digits, so that they share lines in its L2
   const uint32_t wg = kGroups >= 8 ? blockIdx.x % 8 * (kGroups / 8) + blockIdx.x / 8 : blockIdx.x;
   const uint32_t c = tid % kCols, chunk = tid / kCols, col = wg * kCols + c;
-  const uint32_t per = (T + kChunks - 1) / kChunks, r0 = min(T, chunk * per), r1 = min(T, r0 + per);
-  const uint2* src = reinterpret_cast<const uint2*>(rows) + col;
+  const uint32_t G = (T + kRowGroup - 1) / kRowGroup, per = (G + kChunks - 1) / kChunks;
+  const uint32_t g0 = min(G, chunk * per), g1 = min(G, g0 + per);
+  const u32x4* src = reinterpret_cast<const u32x4*>(rows) + 2 * col;
+  // the sums over a group's rows, digits packed in pairs (four counts of up to 8192 in 16 bits)
+  const auto load = [&](uint32_t g) {
+    u32x4 lo = src[(uint64_t)g * (kD / 2)], hi = src[(uint64_t)g * (kD / 2) + 1];
+    if (g == G - 1) {  // the last group: rows from T on don't exist
+      const uint32_t left = T - g * kRowGroup;
+      if (left < 2) lo.z = lo.w = 0u;
+      if (left < 3) hi.x = hi.y = 0u;
+      if (left < 4) hi.z = hi.w = 0u;
+    }
+    return make_uint2(lo.x + lo.z + hi.x + hi.z, lo.y + lo.w + hi.y + hi.w);
+  };
   uint32_t sum[4] = {0, 0, 0, 0};
   uint2 held[kHeld];
 #pragma unroll
-  for (uint32_t i = 0; i < kHeld; ++i) held[i] = r0 + i < r1 ? src[(uint64_t)(r0 + i) * (kD / 4)] : uint2{0u, 0u};
+  for (uint32_t i = 0; i < kHeld; ++i) held[i] = g0 + i < g1 ? load(g0 + i) : make_uint2(0u, 0u);
 #pragma unroll
   for (uint32_t i = 0; i < kHeld; ++i) {
     const uint2 v = held[i];
     sum[0] += v.x & 0xFFFFu, sum[1] += v.x >> 16, sum[2] += v.y & 0xFFFFu, sum[3] += v.y >> 16;
   }
-#pragma unroll 8
-  for (uint32_t r = r0 + kHeld; r < r1; ++r) {
-    const uint2 v = src[(uint64_t)r * (kD / 4)];
+#pragma unroll 4
+  for (uint32_t g = g0 + kHeld; g < g1; ++g) {
+    const uint2 v = load(g);
     sum[0] += v.x & 0xFFFFu, sum[1] += v.x >> 16, sum[2] += v.y & 0xFFFFu, sum[3] += v.y >> 16;
   }
 #pragma unroll
@@ -742,13 +762,13 @@ __global__ __launch_bounds__(1024) void k_rows_scan(const uint16_t* __restrict__
 #pragma unroll
   for (uint32_t i = 0; i < kHeld; ++i) {
     const uint2 v = held[i];
-    if (r0 + i < r1 && (r0 + i) % kRowGroup == 0) dst[(uint64_t)((r0 + i) / kRowGroup) * (kD / 4)] = run;
+    if (g0 + i < g1) dst[(uint64_t)(g0 + i) * (kD / 4)] = run;
     run.x += v.x & 0xFFFFu, run.y += v.x >> 16, run.z += v.y & 0xFFFFu, run.w += v.y >> 16;
   }
-#pragma unroll 8
-  for (uint32_t r = r0 + kHeld; r < r1; ++r) {
-    const uint2 v = src[(uint64_t)r * (kD / 4)];
-    if (r % kRowGroup == 0) dst[(uint64_t)(r / kRowGroup) * (kD / 4)] = run;
+#pragma unroll 4
+  for (uint32_t g = g0 + kHeld; g < g1; ++g) {
+    const uint2 v = load(g);
+    dst[(uint64_t)g * (kD / 4)] = run;
     run.x += v.x & 0xFFFFu, run.y += v.x >> 16, run.z += v.y & 0xFFFFu, run.w += v.y >> 16;
   }
 }
@@ -775,7 +795,7 @@ __device__ __forceinline__ TileRows tile_rows(const RowTable& rt, uint32_t ntile
 // Counts of one tile into its row.  The first pass also zeroes the encoder's
 // look-back words and *reject, and (kOrAnd) records the OR and AND of the
 // tile's keys.
-template <int kBlock, int kItems, int kRounds, class SK>
+template <int kBlock, int kItems, int kRounds, bool kGrouped, class SK>
 __global__ __launch_bounds__(kBlock) void k_radix_count_fixed(const SK* __restrict__ keys, uint16_t* __restrict__ rows,
                                                        uint32_t shift, uint32_t bits, uint32_t n_cap, uint32_t ntiles,
                                                        uint32_t* __restrict__ reject,
@@ -784,11 +804,11 @@ __global__ __launch_bounds__(kBlock) void k_radix_count_fixed(const SK* __restri
   clear_words(cw);
   if (reject && blockIdx.x == 0 && threadIdx.x == 0) *reject = 0u;
   const uint32_t tile = xcd_tile(blockIdx.x, ntiles);
-  uint16_t* const row = rows + ((uint64_t)tile << bits);
+  uint16_t* const row = rows + ((uint64_t)(kGrouped ? tile / kRowGroup * kRowGroup : tile) << bits);
   upsweep_tile<kBlock, kTile, kRounds, false>(
       keys, shift, tile * kTile, tile_len(tile, kTile, n_cap, d_n),
       [&](uint32_t d, uint32_t c) {
-        if (d >> bits == 0u) row[d] = (uint16_t)c;
+        if (d >> bits == 0u) row[kGrouped ? grouped_digit(tile, d) : d] = (uint16_t)c;
       },
       tile, nullptr, (1u << bits) - 1u);
 }
@@ -818,7 +838,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_radix_scatter_fixed(PassIoT<SK, D
 // Plan-driven passes over uint32 keys (8-bit digits).  With kSum the first
 // scatter forms the plan from the tiles' OR and AND in every work-group, and
 // work-group 0 stores it for the later launches.
-template <bool kFirst, int kBlock, int kItems>
+template <bool kFirst, int kBlock, int kItems, bool kGrouped>
 __global__ __launch_bounds__(kBlock) void k_radix_count(PassBuffers buf, const SortPlan* __restrict__ plan,
                                                             uint16_t* __restrict__ rows, uint32_t* __restrict__ orand,
                                                             uint32_t pass, uint32_t n_cap, uint32_t ntiles,
@@ -832,10 +852,10 @@ __global__ __launch_bounds__(kBlock) void k_radix_count(PassBuffers buf, const S
     keys = pass_io(buf, active, pass).src_keys;
   }
   const uint32_t tile = xcd_tile(blockIdx.x, ntiles);
-  uint16_t* const row = rows + (uint64_t)tile * kRadix;
+  uint16_t* const row = rows + (uint64_t)(kGrouped ? tile / kRowGroup * kRowGroup : tile) * kRadix;
   upsweep_tile<kBlock, kTile, kFirst ? 1 : -1, kFirst>(
       keys, pass * kRadixBits, tile * kTile, tile_len(tile, kTile, n_cap, d_n),
-      [&](uint32_t d, uint32_t c) { row[d] = (uint16_t)c; }, tile, orand);
+      [&](uint32_t d, uint32_t c) { row[kGrouped ? grouped_digit(tile, d) : d] = (uint16_t)c; }, tile, orand);
 }
 
 template <bool kFirst, int kStarts, int kBlock, int kItems>
@@ -1079,9 +1099,10 @@ struct RowScratch {
   uint32_t *pre = nullptr, *totals = nullptr;
   bool ok = false;
   RowScratch(Env& env, uint32_t ntiles, bool scanned) {
-    rows = static_cast<uint16_t*>(env.scratch((uint64_t)ntiles * kRadix * 2));
+    const uint64_t groups = ((uint64_t)ntiles + kRowGroup - 1) / kRowGroup;
+    rows = static_cast<uint16_t*>(env.scratch(groups * kRowGroup * kRadix * 2));
     if (scanned) {
-      pre = static_cast<uint32_t*>(env.scratch(((uint64_t)ntiles + kRowGroup - 1) / kRowGroup * kRadix * 4));
+      pre = static_cast<uint32_t*>(env.scratch(groups * kRadix * 4));
       totals = static_cast<uint32_t*>(env.scratch(kRadix * 4));
     }
     ok = rows && (!scanned || (pre && totals));
@@ -1090,7 +1111,8 @@ struct RowScratch {
 };
 
 // Beyond 2048 tiles a work-group takes 4 digits instead of 16 (4096 tiles of
-// 6-bit digits 8.9 -> 7.6 us, 8192 of 8-bit ones 17.7 -> 12.0; the same at 2048).
+// 6-bit digits 8.9 -> 7.6 us, 8192 of 8-bit ones 17.7 -> 12.0, the same at 2048,
+// measured with rows one after the other).
 int scan_rows(Env& env, const RowScratch& rs, uint32_t bits, uint32_t ntiles, const SortPlan* plan, uint32_t pass,
               const uint32_t* orand, SortPlan* plan_out) {
   env.prof_begin("radix_rows_scan");
@@ -1130,7 +1152,7 @@ int rows_pass16(Env& env, const PassIoT<SK, DK>& io, const RowScratch& rs, uint3
   constexpr int kCount = kStarts == kScanned ? 256 : kBlock;
   const dim3 g(ntiles), b(kBlock);
   env.prof_begin(kCheck ? "radix_upsweep0" : "radix_upsweep");
-  k_radix_count_fixed<kCount, kBlock * kItems / kCount, kCheck ? 1 : -1, SK>
+  k_radix_count_fixed<kCount, kBlock * kItems / kCount, kCheck ? 1 : -1, kStarts == kScanned, SK>
       <<<g, dim3(kCount), 0, env.stream()>>>(io.src_keys, rs.rows, shift, bits, nn, ntiles, reject, d_n, cw);
   env.prof_end(kCheck ? "radix_upsweep0" : "radix_upsweep");
   int rc = check_launch(env, "radix_count launch");
@@ -1211,10 +1233,10 @@ int rows_sort32(Env& env, const uint32_t* keys, const uint32_t* rows_in, uint32_
     const char* name = pass ? "radix_upsweep" : "radix_upsweep0";
     env.prof_begin(name);
     if (pass == 0)
-      k_radix_count<true, kCount, kTile / kCount><<<g, bc, 0, env.stream()>>>(buf, plan, rs.rows, orand, pass, nn,
+      k_radix_count<true, kCount, kTile / kCount, kStarts == kScanned><<<g, bc, 0, env.stream()>>>(buf, plan, rs.rows, orand, pass, nn,
                                                                                   ntiles, d_n, cw);
     else
-      k_radix_count<false, kCount, kTile / kCount><<<g, bc, 0, env.stream()>>>(buf, plan, rs.rows, orand, pass, nn,
+      k_radix_count<false, kCount, kTile / kCount, kStarts == kScanned><<<g, bc, 0, env.stream()>>>(buf, plan, rs.rows, orand, pass, nn,
                                                                                    ntiles, d_n, cw);
     env.prof_end(name);
     int rc = check_launch(env, "radix_upsweep launch");
