@@ -466,8 +466,11 @@ KA_API int ka_batch_plan_run(ka_batch_plan* plan, const uint32_t* values, uint32
 KA_API int ka_batch_plan_run_batch(ka_batch_plan* plan, const uint32_t* values, const uint32_t* req_off,
                                    uint32_t nreq, uint32_t flags);
 /* Waits for the last run and returns its outputs as host arrays (free with
- * ka_wah_batch_result_free); KA_E_ARG if a value was at or above 2^value_bits.
- * An any-batch plan returns its last batch's requests only. */
+ * ka_wah_batch_result_free); KA_E_ARG if a value was at or above 2^value_bits,
+ * KA_E_STATE if a plan of one batch shape has not run or the last run failed.
+ * An any-batch plan returns its last batch's requests only (none before the
+ * first); a batch whose upload failed is not taken: the result stays the last
+ * one's, and ka_batch_plan_run is refused (KA_E_STATE) until a batch is. */
 KA_API int ka_batch_plan_result(ka_batch_plan* plan, ka_wah_batch_result* out);
 /* The tile shape the runs use (-1 before the first run of an autotuned plan)
  * and, for an autotuned plan, the time of its first run with each shape

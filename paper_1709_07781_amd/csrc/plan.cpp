@@ -72,6 +72,8 @@ struct Plan {
   uint32_t* h_tab[2] = {nullptr, nullptr};
   hipEvent_t tab_done[2] = {nullptr, nullptr};
   int tab_next = 0;
+  bool table_ok = true;  // the table on the device is that of n and nreq
+  bool holds = false;    // the outputs are those of the values and table last run
   hipStream_t s = nullptr;
   void* mem = nullptr;  // one device allocation for everything
   uint32_t *input = nullptr, *req_off = nullptr, *keys = nullptr, *offsets = nullptr, *words = nullptr;
@@ -202,9 +204,16 @@ static int plan_build(ka_system* sys, const uint32_t* req_off, uint64_t n, uint3
         return set_error(KA_E_OOM, "plan: pinned request tables");
       }
   }
-  // the request table is uploaded (a fixed plan's once and for all)
-  if (hipMemcpyAsync(p->req_off, req_off, 4 * (nreq + 1ull), hipMemcpyHostToDevice, p->s) != hipSuccess ||
-      hipStreamSynchronize(p->s) != hipSuccess) {
+  // The request table is uploaded (a fixed plan's once and for all); an
+  // any-batch plan also gets the outputs of the empty batch that it starts with.
+  const uint64_t none[5] = {0, nreq, 0, nreq + 1ull, nreq + 1ull};
+  hipError_t up = hipMemcpyAsync(p->req_off, req_off, 4 * (nreq + 1ull), hipMemcpyHostToDevice, p->s);
+  if (any_batch) {
+    for (uint32_t* start : {p->key_start, p->word_start})
+      if (up == hipSuccess) up = hipMemcpyAsync(start, req_off, 4 * (nreq + 1ull), hipMemcpyHostToDevice, p->s);
+    if (up == hipSuccess) up = hipMemcpyAsync(p->lens, none, sizeof(none), hipMemcpyHostToDevice, p->s);
+  }
+  if (up != hipSuccess || hipStreamSynchronize(p->s) != hipSuccess) {
     (void)hipGetLastError();
     plan_free(p);
     return set_error(KA_E_DEVICE, "plan: initialisation");
@@ -249,6 +258,7 @@ static int plan_build(ka_system* sys, const uint32_t* req_off, uint64_t n, uint3
   if (any_batch) {  // the plan starts out holding an empty batch
     p->n = 0;
     p->nreq = 0;
+    p->holds = true;
   }
   *out = p;
   return KA_OK;
@@ -294,20 +304,20 @@ KA_API int ka_batch_plan_stream(ka_batch_plan* plan, void** stream) {
   return KA_OK;
 }
 
-// Values (and, of an any-batch plan, the table in t) to the plan's buffers.
+// n values (and, of an any-batch plan, the table in t) to the plan's buffers.
 // Small ones from the host go through pinned memory and one kernel, larger ones
 // by copy commands.
 constexpr uint64_t kPlanStaged = 8ull << 20;
-static int plan_upload(ka_batch_plan* plan, const uint32_t* values, uint32_t flags, const uint32_t* t) {
+static int plan_upload(ka_batch_plan* plan, const uint32_t* values, uint64_t n, uint32_t flags, const uint32_t* t) {
   System* sys = plan->sys;
-  const uint64_t bytes = values ? 4 * plan->n : 0, tab = t ? 4 * (plan->nreq_cap + 1ull) : 0;
+  const uint64_t bytes = values ? 4 * n : 0, tab = t ? 4 * (plan->nreq_cap + 1ull) : 0;
   if (!(flags & KA_WAH_INPUT_DEVICE) && bytes + tab <= kPlanStaged) {
     CopyList l;
     if (t) l.add(t, plan->req_off, plan->nreq_cap + 1ull);
     void* st = nullptr;
     if (bytes && (st = sys->stage.get(sys, bytes))) {
       std::memcpy(st, values, bytes);
-      l.add(static_cast<const uint32_t*>(st), plan->input, plan->n);
+      l.add(static_cast<const uint32_t*>(st), plan->input, n);
     }
     if (!bytes || st) {
       int rc = launch_copy(plan->env, l);
@@ -336,6 +346,7 @@ static int plan_upload(ka_batch_plan* plan, const uint32_t* values, uint32_t fla
 }
 
 static int plan_replay(ka_batch_plan* plan) {
+  plan->holds = false;
   if (plan->chosen < 0) {
     // Autotuning: the first run times every recorded shape on these values
     // (each leaves the same outputs) and keeps the fastest for later runs.
@@ -370,12 +381,11 @@ static int plan_replay(ka_batch_plan* plan) {
     (void)hipEventDestroy(a);
     (void)hipEventDestroy(b);
     plan->chosen = best;
-    return KA_OK;
-  }
-  if (hipGraphLaunch(plan->exec[plan->chosen], plan->s) != hipSuccess) {
+  } else if (hipGraphLaunch(plan->exec[plan->chosen], plan->s) != hipSuccess) {
     (void)hipGetLastError();
     return set_error(KA_E_LAUNCH, "plan: graph launch");
   }
+  plan->holds = true;
   return KA_OK;
 }
 
@@ -384,7 +394,8 @@ KA_API int ka_batch_plan_run(ka_batch_plan* plan, const uint32_t* values, uint32
   if (!plan) return set_error(KA_E_ARG, "null plan");
   int rc = plan->sys->use_device();
   if (rc) return rc;
-  if ((rc = plan_upload(plan, values, flags, nullptr))) return rc;
+  if (!plan->table_ok) return set_error(KA_E_STATE, "the plan's last batch did not arrive");
+  if ((rc = plan_upload(plan, values, plan->n, flags, nullptr))) return rc;
   return plan_replay(plan);
   KA_GUARD_END
 }
@@ -415,13 +426,21 @@ KA_API int ka_batch_plan_run_batch(ka_batch_plan* plan, const uint32_t* values, 
   uint32_t* t = plan->h_tab[k];
   std::memcpy(t, req_off, 4 * (nreq + 1ull));
   for (uint32_t j = nreq + 1; j <= plan->nreq_cap; ++j) t[j] = (uint32_t)n;
+  // The plan's batch is the new one once its upload is queued; after a failure
+  // the outputs are still the last batch's, but part of the new one may arrive.
+  plan->table_ok = false;
+  rc = plan_upload(plan, values, n, flags, t);
+  if (!rc && hipEventRecord(plan->tab_done[k], plan->s) != hipSuccess) {
+    (void)hipGetLastError();
+    rc = set_error(KA_E_DEVICE, "plan: table upload");
+  }
+  if (rc) {
+    if (hipStreamSynchronize(plan->s) != hipSuccess) (void)hipGetLastError();  // nothing may still read the table
+    return rc;
+  }
+  plan->table_ok = true;
   plan->n = n;
   plan->nreq = nreq;
-  if ((rc = plan_upload(plan, values, flags, t))) return rc;
-  if (hipEventRecord(plan->tab_done[k], plan->s) != hipSuccess) {
-    (void)hipGetLastError();
-    return set_error(KA_E_DEVICE, "plan: table upload");
-  }
   plan->tab_next = k ^ 1;
   return plan_replay(plan);
   KA_GUARD_END
@@ -437,6 +456,7 @@ KA_API int ka_batch_plan_shape(ka_batch_plan* plan, int* shape, float* ms, uint3
 KA_API int ka_batch_plan_result(ka_batch_plan* plan, ka_wah_batch_result* out) {
   KA_GUARD_BEGIN
   if (!plan || !out) return set_error(KA_E_ARG, "null argument");
+  if (!plan->holds) return set_error(KA_E_STATE, "the plan holds no finished run");
   int rc = plan->sys->use_device();
   if (rc) return rc;
   uint64_t len[5];
@@ -472,6 +492,8 @@ KA_API int ka_batch_plan_result(ka_batch_plan* plan, ka_wah_batch_result* out) {
   }
   if (st.p) std::memcpy(len, st.p, sizeof(len));
   if (len[3] == 0) return set_error(KA_E_ARG, "a value is at or above 2^value_bits");
+  if (len[0] > cap[0] || len[1] != len[0] + plan->nreq_cap || len[2] > cap[2] || len[3] != tab || len[4] != tab)
+    return set_error(KA_E_DEVICE, "inconsistent batch index lengths");
   // an any-batch plan's padding (empty requests after the real ones) adds one
   // offsets entry and one table entry each, at the ends
   const uint64_t pad = plan->nreq_cap - plan->nreq;
