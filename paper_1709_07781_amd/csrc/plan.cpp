@@ -483,7 +483,10 @@ KA_API int ka_batch_plan_result(ka_batch_plan* plan, ka_wah_batch_result* out) {
     l.add(reinterpret_cast<const uint32_t*>(plan->lens), reinterpret_cast<uint32_t*>(st.p), 10);
     for (int i = 0; i < 5; ++i)
       if (cap[i]) l.add(src[i], reinterpret_cast<uint32_t*>(st.p + at[i]), cap[i], plan->lens + i);
-    if ((rc = launch_copy(plan->env, l))) return rc;
+    if ((rc = launch_copy(plan->env, l))) {  // the error may be an earlier call's, and the copy queued
+      (void)hipStreamSynchronize(plan->s);
+      return rc;
+    }
   }
   if (hipStreamSynchronize(plan->s) != hipSuccess ||
       (!st.p && hipMemcpy(len, plan->lens, sizeof(len), hipMemcpyDeviceToHost) != hipSuccess)) {

@@ -1757,7 +1757,10 @@ static bool stage_outputs(System* sys, Ref* const* refs, const uint64_t* caps, u
           std::min(known ? refs[i]->len : caps[i], refs[i]->cap), known ? nullptr : refs[i]->d_len);
   }
   CmdEnv env(sys, si);
-  if (launch_copy(env, l) != kOk) return false;
+  if (launch_copy(env, l) != kOk) {  // the error may be an earlier call's, and the copy queued
+    (void)hipStreamSynchronize(env.stream());
+    return false;
+  }
   so->done = sys->get_event();
   if (!so->done || hipEventRecord(so->done, env.stream()) != hipSuccess) {
     (void)hipGetLastError();

@@ -1,5 +1,5 @@
-"""GPU tests of a batch plan's states: a result before the first run, and after a
-batch whose upload was reported as failed."""
+"""GPU tests of a batch plan's states: a result before the first run, after a
+batch whose upload was reported as failed and after a copy that was."""
 import ctypes
 
 import numpy as np
@@ -102,5 +102,29 @@ def test_failed_upload_keeps_the_last_batch(sess, second):
         assert e.value.code == ka.KA_E_STATE
         plan.run_batch(v2, off2)
         _check(plan.result(), off2, v2)
+    finally:
+        plan.close()
+
+
+def test_result_after_a_failed_copy(sess):
+    """A copy of the outputs that was reported as failed may have been queued: its pinned memory is not handed out
+    before the plan's stream has passed it, and the next result is exact."""
+    import torch
+    import paper_1709_07781_amd as ka
+    from paper_1709_07781_amd.session import BatchPlan
+    off, v = _batch(13, [200_000, 3, 100_000], 8)
+    plan = BatchPlan(sess, off, 8)
+    try:
+        plan.run(v)
+        plan.result()
+        if not _leave_error():
+            ka.lib.hipGetLastError()
+            pytest.skip("no error is kept past a call that succeeds")
+        for _ in range(300):  # keeps the stream busy for longer than the call takes
+            plan.run()
+        with pytest.raises(ka.KaError):
+            plan.result()
+        assert torch.cuda.ExternalStream(plan.stream_handle()).query()
+        _check(plan.result(), off, v)
     finally:
         plan.close()
