@@ -194,6 +194,15 @@ struct BatchLens {
   uint64_t *keys, *offsets, *words, *key_start, *word_start;
   LenHost host;
 };
+// Lookup entries that a batch of nreq requests and n values makes at most, the
+// entries of rejected requests among them: a value out of range is cut to
+// value_bits (in the segmented sort, of values of at most 16 bits, to an even
+// number of bits) before the entries are made.
+inline uint64_t batch_keys_max(uint64_t n, uint32_t nreq, uint32_t value_bits) {
+  const uint32_t bits = value_bits <= 16 ? (value_bits + 1u) & ~1u : value_bits;
+  const uint64_t most = bits < 32 ? (uint64_t)nreq << bits : n;
+  return most < n ? most : n;
+}
 int launch_wah_batch(Env& env, const uint32_t* values, uint64_t n, const uint32_t* req_off, uint32_t nreq,
                      uint32_t value_bits, uint32_t* keys, uint32_t* offsets, uint32_t* words, uint32_t* key_start,
                      uint32_t* word_start, const BatchLens& lens, int sort_shape = 0,

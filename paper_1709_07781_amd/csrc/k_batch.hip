@@ -260,7 +260,9 @@ struct PackedPairs {
 };
 
 // The n <= kSmallMax values of a request sorted into s (packed pairs); whether
-// a value is at or above 2^value_bits (value_bits <= 32 - kSmallRowBits).
+// a value is at or above 2^value_bits (value_bits <= 32 - kSmallRowBits).  Such a
+// value is cut to value_bits, so that a rejected request fills no more of the
+// tables than batch_keys_max.
 // Starts and ends with a barrier.  (A radix sort by two 8-bit digits; the 55
 // compare-exchange steps of a bitonic sort, a barrier each, took 32 us of a
 // batch of 256 requests.)
@@ -268,11 +270,12 @@ __device__ __forceinline__ bool sort_request(const uint32_t* __restrict__ values
                                              LdsSort<kSmallBlock>& S, uint32_t value_bits) {
   __syncthreads();
   if (n == 0) return false;  // uniform over the work-group
+  const uint32_t mask = (1u << value_bits) - 1u;
   uint32_t keys_or;
   if (n <= (uint32_t)kSmallBlock)  // a ranking step per value and work-item
-    keys_or = lds_sort<kSmallBlock, 1>(values, n, PackedPairs{s}, S);
+    keys_or = lds_sort<kSmallBlock, 1>(values, n, PackedPairs{s}, S, mask);
   else
-    keys_or = lds_sort<kSmallBlock, kSmallPer>(values, n, PackedPairs{s}, S);
+    keys_or = lds_sort<kSmallBlock, kSmallPer>(values, n, PackedPairs{s}, S, mask);
   return (keys_or >> value_bits) != 0u;
 }
 

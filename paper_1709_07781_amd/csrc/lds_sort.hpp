@@ -12,14 +12,15 @@ struct LdsSort {
   uint32_t scan[kWaves], k_or[kWaves], k_and[kWaves];
 };
 
-// n <= kBlock * kItems values (n > 0): element i's value and row i are put in
-// order of value, equal values in row order, into store; wave w owns 64 kItems
-// consecutive elements.  8-bit digits over the bits that differ between the
-// values at all, ranked inside each wave by ballots; about 1.2 us a digit at
-// kItems = 1.  Returns the OR of the values.  Ends with a barrier.
+// n <= kBlock * kItems values (n > 0): element i's value (its bits in mask) and
+// row i are put in order of value, equal values in row order, into store; wave w
+// owns 64 kItems consecutive elements.  8-bit digits over the bits that differ
+// between the values at all, ranked inside each wave by ballots; about 1.2 us a
+// digit at kItems = 1.  Returns the OR of the values, all their bits.  Ends with
+// a barrier.
 template <int kBlock, int kItems, class Store>
 __device__ __forceinline__ uint32_t lds_sort(const uint32_t* __restrict__ values, uint32_t n, const Store& store,
-                                             LdsSort<kBlock>& S) {
+                                             LdsSort<kBlock>& S, uint32_t mask = ~0u) {
   constexpr int kWaves = kBlock / 64;
   static_assert(kBlock >= 256, "one work-item per digit");
   const uint32_t tid = threadIdx.x, w = tid / 64, lane = lane_id();
@@ -35,6 +36,7 @@ __device__ __forceinline__ uint32_t lds_sort(const uint32_t* __restrict__ values
   for (int i = 0; i < kItems; ++i) {
     o |= key[i];
     if (row[i] < n) a &= key[i];
+    key[i] &= mask;
   }
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) {
@@ -52,7 +54,7 @@ __device__ __forceinline__ uint32_t lds_sort(const uint32_t* __restrict__ values
     o |= S.k_or[ww];
     a &= S.k_and[ww];
   }
-  const uint32_t diff = (uint32_t)__builtin_amdgcn_readfirstlane((int)(o ^ a));  // bits in which values differ
+  const uint32_t diff = (uint32_t)__builtin_amdgcn_readfirstlane((int)((o ^ a) & mask));  // bits in which values differ
   const uint32_t lo = diff ? (uint32_t)__builtin_ctz(diff) : 32u, hi = diff ? 32u - (uint32_t)__builtin_clz(diff) : 0u;
   if (!diff) {  // all values equal: in order already
 #pragma unroll

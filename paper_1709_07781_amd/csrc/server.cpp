@@ -287,8 +287,7 @@ Batch* Server::launch(std::vector<SrvReq*>& take, uint64_t bytes) {
   };
   const uint64_t d_vw = place(4 * nw), d_vs = place(4 * ns), d_vc = place(4 * nc);
   const uint64_t d_rw = place(4 * (rw + 1ull)), d_rs = place(4 * (rs + 1ull));
-  // a request has at most 2^value_bits distinct values: that bounds the lookup tables
-  const uint64_t dcap = value_bits >= 32 ? nw : std::min<uint64_t>(nw, (uint64_t)rw << value_bits);
+  const uint64_t dcap = batch_keys_max(nw, rw, value_bits);  // bounds the lookup tables
   const uint64_t d_keys = place(4 * dcap), d_offs = place(4 * (dcap + rw)), d_words = place(8 * nw);
   const uint64_t d_ks = place(4 * (rw + 1ull)), d_ws = place(4 * (rw + 1ull)), d_lens = place(5 * 8);
   const uint64_t d_bad = place(4 * (rw + 1ull));  // per-request rejection flags
