@@ -309,6 +309,7 @@ void* HostStage::get(System* sys, uint64_t bytes) {
   const uint64_t c = Pool::size_class(bytes);
   {
     std::lock_guard<std::mutex> g(mu_);
+    if (closed_) return nullptr;
     for (size_t i = 0; i < busy_.size();) {
       const hipError_t q = hipEventQuery(busy_[i].done);
       if (q != hipSuccess) (void)hipGetLastError();  // "not ready" must not stay pending
@@ -341,16 +342,26 @@ void* HostStage::get(System* sys, uint64_t bytes) {
 void HostStage::retire(System* sys, void* p, hipEvent_t done) {
   (void)sys;
   std::lock_guard<std::mutex> g(mu_);
+  if (closed_) {
+    (void)hipEventSynchronize(done);
+    (void)hipEventDestroy(done);
+    (void)hipHostFree(p);
+    return;
+  }
   busy_.push_back({p, sizes_[p], done});
 }
 
 void HostStage::give_back(void* p) {
   std::lock_guard<std::mutex> g(mu_);
-  free_.emplace(sizes_[p], p);
+  if (closed_)
+    (void)hipHostFree(p);
+  else
+    free_.emplace(sizes_[p], p);
 }
 
 void HostStage::destroy(System* sys) {
   std::lock_guard<std::mutex> g(mu_);
+  closed_ = true;
   for (auto& b : busy_) {
     hipEventSynchronize(b.done);
     sys->put_event(b.done);

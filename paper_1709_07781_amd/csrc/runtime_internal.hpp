@@ -62,9 +62,11 @@ class Pool {
 // ---- pinned host staging for value inputs -------------------------------------
 class HostStage {
  public:
-  void* get(System* sys, uint64_t bytes);                  // pinned buffer of >= bytes
+  void* get(System* sys, uint64_t bytes);                  // pinned buffer of >= bytes; null once destroyed
   void retire(System* sys, void* p, hipEvent_t done);      // reusable once `done` completed
   void give_back(void* p);                                 // reusable at once
+  // Frees the buffers; those still out are freed when they come back (a plan or a
+  // result may outlive its system).
   void destroy(System* sys);
 
  private:
@@ -77,6 +79,7 @@ class HostStage {
   std::vector<Entry> busy_;
   std::multimap<uint64_t, void*> free_;
   std::unordered_map<void*, uint64_t> sizes_;
+  bool closed_ = false;
 };
 
 // ---- lengths on the host -----------------------------------------------------------
