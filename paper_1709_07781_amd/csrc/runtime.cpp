@@ -1731,7 +1731,8 @@ static int read_lengths3(System* sys, Ref* const r[3], uint64_t len[3]) {
 // queued behind the ones that make them, which reads the lengths on the device:
 // the host waits once for the whole request.  (Lengths, then a copy each, took two
 // waits and three copy commands.)  Their places are those of the capacities, so
-// only outputs up to this many bytes in all go this way.
+// only outputs up to this many bytes in all go this way; an index whose
+// capacities exceed it is staged once its lengths are known, if these do not.
 constexpr uint64_t kStagedMax = 8ull << 20;
 struct StagedOutputs {
   System* sys = nullptr;
@@ -1854,6 +1855,7 @@ KA_API int ka_wah_index(ka_system* sys, const uint32_t* values, uint64_t n, uint
     if (!rc) {
       void* const dst[3] = {r.keys, r.offsets, r.words};
       const uint64_t bytes[3] = {D * 4, (D + 1) * 4, W * 4};
+      if (!staged && !so.p) staged = stage_outputs(sys, outs, lens, 3, outs[0]->home, &so);
       if (staged) KA_HIP_RC(rc, hipEventSynchronize(so.done), "result read-back");
       for (int i = 0; i < 3 && !rc; ++i) {
         if (staged)
