@@ -249,10 +249,13 @@ __device__ __forceinline__ DenseEmits dense_emits(uint32_t x, uint32_t p) {
 }
 
 // Summary of a tile of groups: the words it emits, its last non-empty group's
-// index + 1 (0: none), its leading full groups.
+// index + 1 (0: none), its leading full groups.  Of many tiles (last1 not null)
+// the last two also over every 64 and every 4096 of them.
 struct TileSums {
   uint32_t *words, *last, *lead;
+  uint32_t *last1, *lead1, *last2, *lead2;
 };
+constexpr uint32_t kLevel = 64;  // entries of a level in one of the next: a wave's window
 
 template <int kFmt, int kOutFmt>
 __global__ __launch_bounds__(kBlock) void k_combine(Bitmap a, Bitmap b, uint32_t ngroups, uint32_t op,
@@ -335,6 +338,95 @@ __device__ __forceinline__ uint32_t wave_words_before(const uint32_t* __restrict
   return wave_sum(s);
 }
 
+// The last entry that is not 0 of v[lo .. t), or 0, by one wave.
+__device__ __forceinline__ uint32_t wave_last_before(const uint32_t* __restrict__ v, uint32_t lo, uint32_t t) {
+  for (int64_t j = (int64_t)t - 1; j >= (int64_t)lo; j -= 64) {
+    const int64_t i = j - (int64_t)lane_id();
+    const uint32_t l = i >= (int64_t)lo ? v[i] : 0u;
+    const uint64_t some = __ballot(l != 0u);
+    if (some) return (uint32_t)__builtin_amdgcn_readlane((int)l, (int)__builtin_ctzll(some));
+  }
+  return 0u;
+}
+
+// Adds the leading full groups of v[t .. end) to ext, by one wave, up to the first
+// entry that is not `whole` (then true).
+__device__ __forceinline__ bool wave_lead_after(const uint32_t* __restrict__ v, uint32_t t, uint32_t end,
+                                                uint32_t whole, uint32_t& ext) {
+  for (uint64_t j = t; j < end; j += 64) {
+    const uint64_t i = j + lane_id();
+    const uint32_t l = i < end ? v[i] : 0u;
+    const uint64_t stop = __ballot(i < end && l != whole);
+    if (stop) {
+      const uint32_t at = (uint32_t)__builtin_ctzll(stop);
+      ext += at * whole + (uint32_t)__builtin_amdgcn_readlane((int)l, (int)at);
+      return true;
+    }
+    ext += (uint32_t)min((uint64_t)64, end - j) * whole;
+  }
+  return false;
+}
+
+// The last non-empty group before tile t (index + 1, or 0) and the full groups
+// right after it, by one wave each: the tiles beside it, or up to a window of
+// them, of blocks of 64 and then blocks of 4096.
+__device__ __forceinline__ uint32_t wave_carry(const TileSums& sums, uint32_t t) {
+  if (!sums.last1) return wave_last_before(sums.last, 0u, t);
+  const uint32_t b = t / kLevel, c = b / kLevel;
+  uint32_t r = wave_last_before(sums.last, b * kLevel, t);
+  if (!r) r = wave_last_before(sums.last1, c * kLevel, b);
+  return r ? r : wave_last_before(sums.last2, 0u, c);
+}
+__device__ __forceinline__ uint32_t wave_full_after(const TileSums& sums, uint32_t t, uint32_t ntiles) {
+  uint32_t ext = 0;
+  if (!sums.last1) {
+    (void)wave_lead_after(sums.lead, t + 1u, ntiles, kTile, ext);
+    return ext;
+  }
+  const uint32_t b = t / kLevel, c = b / kLevel;
+  const uint32_t nb = (ntiles + kLevel - 1u) / kLevel, nc = (nb + kLevel - 1u) / kLevel;
+  if (wave_lead_after(sums.lead, t + 1u, min(ntiles, (b + 1u) * kLevel), kTile, ext)) return ext;
+  if (wave_lead_after(sums.lead1, b + 1u, min(nb, (c + 1u) * kLevel), kLevel * kTile, ext)) return ext;
+  (void)wave_lead_after(sums.lead2, c + 1u, nc, kLevel * kLevel * kTile, ext);
+  return ext;
+}
+
+// The upper levels of the tiles' summaries: a work-group takes 4096 tiles, a wave
+// 64 at a time.
+__global__ __launch_bounds__(1024) void k_tile_levels(TileSums sums, uint32_t ntiles) {
+  __shared__ uint32_t s_last[kLevel], s_lead[kLevel];
+  const uint32_t w = threadIdx.x / 64, lane = lane_id(), nb = (ntiles + kLevel - 1u) / kLevel;
+  // (last, lead) of 64 entries; those that don't exist are empty
+  const auto reduce = [&](uint32_t last, uint32_t lead, uint32_t whole, uint32_t& last_all, uint32_t& lead_all) {
+    const uint64_t some = __ballot(last != 0u), stop = __ballot(lead != whole);
+    last_all = some ? (uint32_t)__builtin_amdgcn_readlane((int)last, 63 - (int)__builtin_clzll(some)) : 0u;
+    const uint32_t at = stop ? (uint32_t)__builtin_ctzll(stop) : 64u;
+    lead_all = at * whole + (at < 64u ? (uint32_t)__builtin_amdgcn_readlane((int)lead, (int)at) : 0u);
+  };
+  for (uint32_t i = w; i < kLevel; i += 16) {
+    const uint32_t b = blockIdx.x * kLevel + i, t = b * kLevel + lane;
+    uint32_t last, lead;
+    reduce(t < ntiles ? sums.last[t] : 0u, t < ntiles ? sums.lead[t] : 0u, kTile, last, lead);
+    if (lane == 0) {
+      s_last[i] = last;
+      s_lead[i] = lead;
+      if (b < nb) {
+        sums.last1[b] = last;
+        sums.lead1[b] = lead;
+      }
+    }
+  }
+  __syncthreads();
+  if (w == 0) {
+    uint32_t last, lead;
+    reduce(s_last[lane], s_lead[lane], kLevel * kTile, last, lead);
+    if (lane == 0) {
+      sums.last2[blockIdx.x] = last;
+      sums.lead2[blockIdx.x] = lead;
+    }
+  }
+}
+
 // The words of one tile.  first_word: the scan of the tiles' words, or null
 // (every tile then adds up those before it).  The last tile writes the length:
 // the words' count, or 0 if an input covers more than ngroups groups.  A fill
@@ -365,30 +457,10 @@ __global__ __launch_bounds__(kBlock) void k_dense_encode(Bitmap a, Bitmap b, con
     const uint32_t base = first_word ? first_word[tile] : wave_words_before(sums.words, tile);
     if (lane_id() == 0) s_base = base;
   } else if (w == 1) {  // the last non-empty group before the tile
-    uint32_t carry = 0;
-    for (int64_t j = (int64_t)tile - 1; j >= 0; j -= 64) {
-      const int64_t t = j - (int64_t)lane_id();
-      const uint32_t l = t >= 0 ? sums.last[t] : 0u;
-      const uint64_t some = __ballot(l != 0u);
-      if (some) {
-        carry = (uint32_t)__builtin_amdgcn_readlane((int)l, (int)__builtin_ctzll(some));
-        break;
-      }
-    }
+    const uint32_t carry = wave_carry(sums, tile);
     if (lane_id() == 0) s_carry = carry;
   } else if (w == 2) {  // full groups right after the tile
-    uint32_t ext = 0;
-    for (uint64_t j = (uint64_t)tile + 1; j < ntiles; j += 64) {
-      const uint64_t t = j + lane_id();
-      const uint32_t l = t < ntiles ? sums.lead[t] : 0u;
-      const uint64_t stop = __ballot(l != kTile);
-      if (stop) {
-        const uint32_t at = (uint32_t)__builtin_ctzll(stop);
-        ext += at * kTile + (uint32_t)__builtin_amdgcn_readlane((int)l, (int)at);
-        break;
-      }
-      ext += 64u * kTile;
-    }
+    const uint32_t ext = wave_full_after(sums, tile, ntiles);
     if (lane_id() == 0) s_ext = ext;
   }
   s_last[tid] = x[kPer - 1];
@@ -496,6 +568,14 @@ int launch_zero_u32(Env& env, uint32_t* p) {
 }
 
 // ---- host side --------------------------------------------------------------------------
+// Tiles beyond which the summaries get their upper levels.  Without them a tile of
+// a nearly empty or nearly full result walks over all the others; they cost a
+// launch.  Us an AND of a nearly empty bitmap / an OR of full ones / an OR of two
+// of literals, walking and by levels: 2^23 groups 84, 70, 93 and 74, 57, 96; 2^24
+// 159, 139, 157 and 110, 82, 160; 2^27 3804, 3965, 1123 and 737, 397, 1136; at
+// 2^22 the walk is as fast.
+constexpr uint32_t kLevelTiles = 4096;
+
 // A bitmap with room for the scan of its group counts.
 bool make_bitmap(Env& env, const uint32_t* words, uint64_t cap, const uint64_t* len, Bitmap* out, ScanJob* job) {
   uint32_t* start = static_cast<uint32_t*>(env.scratch(4 * std::max<uint64_t>(cap, 1)));
@@ -516,6 +596,10 @@ int combine_fmt(Env& env, const Bitmap& a, const Bitmap& b, uint32_t ngroups, ui
   int rc = check_launch(env, "combine launch");
   if (rc) return rc;
   if (first_word && (rc = launch_exclusive_scan(env, sums.words, first_word, ntiles, nullptr))) return rc;
+  if (sums.last1) {
+    k_tile_levels<<<dim3((ntiles + kLevel * kLevel - 1) / (kLevel * kLevel)), dim3(1024), 0, env.stream()>>>(sums, ntiles);
+    if ((rc = check_launch(env, "tile_levels launch"))) return rc;
+  }
   if (reject && (rc = launch_zero_u32(env, reject))) return rc;
   env.prof_begin("dense_encode");
   k_dense_encode<kFmt, kOutFmt><<<grid, block, 0, env.stream()>>>(a, b, dense, ngroups, sums, first_word, words, len,
@@ -566,10 +650,17 @@ int launch_wah_combine(Env& env, const uint32_t* a, uint64_t a_cap, const uint64
   // The tiles' words are scanned in a launch of their own only where every
   // tile's own sum would read more (2048 tiles: 8 KiB a tile).
   uint32_t* first_word = ntiles > 2048 ? static_cast<uint32_t*>(env.scratch(4ull * ntiles)) : nullptr;
+  TileSums ts{sums, sums + ntiles, sums + 2ull * ntiles, nullptr, nullptr, nullptr, nullptr};
+  if (ntiles > kLevelTiles) {
+    const uint64_t nb = (ntiles + kLevel - 1) / kLevel, nc = (nb + kLevel - 1) / kLevel;
+    uint32_t* const levels = static_cast<uint32_t*>(env.scratch(8 * (nb + nc)));
+    if (!levels) return env.fail(kErrOom, "wah combine: scratch");
+    ts.last1 = levels, ts.lead1 = levels + nb;
+    ts.last2 = levels + 2 * nb, ts.lead2 = ts.last2 + nc;
+  }
   uint32_t* reject = ngroups > kLen30 ? static_cast<uint32_t*>(env.scratch(4)) : nullptr;
   if (!dense || !sums || (ntiles > 2048 && !first_word) || (ngroups > kLen30 && !reject))
     return env.fail(kErrOom, "wah combine: scratch");
-  const TileSums ts{sums, sums + ntiles, sums + 2ull * ntiles};
   Bitmap ba, bb;
   ScanJob ja, jb;
   if (!make_bitmap(env, a, a_cap, a_len, &ba, &ja) || !make_bitmap(env, b, b_cap, b_len, &bb, &jb))
