@@ -64,3 +64,17 @@ def test_noalloc_refuses_sizes_beyond_the_limit():
     rc = ka.lib.ka_wah_index_noalloc(p, n, p, p, p, p, None)
     assert rc == ka.KA_E_ARG
     assert b"KA_NOALLOC_MAX_N" in ka.lib.ka_last_error()
+
+
+@pytest.mark.parametrize("n", [8192, 8193, 1 << 18, (1 << 18) + 1, (1 << 19) + 1, (1 << 20) + 1, 352 * 8192,
+                               352 * 8192 + 1, 1 << 22])
+def test_noalloc_tile_sizes(n):
+    """Every tile size of the sort and the encoder at the edges of its range, over what the call before left."""
+    import torch
+    import paper_1709_07781_amd as ka
+    torch.cuda.set_device(0)
+    v = workloads.u32(n, n)
+    v[: n // 2] &= np.uint32(0xFFFF)
+    for values in (v, v[::-1].copy()):
+        for g, o in zip(_noalloc(ka, torch, values), oracle.default().wah_index(values)):
+            np.testing.assert_array_equal(g, o)
