@@ -53,7 +53,7 @@ namespace ka {
 namespace {
 
 // 1024 work-items x 8 elements: a tile of 8192 pairs, two work-groups of 16
-// waves per CU (bound by LDS; 63 VGPRs).  The look-back's latency (a few
+// waves per CU (bound by LDS; 63 or 64 VGPRs).  The look-back's latency (a few
 // device-coherent round trips, about 0.75 us each) is paid once per tile while
 // the tile's work-group waits, and the LDS sweeps stall on bank conflicts:
 // twice the waves of 512 x 16 hide both better, 206 -> 181 us on 2^26 Zipf
@@ -239,8 +239,9 @@ struct StagedPairs {
 // ---------------------------------------------------------------------------------
 // write: literals, fills and lookup-table entries of one tile
 // ---------------------------------------------------------------------------------
-// The other formats take up to 83 VGPRs (one work-group per CU): held to 64
-// they spill.
+// The other formats take 59 to 75 VGPRs in work-groups of 256 and 512 (6 or 7
+// waves per SIMD), and a small input's sort 65 to 81 in its one of 1024: held to
+// 64 they spill.
 // One work-group per tile; status[kLbSpread * tile] is the tile's (words, values)
 // look-back word, zeroed before the launch.
 //
@@ -554,7 +555,8 @@ __global__ void k_wah_clear(uint64_t* __restrict__ status, uint32_t ntiles) {
 }
 
 // Work-items of the encoder's work-groups by capacity: tiles small enough for
-// about one per CU.
+// about one per CU; the other formats, whose registers allow one work-group of
+// 1024 per CU, stay at 512.
 uint32_t enc_block(uint64_t n, uint32_t format) {
   return n <= 256ull * 2048 ? 256u : n <= 256ull * 4096 || format != kFmtPaper ? 512u : (uint32_t)kEncBlock;
 }
@@ -599,14 +601,11 @@ int encode_block(Env& env, const KeyT* skeys, const uint32_t* srows, uint32_t n,
 template <int kFmt, class KeyT>
 int encode_fmt(Env& env, const KeyT* skeys, const uint32_t* srows, uint32_t n, const IndexOut& out,
                const EncodeOpts& opt) {
-  switch (enc_block(n, kFmt)) {
-    case 256:
-      return encode_block<256, kFmt>(env, skeys, srows, n, out, opt);
-    case 512:
-      return encode_block<512, kFmt>(env, skeys, srows, n, out, opt);
-    default:
-      return encode_block<kEncBlock, kFmt>(env, skeys, srows, n, out, opt);
-  }
+  const uint32_t block = enc_block(n, kFmt);
+  if (block == 256u) return encode_block<256, kFmt>(env, skeys, srows, n, out, opt);
+  if constexpr (kFmt == kFmtPaper)
+    if (block == (uint32_t)kEncBlock) return encode_block<kEncBlock, kFmt>(env, skeys, srows, n, out, opt);
+  return encode_block<512, kFmt>(env, skeys, srows, n, out, opt);
 }
 
 template <int kFmt>
