@@ -1110,9 +1110,9 @@ struct RowScratch {
   RowTable table() const { return {rows, pre, totals}; }
 };
 
-// Beyond 2048 tiles a work-group takes 4 digits instead of 16 (4096 tiles of
-// 6-bit digits 8.9 -> 7.6 us, 8192 of 8-bit ones 17.7 -> 12.0, the same at 2048,
-// measured with rows one after the other).
+// Beyond 2048 tiles a work-group takes 4 digits instead of 16: us with 4 / 16 digits
+// of 6 bits 1024 tiles 3.9 / 4.3, 2048 4.6 / 4.8, 4096 4.9 / 5.3, 8192 7.4 / 9.5; of
+// 8 bits 4.6 / 4.3, 4.6 / 4.8, 5.0 / 5.4, 7.1 / 9.1.
 int scan_rows(Env& env, const RowScratch& rs, uint32_t bits, uint32_t ntiles, const SortPlan* plan, uint32_t pass,
               const uint32_t* orand, SortPlan* plan_out) {
   env.prof_begin("radix_rows_scan");
@@ -1340,10 +1340,15 @@ int seg_sort(Env& env, const uint32_t* values, uint64_t n, const uint32_t* req_o
   sg.ub = (uint32_t)ub64;
   sg.req_off = req_off;
   // Rows unless a request has too many tiles to sum (or may have, and the batch
-  // has).  12-bit values, us a batch by the scanned table / by rows: requests of
-  // 20,000 values 10^5 84 / 71, 4 10^6 133 / 111, 1.6 10^7 286 / 262; of 200,000
-  // values 10^6 94 / 76, 2.8 10^7 343 / 320.
-  const bool use_rows = sg.ub <= 384 || max_req <= 128ull * kTile;
+  // has): more than 16 where the last digit has 8 bits, more than 128 below.  Us a
+  // batch by the scanned table / by rows, requests of 20,000, 2^17, 2^18, 2^20 and
+  // 2^21 values: 1.7 10^7 values of 12 bits 264/257, 224/218, 224/219, 224/219,
+  // 225/227; of 14 bits 347/337, 237/236, 235/233, 233/232, 236/240; of 16 bits
+  // 416/405, 297/298, 257/259, 241/250, 240/264; of 8 bits 187/180, 162/162,
+  // 160/164, 156/164, 158/175.  3 10^6 values (366 tiles) of 16 bits 129/121,
+  // 115/107, 109/102, 98/93, 97/93.
+  const uint64_t row_request = (ds.bits[ds.passes - 1] > 6 ? 16ull : 128ull) * kTile;
+  const bool use_rows = sg.ub <= 384 || max_req <= row_request;
   uint32_t* tile_base = static_cast<uint32_t*>(env.scratch(4ull * (nreq + 1)));
   uint32_t* tile_req = static_cast<uint32_t*>(env.scratch(4ull * sg.ub));
   uint64_t* tlen = static_cast<uint64_t*>(env.scratch(8));
