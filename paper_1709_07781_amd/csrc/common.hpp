@@ -105,8 +105,6 @@ struct ClearWords {
 int launch_radix_sort_pairs(Env& env, const uint32_t* keys, const uint32_t* rows, uint32_t* skeys,
                             uint32_t* srows, uint64_t n, int shape = 0, const uint64_t* d_n = nullptr,
                             ClearWords cw = {});
-// Number of tile shapes launch_radix_sort_pairs offers (shape 0 is the default).
-int sort_shape_count();
 // Number of variants of the batched index build (its sort_shape argument):
 // 0 the segmented sort with the even digit split for values of at most 16
 // bits, else the tagged sort with tile shape 0; 1 and 2 the tagged sort with

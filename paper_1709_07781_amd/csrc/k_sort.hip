@@ -159,19 +159,19 @@ constexpr int kUpBlock = kRadix;  // one work-item per digit when the counts are
 // kOrAnd the OR and the AND of the tile's keys are written too.
 // The tile is keys[base, base + len); store(d, c) gets digit d's count: rows[tile][d],
 // or the segmented sort's table.
-template <int kUpBlock, int kTile, int kRounds, bool kOrAnd, class SK, class Store>
+template <int kBlock, int kTile, int kRounds, bool kOrAnd, class SK, class Store>
 __device__ __forceinline__ void upsweep_tile(const SK* __restrict__ keys, uint32_t shift, uint32_t base, uint32_t len,
                                              Store&& store, uint32_t tile, uint32_t* __restrict__ orand,
                                              uint32_t mask = kRadix - 1) {
-  constexpr int kUpWaves = kUpBlock / 64;
-  constexpr int kUpVecs = kTile / 4 / kUpBlock;  // 4-key loads per work-item
+  constexpr int kUpWaves = kBlock / 64;
+  constexpr int kUpVecs = kTile / 4 / kBlock;  // 4-key loads per work-item
   constexpr uintptr_t kAlign = 15;  // 16-byte loads
   __shared__ uint32_t s_hist[kUpWaves][kRadix];
   __shared__ uint32_t s_or[kUpWaves], s_and[kUpWaves];
   const uint32_t tid = threadIdx.x, w = tid / 64;
 
-  // Key 4 (j * kUpBlock + tid) + c of the tile in k[j][c] (uint16 keys of a full
-  // tile: key 8 (j/2 * kUpBlock + tid) + 4 (j mod 2) + c).
+  // Key 4 (j * kBlock + tid) + c of the tile in k[j][c] (uint16 keys of a full
+  // tile: key 8 (j/2 * kBlock + tid) + 4 (j mod 2) + c).
   uint32_t k[kUpVecs][4];
   if (len == (uint32_t)kTile && (reinterpret_cast<uintptr_t>(keys + base) & kAlign) == 0) {
     if constexpr (sizeof(SK) == 2 && kUpVecs % 2 == 0) {
@@ -180,25 +180,25 @@ __device__ __forceinline__ void upsweep_tile(const SK* __restrict__ keys, uint32
       // the second pass over 2^26 keys
 #pragma unroll
       for (int j = 0; j < kUpVecs / 2; ++j) {
-        const u32x4 a = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(keys + base) + j * kUpBlock + tid);
+        const u32x4 a = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(keys + base) + j * kBlock + tid);
         k[2 * j][0] = a.x & 0xFFFFu, k[2 * j][1] = a.x >> 16, k[2 * j][2] = a.y & 0xFFFFu, k[2 * j][3] = a.y >> 16;
         k[2 * j + 1][0] = a.z & 0xFFFFu, k[2 * j + 1][1] = a.z >> 16;
         k[2 * j + 1][2] = a.w & 0xFFFFu, k[2 * j + 1][3] = a.w >> 16;
       }
     } else {
 #pragma unroll
-      for (int j = 0; j < kUpVecs; ++j) load_key4(keys + base, (uint64_t)j * kUpBlock + tid, k[j]);
+      for (int j = 0; j < kUpVecs; ++j) load_key4(keys + base, (uint64_t)j * kBlock + tid, k[j]);
     }
   } else {
 #pragma unroll
     for (int j = 0; j < kUpVecs; ++j)
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        const uint32_t e = 4 * (j * kUpBlock + tid) + c;
+        const uint32_t e = 4 * (j * kBlock + tid) + c;
         k[j][c] = e < len ? (uint32_t)keys[base + e] : 0u;
       }
   }
-  for (int i = tid; i < kUpWaves * kRadix; i += kUpBlock) (&s_hist[0][0])[i] = 0;
+  for (int i = tid; i < kUpWaves * kRadix; i += kBlock) (&s_hist[0][0])[i] = 0;
   __syncthreads();
   uint32_t kor = 0, kand = ~0u;
   // kRounds < 0: two digits are counted in registers -- 0 and the digit of the
@@ -245,30 +245,31 @@ __device__ __forceinline__ void upsweep_tile(const SK* __restrict__ keys, uint32
     }
   }
   const uint32_t hot = (uint32_t)__builtin_amdgcn_readfirstlane((int)((k[0][0] >> shift) & mask));
-  if (!clustered)
+  if (!clustered) {
 #pragma unroll
-  for (int j = 0; j < kUpVecs; ++j)
+    for (int j = 0; j < kUpVecs; ++j)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const bool valid = 4 * (j * kUpBlock + tid) + c < len;
-      if (kRounds < 0) {
-        const uint32_t d = (k[j][c] >> shift) & mask;
-        if (valid) {
-          if (d == hot)
-            ++ch;
-          else if (d == 0)
-            ++c0;
-          else
-            atomicAdd(&s_hist[w][d], 1u);
+      for (int c = 0; c < 4; ++c) {
+        const bool valid = 4 * (j * kBlock + tid) + c < len;
+        if (kRounds < 0) {
+          const uint32_t d = (k[j][c] >> shift) & mask;
+          if (valid) {
+            if (d == hot)
+              ++ch;
+            else if (d == 0)
+              ++c0;
+            else
+              atomicAdd(&s_hist[w][d], 1u);
+          }
+        } else {
+          lds_add_aggregated<(kRounds < 0 ? 0 : kRounds)>(s_hist[w], (k[j][c] >> shift) & mask, valid);
         }
-      } else {
-        lds_add_aggregated<(kRounds < 0 ? 0 : kRounds)>(s_hist[w], (k[j][c] >> shift) & mask, valid);
+        if (kOrAnd && valid) {
+          kor |= k[j][c];
+          kand &= k[j][c];
+        }
       }
-      if (kOrAnd && valid) {
-        kor |= k[j][c];
-        kand &= k[j][c];
-      }
-    }
+  }
   if (kRounds < 0 && !clustered) {
     const uint32_t z = wave_sum(c0), h = wave_sum(ch);
     if (lane_id() == 0) {
@@ -288,7 +289,7 @@ __device__ __forceinline__ void upsweep_tile(const SK* __restrict__ keys, uint32
     }
   }
   __syncthreads();
-  if (kUpBlock == kRadix || tid < (uint32_t)kRadix) {
+  if (kBlock == kRadix || tid < (uint32_t)kRadix) {
     uint32_t c = 0;
 #pragma unroll
     for (int ww = 0; ww < kUpWaves; ++ww) c += s_hist[ww][tid];
@@ -1391,7 +1392,6 @@ int seg_sort(Env& env, const uint32_t* values, uint64_t n, const uint32_t* req_o
 
 }  // namespace
 
-int sort_shape_count() { return kNumShapes; }
 int batch_variant_count() { return kNumShapes + 1; }
 
 int launch_radix_sort_segments(Env& env, const uint32_t* values, uint64_t n, const uint32_t* req_off, uint32_t nreq,
