@@ -924,40 +924,39 @@ __device__ __forceinline__ uint32_t request_tiles(const uint32_t* __restrict__ r
 }
 
 // The layout of up to kSegLayoutMax requests by one work-group: tile_base,
-// tile_req (ub entries), the table's length, the cleared flags.
-constexpr uint32_t kSegLayoutMax = 16384;
+// tile_req (ub entries), the table's length, the cleared flags.  One launch for
+// three, but its waves take the requests in turn: us a batch of 12-bit values by
+// three launches / by this one, 192 requests of 20,000 values 118 / 113, 512 of
+// 1100 89 / 84, 1024 110 / 109, 2048 152 / 160 (of 5000 values 259 / 270), 4096 242
+// / 269, 8192 405 / 463.
+constexpr uint32_t kSegLayoutMax = 1024;
 template <int kTile>
 __global__ __launch_bounds__(1024) void k_seg_layout(const uint32_t* __restrict__ req_off, uint32_t nreq, uint32_t ub,
                                                      uint32_t* __restrict__ tile_base, uint32_t* __restrict__ tile_req,
                                                      uint64_t* __restrict__ tlen, uint32_t* __restrict__ bad,
                                                      uint32_t* __restrict__ req_bad) {
-  __shared__ uint32_t s_scan[16], s_base[1025];
-  const uint32_t tid = threadIdx.x, w = tid / 64, lane = lane_id();
-  uint32_t run = 0;
-  for (uint32_t c0 = 0; c0 < nreq; c0 += 1024) {
-    const uint32_t j = c0 + tid;
-    uint32_t nt = 0;
-    if (j < nreq) {
-      nt = request_tiles<kTile>(req_off, j);
-      if (req_bad) req_bad[j] = 0u;
-    }
-    uint32_t total;
-    const uint32_t base = run + block_excl_scan<1024>(nt, s_scan, &total);
-    if (j < nreq) tile_base[j] = base;
-    s_base[tid] = base;
-    if (tid == 0) s_base[1024] = run + total;
-    __syncthreads();
-    for (uint32_t q = w; q < min(1024u, nreq - c0); q += 16)  // a wave per request
-      for (uint32_t t = s_base[q] + lane; t < min(s_base[q + 1], ub); t += 64) tile_req[t] = c0 + q;
-    run += total;
-    __syncthreads();
+  static_assert(kSegLayoutMax == 1024, "a request per work-item");
+  __shared__ uint32_t s_scan[16], s_base[kSegLayoutMax];
+  const uint32_t tid = threadIdx.x;
+  uint32_t nt = 0, all;
+  if (tid < nreq) {
+    nt = request_tiles<kTile>(req_off, tid);
+    if (req_bad) req_bad[tid] = 0u;
+  }
+  const uint32_t base = block_excl_scan<1024>(nt, s_scan, &all);
+  if (tid < nreq) tile_base[tid] = base;
+  s_base[tid] = base;
+  __syncthreads();
+  for (uint32_t q = tid / 64; q < nreq; q += 16) {  // a wave per request
+    const uint32_t t1 = min(q + 1 < nreq ? s_base[q + 1] : all, ub);
+    for (uint32_t t = s_base[q] + lane_id(); t < t1; t += 64) tile_req[t] = q;
   }
   if (tid == 0) {
-    tile_base[nreq] = run;
-    *tlen = (uint64_t)kRadix * run;
+    tile_base[nreq] = all;
+    *tlen = (uint64_t)kRadix * all;
     *bad = 0u;
   }
-  for (uint32_t t = run + tid; t < ub; t += 1024) tile_req[t] = ~0u;
+  for (uint32_t t = all + tid; t < ub; t += 1024) tile_req[t] = ~0u;
 }
 
 // The same for more requests: the tile counts (scanned by the launch between),

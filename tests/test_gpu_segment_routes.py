@@ -60,3 +60,23 @@ def test_clustered_keys_in_every_form(sess, bits, shape):
             _check(plan.result(), off, v)
     finally:
         plan.close()
+
+
+@pytest.mark.parametrize("nreq", [1, 1023, 1024, 1025, 2500])
+def test_requests_laid_out_by_one_and_by_many_work_groups(sess, nreq):
+    """The batch's layout on both sides of its limit, eager and in a plan of that many requests, of which a batch may
+    have fewer."""
+    from paper_1709_07781_amd.session import BatchPlan
+    rng = np.random.default_rng(nreq)
+    sizes = rng.integers(0, 40, nreq)
+    sizes[rng.integers(0, nreq, 3)] = [1025, 9000, 20_000]
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.uint32)
+    v = _values(int(off[-1]), 12, False, nreq)
+    _check(sess.wah_batch(sess.upload(v), off, 12), off, v)
+    plan = BatchPlan(sess, None, 12, any_batch=(int(off[-1]), nreq, 0))
+    try:
+        for k in (nreq, max(1, nreq // 2), nreq):
+            plan.run_batch(v[: off[k]], off[: k + 1])
+            _check(plan.result(), off[: k + 1], v)
+    finally:
+        plan.close()
