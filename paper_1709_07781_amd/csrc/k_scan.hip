@@ -29,8 +29,7 @@
 // 16 above, where fewer tiles mean fewer look-backs per byte.  Scans, us a
 // request with 8 / 16 rounds: 4 10^6 values 21.4 / 21.7, 8 10^6 29.6 / 24.8, 1.6
 // 10^7 43 / 37.  Compactions, whose tile is staged in LDS (32 / 64 KiB: four or
-// two work-groups per CU), us of the kernel after a scan of the same values: 3
-// 10^7 36 / 39, 4 10^7 46 / 49, 6 10^7 69 / 74, 2^26 82 / 83.
+// two work-groups per CU): 1.6 10^7 42 / 44, 3 10^7 75 / 74, 6 10^7 121 / 110.
 #include <algorithm>
 #include <type_traits>
 
@@ -42,19 +41,15 @@ namespace {
 constexpr int kScanBlock = 256;
 constexpr int kWaves = kScanBlock / 64;
 constexpr int kSmallRounds = 8, kLargeRounds = 16;
-constexpr uint64_t kLargeScan = 1ull << 22, kLargeCompact = 3ull << 24;  // capacities above use kLargeRounds
+constexpr uint64_t kLargeScan = 1ull << 22, kLargeCompact = 1ull << 25;  // capacities above use kLargeRounds
 template <int R>
 constexpr int kTileElems = kScanBlock * R * 4;
 
 // Loads are kept in the caches (kStream: not).  The 256 MB behind the L2 hold an
-// input for what reads it next: us of a scan and a compaction of the same values in
-// turn, both streamed / both cached, 3 10^7 values 47 + 41 / 42 + 36, 4 10^7 79 + 52
-// / 54 + 46.  Only the compactions of kLargeRounds stream, whose inputs begin at 200
-// MB: beside those the caches have no room for the outputs.  Compactions streamed /
-// cached in their tiles of 16 / 8 rounds, after a scan (with its time) and alone, of
-// the same values again: 4 10^7 71 + 50 / 54 + 46, 54 / 46; 5 10^7 84 + 60 / 66 +
-// 56, 64 / 65; 6 10^7 98 + 70 / 88 + 70, 76 / 79; 2^26 104 + 77 / 97 + 83, 83 / 89.
-// Stores are streamed.
+// input of up to that size for what reads it next: a scan and a compaction of
+// the same 30,000,001 values 67 + 41 us streamed, 48 + 37 us cached.  Only the
+// compactions of kLargeRounds stream: their inputs begin at half of it (6.7 10^7
+// values 91 / 101 us streamed / cached).  Stores are streamed.
 template <bool kVec, bool kFull, bool kStream>
 __device__ __forceinline__ void load4(const uint32_t* __restrict__ p, uint64_t e, uint64_t n, uint32_t v[4]) {
   if (kVec && (kFull || e + 4 <= n)) {
