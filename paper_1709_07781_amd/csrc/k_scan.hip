@@ -29,7 +29,10 @@
 // 16 above, where fewer tiles mean fewer look-backs per byte.  Scans, us a
 // request with 8 / 16 rounds: 4 10^6 values 21.4 / 21.7, 8 10^6 29.6 / 24.8, 1.6
 // 10^7 43 / 37.  Compactions, whose tile is staged in LDS (32 / 64 KiB: four or
-// two work-groups per CU): 1.6 10^7 42 / 44, 3 10^7 75 / 74, 6 10^7 121 / 110.
+// two work-groups per CU), us of the kernel, half the values kept, all kept: 8 10^6
+// 13.2 / 13.4, 15.6 / 16.6; 2.4 10^7 30.6 / 34.4, 35.6 / 39.7; 3.4 10^7 40 / 43, 52 /
+// 57; 4.2 10^7 48 / 52, 76 / 70; 5 10^7 65 / 67, 88 / 85; 6.8 10^7 90 / 90, 118 /
+// 111; 1.34 10^8 172 / 166, 222 / 210.
 #include <algorithm>
 #include <type_traits>
 
@@ -46,10 +49,16 @@ template <int R>
 constexpr int kTileElems = kScanBlock * R * 4;
 
 // Loads are kept in the caches (kStream: not).  The 256 MB behind the L2 hold an
-// input of up to that size for what reads it next: a scan and a compaction of
-// the same 30,000,001 values 67 + 41 us streamed, 48 + 37 us cached.  Only the
-// compactions of kLargeRounds stream: their inputs begin at half of it (6.7 10^7
-// values 91 / 101 us streamed / cached).  Stores are streamed.
+// input for what reads it next: us of a scan and a compaction of the same values in
+// turn, both streamed / both cached, 3 10^7 values 47 + 41 / 42 + 36, 4 10^7 79 + 52
+// / 54 + 46.  Only the compactions of kLargeRounds stream: from 2^25 values on, an
+// input and the up to as many values kept exceed the caches, and what a launch
+// keeps isn't known before it.  Compactions alone, of the same values again, in tiles
+// of 16 streamed / of 8 cached, all, half and a tenth of the values kept: 3.4 10^7
+// 57, 47, 39 / 52, 40, 34; 3.8 10^7 60, 51, 43 / 67, 44, 38; 4.2 10^7 66, 55, 48 / 76,
+// 48, 41; 5 10^7 76, 64, 55 / 88, 65, 48; 6.8 10^7 101, 85, 74 / 118, 90, 70.  (After
+// a scan of the same half-empty values the cached ones gain more: 4 10^7 71 + 50 / 54
+// + 46, 6 10^7 98 + 70 / 88 + 70.)  Stores are streamed.
 template <bool kVec, bool kFull, bool kStream>
 __device__ __forceinline__ void load4(const uint32_t* __restrict__ p, uint64_t e, uint64_t n, uint32_t v[4]) {
   if (kVec && (kFull || e + 4 <= n)) {
