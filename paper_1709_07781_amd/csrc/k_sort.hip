@@ -912,8 +912,8 @@ namespace {
 //  * as a table, request j's at 256 tile_base[j] + d ntiles_j + l: scanned in
 //    that order, each entry is the position in the batch of the tile's first
 //    key with digit d, and no key leaves its request; or
-//  * in batches of few tiles as rows (see k_radix_count_fixed), of which a tile sums
-//    its own request's.
+//  * as rows (see k_radix_count_fixed), of which a tile sums its own request's, in
+//    batches of few tiles or of requests of few (see seg_sort).
 // Rows are made relative to the request's first position; the last pass writes
 // the key tagged with its request (j << value_bits | key), which is what the
 // encoder and the per-request split read.
