@@ -568,7 +568,7 @@ KA_API int ka_server_destroy(ka_server* srv);
  * capture, serving loops and harnesses that forbid hipMalloc.  The same
  * composed build as ka_wah_index (same kernels, same words), with every
  * scratch buffer carved from one static device array of the library (about
- * 66 MiB per device, held by each device the library runs on until the process
+ * 64 MiB per device, held by each device the library runs on until the process
  * ends).  The array's device address is looked up on the first call on each
  * device; no call allocates or frees device memory.
  *

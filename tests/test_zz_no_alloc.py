@@ -78,3 +78,37 @@ def test_noalloc_tile_sizes(n):
     for values in (v, v[::-1].copy()):
         for g, o in zip(_noalloc(ka, torch, values), oracle.default().wah_index(values)):
             np.testing.assert_array_equal(g, o)
+
+
+@pytest.mark.parametrize("n", [777, 20_000, 3_000_000])
+def test_noalloc_replayed_in_a_graph(n):
+    """Captured once and replayed over new inputs, another eager call of the same array between the replays: every
+    replay equals the oracle (the look-back words are zeroed inside the graph)."""
+    import torch
+    import paper_1709_07781_amd as ka
+    torch.cuda.set_device(0)
+    dv = torch.zeros(n, dtype=torch.int32, device="cuda")
+    keys, offs = torch.zeros(n, dtype=torch.int32, device="cuda"), torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+    words, lens = torch.zeros(2 * n, dtype=torch.int32, device="cuda"), torch.zeros(3, dtype=torch.int64, device="cuda")
+
+    def call():
+        ka.check(ka.lib.ka_wah_index_noalloc(
+            *(ctypes.c_void_p(dv.data_ptr()), n), *(ctypes.c_void_p(t.data_ptr()) for t in (keys, offs, words, lens)),
+            ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)), "ka_wah_index_noalloc")
+
+    call()  # the array's address is looked up outside the capture
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call()
+    for seed in range(4):
+        v = workloads.u32(seed + n, n)
+        v[n // 3:] &= np.uint32(0xFFF)
+        dv.copy_(torch.from_numpy(v.view(np.int32)))
+        g.replay()
+        torch.cuda.synchronize()
+        D, _, W = lens.tolist()
+        got = [t.cpu().numpy().view(np.uint32)[:m] for t, m in ((keys, D), (offs, D + 1), (words, W))]
+        for a, e in zip(got, oracle.default().wah_index(v)):
+            np.testing.assert_array_equal(a, e, err_msg=f"replay {seed}")
+        _noalloc(ka, torch, workloads.u32(seed, 100_003))  # eager, over the same array
